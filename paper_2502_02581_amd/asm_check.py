@@ -8,6 +8,9 @@ not look into.  Two things it would otherwise guarantee are therefore checked on
     the five wait states before the load, along any path of the control flow that reaches the load:
     loop back edges and both arms of a branch are followed (the M0 write in front of the load is a
     scalar instruction and has its own wait state inside the inline assembly);
+  * the A and B operands of a matrix instruction (inline assembly too) must not have been written by a vector
+    instruction in the two wait states before it: fragments come straight from LDS reads, whose wait the
+    compiler places itself, and this makes sure that no register move is put in between;
   * no GEMM kernel keeps anything in scratch memory: accumulator tiles that end up there (an
     epilogue too large to unroll did that once) cost a factor of four and show up nowhere else;
   * no packed fp32 arithmetic (v_pk_add_f32, v_pk_mul_f32, v_pk_fma_f32): the build switches the
@@ -125,6 +128,40 @@ def check_descriptor_hazards(lines: List[str]) -> List[str]:
     return findings
 
 
+def _vregs(tok: str) -> Set[int]:
+    tok = tok.strip().split()[0] if tok.strip() else ""
+    m = re.match(r"v\[(\d+):(\d+)\]$", tok)
+    if m:
+        return set(range(int(m.group(1)), int(m.group(2)) + 1))
+    m = re.match(r"v(\d+)$", tok)
+    return {int(m.group(1))} if m else set()
+
+
+def check_mfma_sources(lines: List[str], wait_states: int = 2) -> List[str]:
+    ins, preds = _control_flow(lines)
+    findings = []
+    for k, (ln, t) in enumerate(ins):
+        if not t.startswith("v_mfma"):
+            continue
+        ops = t.split(None, 1)[1].split(",")
+        read = _vregs(ops[1]) | _vregs(ops[2])
+        stack = [(j, 0) for j in preds[k]]
+        while stack:
+            j, ws = stack.pop()
+            if ws >= wait_states:
+                continue
+            u = ins[j][1]
+            op = u.split()[0]
+            if op.startswith("v_") and not op.startswith(("v_mfma", "v_cmp")) and len(u.split(None, 1)) > 1:
+                hit = _vregs(u.split(None, 1)[1].split(",")[0]) & read
+                if hit:
+                    findings.append(f"line {ln}: `{t}` reads v{sorted(hit)} written by `{u}` (line {ins[j][0]}) {ws} wait "
+                                    "states earlier")
+            nxt = ws + (int(u.split()[1]) + 1 if op == "s_nop" else 1)
+            stack.extend((q, nxt) for q in preds[j])
+    return findings
+
+
 def check_no_scratch(lines: List[str], name_part: str = "gemm_kernel") -> List[str]:
     findings = []
     kernel = None
@@ -152,7 +189,7 @@ def check_no_packed_fp32(lines: List[str]) -> List[str]:
 def check(path: str) -> List[str]:
     with open(path) as f:
         lines = f.read().split("\n")
-    return check_descriptor_hazards(lines) + check_no_scratch(lines) + check_no_packed_fp32(lines)
+    return check_descriptor_hazards(lines) + check_mfma_sources(lines) + check_no_scratch(lines) + check_no_packed_fp32(lines)
 
 
 if __name__ == "__main__":

@@ -8,6 +8,7 @@
 //           B3 : dWd_e = H_e^T dYin_e;  [dWg_e | dWu_e] = Xin_e^T [dG_e | dU_e]
 // A device-built plan turns the row offsets into a list of row tiles (largest group first,
 // groups without rows contribute nothing) so that no host synchronisation is needed.
+#include <algorithm>
 #include <atomic>
 
 #include "gemm_cores.h"
@@ -27,8 +28,8 @@ __device__ __forceinline__ void block_scan_inclusive(int32_t* sc, int e) {
 
 // One block of 1024 threads; thread e owns group e.
 __global__ __launch_bounds__(1024) void plan_kernel(const int32_t* __restrict__ offsets, int n_groups,
-                                                    int n_rows, int BM, Plan pl, int32_t* active_ids,
-                                                    int32_t* n_active) {
+                                                    int n_rows, int BM, int mixed, Plan pl,
+                                                    int32_t* active_ids, int32_t* n_active) {
   __shared__ int32_t cnt[1024], sc[1024], ord[1024], st_[1024];
   const int e = threadIdx.x;
   int c = 0, st = 0;
@@ -71,53 +72,40 @@ __global__ __launch_bounds__(1024) void plan_kernel(const int32_t* __restrict__ 
   if (e < n_groups) pl.ginfo[rank] = make_int4(e, c, st, c > 0 ? sc[e] - 1 : -1);
   if (e == 0 && n_active) *n_active = total_active;
   __syncthreads();
-  // Row tiles, groups in descending size.  BM > 0: tiles of BM rows.  BM == 0: mixed heights -- full
-  // 256-row tiles, and the remainder r of a group cut so that little MFMA work is spent on padding:
-  // r > 192: one 256 tile; (160,192]: 128 + 64; (128,160]: 128 + 32; (96,128]: 128; (64,96]: 64 + 32;
-  // (32,64]: 64; (0,32]: 32.
+  // Row tiles of BM rows, groups in descending size.  mixed: full tiles of BM rows, and the remainder r of a
+  // group cut into tiles of BM/2, BM/4 and BM/8 rows so that little MFMA work is spent on padding; in
+  // eighths of BM: r > 6: one full tile; (5,6]: 4 + 2; (4,5]: 4 + 1; (3,4]: 4; (2,3]: 2 + 1; (1,2]: 2; (0,1]: 1.
   const int g = e < n_groups ? ord[e] : 0;
   const int cg = e < n_groups ? cnt[g] : 0;
-  int nt, h0 = 0, h1 = 0;  // heights of the (up to two) remainder tiles
-  if (BM > 0) {
-    nt = (cg + BM - 1) / BM;
-  } else {
-    const int r = cg & 255;
-    if (r > 192) h0 = 256;
-    else if (r > 160) { h0 = 128; h1 = 64; }
-    else if (r > 128) { h0 = 128; h1 = 32; }
-    else if (r > 96) h0 = 128;
-    else if (r > 64) { h0 = 64; h1 = 32; }
-    else if (r > 32) h0 = 64;
-    else if (r > 0) h0 = 32;
-    nt = (cg >> 8) + (h0 > 0) + (h1 > 0);
+  const int full = cg / BM;
+  int k0 = -1, k1 = -1;  // kinds (heights BM >> kind) of the up to two remainder tiles
+  if (mixed) {
+    const int r8 = ((cg - full * BM) * 8 + BM - 1) / BM;  // eighths of BM, rounded up
+    if (r8 > 6) k0 = 0;
+    else if (r8 > 4) { k0 = 1; k1 = r8 == 6 ? 2 : 3; }
+    else if (r8 == 4) k0 = 1;
+    else if (r8 == 3) { k0 = 2; k1 = 3; }
+    else if (r8 == 2) k0 = 2;
+    else if (r8 == 1) k0 = 3;
+  } else if (cg > full * BM) {
+    k0 = 0;
   }
+  const int nt = full + (k0 >= 0) + (k1 >= 0);
   sc[e] = nt;
   __syncthreads();
   block_scan_inclusive(sc, e);
   const int base = sc[e] - nt;
-  if (BM > 0) {
-    for (int i = 0; i < nt; i++) {
-      RowTile t;
-      t.group = g;
-      t.row0_in = st_[g] + i * BM;
-      t.rows = min(BM, cg - i * BM);
-      t.row0_out = offsets ? t.row0_in : g * n_rows + i * BM;
-      pl.tiles[base + i] = t;
-    }
-  } else {
-    int row = 0;
-    for (int i = 0; i < nt; i++) {
-      const int full = cg >> 8;
-      const int h = i < full ? 256 : (i == full ? h0 : h1);
-      const int kind = h == 256 ? 0 : h == 128 ? 1 : h == 64 ? 2 : 3;
-      RowTile t;
-      t.group = g;
-      t.row0_in = st_[g] + row;
-      t.rows = min(h, cg - row) | (kind << 16);
-      t.row0_out = offsets ? t.row0_in : g * n_rows + row;
-      pl.tiles[base + i] = t;
-      row += h;
-    }
+  int row = 0;
+  for (int i = 0; i < nt; i++) {
+    const int kind = i < full ? 0 : (i == full ? k0 : k1);
+    const int h = BM >> kind;
+    RowTile t;
+    t.group = g;
+    t.row0_in = st_[g] + row;
+    t.rows = min(h, cg - row) | (kind << 16);
+    t.row0_out = offsets ? t.row0_in : g * n_rows + row;
+    pl.tiles[base + i] = t;
+    row += h;
   }
   if (e == 1023) *pl.n_tiles = sc[1023];
 }
@@ -366,7 +354,7 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm& p, const RowTile& t
 }
 
 template <class CoreSet, int NB, int EPI, bool B_KC>
-__global__ __launch_bounds__(CoreSet::template tile<0>::NT) void row_gemm_kernel(RowGemm p) {
+__global__ __launch_bounds__(CoreSet::template tile<0>::NT, CoreSet::template tile<0>::BLOCKS_PER_CU) void row_gemm_kernel(RowGemm p) {
   extern __shared__ __align__(16) char smem[];
   typedef typename CoreSet::template tile<0> Core0;
   const int ntn = (p.N + Core0::BN - 1) / Core0::BN;
@@ -395,7 +383,7 @@ __global__ __launch_bounds__(CoreSet::template tile<0>::NT) void row_gemm_kernel
     // direct tiling: tiles of one height (on the LDS-DMA path the caller may pick a shorter kind, so
     // that a GEMM with few column tiles still fills the chip)
     const int kind = CoreSet::kKinds == 4 ? p.direct_kind : 0;
-    const int bm = CoreSet::kKinds == 4 ? kind_height(kind) : Core0::BM;
+    const int bm = Core0::BM >> kind;
     t.group = 0;
     t.row0_in = mt * bm;
     if (t.row0_in >= p.n_rows) return;
@@ -418,7 +406,7 @@ __global__ __launch_bounds__(CoreSet::template tile<0>::NT) void row_gemm_kernel
 
 // ------------------------------------------------------------------- weight-gradient kernel
 template <class Core, int NB>
-__global__ __launch_bounds__(Core::NT) void w_gemm_kernel(WGemm p) {
+__global__ __launch_bounds__(Core::NT, Core::BLOCKS_PER_CU) void w_gemm_kernel(WGemm p) {
   typedef typename Core::T T;
   extern __shared__ __align__(16) char smem[];
   constexpr int BM = Core::BM, BN = Core::BN, BK = Core::BK;
@@ -472,13 +460,19 @@ __global__ __launch_bounds__(Core::NT) void w_gemm_kernel(WGemm p) {
 }
 
 // ------------------------------------------------------------------------------ host side
-// Three families of tile cores: fp32 FMA (MOE_F32), the general bf16 MFMA core (any d, d_ff that are
+// Three families of tile cores: fp32 (MOE_F32), the general bf16 MFMA core (any d, d_ff that are
 // multiples of 8) and the bf16 core with LDS DMA loads (d and d_ff multiples of 64).
 enum { PATH_F32 = 0, PATH_BF16 = 1, PATH_BF16_DMA = 2 };
 template <int PATH> struct Cores;
 template <> struct Cores<PATH_F32> {
-  static constexpr int BM = 64, BN = 64;
-  template <int NB, bool A_KC, bool B_KC> using core = F32Core<NB, A_KC, B_KC>;
+  static constexpr int BM = 64, BN = 128;
+  // Bound by the fp32 matrix pipe (157 TFLOP/s).  An fp32 MFMA takes an eighth of the operand bytes per cycle of
+  // a bf16 one, so even 64 x 128 tiles (dual GEMMs: 64 x 64 of each product) keep it fed from L2; small tiles
+  // balance better and two blocks fit on a CU, one multiplying while the other stores.  Forward + backward of
+  // T = 2048, d = 1024, 16 experts, top-2, d_ff = 2816: 4.85 ms with fp32 FMA tiles (44 TFLOP/s), 2.51 ms with
+  // 128 x 128 MFMA tiles, 2.49 ms with 64 x 128 on the ring pipeline, 2.33 ms with two whole K steps in flight
+  // (91 TFLOP/s; the ring requests B too late for an iteration of 32 MFMAs); d = 128, d_ff = 256, T = 256: 275 -> 121 us.
+  template <int NB, bool A_KC, bool B_KC> using core = MfmaDmaCore<float, 128, 128 / NB, NB, A_KC, B_KC, 2, 2, 1, true>;
 };
 template <> struct Cores<PATH_BF16> {
   static constexpr int BM = 128, BN = 128;
@@ -489,9 +483,9 @@ template <> struct Cores<PATH_BF16_DMA> {
   // one block of 4 wavefronts (one per SIMD, each with a 128 x 128 share: the fewest LDS reads and
   // scalar instructions per MFMA, which is what the K loop is short of) computes 256 x 256 outputs
   // (dual GEMMs: 256 x 128 of each product)
-  template <int NB, bool A_KC, bool B_KC> using core = MfmaDmaCore<256, 256 / NB, NB, A_KC, B_KC, 2, 2>;
+  template <int NB, bool A_KC, bool B_KC> using core = MfmaDmaCore<bf16_t, 256, 256 / NB, NB, A_KC, B_KC, 2, 2>;
   // weight gradients of groups with few rows: 128 x 128 outputs per product, one tile slot
-  template <int NB> using core_light = MfmaDmaCore<128, 128, NB, false, false, 2, 2, 0>;
+  template <int NB> using core_light = MfmaDmaCore<bf16_t, 128, 128, NB, false, false, 2, 2, 0>;
 };
 constexpr int kLightGroupRows = 256;  // groups up to this many rows take the light dW kernel
 constexpr int kLightReps = 2;         // column tiles per block of that kernel (1: +5 % time on the DeepSeek shape, 8: +3 %)
@@ -502,13 +496,20 @@ template <int PATH, int NB, bool B_KC> struct RowCores {
   static constexpr int kKinds = 1;
   template <int KIND> using tile = typename Cores<PATH>::template core<NB, true, B_KC>;
 };
+template <int NB, bool B_KC> struct RowCores<PATH_F32, NB, B_KC> {
+  static constexpr int kKinds = 4;
+  // heights 64, 32, 16, 8
+  template <int KIND>
+  using tile = std::conditional_t<(KIND == 0 || NB == 2), MfmaDmaCore<float, 64, 128 / NB, NB, true, B_KC, 2, 2, 2, true>,
+                                  MfmaDmaCore<float, 32, 128, NB == 2 ? 1 : NB, true, B_KC, 1, 4, 2, true>>;
+};
 template <int NB, bool B_KC> struct RowCores<PATH_BF16_DMA, NB, B_KC> {
   static constexpr int kKinds = 4;
   // tile kinds 0..3 are cut for 256, 128, 64 and 32 rows; the last two share the 64-row core (those
   // tiles are bound by streaming the weights, not by MFMA work).  Pipeline depth by height: the
   // 128-row tile fits 3 slots per operand, the 64-row one 4.
   template <int KIND>
-  using tile = MfmaDmaCore<(KIND == 0 ? 256 : KIND == 1 ? 128 : 64), 256 / NB, NB, true, B_KC, 2, 2,
+  using tile = MfmaDmaCore<bf16_t, (KIND == 0 ? 256 : KIND == 1 ? 128 : 64), 256 / NB, NB, true, B_KC, 2, 2,
                            (KIND == 0 ? 1 : KIND == 1 ? 2 : 3)>;
 };
 
@@ -534,28 +535,35 @@ struct LdsAttr {
   }
 };
 
-// upper bound of the row tiles the plan kernel may emit (BM == 0: mixed heights, at most two
-// remainder tiles per group)
-static int max_row_tiles(int n_groups, int n_rows, bool shared, int BM) {
-  if (BM == 0) return shared ? n_groups * (n_rows / 256 + 2) : n_rows / 256 + 2 * n_groups;
+// upper bound of the row tiles the plan kernel may emit (mixed heights: at most two remainder tiles per group)
+static int max_row_tiles(int n_groups, int n_rows, bool shared, int BM, bool mixed) {
+  if (mixed) return shared ? n_groups * (n_rows / BM + 2) : n_rows / BM + 2 * n_groups;
   return shared ? n_groups * ceil_div(n_rows, BM) : ceil_div(n_rows, BM) + n_groups;
 }
-template <int PATH> constexpr int plan_bm() { return PATH == PATH_BF16_DMA ? 0 : Cores<PATH>::BM; }
+template <int PATH> constexpr bool plan_mixed() { return PATH != PATH_BF16; }
+
+// LDS of a launch: one block may run any of the tile kinds
+template <class CoreSet> constexpr int row_lds_bytes() {
+  constexpr int n0 = CoreSet::template tile<0>::LDS_BYTES;
+  if constexpr (CoreSet::kKinds == 1) return n0;
+  else return std::max({n0, CoreSet::template tile<1>::LDS_BYTES, CoreSet::template tile<2>::LDS_BYTES, CoreSet::template tile<3>::LDS_BYTES});
+}
 
 template <class CoreSet, int NB, int EPI, bool B_KC>
 static void launch_row(const char* label, const RowGemm& p, int max_tiles, hipStream_t st) {
   typedef typename CoreSet::template tile<0> Core;
   const int ntn = ceil_div(p.N, Core::BN);
-  const int n_mt = p.tiles ? max_tiles : ceil_div(p.n_rows, CoreSet::kKinds == 4 ? kind_height(p.direct_kind) : Core::BM);
+  const int n_mt = p.tiles ? max_tiles : ceil_div(p.n_rows, Core::BM >> (CoreSet::kKinds == 4 ? p.direct_kind : 0));
   if (n_mt == 0 || ntn == 0) return;
   auto kern = row_gemm_kernel<CoreSet, NB, EPI, B_KC>;
   static LdsAttr attr;
-  attr.ensure((const void*)kern, Core::LDS_BYTES);
+  constexpr int kLds = row_lds_bytes<CoreSet>();
+  attr.ensure((const void*)kern, kLds);
   ProfScope prof(label, st);
   // LDS-DMA path: whole bands of kBandRows row tiles, handed out in runs of 32 tiles to 8 XCDs
   const unsigned n_blocks = CoreSet::kKinds == 4 ? (unsigned)ceil_div(ceil_div(n_mt, kBandRows) * kBandRows * ntn, 256) * 256u
                                                  : (unsigned)(n_mt * ntn);
-  hipLaunchKernelGGL(kern, dim3(n_blocks), dim3(Core::NT), Core::LDS_BYTES, st, p);
+  hipLaunchKernelGGL(kern, dim3(n_blocks), dim3(Core::NT), kLds, st, p);
 }
 
 template <class Core, int NB>
@@ -584,11 +592,11 @@ struct FwdArgs {
 template <int PATH>
 static void expert_fwd_impl(const FwdArgs& a, hipStream_t st) {
   const bool shared = a.offsets == nullptr;
-  const int max_tiles = max_row_tiles(a.n_groups, a.n_rows, shared, plan_bm<PATH>());
+  const int max_tiles = max_row_tiles(a.n_groups, a.n_rows, shared, Cores<PATH>::BM, plan_mixed<PATH>());
   Plan pl = carve_plan(a.ws, a.n_groups, max_tiles);
   {
     ProfScope prof("plan_kernel", st);
-    hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(1024), 0, st, a.offsets, a.n_groups, a.n_rows, plan_bm<PATH>(), pl,
+    hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(1024), 0, st, a.offsets, a.n_groups, a.n_rows, Cores<PATH>::BM, plan_mixed<PATH>(), pl,
                        (int32_t*)nullptr, (int32_t*)nullptr);
   }
   // F4: dual GEMM with the SwiGLU epilogue, or (two-matrix expert, Wu == NULL) one GEMM with the GELU epilogue
@@ -638,14 +646,14 @@ static void expert_bwd_impl(const BwdArgs& a, hipStream_t st) {
   typedef Cores<PATH> C;
   const bool shared = a.offsets == nullptr;
   const size_t es = PATH == PATH_F32 ? 4 : 2;
-  const int max_tiles = max_row_tiles(a.n_groups, a.n_rows, shared, plan_bm<PATH>());
+  const int max_tiles = max_row_tiles(a.n_groups, a.n_rows, shared, Cores<PATH>::BM, plan_mixed<PATH>());
   Plan pl = carve_plan(a.ws, a.n_groups, max_tiles);
   const size_t act_rows = (size_t)(shared ? a.n_groups : 1) * a.n_rows;
   char* dG = (char*)a.ws + a.plan_sz;
   char* dU = dG + align_up(act_rows * a.F * es, 256);
   {
     ProfScope prof("plan_kernel", st);
-    hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(1024), 0, st, a.offsets, a.n_groups, a.n_rows, plan_bm<PATH>(), pl,
+    hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(1024), 0, st, a.offsets, a.n_groups, a.n_rows, Cores<PATH>::BM, plan_mixed<PATH>(), pl,
                        a.active_ids, a.n_active);
   }
   // B2a: dH = dYin Wd^T, epilogue turns it into dG, dU
@@ -723,7 +731,7 @@ static void expert_bwd_impl(const BwdArgs& a, hipStream_t st) {
 
 static size_t plan_size_for(int n_groups, int n_rows, bool shared) {
   // sized for the smallest row tile of any path, so the query does not depend on the path taken
-  const int bound = max_row_tiles(n_groups, n_rows, shared, 64) + max_row_tiles(n_groups, n_rows, shared, 0);
+  const int bound = max_row_tiles(n_groups, n_rows, shared, 64, true);
   return align_up(plan_bytes(n_groups, bound + 1), 256);
 }
 
@@ -951,7 +959,7 @@ static void router_fwd_impl(const moe_shape_t* s, const void* X, const void* Wr,
     B = WrP;
   }
   RowGemm p = {};
-  p.n_rows = s->T; p.direct_kind = 2;  // 64-row tiles: E is small, so the rows have to fill the chip
+  p.n_rows = s->T; p.direct_kind = 2;  // quarter-height tiles: E is small, so the rows have to fill the chip
   p.N = Ep; p.K = s->d; p.n_pairs = 1; p.n_segs = 1;
   p.A[0] = X; p.lda = s->d;
   p.B[0] = B; p.ldb = Ep;

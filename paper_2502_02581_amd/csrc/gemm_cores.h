@@ -1,5 +1,5 @@
-// Tile cores of the grouped GEMMs: an fp32 FMA core (correctness path for MOE_F32) and a
-// bf16 MFMA core for gfx950 (v_mfma_f32_32x32x16_bf16, operands staged through LDS).
+// Tile cores of the grouped GEMMs for gfx950: matrix-core tiles (bf16: v_mfma_f32_32x32x16_bf16, fp32:
+// v_mfma_f32_32x32x2_f32) with operands staged through LDS.
 //
 // Both cores compute, for one block, acc[nb][..] = sum over iterations of A_tile * B_tile(nb)
 // and hand groups of four consecutive columns to an epilogue functor:
@@ -63,85 +63,12 @@ __device__ __forceinline__ IterSrc<T, NB> iter_src(SegFn& segf, int it, int nk, 
   return s;
 }
 
-// ------------------------------------------------------------------------------ fp32 core
-template <int NB, bool A_KC, bool B_KC>
-struct F32Core {
-  typedef float T;
-  static constexpr int BM = 64, BN = 64, BK = 16, NT = 256;
-  static constexpr int LD = 64 + 4;
-  static constexpr int LDS_BYTES = (BK * LD + NB * BK * LD) * 4;
-
-  template <class SegFn, class Epi>
-  __device__ static void run(char* smem, int n_segs, int nk, SegFn segf, int64_t lda, int64_t ldb, int m_valid,
-                             int n_valid, Epi epi, const RowMap& amap) {
-    const int n_iters = n_segs * nk;
-    auto src = [&](int it) { return iter_src<float, NB, A_KC, B_KC>(segf, it, nk, BK, lda, ldb); };
-    float* As = (float*)smem;            // [BK][LD]  (k major)
-    float* Bs = As + BK * LD;            // [NB][BK][LD]
-    const int tid = threadIdx.x;
-    const int ty = tid / 16, tx = tid % 16;
-    float acc[NB][4][4];
-#pragma unroll
-    for (int nb = 0; nb < NB; nb++)
-#pragma unroll
-      for (int i = 0; i < 4; i++)
-#pragma unroll
-        for (int j = 0; j < 4; j++) acc[nb][i][j] = 0.f;
-
-    for (int it = 0; it < n_iters; it++) {
-      IterSrc<float, NB> s = src(it);
-      for (int idx = tid; idx < BM * BK; idx += NT) {
-        int m, k;
-        if (A_KC) { m = idx / BK; k = idx % BK; } else { k = idx / BM; m = idx % BM; }
-        float v = 0.f;
-        if (m < m_valid && k < s.k_left) v = A_KC ? s.a[amap(m) * lda + k] : s.a[(int64_t)k * lda + m];
-        As[k * LD + m] = v;
-      }
-#pragma unroll
-      for (int nb = 0; nb < NB; nb++)
-        for (int idx = tid; idx < BN * BK; idx += NT) {
-          int n, k;
-          if (B_KC) { n = idx / BK; k = idx % BK; } else { k = idx / BN; n = idx % BN; }
-          float v = 0.f;
-          if (n < n_valid && k < s.k_left) v = B_KC ? s.b[nb][(int64_t)n * ldb + k] : s.b[nb][(int64_t)k * ldb + n];
-          Bs[(nb * BK + k) * LD + n] = v;
-        }
-      __syncthreads();
-#pragma unroll
-      for (int k = 0; k < BK; k++) {
-        float a[4], b[NB][4];
-#pragma unroll
-        for (int i = 0; i < 4; i++) a[i] = As[k * LD + ty * 4 + i];
-#pragma unroll
-        for (int nb = 0; nb < NB; nb++)
-#pragma unroll
-          for (int j = 0; j < 4; j++) b[nb][j] = Bs[(nb * BK + k) * LD + tx * 4 + j];
-#pragma unroll
-        for (int nb = 0; nb < NB; nb++)
-#pragma unroll
-          for (int i = 0; i < 4; i++)
-#pragma unroll
-            for (int j = 0; j < 4; j++) acc[nb][i][j] = fmaf(a[i], b[nb][j], acc[nb][i][j]);
-      }
-      __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-      float vals[NB][4];
-#pragma unroll
-      for (int nb = 0; nb < NB; nb++)
-#pragma unroll
-        for (int j = 0; j < 4; j++) vals[nb][j] = acc[nb][i][j];
-      epi(ty * 4 + i, tx * 4, vals);
-    }
-  }
-};
-
 // ------------------------------------------------------------------------------ bf16 MFMA core
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(4))) short short4_t;
 typedef __attribute__((ext_vector_type(8))) short short8_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
 // LDS layouts (bf16 elements), BK = 64:
 //  K-contiguous operand: [rows][64], the eight 16-byte pieces of a row are XOR-swizzled with
@@ -159,6 +86,7 @@ struct MfmaCore {
   static constexpr int B_ELEMS = B_KC ? BN * BK : BK * (BN + PAD);
   static constexpr int STAGE_ELEMS = A_ELEMS + NB * B_ELEMS;
   static constexpr int LDS_BYTES = 2 * STAGE_ELEMS * 2;  // two stages
+  static constexpr int BLOCKS_PER_CU = 1;
   static constexpr int A_VEC = (BM * BK / 8 + NT - 1) / NT;
   static constexpr int B_VEC = (BN * BK / 8 + NT - 1) / NT;
   static_assert(WM * WN == 4, "four wavefronts per block");
@@ -327,24 +255,37 @@ struct MfmaCore {
   }
 };
 
-// ------------------------------------------------------------------ bf16 MFMA core, LDS DMA loads
-// Same math as MfmaCore, but tiles travel HBM/L2 -> LDS directly (buffer_load_dwordx4 ... lds),
+// ------------------------------------------------------------------ MFMA core, LDS DMA loads
+// Tiles travel HBM/L2 -> LDS directly (buffer_load_dwordx4 ... lds),
 // so no registers stage them.  Lane l of a wave-wide load lands at lds_base + 16*l, which fixes
 // each tile to whole 1 KB pieces per instruction; the swizzles are applied on the global side
 // (which 16-byte piece a lane fetches).  Out-of-range pieces read as zero through the buffer
-// descriptor's num_records, which provides the zero fill of ragged row and K tails.
-// Requires K-contiguous operands to have K % 64 == 0 (a K tail inside a row cannot be masked).
+// descriptor's num_records, which provides the zero fill of ragged row tails and, for operands whose
+// rows are K values, of the K tail.  A K tail inside the rows of a K-contiguous operand is masked with
+// KTAIL: the lanes whose piece lies at or beyond K fetch from an offset no descriptor reaches.
 //
-// LDS layouts (bf16 elements), BK = 64, no padding:
-//  K-contiguous operand [rows][64]: 16-byte piece c of a row sits at position c ^ ((row/2)%8), so
+// Types: bf16 (v_mfma_f32_32x32x16_bf16) and fp32 (v_mfma_f32_32x32x2_f32: fp32 products and sums).  The
+// geometry is the same in bytes: a tile row is 128 bytes of K (64 bf16 or 32 fp32 values), a k-step is
+// 32 bytes of them, and a lane's fragment of a k-step is 16 bytes.  In fp32 the four values of a
+// fragment feed four MFMAs, MFMA j taking value j of both half-waves (k = 8 ks + j and 8 ks + 4 + j).
+//
+// LDS layouts, BK = 128 bytes of K, no padding:
+//  K-contiguous operand [rows][BK]: 16-byte piece c of a row sits at position c ^ ((row/2)%8), so
 //    that the 16 rows one phase of a 16-byte-per-lane read touches cover all banks once.
-//  row-contiguous operand [64 k][ROWS]: piece c (8 columns) of k-row k sits at position
-//    c ^ (4*(k%4)), which spreads the four k rows of a transposing read over all banks.
-template <int BM_, int BN_, int NB, bool A_KC, bool B_KC, int WM_ = 2, int WN_ = 2, int DEPTH = 1>
+//  row-contiguous operand [BK][ROWS]: bf16: piece c (8 columns) of k-row k sits at position
+//    c ^ (4*(k%4)), which spreads the four k rows of a transposing read over all banks.  fp32: the
+//    fragment is read value by value; piece c (4 columns) sits at c ^ (8*((k/4)%2)), so that the two
+//    half-waves, four k rows apart, use different banks.
+template <typename T_, int BM_, int BN_, int NB, bool A_KC, bool B_KC, int WM_ = 2, int WN_ = 2, int DEPTH = 1,
+          bool KTAIL = false>
 struct MfmaDmaCore {
-  typedef bf16_t T;
-  static constexpr int BM = BM_, BN = BN_, BK = 64;
-  static constexpr int KS = BK / 16;  // MFMA k-steps per tile slot
+  typedef T_ T;
+  static constexpr int ES = sizeof(T);
+  static constexpr int PE = 16 / ES;  // elements per 16-byte piece
+  static constexpr int BM = BM_, BN = BN_, BK = 8 * PE;
+  static constexpr int KS = 4;        // MFMA k-steps per tile slot
+  static constexpr int SUB = ES == 4 ? 4 : 1;  // MFMAs per accumulator tile and k-step
+  typedef std::conditional_t<ES == 4, f32x4_t, bf16x8_t> frag_t;
   static constexpr int WM = WM_, WN = WN_;
   static constexpr int NW = WM * WN, NT = 64 * NW;  // wavefronts and threads per block
   static constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
@@ -365,17 +306,21 @@ struct MfmaDmaCore {
   static constexpr int A_SLOTS = DEPTH == 0 ? 1 : DEPTH == 1 ? 3 : DEPTH + 1;
   static constexpr int B_SLOTS = DEPTH == 0 ? 1 : DEPTH == 1 ? 2 : DEPTH + 1;
   static constexpr int B_SET_ELEMS = NB * B_ELEMS;
-  static constexpr int TILE_BYTES = (A_SLOTS * A_ELEMS + B_SLOTS * B_SET_ELEMS) * 2;
+  static constexpr int TILE_BYTES = (A_SLOTS * A_ELEMS + B_SLOTS * B_SET_ELEMS) * ES;
   static constexpr int STAGING_BYTES = NW * NB * 32 * ((BN_ / WN_) + 4) * 4;  // epilogue, see run()
   static constexpr int LDS_BYTES = TILE_BYTES > STAGING_BYTES ? TILE_BYTES : STAGING_BYTES;
-  static constexpr int A_NI = BM * BK / (512 * NW), B_NI = BN * BK / (512 * NW);  // wave-wide loads per wave and tile
-  static constexpr int PR_KC = BK / 8;  // 16-byte pieces per row of a K-contiguous tile
+  // blocks per CU the register allocation aims at (LDS allows as many)
+  static constexpr int BLOCKS_PER_CU = LDS_BYTES > 80 * 1024 ? 1 : NB * TM * TN <= 4 ? 2 : 1;
+  static constexpr int A_NI = BM / (8 * NW), B_NI = BN / (8 * NW);  // wave-wide loads per wave and tile
+  static constexpr int PR_KC = 8;  // 16-byte pieces per row of a K-contiguous tile
   static_assert(NW == 4 || NW == 8, "four or eight wavefronts per block");
-  static_assert(BM * BK % (512 * NW) == 0 && BN * BK % (512 * NW) == 0,
+  static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0,
                 "every wave issues the same number of 1 KB loads per tile");
   static_assert(BM % (32 * WM) == 0 && BN % (32 * WN) == 0, "wave tile must be a multiple of 32");
-  static_assert((A_KC || BM % 128 == 0) && (B_KC || BN % 128 == 0),
+  static_assert((A_KC || BM * ES % 256 == 0) && (B_KC || BN * ES % 256 == 0),
                 "swizzle of row-contiguous tiles needs >= 16 pieces per k row");
+  static_assert(ES == 2 || ((A_KC || BM <= 128) && (B_KC || BN <= 128)),
+                "fp32: the loads of a wave are a multiple of 8 k rows apart, so the swizzle is the same for all");
   static_assert(LDS_BYTES <= 160 * 1024, "LDS budget of a gfx950 CU");
   typedef __attribute__((address_space(3))) void* lds_vptr;
 
@@ -391,18 +336,24 @@ struct MfmaDmaCore {
     if (KC) {
       const int row = q / PR_KC, pos = q % PR_KC;
       const int c = pos ^ kc_swizzle(row);
-      return (uint32_t)row * ld * 2u + (uint32_t)c * 16u;
+      return (uint32_t)row * ld * ES + (uint32_t)c * 16u;
     } else {
-      constexpr int PR = ROWS / 8;
+      constexpr int PR = ROWS / PE;
       const int k = q / PR, pos = q % PR;
-      const int c = pos ^ (4 * (k & 3));
-      return (uint32_t)k * ld * 2u + (uint32_t)c * 16u;
+      const int c = pos ^ (ES == 4 ? 8 * ((k >> 2) & 1) : 4 * (k & 3));
+      return (uint32_t)k * ld * ES + (uint32_t)c * 16u;
     }
+  }
+  // first K value (within a tile) of the piece that a lane fetches from a K-contiguous operand: the same
+  // for all of its loads
+  __device__ static __forceinline__ int piece_k(int wave, int lane) {
+    const int q = wave * 64 + lane;
+    return ((q % PR_KC) ^ kc_swizzle(q / PR_KC)) * PE;
   }
   // rows of the memory operand (K-contiguous: tile rows; row-contiguous: k rows) between two
   // consecutive loads of a wave: NW waves x 1 KB of LDS tile per round
   template <int ROWS, bool KC>
-  __device__ static constexpr int load_stride() { return KC ? 512 * NW / BK : 512 * NW / ROWS; }
+  __device__ static constexpr int load_stride() { return KC ? 8 * NW : 64 * PE * NW / ROWS; }
 
   // One wave-wide 16-byte-per-lane load straight into LDS: the n-th 1 KB piece of this wave's share
   // of a tile.  Written as inline assembly so that the compiler does not serialise it against the
@@ -433,12 +384,20 @@ struct MfmaDmaCore {
   //                        (the swizzle repeats every 16 rows)
   //   row-contiguous tile: off[t] for the t-th group of 32 columns at k-step 0;
   //                        k-step ks = +16*ks*ROWS elements, second half of the 8 k = +4*ROWS
+  //                        (fp32: k-step ks = +8*ks*ROWS, value j = +j*ROWS)
   template <int ROWS, bool KC, int NTILE>
   __device__ static __forceinline__ void lane_offsets(int w0, int lane, int (&off)[4]) {
     if (KC) {
       const int row = w0 + (lane & 31);
 #pragma unroll
-      for (int ks = 0; ks < KS; ks++) off[ks] = row * BK + (((ks * 2 + (lane >> 5)) ^ kc_swizzle(row)) << 3);
+      for (int ks = 0; ks < KS; ks++) off[ks] = row * BK + ((ks * 2 + (lane >> 5)) ^ kc_swizzle(row)) * PE;
+    } else if (ES == 4) {
+      const int h = lane >> 5;  // half-wave: k values 8 ks + 4 h + 0..3
+#pragma unroll
+      for (int t = 0; t < 4; t++) {
+        const int col = w0 + t * 32 + (lane & 31);
+        off[t] = 4 * h * ROWS + ((((col >> 2) ^ (8 * h)) << 2) | (col & 3));
+      }
     } else {
       // transposing read: within 16 lanes, lane s points at 4 consecutive columns of k-row
       // kb + s/4, starting at column 4*(s%4); it receives k = kb..kb+3 of column s.
@@ -452,26 +411,29 @@ struct MfmaDmaCore {
     }
   }
   template <int ROWS, bool KC>
-  __device__ static __forceinline__ bf16x8_t frag(const bf16_t* tile, const int (&off)[4], int t, int ks) {
+  __device__ static __forceinline__ frag_t frag(const T* tile, const int (&off)[4], int t, int ks) {
     if (KC) {
       const uint4 v = *reinterpret_cast<const uint4*>(tile + off[ks] + t * 32 * BK);
-      return __builtin_bit_cast(bf16x8_t, v);
+      return __builtin_bit_cast(frag_t, v);
+    } else if constexpr (ES == 4) {
+      const T* p = tile + off[t] + ks * 8 * ROWS;
+      return frag_t{p[0], p[ROWS], p[2 * ROWS], p[3 * ROWS]};
     } else {
       typedef __attribute__((address_space(3))) short4_t* lds_ptr;
-      const bf16_t* p0 = tile + off[t] + ks * 16 * ROWS;
+      const T* p0 = tile + off[t] + ks * 16 * ROWS;
       short4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p0));
       short4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p0 + 4 * ROWS));
       short8_t both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-      return __builtin_bit_cast(bf16x8_t, both);
+      return __builtin_bit_cast(frag_t, both);
     }
   }
 
   struct Frags {
-    bf16x8_t a[TM], b[NB][TN];
+    frag_t a[TM], b[NB][TN];
   };
   // the r-th fragment load of a k-step: first the TM fragments of A, then the NB*TN of B
   static constexpr int kFragLoads = TM + NB * TN;
-  __device__ static __forceinline__ void load_frag_n(const bf16_t* As, const bf16_t* Bs, const int (&ao)[4],
+  __device__ static __forceinline__ void load_frag_n(const T* As, const T* Bs, const int (&ao)[4],
                                                      const int (&bo)[4], int ks, int r, Frags& f) {
     if (r < TM) {
       f.a[r] = frag<BM, A_KC>(As, ao, r, ks);
@@ -484,19 +446,31 @@ struct MfmaDmaCore {
   // the K loop is then exactly the order written in run() (LDS reads, tile loads and MFMAs
   // interleaved by hand), the compiler only allocates registers and inserts the waits.
   // Operands exchanged: result register r of lane l is C[m = l%32][n = 8*(r/4) + 4*(l/32) + r%4].
-  static constexpr int kMfma = NB * TM * TN;
+  // (fp32: all accumulator tiles take value 0 of the fragments, then value 1, ...)
+  static constexpr int kTiles = NB * TM * TN;
+  static constexpr int kMfma = kTiles * SUB;
   __device__ static __forceinline__ void mfma_n(f32x16_t (&acc)[NB][TM][TN], const Frags& f, int m) {
-    const int nb = m / (TM * TN), i = (m / TN) % TM, j = m % TN;
-    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0"
-                 : "+a"(acc[nb][i][j])
-                 : "v"(f.b[nb][j]), "v"(f.a[i])
-                 : "memory");
+    const int sub = m / kTiles, q = m % kTiles;
+    const int nb = q / (TM * TN), i = (q / TN) % TM, j = q % TN;
+    if constexpr (ES == 4) {
+      asm volatile("v_mfma_f32_32x32x2_f32 %0, %1, %2, %0"
+                   : "+a"(acc[nb][i][j])
+                   : "v"(f.b[nb][j][sub]), "v"(f.a[i][sub])
+                   : "memory");
+    } else {
+      asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0"
+                   : "+a"(acc[nb][i][j])
+                   : "v"(f.b[nb][j]), "v"(f.a[i])
+                   : "memory");
+    }
   }
 
   // Position of a stream of tile loads along K.  The K loop pays for every scalar instruction between
   // its MFMAs, so stepping is a handful of additions; the segment functor is consulted only where a
   // segment starts.  Once the product is exhausted the steps are zero and the byte counts stay at
   // zero: loads issued from there on read nothing and deliver zeros.
+  // byte offset beyond any descriptor's range (the operands of a tile span less than that: see the callers)
+  static constexpr uint32_t kNowhere = 0xffffff00u;
   struct Cursor {
     rsrc_t ad, bd[NB];      // buffer descriptors of the A tile and the B tile(s) at this position
     int64_t a_rem, b_rem;   // bytes from the tile origins to the end of the tile's valid data
@@ -509,7 +483,7 @@ struct MfmaDmaCore {
     const int32_t hi = (int32_t)(v >> 32);
     return hi < 0 ? 0 : hi > 0 ? -1 : (int)(uint32_t)v;
   }
-  __device__ static __forceinline__ rsrc_t make_desc(const bf16_t* base, int64_t bytes) {
+  __device__ static __forceinline__ rsrc_t make_desc(const T* base, int64_t bytes) {
     const uint64_t p = (uint64_t)base;
     rsrc_t r;
     r[0] = __builtin_amdgcn_readfirstlane((int)(uint32_t)p);
@@ -531,7 +505,7 @@ struct MfmaDmaCore {
     c.ki = 0;
     c.sg = sg;
     if (sg < n_segs && nk > 0) {
-      const SegSrc<bf16_t, NB> g = segf(sg);
+      const SegSrc<T, NB> g = segf(sg);
       c.a_rem = g.a_bytes;
       c.b_rem = g.b_bytes;
       c.ad = make_desc(g.a, c.a_rem);
@@ -544,8 +518,8 @@ struct MfmaDmaCore {
 #pragma unroll
       for (int nb = 0; nb < NB; nb++) asm volatile("" : "+s"(c.bd[nb]) : : "memory");
       asm volatile("s_nop 4" : "+s"(c.ad) : : "memory");
-      c.a_step = A_KC ? (int64_t)BK * 2 : (int64_t)BK * 2 * lda;
-      c.b_step = B_KC ? (int64_t)BK * 2 : (int64_t)BK * 2 * ldb;
+      c.a_step = A_KC ? (int64_t)BK * ES : (int64_t)BK * ES * lda;
+      c.b_step = B_KC ? (int64_t)BK * ES : (int64_t)BK * ES * ldb;
       c.k_left = g.k_len;
       c.k_step = BK;
     } else {
@@ -585,7 +559,7 @@ struct MfmaDmaCore {
                                              int /*m_valid*/, int /*n_valid*/, Epi epi, const RowMap& amap) {
     const int n_iters = n_segs * nk;
     MOE_PHASE(0);
-    bf16_t* lds = (bf16_t*)smem;
+    T* lds = (T*)smem;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm0 = (wave / WN) * (BM / WM), wn0 = (wave % WN) * (BN / WN);
@@ -618,7 +592,7 @@ struct MfmaDmaCore {
     uint32_t voa[A_NI], vob[B_NI];
 #pragma unroll
     for (int j = 0; j < A_NI; j++)
-      voa[j] = piece_offset<BM, A_KC>(wave, lane, (uint32_t)lda) + (uint32_t)(j * load_stride<BM, A_KC>()) * (uint32_t)lda * 2u;
+      voa[j] = piece_offset<BM, A_KC>(wave, lane, (uint32_t)lda) + (uint32_t)(j * load_stride<BM, A_KC>()) * (uint32_t)lda * ES;
     if constexpr (A_KC) {
       // gathered A rows: the same pieces, from the rows the map names.  The descriptor then spans the
       // whole operand, so the rows beyond the tile's valid ones get an offset no descriptor reaches
@@ -628,26 +602,35 @@ struct MfmaDmaCore {
 #pragma unroll
         for (int j = 0; j < A_NI; j++) {
           const int r = row + j * load_stride<BM, A_KC>();
-          voa[j] = r < amap.rows ? (uint32_t)amap(r) * (uint32_t)lda * 2u + (uint32_t)c * 16u : 0xffffff00u;
+          voa[j] = r < amap.rows ? (uint32_t)amap(r) * (uint32_t)lda * ES + (uint32_t)c * 16u : kNowhere;
         }
       }
     }
 #pragma unroll
     for (int j = 0; j < B_NI; j++)
-      vob[j] = piece_offset<BN, B_KC>(wave, lane, (uint32_t)ldb) + (uint32_t)(j * load_stride<BN, B_KC>()) * (uint32_t)ldb * 2u;
+      vob[j] = piece_offset<BN, B_KC>(wave, lane, (uint32_t)ldb) + (uint32_t)(j * load_stride<BN, B_KC>()) * (uint32_t)ldb * ES;
     // LDS byte addresses: this wave's first piece of A slot 0 and of B slot 0
     const uint32_t lds_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
     const uint32_t lds_a0 = lds_addr + (uint32_t)wave * 1024u;
-    const uint32_t lds_b0 = lds_a0 + (uint32_t)(A_SLOTS * A_ELEMS * 2);
+    const uint32_t lds_b0 = lds_a0 + (uint32_t)(A_SLOTS * A_ELEMS * ES);
+    // KTAIL: all-ones-like offsets for the lanes whose piece lies at or beyond the K values that are left (one
+    // mask per stream of loads: the streams are at different iterations)
+    const int pk = piece_k(wave, lane);
+    uint32_t tail_a = 0, tail_b = 0;
     auto load_a = [&](const Cursor& c, int slot, int j) __attribute__((always_inline)) {
-      issue_one(c.ad, lds_a0 + (uint32_t)(slot * A_ELEMS * 2) + (uint32_t)(j * NW) * 1024u, voa[j]);
+      issue_one(c.ad, lds_a0 + (uint32_t)(slot * A_ELEMS * ES) + (uint32_t)(j * NW) * 1024u,
+                KTAIL && A_KC ? voa[j] | tail_a : voa[j]);
     };
     auto load_b = [&](const Cursor& c, int slot, int n) __attribute__((always_inline)) {
       const int nb = n / B_NI, j = n % B_NI;
-      issue_one(c.bd[nb], lds_b0 + (uint32_t)((slot * B_SET_ELEMS + nb * B_ELEMS) * 2) + (uint32_t)(j * NW) * 1024u, vob[j]);
+      issue_one(c.bd[nb], lds_b0 + (uint32_t)((slot * B_SET_ELEMS + nb * B_ELEMS) * ES) + (uint32_t)(j * NW) * 1024u,
+                KTAIL && B_KC ? vob[j] | tail_b : vob[j]);
     };
     // Loads beyond the last iteration still issue (the wait counts below stay constant and the K
     // loop free of branches): an exhausted cursor makes them read nothing.
+    auto mask = [&](const Cursor& c, uint32_t& tail) __attribute__((always_inline)) {
+      if (KTAIL) tail = pk < c.k_left ? 0u : kNowhere;
+    };
     auto start = [&](Cursor& c) __attribute__((always_inline)) { seek(c, segf, 0, n_segs, nk, lda, ldb); };
     auto step = [&](Cursor& c) __attribute__((always_inline)) { next(c, segf, n_segs, nk, lda, ldb); };
 
@@ -665,6 +648,8 @@ struct MfmaDmaCore {
       start(s0);
       auto issue_tile = [&](int it) __attribute__((always_inline)) {
         const int slot = it % (DEPTH + 1);
+        mask(s0, tail_a);
+        tail_b = tail_a;
 #pragma unroll
         for (int j = 0; j < A_NI; j++) load_a(s0, slot, j);
 #pragma unroll
@@ -683,8 +668,8 @@ struct MfmaDmaCore {
         __syncthreads();
         issue_tile(it + DEPTH);
         const int slot = it % (DEPTH + 1);
-        const bf16_t* As = lds + slot * A_ELEMS;
-        const bf16_t* Bs = lds + A_SLOTS * A_ELEMS + slot * B_SET_ELEMS;
+        const T* As = lds + slot * A_ELEMS;
+        const T* Bs = lds + A_SLOTS * A_ELEMS + slot * B_SET_ELEMS;
 #pragma unroll
         for (int ks = 0; ks < KS; ks++) {
           Frags f;
@@ -701,6 +686,8 @@ struct MfmaDmaCore {
       zero_acc();
       for (int it = 0; it < n_iters; it++) {
         if (it > 0) __syncthreads();
+        mask(s0, tail_a);
+        tail_b = tail_a;
 #pragma unroll
         for (int j = 0; j < A_NI; j++) load_a(s0, 0, j);
 #pragma unroll
@@ -709,7 +696,7 @@ struct MfmaDmaCore {
         __syncthreads();
 #pragma unroll
         for (int ks = 0; ks < KS; ks++) {
-          if (ks * 16 >= s0.k_left) continue;  // uniform: the remaining k rows of the tile are zero
+          if (ks * 2 * PE >= s0.k_left) continue;  // uniform: the remaining k rows of the tile are zero
           Frags f;
 #pragma unroll
           for (int r = 0; r < kFragLoads; r++) load_frag_n(lds, lds + A_SLOTS * A_ELEMS, ao, bo, ks, r, f);
@@ -722,6 +709,8 @@ struct MfmaDmaCore {
     Cursor s1, s2;  // s1: the B tiles of iteration it + 1; s2: the A tile of iteration it + 2
     start(s1);
     start(s2);
+    mask(s1, tail_b);
+    mask(s2, tail_a);
     if (n_iters > 0) {
 #pragma unroll
       for (int j = 0; j < A_NI; j++) load_a(s2, 0, j);
@@ -729,9 +718,12 @@ struct MfmaDmaCore {
       for (int n = 0; n < kLoadsB; n++) load_b(s1, 0, n);
       step(s1);
       step(s2);
+      mask(s1, tail_b);
+      mask(s2, tail_a);
 #pragma unroll
       for (int j = 0; j < A_NI; j++) load_a(s2, 1, j);
       step(s2);
+      mask(s2, tail_a);
     }
     zero_acc();
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -759,10 +751,10 @@ struct MfmaDmaCore {
       const int a_nxt = a_cur == A_SLOTS - 1 ? 0 : a_cur + 1;   // A(t+1)
       const int a_nn = a_nxt == A_SLOTS - 1 ? 0 : a_nxt + 1;    // A(t+2) goes here
       const int b_nxt = b_cur ^ 1;
-      const bf16_t* As = lds + a_cur * A_ELEMS;
-      const bf16_t* Bs = lds + A_SLOTS * A_ELEMS + b_cur * B_SET_ELEMS;
-      const bf16_t* An = lds + a_nxt * A_ELEMS;
-      const bf16_t* Bn = lds + A_SLOTS * A_ELEMS + b_nxt * B_SET_ELEMS;
+      const T* As = lds + a_cur * A_ELEMS;
+      const T* Bs = lds + A_SLOTS * A_ELEMS + b_cur * B_SET_ELEMS;
+      const T* An = lds + a_nxt * A_ELEMS;
+      const T* Bn = lds + A_SLOTS * A_ELEMS + b_nxt * B_SET_ELEMS;
 #pragma unroll
       for (int ks = 0; ks < KS; ks++) {
 #pragma unroll
@@ -800,6 +792,8 @@ struct MfmaDmaCore {
       }
       step(s1);
       step(s2);
+      mask(s1, tail_b);
+      mask(s2, tail_a);
       a_cur = a_nxt;
       b_cur = b_nxt;
     }

@@ -9,14 +9,12 @@ namespace moe {
 struct RowTile {
   int32_t group;     // expert that owns the rows
   int32_t row0_in;   // first row in the [n_rows, .] input/output of the call
-  int32_t rows;      // valid rows (<= tile height) in bits 0..15, tile kind in bits 16..17
+  int32_t rows;      // valid rows (<= tile height) in bits 0..15, tile kind in bits 16..17 (height: that of the full tile >> kind)
   int32_t row0_out;  // first row in the per-group saved activations (differs in shared mode)
 };
 
 __host__ __device__ inline int tile_rows(const RowTile& t) { return t.rows & 0xffff; }
 __host__ __device__ inline int tile_kind(const RowTile& t) { return (t.rows >> 16) & 3; }
-// heights of the tile kinds of the mixed-height plan (kind 0 is the full tile)
-__host__ __device__ inline int kind_height(int kind) { return 256 >> kind; }
 // row tiles per band of the XCD-aware tile order of the LDS-DMA path
 constexpr int kBandRows = 4;
 
@@ -47,7 +45,7 @@ struct RowGemm {
   const RowTile* tiles;     // NULL: direct tiling of n_rows rows, single group 0
   const int32_t* n_tiles;
   int32_t n_rows;
-  int32_t direct_kind;      // tiles == NULL on the LDS-DMA path: tile kind (height 256 >> kind) of the direct tiling
+  int32_t direct_kind;      // tiles == NULL on the LDS-DMA path: tile kind (height: that of the full tile >> kind) of the direct tiling
   int32_t N, K;
   int32_t n_pairs, n_segs;
   const void* A[2];         // per pair; element (row, k) at A + seg*a_seg + row*lda + k

@@ -25,6 +25,13 @@ def test_descriptor_written_by_vector_instruction_is_flagged():
     assert asm_check.check_descriptor_hazards(_asm("\tv_add_co_u32_e64 v1, s[4:5], v2, v3", "\ts_nop 0", LOAD))
 
 
+def test_matrix_operand_written_right_before_is_flagged():
+    mfma = "\tv_mfma_f32_32x32x2_f32 a[0:15], v4, v9, a[0:15]"
+    assert len(asm_check.check_mfma_sources(_asm("\tv_mov_b32_e32 v9, v1", "\ts_nop 0", mfma))) == 1
+    assert asm_check.check_mfma_sources(_asm("\tv_mov_b32_e32 v9, v1", "\ts_nop 1", mfma)) == []
+    assert asm_check.check_mfma_sources(_asm("\tds_read_b32 v9, v1", "\ts_waitcnt lgkmcnt(0)", mfma)) == []
+
+
 def test_enough_wait_states_or_other_registers_pass():
     ok = _asm("\tv_readlane_b32 s6, v106, 55", "\ts_mov_b32 m0, s3", "\ts_nop 4", LOAD)       # 1 + 5 wait states
     assert asm_check.check_descriptor_hazards(ok) == []

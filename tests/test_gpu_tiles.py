@@ -1,0 +1,71 @@
+"""GPU: the expert calls at the edges of their tiles, group by group against products in fp64.
+
+Row counts straddle every tile height and its remainder rule, hidden sizes and widths end inside a K step and
+inside a column tile.  Tolerances (2-norm of the error over the 2-norm of the result): a value passes at most five
+roundings of relative size 2^-9 in bf16 on its way (operand, activation, its derivative, product, store):
+sqrt(5) * 2^-9 / sqrt(3) = 2.5e-3, and twice that for correlated ones; in fp32 the sums of K <= 520 terms contribute
+sqrt(K) * 2^-24 each, 1.4e-6, over three products: 5e-6.
+"""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"f32": 5e-6, "bf16": 5e-3}
+# rows per group: empty, single, both sides of every tile height, several full tiles with a remainder
+ROWS = [1, 0, 15, 17, 33, 64, 65, 95, 97, 0, 128, 129, 161, 192, 193, 255, 257, 449, 600]
+DIMS = [(72, 104), (136, 200), (264, 520), (64, 192), (320, 64)]
+
+
+def rel(got, ref):
+    return float((got.double().cpu() - ref).norm() / ref.norm()) if ref.numel() else 0.0
+
+
+@pytest.mark.parametrize("ffn", ["swiglu", "gelu"])
+@pytest.mark.parametrize("d,F", DIMS)
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_expert_tiles(dtype, d, F, ffn):
+    import paper_2502_02581_amd as moe
+
+    dev, E, n = "cuda:0", len(ROWS), sum(ROWS)
+    shape = moe.MoEShape(n, d, E, 1, F, dtype)
+    dt = shape.torch_dtype
+    g = torch.Generator().manual_seed(d * 1000 + F)
+    rnd = lambda std, *s: (torch.randn(*s, generator=g) * std).to(dt)
+    gated = ffn == "swiglu"
+    X, dY = rnd(1.0, n, d), rnd(1.0, n, d)
+    Wg, Wd = rnd(d ** -0.5, E, d, F), rnd(F ** -0.5, E, F, d)
+    Wu = rnd(d ** -0.5, E, d, F) if gated else None
+    off = torch.tensor([0] + ROWS).cumsum(0)
+    gpu = lambda t: None if t is None else t.to(dev)
+    new = lambda *s: torch.full(s, float("nan"), dtype=dt, device=dev)
+    G, U, H, Y, dX = new(n, F), new(n, F), new(n, F), new(n, d), new(n, d)
+    dWg, dWu, dWd = new(E, d, F), new(E, d, F), new(E, F, d)
+    ids, n_act = torch.empty(E, dtype=torch.int32, device=dev), torch.empty(1, dtype=torch.int32, device=dev)
+    ws = torch.empty(max(moe.moe_expert_fwd_workspace_bytes(shape, E, n, False),
+                         moe.moe_expert_bwd_workspace_bytes(shape, E, n, False)), dtype=torch.uint8, device=dev)
+    ws.fill_(0xff)   # NaNs: nothing may be read before it is written
+    offs, Xd, dYd, w = gpu(off.int()), gpu(X), gpu(dY), [gpu(Wg), gpu(Wu), gpu(Wd)]
+    moe.moe_expert_fwd(shape, E, offs, n, Xd, *w, G, U, H, Y, ws)
+    moe.moe_expert_bwd(shape, E, offs, n, Xd, *w, G, U, H, dYd, dX, ids, n_act, dWg, dWu, dWd, ws)
+    torch.cuda.synchronize()
+    active = [e for e in range(E) if ROWS[e]]
+    assert ids.tolist() == active + [-1] * (E - len(active)) and int(n_act) == len(active)
+    worst = {}
+    for slot, e in enumerate(active):
+        r = slice(int(off[e]), int(off[e + 1]))
+        x, dy = X[r].double(), dY[r].double()
+        x.requires_grad_(True)
+        ws_ = [t[e].double().requires_grad_(True) for t in ([Wg, Wu, Wd] if gated else [Wg, Wd])]
+        z = x @ ws_[0]
+        h = torch.nn.functional.silu(z) * (x @ ws_[1]) if gated else torch.nn.functional.gelu(z)
+        y = h @ ws_[-1]
+        y.backward(dy)
+        pairs = {"G": (G[r], z), "H": (H[r], h), "Y": (Y[r], y), "dX": (dX[r], x.grad), "dWg": (dWg[slot], ws_[0].grad),
+                 "dWd": (dWd[slot], ws_[-1].grad)}
+        if gated:
+            pairs["dWu"] = (dWu[slot], ws_[1].grad)
+        for k, (got, ref) in pairs.items():
+            worst[k] = max(worst.get(k, 0.0), rel(got, ref.detach()))
+    print(dtype, d, F, ffn, {k: f"{v:.1e}" for k, v in worst.items()})
+    assert all(v <= TOL[dtype] for v in worst.values()), worst
