@@ -28,8 +28,8 @@ __device__ __forceinline__ void block_scan_inclusive(int32_t* sc, int e) {
 
 // One block of 1024 threads; thread e owns group e.
 __global__ __launch_bounds__(1024) void plan_kernel(const int32_t* __restrict__ offsets, int n_groups,
-                                                    int n_rows, int BM, int mixed, Plan pl,
-                                                    int32_t* active_ids, int32_t* n_active) {
+                                                    int n_rows, int BM, Plan pl, int32_t* active_ids,
+                                                    int32_t* n_active) {
   __shared__ int32_t cnt[1024], sc[1024], ord[1024], st_[1024];
   const int e = threadIdx.x;
   int c = 0, st = 0;
@@ -72,24 +72,19 @@ __global__ __launch_bounds__(1024) void plan_kernel(const int32_t* __restrict__ 
   if (e < n_groups) pl.ginfo[rank] = make_int4(e, c, st, c > 0 ? sc[e] - 1 : -1);
   if (e == 0 && n_active) *n_active = total_active;
   __syncthreads();
-  // Row tiles of BM rows, groups in descending size.  mixed: full tiles of BM rows, and the remainder r of a
-  // group cut into tiles of BM/2, BM/4 and BM/8 rows so that little MFMA work is spent on padding; in
-  // eighths of BM: r > 6: one full tile; (5,6]: 4 + 2; (4,5]: 4 + 1; (3,4]: 4; (2,3]: 2 + 1; (1,2]: 2; (0,1]: 1.
+  // Row tiles, groups in descending size: full tiles of BM rows, and the remainder r of a group cut into tiles of
+  // BM/2, BM/4 and BM/8 rows so that little MFMA work is spent on padding; in eighths of BM: r > 6: one full tile; (5,6]: 4 + 2; (4,5]: 4 + 1; (3,4]: 4; (2,3]: 2 + 1; (1,2]: 2; (0,1]: 1.
   const int g = e < n_groups ? ord[e] : 0;
   const int cg = e < n_groups ? cnt[g] : 0;
   const int full = cg / BM;
   int k0 = -1, k1 = -1;  // kinds (heights BM >> kind) of the up to two remainder tiles
-  if (mixed) {
-    const int r8 = ((cg - full * BM) * 8 + BM - 1) / BM;  // eighths of BM, rounded up
-    if (r8 > 6) k0 = 0;
-    else if (r8 > 4) { k0 = 1; k1 = r8 == 6 ? 2 : 3; }
-    else if (r8 == 4) k0 = 1;
-    else if (r8 == 3) { k0 = 2; k1 = 3; }
-    else if (r8 == 2) k0 = 2;
-    else if (r8 == 1) k0 = 3;
-  } else if (cg > full * BM) {
-    k0 = 0;
-  }
+  const int r8 = ((cg - full * BM) * 8 + BM - 1) / BM;  // eighths of BM, rounded up
+  if (r8 > 6) k0 = 0;
+  else if (r8 > 4) { k0 = 1; k1 = r8 == 6 ? 2 : 3; }
+  else if (r8 == 4) k0 = 1;
+  else if (r8 == 3) { k0 = 2; k1 = 3; }
+  else if (r8 == 2) k0 = 2;
+  else if (r8 == 1) k0 = 3;
   const int nt = full + (k0 >= 0) + (k1 >= 0);
   sc[e] = nt;
   __syncthreads();
@@ -111,7 +106,7 @@ __global__ __launch_bounds__(1024) void plan_kernel(const int32_t* __restrict__ 
 }
 
 // ------------------------------------------------------------------------------- epilogues
-// W consecutive elements (W = 4 or 8) narrowed from / widened to fp32, one or two 16-byte accesses
+// W = 8 consecutive elements narrowed from / widened to fp32, one or two 16-byte accesses
 template <typename T, int W> struct Pack;
 template <int W> struct Pack<float, W> {
   __device__ static __forceinline__ void widen(const uint4&, float (&)[W]) {}  // (bf16 only)
@@ -133,49 +128,28 @@ template <int W> struct Pack<bf16_t, W> {
     uint32_t w[W / 2];
 #pragma unroll
     for (int i = 0; i < W / 2; i++) w[i] = f32x2_to_bf16x2(v[2 * i], v[2 * i + 1]);
-    if (W == 4) *reinterpret_cast<uint2*>(p) = make_uint2(w[0], w[1]);
-    else *reinterpret_cast<uint4*>(p) = make_uint4(w[0], w[1], w[W / 2 - 2], w[W / 2 - 1]);
+    *reinterpret_cast<uint4*>(p) = make_uint4(w[0], w[1], w[2], w[3]);
   }
   // the same with a streaming hint: for outputs that nothing on the chip reads again soon
   __device__ static __forceinline__ void store_nt(bf16_t* p, const float (&v)[W]) {
     typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
-    typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
     uint32_t w[W / 2];
 #pragma unroll
     for (int i = 0; i < W / 2; i++) w[i] = f32x2_to_bf16x2(v[2 * i], v[2 * i + 1]);
-    if (W == 4) {
-      u32x2 t = {w[0], w[1]};
-      __builtin_nontemporal_store(t, reinterpret_cast<u32x2*>(p));
-    } else {
-      u32x4 t = {w[0], w[1], w[W / 2 - 2], w[W / 2 - 1]};
-      __builtin_nontemporal_store(t, reinterpret_cast<u32x4*>(p));
-    }
+    const u32x4 t = {w[0], w[1], w[2], w[3]};
+    __builtin_nontemporal_store(t, reinterpret_cast<u32x4*>(p));
   }
-  // the same from a 16-byte piece that is already in registers (W == 8)
+  // the same from a 16-byte piece that is already in registers
   __device__ static __forceinline__ void widen(const uint4& t, float (&v)[W]) {
-    if constexpr (W == 8) {  // (cores that hand over four values at a time do their own loads)
-      const uint32_t w[4] = {t.x, t.y, t.z, t.w};
+    const uint32_t w[4] = {t.x, t.y, t.z, t.w};
 #pragma unroll
-      for (int i = 0; i < 4; i++) {
-        v[2 * i] = __uint_as_float(w[i] << 16);
-        v[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
-      }
-    }
-  }
-  __device__ static __forceinline__ void load(const bf16_t* p, float (&v)[W]) {
-    uint32_t w[W / 2];
-    if (W == 4) {
-      uint2 t = *reinterpret_cast<const uint2*>(p);
-      w[0] = t.x; w[1] = t.y;
-    } else {
-      uint4 t = *reinterpret_cast<const uint4*>(p);
-      w[0] = t.x; w[1] = t.y; w[W / 2 - 2] = t.z; w[W / 2 - 1] = t.w;
-    }
-#pragma unroll
-    for (int i = 0; i < W / 2; i++) {
+    for (int i = 0; i < 4; i++) {
       v[2 * i] = __uint_as_float(w[i] << 16);
       v[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
     }
+  }
+  __device__ static __forceinline__ void load(const bf16_t* p, float (&v)[W]) {
+    widen(*reinterpret_cast<const uint4*>(p), v);
   }
 };
 
@@ -268,7 +242,7 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm& p, const RowTile& t
     return s;
   };
   const int c_row0 = p.c_rows_out ? t.row0_out : t.row0_in;
-  // W consecutive columns of one row (W = 4 from the fp32 and general cores, 8 from the DMA core)
+  // W = 8 consecutive columns of one row
   // 16-byte pieces the epilogue reads at its own position, requested ahead of time by the LDS-DMA
   // core (bf16): the saved inputs of the activation's derivative, or the output to accumulate into
   constexpr int kAuxLoads = sizeof(T) != 2 ? 0 : EPI == EPI_SWIGLU_BWD ? 2 : (EPI == EPI_GELU_BWD || EPI == EPI_ADD) ? 1 : 0;
@@ -358,42 +332,35 @@ __global__ __launch_bounds__(CoreSet::template tile<0>::NT, CoreSet::template ti
   extern __shared__ __align__(16) char smem[];
   typedef typename CoreSet::template tile<0> Core0;
   const int ntn = (p.N + Core0::BN - 1) / Core0::BN;
-  int mt, nt;
-  if (CoreSet::kKinds == 4) {
-    // Blocks go to the XCDs round-robin (block b runs on XCD b % 8) and the 32 CUs of an XCD share
-    // one L2, so the 32 blocks an XCD holds at a time should read as few different operand tiles as
-    // possible.  Tiles are numbered band by band (a band: kBandRows consecutive row tiles), column
-    // by column within a band, and each XCD takes runs of 32 consecutive tiles: 4 row tiles x 8
-    // column tiles, 12 operand streams for 32 tiles.  What is left after the last whole round of 8 runs is
-    // cut into 8 equal runs, so that no XCD is a run ahead of another (a training step with 4 shared experts on a
-    // second stream, T = 4096, d = 2048: 2.40 -> 2.21 ms; launches of many rounds: the same).
-    const int per_band = kBandRows * ntn;
-    const int n_mt = p.tiles ? *p.n_tiles : (p.n_rows + (Core0::BM >> p.direct_kind) - 1) / (Core0::BM >> p.direct_kind);
-    const int total = (n_mt + kBandRows - 1) / kBandRows * per_band;
-    const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
-    const int whole = total >> 8, in_run = j & 31;
-    int q = ((j >> 5) * 8 + xcd) * 32 + in_run;
-    if ((j >> 5) >= whole) {
-      const int run = (total - (whole << 8) + 7) >> 3;
-      if ((j >> 5) > whole || in_run >= run) return;
-      q = (whole << 8) + xcd * run + in_run;
-      if (q >= total) return;
-    }
-    const int band = q / per_band, r = q - band * per_band;
-    mt = band * kBandRows + r % kBandRows;
-    nt = r / kBandRows;
-  } else {
-    mt = blockIdx.x / ntn;
-    nt = blockIdx.x % ntn;
+  // Blocks go to the XCDs round-robin (block b runs on XCD b % 8) and the 32 CUs of an XCD share
+  // one L2, so the 32 blocks an XCD holds at a time should read as few different operand tiles as
+  // possible.  Tiles are numbered band by band (a band: kBandRows consecutive row tiles), column
+  // by column within a band, and each XCD takes runs of 32 consecutive tiles: 4 row tiles x 8
+  // column tiles, 12 operand streams for 32 tiles.  What is left after the last whole round of 8 runs is
+  // cut into 8 equal runs, so that no XCD is a run ahead of another (a training step with 4 shared experts on a
+  // second stream, T = 4096, d = 2048: 2.40 -> 2.21 ms; launches of many rounds: the same).
+  const int per_band = kBandRows * ntn;
+  const int n_mt = p.tiles ? *p.n_tiles : (p.n_rows + (Core0::BM >> p.direct_kind) - 1) / (Core0::BM >> p.direct_kind);
+  const int total = (n_mt + kBandRows - 1) / kBandRows * per_band;
+  const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
+  const int whole = total >> 8, in_run = j & 31;
+  int q = ((j >> 5) * 8 + xcd) * 32 + in_run;
+  if ((j >> 5) >= whole) {
+    const int run = (total - (whole << 8) + 7) >> 3;
+    if ((j >> 5) > whole || in_run >= run) return;
+    q = (whole << 8) + xcd * run + in_run;
+    if (q >= total) return;
   }
+  const int band = q / per_band, r = q - band * per_band;
+  const int mt = band * kBandRows + r % kBandRows, nt = r / kBandRows;
   RowTile t;
   if (p.tiles) {
     if (mt >= *p.n_tiles) return;
     t = p.tiles[mt];
   } else {
-    // direct tiling: tiles of one height (on the LDS-DMA path the caller may pick a shorter kind, so
-    // that a GEMM with few column tiles still fills the chip)
-    const int kind = CoreSet::kKinds == 4 ? p.direct_kind : 0;
+    // direct tiling: tiles of one height (the caller may pick a shorter kind, so that a GEMM with few column
+    // tiles still fills the chip)
+    const int kind = p.direct_kind;
     const int bm = Core0::BM >> kind;
     t.group = 0;
     t.row0_in = mt * bm;
@@ -402,15 +369,11 @@ __global__ __launch_bounds__(CoreSet::template tile<0>::NT, CoreSet::template ti
     t.row0_out = t.row0_in;
   }
   MOE_TRACE_BEGIN();
-  if (CoreSet::kKinds == 1) {
-    row_gemm_tile<Core0, NB, EPI, B_KC>(p, t, nt, smem);
-  } else {
-    switch (tile_kind(t)) {  // uniform over the block
-      case 0: row_gemm_tile<Core0, NB, EPI, B_KC>(p, t, nt, smem); break;
-      case 1: row_gemm_tile<typename CoreSet::template tile<1>, NB, EPI, B_KC>(p, t, nt, smem); break;
-      case 2: row_gemm_tile<typename CoreSet::template tile<2>, NB, EPI, B_KC>(p, t, nt, smem); break;
-      default: row_gemm_tile<typename CoreSet::template tile<3>, NB, EPI, B_KC>(p, t, nt, smem); break;
-    }
+  switch (tile_kind(t)) {  // uniform over the block
+    case 0: row_gemm_tile<Core0, NB, EPI, B_KC>(p, t, nt, smem); break;
+    case 1: row_gemm_tile<typename CoreSet::template tile<1>, NB, EPI, B_KC>(p, t, nt, smem); break;
+    case 2: row_gemm_tile<typename CoreSet::template tile<2>, NB, EPI, B_KC>(p, t, nt, smem); break;
+    default: row_gemm_tile<typename CoreSet::template tile<3>, NB, EPI, B_KC>(p, t, nt, smem); break;
   }
   MOE_TRACE_ROW_TILE(EPI | (NB << 4) | ((int)B_KC << 8), nt | (tile_kind(t) << 8) | (tile_rows(t) << 16));
 }
@@ -471,9 +434,12 @@ __global__ __launch_bounds__(Core::NT, Core::BLOCKS_PER_CU) void w_gemm_kernel(W
 }
 
 // ------------------------------------------------------------------------------ host side
-// Three families of tile cores: fp32 (MOE_F32), the general bf16 MFMA core (any d, d_ff that are
-// multiples of 8) and the bf16 core with LDS DMA loads (d and d_ff multiples of 64).
-enum { PATH_F32 = 0, PATH_BF16 = 1, PATH_BF16_DMA = 2 };
+// Three families of tile cores: fp32 (MOE_F32), bf16 with d and d_ff multiples of 64, and bf16 with any
+// multiples of 8.  The last differs in one point: the row GEMMs mask the K tail of their K-contiguous
+// operands (a VALU instruction per tile load; the weight gradients have no such operands).  Before, such sizes
+// ran on 128 x 128 tiles staged through registers: forward + backward of T = 3001, d = 1000, d_ff = 1368,
+// 24 experts, top-3, one shared expert: 1.63 ms; on these cores 0.91 ms, with the same bits.
+enum { PATH_F32 = 0, PATH_BF16_TAIL = 1, PATH_BF16 = 2 };
 template <int PATH> struct Cores;
 template <> struct Cores<PATH_F32> {
   static constexpr int BM = 64, BN = 128;
@@ -486,10 +452,6 @@ template <> struct Cores<PATH_F32> {
   template <int NB, bool A_KC, bool B_KC> using core = MfmaDmaCore<float, 128, 128 / NB, NB, A_KC, B_KC, 2, 2, 1, true>;
 };
 template <> struct Cores<PATH_BF16> {
-  static constexpr int BM = 128, BN = 128;
-  template <int NB, bool A_KC, bool B_KC> using core = MfmaCore<128, 128, NB, A_KC, B_KC, 2, 2>;
-};
-template <> struct Cores<PATH_BF16_DMA> {
   static constexpr int BM = 256, BN = 256;
   // one block of 4 wavefronts (one per SIMD, each with a 128 x 128 share: the fewest LDS reads and
   // scalar instructions per MFMA, which is what the K loop is short of) computes 256 x 256 outputs
@@ -498,35 +460,30 @@ template <> struct Cores<PATH_BF16_DMA> {
   // weight gradients of groups with few rows: 128 x 128 outputs per product, one tile slot
   template <int NB> using core_light = MfmaDmaCore<bf16_t, 128, 128, NB, false, false, 2, 2, 0>;
 };
+template <> struct Cores<PATH_BF16_TAIL> : Cores<PATH_BF16> {};
 constexpr int kLightGroupRows = 256;  // groups up to this many rows take the light dW kernel
 constexpr int kLightReps = 2;         // column tiles per block of that kernel (1: +5 % time on the DeepSeek shape, 8: +3 %)
 
-// The tile cores a row-tiled GEMM launch may use: one for the fp32 and the general bf16 path, four
-// heights (256, 128, 64, 32 rows) for the DMA path so that ragged groups waste little MFMA work.
+// The tile cores a row-tiled GEMM launch may use: tile kinds of heights BM, BM/2, BM/4, BM/8, so that ragged
+// groups waste little MFMA work.
 template <int PATH, int NB, bool B_KC> struct RowCores {
-  static constexpr int kKinds = 1;
-  template <int KIND> using tile = typename Cores<PATH>::template core<NB, true, B_KC>;
+  // bf16: heights 256, 128, 64 and 32; the last two share the 64-row core (those tiles are bound by streaming the
+  // weights, not by MFMA work).  Pipeline depth by height: the 128-row tile fits 3 slots per operand, the
+  // 64-row one 4.
+  template <int KIND>
+  using tile = MfmaDmaCore<bf16_t, (KIND == 0 ? 256 : KIND == 1 ? 128 : 64), 256 / NB, NB, true, B_KC, 2, 2,
+                           (KIND == 0 ? 1 : KIND == 1 ? 2 : 3), PATH == PATH_BF16_TAIL>;
 };
 template <int NB, bool B_KC> struct RowCores<PATH_F32, NB, B_KC> {
-  static constexpr int kKinds = 4;
   // heights 64, 32, 16, 8
   template <int KIND>
   using tile = std::conditional_t<(KIND == 0 || NB == 2), MfmaDmaCore<float, 64, 128 / NB, NB, true, B_KC, 2, 2, 2, true>,
                                   MfmaDmaCore<float, 32, 128, NB == 2 ? 1 : NB, true, B_KC, 1, 4, 2, true>>;
 };
-template <int NB, bool B_KC> struct RowCores<PATH_BF16_DMA, NB, B_KC> {
-  static constexpr int kKinds = 4;
-  // tile kinds 0..3 are cut for 256, 128, 64 and 32 rows; the last two share the 64-row core (those
-  // tiles are bound by streaming the weights, not by MFMA work).  Pipeline depth by height: the
-  // 128-row tile fits 3 slots per operand, the 64-row one 4.
-  template <int KIND>
-  using tile = MfmaDmaCore<bf16_t, (KIND == 0 ? 256 : KIND == 1 ? 128 : 64), 256 / NB, NB, true, B_KC, 2, 2,
-                           (KIND == 0 ? 1 : KIND == 1 ? 2 : 3)>;
-};
 
 static int pick_path(const moe_shape_t* s) {
   if (s->dtype == MOE_F32) return PATH_F32;
-  return (s->d % 64 == 0 && s->d_ff % 64 == 0) ? PATH_BF16_DMA : PATH_BF16;
+  return (s->d % 64 == 0 && s->d_ff % 64 == 0) ? PATH_BF16 : PATH_BF16_TAIL;
 }
 
 static inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
@@ -546,34 +503,30 @@ struct LdsAttr {
   }
 };
 
-// upper bound of the row tiles the plan kernel may emit (mixed heights: at most two remainder tiles per group)
-static int max_row_tiles(int n_groups, int n_rows, bool shared, int BM, bool mixed) {
-  if (mixed) return shared ? n_groups * (n_rows / BM + 2) : n_rows / BM + 2 * n_groups;
-  return shared ? n_groups * ceil_div(n_rows, BM) : ceil_div(n_rows, BM) + n_groups;
+// upper bound of the row tiles the plan kernel may emit (at most two remainder tiles per group)
+static int max_row_tiles(int n_groups, int n_rows, bool shared, int BM) {
+  return shared ? n_groups * (n_rows / BM + 2) : n_rows / BM + 2 * n_groups;
 }
-template <int PATH> constexpr bool plan_mixed() { return PATH != PATH_BF16; }
 
 // LDS of a launch: one block may run any of the tile kinds
 template <class CoreSet> constexpr int row_lds_bytes() {
   constexpr int n0 = CoreSet::template tile<0>::LDS_BYTES;
-  if constexpr (CoreSet::kKinds == 1) return n0;
-  else return std::max({n0, CoreSet::template tile<1>::LDS_BYTES, CoreSet::template tile<2>::LDS_BYTES, CoreSet::template tile<3>::LDS_BYTES});
+  return std::max({n0, CoreSet::template tile<1>::LDS_BYTES, CoreSet::template tile<2>::LDS_BYTES, CoreSet::template tile<3>::LDS_BYTES});
 }
 
 template <class CoreSet, int NB, int EPI, bool B_KC>
 static void launch_row(const char* label, const RowGemm& p, int max_tiles, hipStream_t st) {
   typedef typename CoreSet::template tile<0> Core;
   const int ntn = ceil_div(p.N, Core::BN);
-  const int n_mt = p.tiles ? max_tiles : ceil_div(p.n_rows, Core::BM >> (CoreSet::kKinds == 4 ? p.direct_kind : 0));
+  const int n_mt = p.tiles ? max_tiles : ceil_div(p.n_rows, Core::BM >> p.direct_kind);
   if (n_mt == 0 || ntn == 0) return;
   auto kern = row_gemm_kernel<CoreSet, NB, EPI, B_KC>;
   static LdsAttr attr;
   constexpr int kLds = row_lds_bytes<CoreSet>();
   attr.ensure((const void*)kern, kLds);
   ProfScope prof(label, st);
-  // LDS-DMA path: whole bands of kBandRows row tiles, handed out in runs of 32 tiles to 8 XCDs
-  const unsigned n_blocks = CoreSet::kKinds == 4 ? (unsigned)ceil_div(ceil_div(n_mt, kBandRows) * kBandRows * ntn, 256) * 256u
-                                                 : (unsigned)(n_mt * ntn);
+  // whole bands of kBandRows row tiles, handed out in runs of 32 tiles to 8 XCDs
+  const unsigned n_blocks = (unsigned)ceil_div(ceil_div(n_mt, kBandRows) * kBandRows * ntn, 256) * 256u;
   hipLaunchKernelGGL(kern, dim3(n_blocks), dim3(Core::NT), kLds, st, p);
 }
 
@@ -603,11 +556,11 @@ struct FwdArgs {
 template <int PATH>
 static void expert_fwd_impl(const FwdArgs& a, hipStream_t st) {
   const bool shared = a.offsets == nullptr;
-  const int max_tiles = max_row_tiles(a.n_groups, a.n_rows, shared, Cores<PATH>::BM, plan_mixed<PATH>());
+  const int max_tiles = max_row_tiles(a.n_groups, a.n_rows, shared, Cores<PATH>::BM);
   Plan pl = carve_plan(a.ws, a.n_groups, max_tiles);
   {
     ProfScope prof("plan_kernel", st);
-    hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(1024), 0, st, a.offsets, a.n_groups, a.n_rows, Cores<PATH>::BM, plan_mixed<PATH>(), pl,
+    hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(1024), 0, st, a.offsets, a.n_groups, a.n_rows, Cores<PATH>::BM, pl,
                        (int32_t*)nullptr, (int32_t*)nullptr);
   }
   // F4: dual GEMM with the SwiGLU epilogue, or (two-matrix expert, Wu == NULL) one GEMM with the GELU epilogue
@@ -657,14 +610,14 @@ static void expert_bwd_impl(const BwdArgs& a, hipStream_t st) {
   typedef Cores<PATH> C;
   const bool shared = a.offsets == nullptr;
   const size_t es = PATH == PATH_F32 ? 4 : 2;
-  const int max_tiles = max_row_tiles(a.n_groups, a.n_rows, shared, Cores<PATH>::BM, plan_mixed<PATH>());
+  const int max_tiles = max_row_tiles(a.n_groups, a.n_rows, shared, Cores<PATH>::BM);
   Plan pl = carve_plan(a.ws, a.n_groups, max_tiles);
   const size_t act_rows = (size_t)(shared ? a.n_groups : 1) * a.n_rows;
   char* dG = (char*)a.ws + a.plan_sz;
   char* dU = dG + align_up(act_rows * a.F * es, 256);
   {
     ProfScope prof("plan_kernel", st);
-    hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(1024), 0, st, a.offsets, a.n_groups, a.n_rows, Cores<PATH>::BM, plan_mixed<PATH>(), pl,
+    hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(1024), 0, st, a.offsets, a.n_groups, a.n_rows, Cores<PATH>::BM, pl,
                        a.active_ids, a.n_active);
   }
   // B2a: dH = dYin Wd^T, epilogue turns it into dG, dU
@@ -708,7 +661,7 @@ static void expert_bwd_impl(const BwdArgs& a, hipStream_t st) {
   v.C[0] = a.dWg; v.C[1] = a.dWu; v.c_slot = (int64_t)a.d * a.F;
   w.k_min = v.k_min = 1;
   w.k_max = v.k_max = 0x7fffffff;
-  if constexpr (PATH == PATH_BF16_DMA) {
+  if constexpr (PATH != PATH_F32) {
     // groups with few rows are bound by writing their gradient, not by MFMA work: they go to a
     // kernel that keeps several blocks per CU in flight
     if (!shared) {
@@ -742,7 +695,7 @@ static void expert_bwd_impl(const BwdArgs& a, hipStream_t st) {
 
 static size_t plan_size_for(int n_groups, int n_rows, bool shared) {
   // sized for the smallest row tile of any path, so the query does not depend on the path taken
-  const int bound = max_row_tiles(n_groups, n_rows, shared, 64, true);
+  const int bound = max_row_tiles(n_groups, n_rows, shared, 64);
   return align_up(plan_bytes(n_groups, bound + 1), 256);
 }
 
@@ -800,8 +753,8 @@ extern "C" int moe_expert_fwd(const moe_shape_t* shape, int32_t n_groups, const 
   FwdArgs a = {shape->d, shape->d_ff, n_groups, n_rows, offsets, Xin, Wg, Wu, Wd, G, U, H, Yout, ws};
   switch (pick_path(shape)) {
     case PATH_F32: expert_fwd_impl<PATH_F32>(a, (hipStream_t)stream); break;
-    case PATH_BF16: expert_fwd_impl<PATH_BF16>(a, (hipStream_t)stream); break;
-    default: expert_fwd_impl<PATH_BF16_DMA>(a, (hipStream_t)stream); break;
+    case PATH_BF16_TAIL: expert_fwd_impl<PATH_BF16_TAIL>(a, (hipStream_t)stream); break;
+    default: expert_fwd_impl<PATH_BF16>(a, (hipStream_t)stream); break;
   }
   return launch_status("moe_expert_fwd");
 }
@@ -834,8 +787,8 @@ extern "C" int moe_expert_bwd(const moe_shape_t* shape, int32_t n_groups, const 
                active_ids, n_active, dWg_c, dWu_c, dWd_c, ws, plan_size_for(n_groups, n_rows, offsets == nullptr)};
   switch (pick_path(shape)) {
     case PATH_F32: expert_bwd_impl<PATH_F32>(a, (hipStream_t)stream); break;
-    case PATH_BF16: expert_bwd_impl<PATH_BF16>(a, (hipStream_t)stream); break;
-    default: expert_bwd_impl<PATH_BF16_DMA>(a, (hipStream_t)stream); break;
+    case PATH_BF16_TAIL: expert_bwd_impl<PATH_BF16_TAIL>(a, (hipStream_t)stream); break;
+    default: expert_bwd_impl<PATH_BF16>(a, (hipStream_t)stream); break;
   }
   return launch_status("moe_expert_bwd");
 }
@@ -872,8 +825,8 @@ extern "C" int moe_expert_fwd_gather(const moe_shape_t* shape, const int32_t* of
   a.src_of = src_of; a.src_div = shape->k; a.src_rows = shape->T;
   switch (pick_path(shape)) {
     case PATH_F32: expert_fwd_impl<PATH_F32>(a, (hipStream_t)stream); break;
-    case PATH_BF16: expert_fwd_impl<PATH_BF16>(a, (hipStream_t)stream); break;
-    default: expert_fwd_impl<PATH_BF16_DMA>(a, (hipStream_t)stream); break;
+    case PATH_BF16_TAIL: expert_fwd_impl<PATH_BF16_TAIL>(a, (hipStream_t)stream); break;
+    default: expert_fwd_impl<PATH_BF16>(a, (hipStream_t)stream); break;
   }
   return launch_status("moe_expert_fwd_gather");
 }
@@ -912,8 +865,8 @@ extern "C" int moe_expert_bwd_gather(const moe_shape_t* shape, const int32_t* of
   a.dY = dY; a.src_of = src_of; a.row_w = topk_w; a.src_div = shape->k; a.src_rows = shape->T;
   switch (pick_path(shape)) {
     case PATH_F32: expert_bwd_impl<PATH_F32>(a, (hipStream_t)stream); break;
-    case PATH_BF16: expert_bwd_impl<PATH_BF16>(a, (hipStream_t)stream); break;
-    default: expert_bwd_impl<PATH_BF16_DMA>(a, (hipStream_t)stream); break;
+    case PATH_BF16_TAIL: expert_bwd_impl<PATH_BF16_TAIL>(a, (hipStream_t)stream); break;
+    default: expert_bwd_impl<PATH_BF16>(a, (hipStream_t)stream); break;
   }
   return launch_status("moe_expert_bwd_gather");
 }
@@ -952,7 +905,7 @@ static void recolumn(const char* label, const void* src, void* dst, int64_t rows
 
 static int router_path(const moe_shape_t* s) {
   if (s->dtype == MOE_F32) return PATH_F32;
-  return s->d % 64 == 0 ? PATH_BF16_DMA : PATH_BF16;
+  return s->d % 64 == 0 ? PATH_BF16 : PATH_BF16_TAIL;
 }
 static int padded_experts(const moe_shape_t* s) { return (s->E + 63) / 64 * 64; }
 
@@ -1058,8 +1011,8 @@ extern "C" int moe_router_fwd(const moe_shape_t* shape, const void* X, const voi
   }
   switch (router_path(shape)) {
     case PATH_F32: router_fwd_impl<PATH_F32>(shape, X, Wr, logits, (char*)ws, (hipStream_t)stream); break;
-    case PATH_BF16: router_fwd_impl<PATH_BF16>(shape, X, Wr, logits, (char*)ws, (hipStream_t)stream); break;
-    default: router_fwd_impl<PATH_BF16_DMA>(shape, X, Wr, logits, (char*)ws, (hipStream_t)stream); break;
+    case PATH_BF16_TAIL: router_fwd_impl<PATH_BF16_TAIL>(shape, X, Wr, logits, (char*)ws, (hipStream_t)stream); break;
+    default: router_fwd_impl<PATH_BF16>(shape, X, Wr, logits, (char*)ws, (hipStream_t)stream); break;
   }
   return launch_status("moe_router_fwd");
 }
@@ -1088,8 +1041,8 @@ extern "C" int moe_router_bwd(const moe_shape_t* shape, const void* X, const voi
   }
   switch (router_path(shape)) {
     case PATH_F32: router_bwd_impl<PATH_F32>(shape, X, Wr, dlogits, dWr, dX, accumulate != 0, (char*)ws, (hipStream_t)stream); break;
-    case PATH_BF16: router_bwd_impl<PATH_BF16>(shape, X, Wr, dlogits, dWr, dX, accumulate != 0, (char*)ws, (hipStream_t)stream); break;
-    default: router_bwd_impl<PATH_BF16_DMA>(shape, X, Wr, dlogits, dWr, dX, accumulate != 0, (char*)ws, (hipStream_t)stream); break;
+    case PATH_BF16_TAIL: router_bwd_impl<PATH_BF16_TAIL>(shape, X, Wr, dlogits, dWr, dX, accumulate != 0, (char*)ws, (hipStream_t)stream); break;
+    default: router_bwd_impl<PATH_BF16>(shape, X, Wr, dlogits, dWr, dX, accumulate != 0, (char*)ws, (hipStream_t)stream); break;
   }
   return launch_status("moe_router_bwd");
 }

@@ -1,12 +1,12 @@
 // Tile cores of the grouped GEMMs for gfx950: matrix-core tiles (bf16: v_mfma_f32_32x32x16_bf16, fp32:
 // v_mfma_f32_32x32x2_f32) with operands staged through LDS.
 //
-// Both cores compute, for one block, acc[nb][..] = sum over iterations of A_tile * B_tile(nb)
-// and hand groups of four consecutive columns to an epilogue functor:
-//     epi(m, n, vals)   m, n relative to the block tile;  vals[nb][0..3] = C[m][n..n+3]
+// The core computes, for one block, acc[nb][..] = sum over iterations of A_tile * B_tile(nb)
+// and hands groups of eight consecutive columns to an epilogue functor:
+//     epi(m, n, vals)   m, n relative to the block tile;  vals[nb][0..7] = C[m][n..n+7]
 // The sum over K runs over n_segs segments of nk iterations each (segments: the shared experts of
 // a down projection, the two products of an input gradient); a segment functor supplies where the
-// tiles of a segment start, and the cores step along K from there themselves.
+// tiles of a segment start, and the core steps along K from there themselves.
 #pragma once
 
 #include "moe_common.h"
@@ -41,219 +41,14 @@ struct RowMap {
   const int32_t* idx;  // NULL: plain
   int32_t div, row0, rows;  // rows: valid rows of the tile (rows at or beyond read as zero)
   __device__ __forceinline__ bool gathered() const { return idx != nullptr; }
-  __device__ __forceinline__ int64_t operator()(int m) const { return idx ? (int64_t)(idx[row0 + m] / div) : (int64_t)m; }
+  __device__ __forceinline__ int operator()(int m) const { return idx[row0 + m] / div; }
 };
 
-// What one K iteration reads, for the cores that address element by element.
-template <typename T, int NB>
-struct IterSrc {
-  const T* a;        // A tile origin for this iteration (k offset included)
-  const T* b[NB];    // B tile origin(s)
-  int k_left;        // valid K elements from this origin on
-};
-template <typename T, int NB, bool A_KC, bool B_KC, class SegFn>
-__device__ __forceinline__ IterSrc<T, NB> iter_src(SegFn& segf, int it, int nk, int BK, int64_t lda, int64_t ldb) {
-  const int sg = it / nk, k0 = (it - sg * nk) * BK;
-  const SegSrc<T, NB> g = segf(sg);
-  IterSrc<T, NB> s;
-  s.a = g.a + (A_KC ? (int64_t)k0 : (int64_t)k0 * lda);
-#pragma unroll
-  for (int nb = 0; nb < NB; nb++) s.b[nb] = g.b[nb] + (B_KC ? (int64_t)k0 : (int64_t)k0 * ldb);
-  s.k_left = g.k_len - k0;
-  return s;
-}
-
-// ------------------------------------------------------------------------------ bf16 MFMA core
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(4))) short short4_t;
 typedef __attribute__((ext_vector_type(8))) short short8_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
-
-// LDS layouts (bf16 elements), BK = 64:
-//  K-contiguous operand: [rows][64], the eight 16-byte pieces of a row are XOR-swizzled with
-//    (row/2)%8 so that the 16 rows one ds_read_b128 phase touches fall into distinct banks.
-//  row-contiguous operand ([K][rows] in memory): [64][rows + 32]; the 64-byte pad moves the four
-//    k rows of a transposing read (ds_read_b64_tr_b16) to four different bank quarters.
-template <int BM_, int BN_, int NB, bool A_KC, bool B_KC, int WM_ = 2, int WN_ = 2>
-struct MfmaCore {
-  typedef bf16_t T;
-  static constexpr int BM = BM_, BN = BN_, BK = 64, NT = 256;
-  static constexpr int WM = WM_, WN = WN_;
-  static constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
-  static constexpr int PAD = 32;
-  static constexpr int A_ELEMS = A_KC ? BM * BK : BK * (BM + PAD);
-  static constexpr int B_ELEMS = B_KC ? BN * BK : BK * (BN + PAD);
-  static constexpr int STAGE_ELEMS = A_ELEMS + NB * B_ELEMS;
-  static constexpr int LDS_BYTES = 2 * STAGE_ELEMS * 2;  // two stages
-  static constexpr int BLOCKS_PER_CU = 1;
-  static constexpr int A_VEC = (BM * BK / 8 + NT - 1) / NT;
-  static constexpr int B_VEC = (BN * BK / 8 + NT - 1) / NT;
-  static_assert(WM * WN == 4, "four wavefronts per block");
-  static_assert(BM % (32 * WM) == 0 && BN % (32 * WN) == 0, "wave tile must be a multiple of 32");
-  static_assert(LDS_BYTES <= 160 * 1024, "LDS budget of a gfx950 CU");
-
-  // ---- global -> registers (16 bytes per access), zero outside the valid extents
-  template <int ROWS, int NVEC, bool KC>
-  __device__ static __forceinline__ void gload(const bf16_t* base, int64_t ld, int rows_valid, int k_left,
-                                               uint4 (&r)[NVEC], const RowMap& map) {
-#pragma unroll
-    for (int i = 0; i < NVEC; i++) {
-      const int v = threadIdx.x + i * NT;
-      int row, kk;
-      if (KC) { row = v / (BK / 8); kk = (v % (BK / 8)) * 8; }
-      else { kk = v / (ROWS / 8); row = (v % (ROWS / 8)) * 8; }
-      const bool ok = row < rows_valid && kk < k_left && (ROWS * BK / 8 % NT == 0 || v < ROWS * BK / 8);
-      r[i] = make_uint4(0, 0, 0, 0);
-      if (ok) {
-        const bf16_t* p = KC ? base + (map.gathered() ? map(row) : (int64_t)row) * ld + kk : base + (int64_t)kk * ld + row;
-        r[i] = *reinterpret_cast<const uint4*>(p);
-      }
-    }
-  }
-  // ---- registers -> LDS
-  template <int ROWS, int NVEC, bool KC>
-  __device__ static __forceinline__ void sstore(bf16_t* lds, const uint4 (&r)[NVEC]) {
-#pragma unroll
-    for (int i = 0; i < NVEC; i++) {
-      const int v = threadIdx.x + i * NT;
-      if (ROWS * BK / 8 % NT != 0 && v >= ROWS * BK / 8) continue;
-      int off;
-      if (KC) {
-        const int row = v / (BK / 8), c = v % (BK / 8);
-        off = row * BK + ((c ^ ((row >> 1) & 7)) << 3);
-      } else {
-        const int kk = v / (ROWS / 8), c = v % (ROWS / 8);
-        off = kk * (ROWS + PAD) + c * 8;
-      }
-      *reinterpret_cast<uint4*>(lds + off) = r[i];
-    }
-  }
-  // ---- LDS -> MFMA fragment: lane l holds k = 16*ks + 8*(l/32) + 0..7 of row (row0 + l%32)
-  template <int ROWS, bool KC>
-  __device__ static __forceinline__ bf16x8_t frag(const bf16_t* lds, int row0, int ks) {
-    const int lane = threadIdx.x & 63;
-    if (KC) {
-      const int row = row0 + (lane & 31);
-      const int c = ks * 2 + (lane >> 5);
-      const uint4 v = *reinterpret_cast<const uint4*>(lds + row * BK + ((c ^ ((row >> 1) & 7)) << 3));
-      return __builtin_bit_cast(bf16x8_t, v);
-    } else {
-      // transposing read: within 16 lanes, lane s points at 4 consecutive columns of row
-      // k = kb + s/4, starting at column 4*(s%4); it receives k = kb..kb+3 of column s.
-      const int s = lane & 15;
-      const int kb = ks * 16 + 8 * (lane >> 5);
-      const int col = row0 + 16 * ((lane >> 4) & 1) + 4 * (s & 3);
-      const bf16_t* p0 = lds + (kb + (s >> 2)) * (ROWS + PAD) + col;
-      const bf16_t* p1 = p0 + 4 * (ROWS + PAD);
-      typedef __attribute__((address_space(3))) short4_t* lds_ptr;
-      short4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p0));
-      short4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p1));
-      short8_t both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-      return __builtin_bit_cast(bf16x8_t, both);
-    }
-  }
-
-  struct Frags {
-    bf16x8_t a[TM], b[NB][TN];
-  };
-  __device__ static __forceinline__ void load_frags(const bf16_t* As, const bf16_t* Bs, int wm0, int wn0, int ks,
-                                                    Frags& f) {
-#pragma unroll
-    for (int i = 0; i < TM; i++) f.a[i] = frag<BM, A_KC>(As, wm0 + i * 32, ks);
-#pragma unroll
-    for (int nb = 0; nb < NB; nb++)
-#pragma unroll
-      for (int j = 0; j < TN; j++) f.b[nb][j] = frag<BN, B_KC>(Bs + nb * B_ELEMS, wn0 + j * 32, ks);
-  }
-  __device__ static __forceinline__ void mma(f32x16_t (&acc)[NB][TM][TN], const Frags& f) {
-#pragma unroll
-    for (int nb = 0; nb < NB; nb++)
-#pragma unroll
-      for (int i = 0; i < TM; i++)
-#pragma unroll
-        for (int j = 0; j < TN; j++)
-          // operands exchanged: result register r of lane l is C[m = l%32][n = 8*(r/4) + 4*(l/32) + r%4]
-          acc[nb][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.b[nb][j], f.a[i], acc[nb][i][j], 0, 0, 0);
-  }
-
-  template <class SegFn, class Epi>
-  __device__ static void run(char* smem, int n_segs, int nk, SegFn segf, int64_t lda, int64_t ldb, int m_valid,
-                             int n_valid, Epi epi, const RowMap& amap) {
-    const int n_iters = n_segs * nk;
-    auto src = [&](int it) { return iter_src<bf16_t, NB, A_KC, B_KC>(segf, it, nk, BK, lda, ldb); };
-    const RowMap plain = {nullptr, 1, 0, 0};
-    bf16_t* lds = (bf16_t*)smem;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wm0 = (wave / WN) * (BM / WM), wn0 = (wave % WN) * (BN / WN);
-
-    f32x16_t acc[NB][TM][TN];
-#pragma unroll
-    for (int nb = 0; nb < NB; nb++)
-#pragma unroll
-      for (int i = 0; i < TM; i++)
-#pragma unroll
-        for (int j = 0; j < TN; j++)
-#pragma unroll
-          for (int r = 0; r < 16; r++) acc[nb][i][j][r] = 0.f;
-
-    uint4 ra[A_VEC], rb[NB][B_VEC];
-    auto fetch = [&](int it) {
-      IterSrc<bf16_t, NB> s = src(it);
-      gload<BM, A_VEC, A_KC>(s.a, lda, m_valid, s.k_left, ra, amap);
-#pragma unroll
-      for (int nb = 0; nb < NB; nb++) gload<BN, B_VEC, B_KC>(s.b[nb], ldb, n_valid, s.k_left, rb[nb], plain);
-    };
-    auto stash = [&](int stage) {
-      bf16_t* As = lds + stage * STAGE_ELEMS;
-      sstore<BM, A_VEC, A_KC>(As, ra);
-#pragma unroll
-      for (int nb = 0; nb < NB; nb++) sstore<BN, B_VEC, B_KC>(As + A_ELEMS + nb * B_ELEMS, rb[nb]);
-    };
-
-    if (n_iters > 0) {
-      fetch(0);
-      stash(0);
-      if (n_iters > 1) fetch(1);
-      __syncthreads();
-    }
-    Frags f0, f1;
-    if (n_iters > 0) load_frags(lds, lds + A_ELEMS, wm0, wn0, 0, f0);
-    for (int it = 0; it < n_iters; it++) {
-      const bf16_t* As = lds + (it & 1) * STAGE_ELEMS;
-      const bf16_t* Bs = As + A_ELEMS;
-      load_frags(As, Bs, wm0, wn0, 1, f1);
-      mma(acc, f0);
-      // the tile of iteration it+1 (in registers since the previous iteration) goes to the other
-      // stage; the tile of iteration it+2 starts its trip from HBM/L2
-      if (it + 1 < n_iters) stash((it + 1) & 1);
-      if (it + 2 < n_iters) fetch(it + 2);
-      load_frags(As, Bs, wm0, wn0, 2, f0);
-      mma(acc, f1);
-      load_frags(As, Bs, wm0, wn0, 3, f1);
-      mma(acc, f0);
-      mma(acc, f1);
-      __syncthreads();
-      if (it + 1 < n_iters) {
-        const bf16_t* An = lds + ((it + 1) & 1) * STAGE_ELEMS;
-        load_frags(An, An + A_ELEMS, wm0, wn0, 0, f0);
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < TM; i++)
-#pragma unroll
-      for (int j = 0; j < TN; j++)
-#pragma unroll
-        for (int g = 0; g < 4; g++) {
-          float vals[NB][4];
-#pragma unroll
-          for (int nb = 0; nb < NB; nb++)
-#pragma unroll
-            for (int q = 0; q < 4; q++) vals[nb][q] = acc[nb][i][j][4 * g + q];
-          epi(wm0 + i * 32 + (lane & 31), wn0 + j * 32 + 8 * g + 4 * (lane >> 5), vals);
-        }
-  }
-};
 
 // ------------------------------------------------------------------ MFMA core, LDS DMA loads
 // Tiles travel HBM/L2 -> LDS directly (buffer_load_dwordx4 ... lds),
