@@ -106,53 +106,6 @@ __global__ __launch_bounds__(1024) void plan_kernel(const int32_t* __restrict__ 
 }
 
 // ------------------------------------------------------------------------------- epilogues
-// W = 8 consecutive elements narrowed from / widened to fp32, one or two 16-byte accesses
-template <typename T, int W> struct Pack;
-template <int W> struct Pack<float, W> {
-  __device__ static __forceinline__ void widen(const uint4&, float (&)[W]) {}  // (bf16 only)
-  __device__ static __forceinline__ void store(float* p, const float (&v)[W]) {
-#pragma unroll
-    for (int i = 0; i < W; i += 4) *reinterpret_cast<float4*>(p + i) = make_float4(v[i], v[i + 1], v[i + 2], v[i + 3]);
-  }
-  __device__ static __forceinline__ void store_nt(float* p, const float (&v)[W]) { store(p, v); }
-  __device__ static __forceinline__ void load(const float* p, float (&v)[W]) {
-#pragma unroll
-    for (int i = 0; i < W; i += 4) {
-      float4 f = *reinterpret_cast<const float4*>(p + i);
-      v[i] = f.x; v[i + 1] = f.y; v[i + 2] = f.z; v[i + 3] = f.w;
-    }
-  }
-};
-template <int W> struct Pack<bf16_t, W> {
-  __device__ static __forceinline__ void store(bf16_t* p, const float (&v)[W]) {
-    uint32_t w[W / 2];
-#pragma unroll
-    for (int i = 0; i < W / 2; i++) w[i] = f32x2_to_bf16x2(v[2 * i], v[2 * i + 1]);
-    *reinterpret_cast<uint4*>(p) = make_uint4(w[0], w[1], w[2], w[3]);
-  }
-  // the same with a streaming hint: for outputs that nothing on the chip reads again soon
-  __device__ static __forceinline__ void store_nt(bf16_t* p, const float (&v)[W]) {
-    typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
-    uint32_t w[W / 2];
-#pragma unroll
-    for (int i = 0; i < W / 2; i++) w[i] = f32x2_to_bf16x2(v[2 * i], v[2 * i + 1]);
-    const u32x4 t = {w[0], w[1], w[2], w[3]};
-    __builtin_nontemporal_store(t, reinterpret_cast<u32x4*>(p));
-  }
-  // the same from a 16-byte piece that is already in registers
-  __device__ static __forceinline__ void widen(const uint4& t, float (&v)[W]) {
-    const uint32_t w[4] = {t.x, t.y, t.z, t.w};
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-      v[2 * i] = __uint_as_float(w[i] << 16);
-      v[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
-    }
-  }
-  __device__ static __forceinline__ void load(const bf16_t* p, float (&v)[W]) {
-    widen(*reinterpret_cast<const uint4*>(p), v);
-  }
-};
-
 enum { EPI_STORE = 0, EPI_SWIGLU_FWD = 1, EPI_SWIGLU_BWD = 2, EPI_STORE_F32 = 3, EPI_ADD = 4, EPI_GELU_FWD = 5,
        EPI_GELU_BWD = 6 };
 
@@ -191,19 +144,72 @@ template <> __device__ __forceinline__ float sigmoidf_<bf16_t>(float z) {
   return __builtin_amdgcn_rcpf(1.f + __expf(-z));
 }
 
-// An epilogue whose global reads the LDS-DMA core may request ahead of time (see EpiAux): `body` does
-// the work, with the pieces `pre` has fetched or, handed a null pointer, with loads of its own.
-template <class Body, class Pre, class Aux, int N_AUX>
-struct EpiWithAux {
-  static constexpr int kAux = N_AUX;
-  Body body;
-  Pre pre;
-  __device__ __forceinline__ Aux prefetch(int m, int n) const { return pre(m, n); }
-  template <class V> __device__ __forceinline__ void operator()(int m, int n, const V& v) const {
-    body(m, n, v, (const Aux*)nullptr);
+// Epilogue object of the tile cores (see gemm_cores.h): four consecutive values of every output from four of
+// every product.
+template <typename T, int NB, int EPI>
+struct Epilogue {
+  static constexpr int NOUT = EPI == EPI_SWIGLU_FWD ? 3 : (EPI == EPI_GELU_FWD || EPI == EPI_SWIGLU_BWD) ? 2
+                              : EPI == EPI_STORE ? NB : 1;
+  static constexpr int NAUX = EPI == EPI_SWIGLU_BWD ? 2 : (EPI == EPI_GELU_BWD || EPI == EPI_ADD) ? 1 : 0;
+  static constexpr int OES = EPI == EPI_STORE_F32 ? 4 : sizeof(T);
+  // bf16 outputs carry the streaming hint: every one is read again only by a later kernel, after gigabytes of
+  // other traffic (2-3 % on the row GEMMs of the Qwen- and stress-shaped workloads)
+  static constexpr bool NT = OES == 2;
+  void* out[NOUT];
+  const void* in[NAUX > 0 ? NAUX : 1];
+  int64_t ldc;
+  int rows, n_valid;
+  // activation-backward epilogues of gathered rows: row m of the product is scaled by scale[index[m]]
+  const float* scale = nullptr;
+  const int32_t* index = nullptr;
+
+  __device__ __forceinline__ float row_scale(int m) const {
+    if (EPI != EPI_SWIGLU_BWD && EPI != EPI_GELU_BWD) return 1.f;
+    return scale ? scale[index[min(m, rows - 1)]] : 1.f;
   }
-  template <class V> __device__ __forceinline__ void operator()(int m, int n, const V& v, const Aux& a) const {
-    body(m, n, v, &a);
+  __device__ __forceinline__ static void pack(void* p, const float (&v)[4]) {
+    if constexpr (OES == 2) *reinterpret_cast<uint2*>(p) = make_uint2(f32x2_to_bf16x2(v[0], v[1]), f32x2_to_bf16x2(v[2], v[3]));
+    else *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
+  }
+  __device__ __forceinline__ static void unpack(const void* p, float (&v)[4]) {
+    if constexpr (OES == 2) {
+      const uint2 t = *reinterpret_cast<const uint2*>(p);
+      v[0] = __uint_as_float(t.x << 16); v[1] = __uint_as_float(t.x & 0xffff0000u);
+      v[2] = __uint_as_float(t.y << 16); v[3] = __uint_as_float(t.y & 0xffff0000u);
+    } else {
+      const float4 t = *reinterpret_cast<const float4*>(p);
+      v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+    }
+  }
+  template <int NA>
+  __device__ __forceinline__ void apply(const float (&v)[NB][4], const float (&a)[NA][4], float sc, float (&o)[NOUT][4]) const {
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      if constexpr (EPI == EPI_STORE) {
+#pragma unroll
+        for (int nb = 0; nb < NB; nb++) o[nb][q] = v[nb][q];
+      } else if constexpr (EPI == EPI_STORE_F32) {  // fp32 output whatever the operand type (router logits)
+        o[0][q] = v[0][q];
+      } else if constexpr (EPI == EPI_ADD) {        // accumulate into the output
+        o[0][q] = a[0][q] + v[0][q];
+      } else if constexpr (EPI == EPI_GELU_FWD) {   // two-matrix expert: keep the pre-activation, store f of it
+        o[0][q] = v[0][q];
+        o[1][q] = gelu_f<T>(v[0][q]);
+      } else if constexpr (EPI == EPI_GELU_BWD) {   // dZ = dH f'(Z)
+        o[0][q] = sc * v[0][q] * gelu_grad_f<T>(a[0][q]);
+      } else if constexpr (EPI == EPI_SWIGLU_FWD) {
+        o[0][q] = v[0][q];
+        o[1][q] = v[NB - 1][q];
+        o[2][q] = v[0][q] * sigmoidf_<T>(v[0][q]) * v[NB - 1][q];
+      } else {                                      // dU = dH g s,  dG = dH u (s + g s (1 - s)),  s = sigmoid(g)
+        const float g = a[0][q], u = a[NA - 1][q];
+        const float s = sigmoidf_<T>(g);
+        const float dh = sc * v[0][q];
+        const float t = g * s;
+        o[1][q] = dh * t;
+        o[0][q] = dh * u * fmaf(t, 1.f - s, s);
+      }
+    }
   }
 };
 
@@ -242,89 +248,21 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm& p, const RowTile& t
     return s;
   };
   const int c_row0 = p.c_rows_out ? t.row0_out : t.row0_in;
-  // W = 8 consecutive columns of one row
-  // 16-byte pieces the epilogue reads at its own position, requested ahead of time by the LDS-DMA
-  // core (bf16): the saved inputs of the activation's derivative, or the output to accumulate into
-  constexpr int kAuxLoads = sizeof(T) != 2 ? 0 : EPI == EPI_SWIGLU_BWD ? 2 : (EPI == EPI_GELU_BWD || EPI == EPI_ADD) ? 1 : 0;
-  struct Aux {
-    uint4 r[kAuxLoads > 0 ? kAuxLoads : 1];
-  };
-  auto pre = [&](int m, int n) __attribute__((always_inline)) {
-    Aux a;
-    // out of range: the first piece of the tile, which exists and is never used
-    const bool ok = m < rows && n < n_valid;
-    const int64_t off = (int64_t)(c_row0 + (ok ? m : 0)) * p.ldc + n0 + (ok ? n : 0);
-    const void* src0 = EPI == EPI_ADD ? (const void*)p.out[0] : p.in[0];
-    a.r[0] = *reinterpret_cast<const uint4*>((const T*)src0 + off);
-    if (kAuxLoads == 2) a.r[kAuxLoads > 1 ? 1 : 0] = *reinterpret_cast<const uint4*>((const T*)p.in[1] + off);
-    return a;
-  };
-  // (all stores carry the streaming hint: every output here is read again only by a later kernel, after
-  // gigabytes of other traffic; 2-3 % on the row GEMMs of the Qwen- and stress-shaped workloads)
-  auto body = [&](int m, int n, const auto& v, const Aux* aux) __attribute__((always_inline)) {
-    constexpr int W = sizeof(v[0]) / sizeof(float);
-    if (m >= rows || n >= n_valid) return;
-    const int64_t off = (int64_t)(c_row0 + m) * p.ldc + n0 + n;
-    if (EPI == EPI_STORE) {
-      Pack<T, W>::store_nt((T*)p.out[0] + off, v[0]);
-    } else if (EPI == EPI_STORE_F32) {  // fp32 output whatever the operand type (router logits)
-      Pack<float, W>::store((float*)p.out[0] + off, v[0]);
-    } else if (EPI == EPI_ADD) {        // accumulate into the output
-      float o[W];
-      if (aux) Pack<T, W>::widen(aux->r[0], o);
-      else Pack<T, W>::load((const T*)p.out[0] + off, o);
+  Epilogue<T, NB, EPI> epi;
+  const int64_t c_off = ((int64_t)c_row0 * p.ldc + n0) * Epilogue<T, NB, EPI>::OES;
 #pragma unroll
-      for (int q = 0; q < W; q++) o[q] += v[0][q];
-      Pack<T, W>::store_nt((T*)p.out[0] + off, o);
-    } else if (EPI == EPI_GELU_FWD) {    // two-matrix expert: keep the pre-activation, store f of it
-      float h[W];
-#pragma unroll
-      for (int q = 0; q < W; q++) h[q] = gelu_f<T>(v[0][q]);
-      Pack<T, W>::store_nt((T*)p.out[0] + off, v[0]);
-      Pack<T, W>::store_nt((T*)p.out[2] + off, h);
-    } else if (EPI == EPI_GELU_BWD) {    // dZ = dH f'(Z)
-      float z[W], dz[W];
-      if (aux) Pack<T, W>::widen(aux->r[0], z);
-      else Pack<T, W>::load((const T*)p.in[0] + off, z);
-      const float sc = p.c_scale ? p.c_scale[p.a_index[a_row0 + m]] : 1.f;
-#pragma unroll
-      for (int q = 0; q < W; q++) dz[q] = sc * v[0][q] * gelu_grad_f<T>(z[q]);
-      Pack<T, W>::store_nt((T*)p.out[0] + off, dz);
-    } else if (EPI == EPI_SWIGLU_FWD) {
-      float h[W];
-#pragma unroll
-      for (int q = 0; q < W; q++) h[q] = v[0][q] * sigmoidf_<T>(v[0][q]) * v[NB - 1][q];
-      Pack<T, W>::store_nt((T*)p.out[0] + off, v[0]);
-      Pack<T, W>::store_nt((T*)p.out[1] + off, v[NB - 1]);
-      Pack<T, W>::store_nt((T*)p.out[2] + off, h);
-    } else {
-      float g[W], u[W], dg[W], du[W];
-      if (aux) {
-        Pack<T, W>::widen(aux->r[0], g);
-        Pack<T, W>::widen(aux->r[kAuxLoads > 1 ? 1 : 0], u);
-      } else {
-        Pack<T, W>::load((const T*)p.in[0] + off, g);
-        Pack<T, W>::load((const T*)p.in[1] + off, u);
-      }
-      const float sc = p.c_scale ? p.c_scale[p.a_index[a_row0 + m]] : 1.f;
-#pragma unroll
-      for (int q = 0; q < W; q++) {
-        const float s = sigmoidf_<T>(g[q]);
-        const float dh = sc * v[0][q];
-        du[q] = dh * g[q] * s;
-        dg[q] = dh * u[q] * s * (1.f + g[q] * (1.f - s));
-      }
-      Pack<T, W>::store_nt((T*)p.out[0] + off, dg);
-      Pack<T, W>::store_nt((T*)p.out[1] + off, du);
-    }
-  };
-  if constexpr (kAuxLoads > 0) {
-    EpiWithAux<decltype(body), decltype(pre), Aux, kAuxLoads> epi{body, pre};
-    Core::run(smem, p.n_pairs * p.n_segs, nk, segf, p.lda, p.ldb, rows, n_valid, epi, amap);
-  } else {
-    auto epi = [&](int m, int n, const auto& v) __attribute__((always_inline)) { body(m, n, v, (const Aux*)nullptr); };
-    Core::run(smem, p.n_pairs * p.n_segs, nk, segf, p.lda, p.ldb, rows, n_valid, epi, amap);
+  for (int x = 0; x < epi.NOUT; x++) epi.out[x] = (char*)p.out[x] + c_off;
+  if (EPI == EPI_ADD) epi.in[0] = epi.out[0];
+  else if (epi.NAUX > 0) {
+    epi.in[0] = (const char*)p.in[0] + c_off;
+    if (epi.NAUX > 1) epi.in[epi.NAUX - 1] = (const char*)p.in[1] + c_off;
   }
+  epi.ldc = p.ldc;
+  epi.rows = rows;
+  epi.n_valid = n_valid;
+  epi.scale = p.c_scale;
+  epi.index = p.a_index + a_row0;
+  Core::run(smem, p.n_pairs * p.n_segs, nk, segf, p.lda, p.ldb, epi, amap);
 }
 
 template <class CoreSet, int NB, int EPI, bool B_KC>
@@ -420,15 +358,14 @@ __global__ __launch_bounds__(Core::NT, Core::BLOCKS_PER_CU) void w_gemm_kernel(W
     s.b_bytes = ((int64_t)(K - 1) * p.ldb + (p.N - n0)) * es;
     return s;
   };
-  auto epi = [&](int m, int n, const auto& v) __attribute__((always_inline)) {
-    constexpr int W = sizeof(v[0]) / sizeof(float);
-    if (m >= m_valid || n >= n_valid) return;
-    const int64_t off = (int64_t)slot * p.c_slot + (int64_t)(m0 + m) * p.N + n0 + n;
-    Pack<T, W>::store_nt((T*)p.C[z] + off, v[0]);
-    if (NB == 2) Pack<T, W>::store_nt((T*)p.C[1] + off, v[NB - 1]);
-  };
+  Epilogue<T, NB, EPI_STORE> epi;
+#pragma unroll
+  for (int x = 0; x < NB; x++) epi.out[x] = (T*)p.C[NB == 1 ? z : x] + (int64_t)slot * p.c_slot + (int64_t)m0 * p.N + n0;
+  epi.ldc = p.N;
+  epi.rows = m_valid;
+  epi.n_valid = n_valid;
   MOE_TRACE_BEGIN();
-  Core::run(smem, 1, (K + BK - 1) / BK, segf, p.lda, p.ldb, m_valid, n_valid, epi, RowMap{nullptr, 1, 0, 0});
+  Core::run(smem, 1, (K + BK - 1) / BK, segf, p.lda, p.ldb, epi, RowMap{nullptr, 1, 0, 0});
   MOE_TRACE_W_TILE(0x1000 | NB | (BM << 4), g, min(K, 0xffff) << 16);
   }
 }
@@ -570,7 +507,7 @@ static void expert_fwd_impl(const FwdArgs& a, hipStream_t st) {
   p.A[0] = a.Xin; p.lda = a.d; p.a_seg = 0; p.a_rows_out = 0;
   p.a_index = a.src_of; p.a_index_div = a.src_div; p.a_src_rows = a.src_rows;
   p.B[0] = a.Wg; p.Bdual = a.Wu; p.ldb = a.F; p.b_group = (int64_t)a.d * a.F; p.b_seg = 0;
-  p.out[0] = a.G; p.out[1] = a.U; p.out[2] = a.H; p.ldc = a.F; p.c_rows_out = 1;
+  p.out[0] = a.G; p.out[1] = a.Wu ? a.U : a.H; p.out[2] = a.H; p.ldc = a.F; p.c_rows_out = 1;
   if (a.Wu) launch_row<RowCores<PATH, 2, false>, 2, EPI_SWIGLU_FWD, false>("gemm_fwd_gate_up", p, max_tiles, st);
   else launch_row<RowCores<PATH, 1, false>, 1, EPI_GELU_FWD, false>("gemm_fwd_gate_up", p, max_tiles, st);
   // F5: Yout = H Wd (shared mode: summed over groups through K segments)

@@ -1,9 +1,11 @@
 // Tile cores of the grouped GEMMs for gfx950: matrix-core tiles (bf16: v_mfma_f32_32x32x16_bf16, fp32:
 // v_mfma_f32_32x32x2_f32) with operands staged through LDS.
 //
-// The core computes, for one block, acc[nb][..] = sum over iterations of A_tile * B_tile(nb)
-// and hands groups of eight consecutive columns to an epilogue functor:
-//     epi(m, n, vals)   m, n relative to the block tile;  vals[nb][0..7] = C[m][n..n+7]
+// The core computes, for one block, acc[nb][..] = sum over iterations of A_tile * B_tile(nb), and turns
+// them into NOUT output matrices (with NAUX input matrices of the same shape) as an epilogue object says:
+//     epi.apply(v, aux, scale, o)   v[nb][0..3] = C[m][n..n+3], aux[x][0..3], scale = epi.row_scale(m) -> o[out][0..3]
+// Its members: NOUT, NAUX, OES (bytes per element of all those matrices), NT (streaming stores);
+// out[], in[] (origins of the tile in them), ldc (their row stride), rows, n_valid (valid extents of the tile).
 // The sum over K runs over n_segs segments of nk iterations each (segments: the shared experts of
 // a down projection, the two products of an input gradient); a segment functor supplies where the
 // tiles of a segment start, and the core steps along K from there themselves.
@@ -13,13 +15,11 @@
 #include "trace.h"
 
 namespace moe {
-// An epilogue functor may read global memory at the position it writes (an activation's saved input,
-// an output it accumulates into).  If it says how many 16-byte pieces per position (`kAux`) and offers
-// `prefetch(m, n)` returning them, the LDS-DMA core requests the pieces of a whole block of rows
-// before it needs them and hands each back through a fourth argument; otherwise the functor does
-// its own loads, one position after the other.
-template <class E, class = void> struct EpiAux { static constexpr int value = 0; };
-template <class E> struct EpiAux<E, std::void_t<decltype(E::kAux)>> { static constexpr int value = E::kAux; };
+// 16 bytes through a bounds-checked buffer descriptor (reads beyond it return zero, writes are dropped)
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
+}
 
 // Start of one segment.  Pointers are already offset to the tile's first row/column at k = 0;
 // "kc" (K-contiguous) operands are [rows][K] row-major, otherwise [K][rows] row-major.
@@ -68,7 +68,8 @@ typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 //  K-contiguous operand [rows][BK]: 16-byte piece c of a row sits at position c ^ ((row/2)%8), so
 //    that the 16 rows one phase of a 16-byte-per-lane read touches cover all banks once.
 //  row-contiguous operand [BK][ROWS]: bf16: piece c (8 columns) of k-row k sits at position
-//    c ^ (4*(k%4)), which spreads the four k rows of a transposing read over all banks.  fp32: the
+//    c ^ (4*(k%4)), which spreads the four k rows of a transposing read over all banks (tiles of 64 columns,
+//    whose rows are half as long: c ^ (4*((k/2)%2))).  fp32: the
 //    fragment is read value by value; piece c (4 columns) sits at c ^ (8*((k/4)%2)), so that the two
 //    half-waves, four k rows apart, use different banks.
 template <typename T_, int BM_, int BN_, int NB, bool A_KC, bool B_KC, int WM_ = 2, int WN_ = 2, int DEPTH = 1,
@@ -102,8 +103,7 @@ struct MfmaDmaCore {
   static constexpr int B_SLOTS = DEPTH == 0 ? 1 : DEPTH == 1 ? 2 : DEPTH + 1;
   static constexpr int B_SET_ELEMS = NB * B_ELEMS;
   static constexpr int TILE_BYTES = (A_SLOTS * A_ELEMS + B_SLOTS * B_SET_ELEMS) * ES;
-  static constexpr int STAGING_BYTES = NW * NB * 32 * ((BN_ / WN_) + 4) * 4;  // epilogue, see run()
-  static constexpr int LDS_BYTES = TILE_BYTES > STAGING_BYTES ? TILE_BYTES : STAGING_BYTES;
+  static constexpr int LDS_BYTES = TILE_BYTES;
   // blocks per CU the register allocation aims at (LDS allows as many)
   static constexpr int BLOCKS_PER_CU = LDS_BYTES > 80 * 1024 ? 1 : NB * TM * TN <= 4 ? 2 : 1;
   static constexpr int A_NI = BM / (8 * NW), B_NI = BN / (8 * NW);  // wave-wide loads per wave and tile
@@ -112,8 +112,8 @@ struct MfmaDmaCore {
   static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0,
                 "every wave issues the same number of 1 KB loads per tile");
   static_assert(BM % (32 * WM) == 0 && BN % (32 * WN) == 0, "wave tile must be a multiple of 32");
-  static_assert((A_KC || BM * ES % 256 == 0) && (B_KC || BN * ES % 256 == 0),
-                "swizzle of row-contiguous tiles needs >= 16 pieces per k row");
+  static_assert((A_KC || BM * ES % 128 == 0) && (B_KC || BN * ES % 128 == 0),
+                "swizzle of row-contiguous tiles needs >= 8 pieces per k row");
   static_assert(ES == 2 || ((A_KC || BM <= 128) && (B_KC || BN <= 128)),
                 "fp32: the loads of a wave are a multiple of 8 k rows apart, so the swizzle is the same for all");
   static_assert(LDS_BYTES <= 160 * 1024, "LDS budget of a gfx950 CU");
@@ -125,6 +125,10 @@ struct MfmaDmaCore {
   // the K loop spends no instructions on addresses and the whole offset stays inside the
   // descriptor's bounds check.
   __device__ static __forceinline__ int kc_swizzle(int row) { return ((row * PR_KC) >> 4) & (PR_KC - 1); }
+  template <int ROWS>
+  __device__ static __forceinline__ int rc_swizzle(int k) {
+    return ES == 4 ? 8 * ((k >> 2) & 1) : ROWS >= 128 ? 4 * (k & 3) : 4 * ((k >> 1) & 1);
+  }
   template <int ROWS, bool KC>
   __device__ static __forceinline__ uint32_t piece_offset(int wave, int lane, uint32_t ld) {
     const int q = wave * 64 + lane;  // linear 16-byte piece of the LDS tile
@@ -135,7 +139,7 @@ struct MfmaDmaCore {
     } else {
       constexpr int PR = ROWS / PE;
       const int k = q / PR, pos = q % PR;
-      const int c = pos ^ (ES == 4 ? 8 * ((k >> 2) & 1) : 4 * (k & 3));
+      const int c = pos ^ rc_swizzle<ROWS>(k);
       return (uint32_t)k * ld * ES + (uint32_t)c * 16u;
     }
   }
@@ -191,7 +195,7 @@ struct MfmaDmaCore {
 #pragma unroll
       for (int t = 0; t < 4; t++) {
         const int col = w0 + t * 32 + (lane & 31);
-        off[t] = 4 * h * ROWS + ((((col >> 2) ^ (8 * h)) << 2) | (col & 3));
+        off[t] = 4 * h * ROWS + ((((col >> 2) ^ rc_swizzle<ROWS>(4 * h)) << 2) | (col & 3));
       }
     } else {
       // transposing read: within 16 lanes, lane s points at 4 consecutive columns of k-row
@@ -201,7 +205,7 @@ struct MfmaDmaCore {
 #pragma unroll
       for (int t = 0; t < 4; t++) {
         const int col = w0 + t * 32 + 16 * ((lane >> 4) & 1) + 4 * (s & 3);
-        off[t] = k * ROWS + (((col >> 3) ^ (4 * (k & 3))) << 3) + (col & 7);
+        off[t] = k * ROWS + (((col >> 3) ^ rc_swizzle<ROWS>(k)) << 3) + (col & 7);
       }
     }
   }
@@ -347,11 +351,132 @@ struct MfmaDmaCore {
     }
   }
 
+  // Epilogue.  In the MFMA result layout a lane owns four consecutive columns of 32 different rows, so direct
+  // global accesses would be scatters of 8- or 16-byte pieces.  The arithmetic is done in that layout, on
+  // registers; the finished outputs, already in their final type, pass through a private LDS region of the
+  // wave in blocks of 32 rows and are picked up again as whole rows, 16 bytes per lane.  Inputs of the epilogue
+  // (the saved activations of a backward product, an output to add to) take the opposite way: whole rows
+  // into registers one block ahead, through the same region into the result layout.  The region's
+  // 16-byte pieces are XOR-swizzled by the row; LDS operations of one wave execute in order, so its reads and
+  // writes need no waits of their own, and the stores of a block are issued after the next block's
+  // arithmetic, under which their LDS reads return.
+  // What bounds it is instruction issue: one wave per SIMD, nothing to switch to.  (Staging fp32 values and
+  // doing arithmetic, rounding and addresses in row order, one pass of 4 rows after the other, took 10.5 k shader
+  // cycles per 256 x 256 tile of plain outputs, 13.8 k with SwiGLU, 50 k with its derivative; without the
+  // global stores still 9.9 k, 13.0 k, 39 k.  This form: 7.3 k, 12 k, 41 k, without the stores 4.5 k, 9.7 k, 34 k: what is
+  // left is arithmetic, two transcendentals per value, and the stores and loads of a launch's first tiles, which
+  // all CUs issue together.  Whole steps gain 1-3 % only, because the shader clock drops as the matrix pipe idles less.)
+  template <class Epi>
+  __device__ static __forceinline__ void epilogue(char* smem, f32x16_t (&acc)[NB][TM][TN], const Epi& epi, int wave, int lane,
+                                                  int wm0, int wn0) {
+    constexpr int OES = Epi::OES, NOUT = Epi::NOUT, NAUX = Epi::NAUX;
+    constexpr int RB = TN * 32 * OES;         // bytes per row of the wave's tile
+    constexpr int LPR = RB / 16;              // lanes (16-byte pieces) per row
+    constexpr int RPP = 64 / LPR;             // rows per wave-wide access
+    constexpr int NPASS = 32 / RPP;
+    constexpr int SWZ = (LPR < 16 ? LPR : 16) - 1;
+    constexpr int BLOCK = 32 * RB;            // one 32-row block of one matrix
+    constexpr int NMAT = NOUT > NAUX ? NOUT : NAUX;
+    constexpr int NA = NAUX > 0 ? NAUX : 1;
+    static_assert(NW * NMAT * BLOCK <= LDS_BYTES, "the waves' staging regions fit into LDS");
+    char* stage = smem + wave * (NMAT * BLOCK);
+    // row order: row pass * RPP + lane / LPR, piece lane % LPR;  result layout: row lane % 32
+    const int rrow = lane / LPR, rpiece = lane % LPR;
+    const uint32_t r_off = rrow * RB + ((rpiece ^ (rrow & SWZ)) << 4);
+    const int mrow = lane & 31, h = lane >> 5;
+    const uint32_t m_off = mrow * RB + ((mrow & SWZ) << 4);
+    auto row_at = [&](int pass) __attribute__((always_inline)) {  // (rrow < RPP, so the row's other bits come from pass)
+      return (r_off ^ (((pass * RPP) & SWZ) << 4)) + pass * RPP * RB;
+    };
+    auto col_at = [&](int j, int g) __attribute__((always_inline)) {
+      return OES == 2 ? (m_off ^ ((4 * j + g) << 4)) + 8 * h : (m_off ^ ((8 * j + 2 * g + h) << 4));
+    };
+    // global side: byte offsets from the tile's origin in every matrix
+    const int c0 = wn0 + rpiece * (16 / OES);
+    const uint32_t ldb = (uint32_t)epi.ldc * OES;
+    const uint32_t g0 = (uint32_t)(wm0 + rrow) * ldb + (uint32_t)c0 * OES;
+    const bool col_ok = c0 < epi.n_valid;
+    const uint32_t bytes = ((uint32_t)epi.rows - 1) * ldb + (uint32_t)epi.n_valid * OES;
+    u32x4_t piece[NMAT][NPASS];
+    auto load_aux = [&](int i) __attribute__((always_inline)) {
+#pragma unroll
+      for (int x = 0; x < NAUX; x++)
+#pragma unroll
+        for (int p = 0; p < NPASS; p++)
+          piece[x][p] = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc(epi.in[x], bytes), g0 + (i * 32 + p * RPP) * ldb, 0, 0);
+    };
+    auto store_out = [&](int i) __attribute__((always_inline)) {
+      if (col_ok) {
+#pragma unroll
+        for (int x = 0; x < NOUT; x++)
+#pragma unroll
+          for (int p = 0; p < NPASS; p++)
+            __builtin_amdgcn_raw_buffer_store_b128(piece[x][p], make_rsrc(epi.out[x], bytes), g0 + (i * 32 + p * RPP) * ldb, 0,
+                                                   Epi::NT ? 2 : 0);
+      }
+    };
+    if (NAUX > 0) load_aux(0);
+    float scale[TM];
+#pragma unroll
+    for (int i = 0; i < TM; i++) scale[i] = epi.row_scale(wm0 + i * 32 + mrow);
+#pragma unroll
+    for (int i = 0; i < TM; i++) {
+      if (NAUX > 0) {
+#pragma unroll
+        for (int x = 0; x < NAUX; x++)
+#pragma unroll
+          for (int p = 0; p < NPASS; p++) *reinterpret_cast<u32x4_t*>(stage + x * BLOCK + row_at(p)) = piece[x][p];
+        asm volatile("" ::: "memory");
+        if (i + 1 < TM) load_aux(i + 1);
+      }
+#pragma unroll
+      for (int j = 0; j < TN; j++)
+#pragma unroll
+        for (int g = 0; g < 4; g++) {
+          float v[NB][4], a[NA][4], o[NOUT][4];
+#pragma unroll
+          for (int x = 0; x < NAUX; x++) Epi::unpack(stage + x * BLOCK + col_at(j, g), a[x]);
+#pragma unroll
+          for (int nb = 0; nb < NB; nb++)
+#pragma unroll
+            for (int q = 0; q < 4; q++) asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v[nb][q]) : "a"(acc[nb][i][j][4 * g + q]));
+          epi.apply(v, a, scale[i], o);
+#pragma unroll
+          for (int x = 0; x < NOUT; x++) Epi::pack(stage + x * BLOCK + col_at(j, g), o[x]);
+        }
+      asm volatile("" ::: "memory");  // other lanes' values are read back below
+      if (NAUX > 0) {
+        // the registers of the row pieces hold the next block's inputs: pass the outputs through others
+        u32x4_t r[NOUT][NPASS];
+#pragma unroll
+        for (int x = 0; x < NOUT; x++)
+#pragma unroll
+          for (int p = 0; p < NPASS; p++) r[x][p] = *reinterpret_cast<const u32x4_t*>(stage + x * BLOCK + row_at(p));
+        if (col_ok) {
+#pragma unroll
+          for (int x = 0; x < NOUT; x++)
+#pragma unroll
+            for (int p = 0; p < NPASS; p++)
+              __builtin_amdgcn_raw_buffer_store_b128(r[x][p], make_rsrc(epi.out[x], bytes), g0 + (i * 32 + p * RPP) * ldb, 0,
+                                                     Epi::NT ? 2 : 0);
+        }
+      } else {
+        if (i > 0) store_out(i - 1);
+#pragma unroll
+        for (int x = 0; x < NOUT; x++)
+#pragma unroll
+          for (int p = 0; p < NPASS; p++) piece[x][p] = *reinterpret_cast<const u32x4_t*>(stage + x * BLOCK + row_at(p));
+      }
+      asm volatile("" ::: "memory");
+    }
+    if (NAUX == 0) store_out(TM - 1);
+  }
+
+  // (the valid extents are not needed here: the descriptors' byte counts zero-fill the loads and bound
+  // the epilogue's accesses)
   template <class SegFn, class Epi>
-  // (the valid extents are not needed here: the descriptors' byte counts zero-fill the loads and the
-  // epilogue functor masks the stores)
   __device__ static __forceinline__ void run(char* smem, int n_segs, int nk, SegFn segf, int64_t lda, int64_t ldb,
-                                             int /*m_valid*/, int /*n_valid*/, Epi epi, const RowMap& amap) {
+                                             const Epi& epi, const RowMap& amap) {
     const int n_iters = n_segs * nk;
     MOE_PHASE(0);
     T* lds = (T*)smem;
@@ -613,84 +738,8 @@ struct MfmaDmaCore {
       for (int i = 0; i < TM; i++)
 #pragma unroll
         for (int j = 0; j < TN; j++) asm volatile("" : "+a"(acc[nb][i][j])::"memory");
-    // Epilogue through LDS.  In the MFMA result layout a lane owns four consecutive columns of one
-    // row, which would make every global store a scatter of 8-byte pieces over 32 rows.  Each wave
-    // therefore passes its 32-row blocks through a private LDS region (fp32, rows padded by 16
-    // bytes: conflict-free 16-byte writes and reads) and picks them up again with eight
-    // consecutive columns per lane, so that the epilogue stores whole 128-byte lines.
     __syncthreads();  // every wave is done with the tile slots (stale fragment reads included)
-    constexpr int CW = TN * 32;          // columns of the wave tile (per product)
-    constexpr int RS = CW + 4;           // row stride of the staging region, in floats
-    constexpr int LPR = CW / 8;          // lanes per row when reading back
-    constexpr int RPP = 64 / LPR;        // rows per read pass
-    static_assert(NW * NB * 32 * RS * 4 <= LDS_BYTES, "staging regions of the waves fit into LDS");
-    static_assert(NW * NB * 32 * RS * 4 == STAGING_BYTES, "STAGING_BYTES matches the staging layout");
-    float* stage = reinterpret_cast<float*>(smem) + wave * (NB * 32 * RS);
-    constexpr int kAux = EpiAux<Epi>::value;
-    constexpr int NPASS = 32 / RPP;
-    auto stage_block = [&](int i) __attribute__((always_inline)) {
-#pragma unroll
-      for (int nb = 0; nb < NB; nb++)
-#pragma unroll
-        for (int j = 0; j < TN; j++)
-#pragma unroll
-          for (int g = 0; g < 4; g++) {
-            float4 v;
-            asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v.x) : "a"(acc[nb][i][j][4 * g + 0]));
-            asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v.y) : "a"(acc[nb][i][j][4 * g + 1]));
-            asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v.z) : "a"(acc[nb][i][j][4 * g + 2]));
-            asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v.w) : "a"(acc[nb][i][j][4 * g + 3]));
-            *reinterpret_cast<float4*>(stage + (nb * 32 + (lane & 31)) * RS + j * 32 + 8 * g + 4 * (lane >> 5)) = v;
-          }
-    };
-    auto read_pass = [&](int pass, float (&vals)[NB][8]) __attribute__((always_inline)) {
-      const int row = pass * RPP + lane / LPR, c0 = (lane % LPR) * 8;
-#pragma unroll
-      for (int nb = 0; nb < NB; nb++) {
-        const float4 lo = *reinterpret_cast<const float4*>(stage + (nb * 32 + row) * RS + c0);
-        const float4 hi = *reinterpret_cast<const float4*>(stage + (nb * 32 + row) * RS + c0 + 4);
-        vals[nb][0] = lo.x; vals[nb][1] = lo.y; vals[nb][2] = lo.z; vals[nb][3] = lo.w;
-        vals[nb][4] = hi.x; vals[nb][5] = hi.y; vals[nb][6] = hi.z; vals[nb][7] = hi.w;
-      }
-    };
-    const int c0 = (lane % LPR) * 8;
-    if constexpr (kAux > 0) {
-      // the functor's own global reads of block i + 1 are in flight while block i is staged,
-      // converted and stored (everything unrolled: the pieces live in registers)
-      typedef decltype(epi.prefetch(0, 0)) Aux;
-      Aux aux[2][NPASS];
-#pragma unroll
-      for (int pass = 0; pass < NPASS; pass++) aux[0][pass] = epi.prefetch(wm0 + pass * RPP + lane / LPR, wn0 + c0);
-#pragma unroll
-      for (int i = 0; i < TM; i++) {
-        stage_block(i);
-        if (i + 1 < TM) {
-#pragma unroll
-          for (int pass = 0; pass < NPASS; pass++)
-            aux[(i + 1) & 1][pass] = epi.prefetch(wm0 + (i + 1) * 32 + pass * RPP + lane / LPR, wn0 + c0);
-        }
-#pragma unroll
-        for (int pass = 0; pass < NPASS; pass++) {
-          float vals[NB][8];
-          read_pass(pass, vals);
-          epi(wm0 + i * 32 + pass * RPP + lane / LPR, wn0 + c0, vals, aux[i & 1][pass]);
-        }
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < TM; i++) {
-        stage_block(i);
-        // not unrolled: the epilogue functor may be large (activation functions), and a body that is
-        // too big keeps the compiler from unrolling the loop over i, which would put the accumulators
-        // into scratch memory (their indices must be compile-time constants)
-#pragma unroll 1
-        for (int pass = 0; pass < NPASS; pass++) {
-          float vals[NB][8];
-          read_pass(pass, vals);
-          epi(wm0 + i * 32 + pass * RPP + lane / LPR, wn0 + c0, vals);
-        }
-      }
-    }
+    epilogue(smem, acc, epi, wave, lane, wm0, wn0);
     MOE_PHASE(3);
   }
 };
