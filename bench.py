@@ -26,8 +26,7 @@ HBM_PEAK_GBS = 8000.0        # MI355X HBM3E, published
 MFMA_BF16_PEAK_TF = 2500.0   # dense bf16 matrix peak, published
 FP32_VEC_PEAK_TF = 157.3
 
-GEMM_LABELS = ("gemm_fwd_gate_up", "gemm_fwd_down", "gemm_bwd_dh", "gemm_bwd_dx", "gemm_bwd_dwd", "gemm_bwd_dwgu",
-               "gemm_bwd_dw_light")
+GEMM_LABELS = ("gemm_fwd_gate_up", "gemm_fwd_down", "gemm_bwd_dh_dwd", "gemm_bwd_dx_dwgu", "gemm_bwd_dw_light")
 LIGHT_GROUP_ROWS = 256       # routed experts with at most this many rows take the light weight-gradient kernels
 PROBE_BYTES = 1 << 30        # size of the calibration copy
 PROBE_LAUNCHES = 5
@@ -38,11 +37,12 @@ MFMA_PROBE_ITERS = 1000
 SYMBOL = {
     "gemm_fwd_gate_up": "moe::row_gemm_kernel<moe::RowCores<2, 2, false>, 2, 1, false>(moe::RowGemm)",
     "gemm_fwd_down": "moe::row_gemm_kernel<moe::RowCores<2, 1, false>, 1, 0, false>(moe::RowGemm)",
-    "gemm_bwd_dh": "moe::row_gemm_kernel<moe::RowCores<2, 1, true>, 1, 2, true>(moe::RowGemm)",
-    "gemm_bwd_dx": "moe::row_gemm_kernel<moe::RowCores<2, 1, true>, 1, 0, true>(moe::RowGemm)",
-    "gemm_bwd_dwd": "moe::w_gemm_kernel<moe::MfmaDmaCore<256, 256, 1, false, false, 2, 2, 1>, 1>(moe::WGemm)",
-    "gemm_bwd_dwgu": "moe::w_gemm_kernel<moe::MfmaDmaCore<256, 128, 2, false, false, 2, 2, 1>, 2>(moe::WGemm)",
-    "gemm_bwd_dw_light": "moe::w_gemm_kernel<moe::MfmaDmaCore<128, 128, 1, false, false, 2, 2, 0>, 1>(moe::WGemm)",
+    "gemm_bwd_dh_dwd": "moe::row_w_gemm_kernel<moe::RowCores<2, 1, true>, 2, moe::MfmaDmaCore<unsigned short, 256, 256, 1, "
+                       "false, false, 2, 2, 1, false>, 1>(moe::RowGemm, moe::WGemm, int)",
+    "gemm_bwd_dx_dwgu": "moe::row_w_gemm_kernel<moe::RowCores<2, 1, true>, 0, moe::MfmaDmaCore<unsigned short, 256, 128, 2, "
+                        "false, false, 2, 2, 1, false>, 2>(moe::RowGemm, moe::WGemm, int)",
+    "gemm_bwd_dw_light": "moe::w_light_kernel<moe::MfmaDmaCore<unsigned short, 128, 128, 1, false, false, 2, 2, 0, false>>"
+                         "(moe::WGemm, moe::WGemm, int)",
 }
 
 
@@ -54,13 +54,14 @@ def algorithmic_work(cfg: wl.MoEConfig, counts):
     shared = cfg.n_shared * T * d * cfg.d_ff_shared
     unit = routed + shared
     m_in = 2.0 if cfg.ffn == "swiglu" else 1.0   # matrices on the input side of the expert (Wg, Wu | W^A)
-    flops = {"gemm_fwd_gate_up": 2.0 * m_in * unit, "gemm_fwd_down": 2.0 * unit, "gemm_bwd_dh": 2.0 * unit,
-             "gemm_bwd_dx": 2.0 * m_in * unit, "gemm_bwd_dwd": 2.0 * unit, "gemm_bwd_dwgu": 2.0 * m_in * unit}
-    if cfg.dtype == "bf16" and d % 64 == 0 and F % 64 == 0:
+    # (two launches each hold an input gradient and a weight gradient that does not depend on it)
+    flops = {"gemm_fwd_gate_up": 2.0 * m_in * unit, "gemm_fwd_down": 2.0 * unit, "gemm_bwd_dh_dwd": 4.0 * unit,
+             "gemm_bwd_dx_dwgu": 4.0 * m_in * unit}
+    if cfg.dtype == "bf16":
         light = int(counts[counts <= LIGHT_GROUP_ROWS].sum()) * d * F
-        flops["gemm_bwd_dw_light"] = (2.0 + 2.0 * m_in) * light  # two launches: dWd, then dWg (and dWu)
-        flops["gemm_bwd_dwd"] -= 2.0 * light
-        flops["gemm_bwd_dwgu"] -= 2.0 * m_in * light
+        flops["gemm_bwd_dw_light"] = (2.0 + 2.0 * m_in) * light  # dWd, dWg and dWu
+        flops["gemm_bwd_dh_dwd"] -= 2.0 * light
+        flops["gemm_bwd_dx_dwgu"] -= 2.0 * m_in * light
     has_sh = 1 if cfg.n_shared else 0
     byts = {
         "route_kernel": T * cfg.E * 4 + T * k * 8,

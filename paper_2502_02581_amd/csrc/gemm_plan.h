@@ -70,12 +70,12 @@ struct RowGemm {
 // per group: C[M, N] = A_g^T B_g over the rows of the group (K = rows of the group)
 struct WGemm {
   const int4* ginfo;        // per launch index (descending rows): {group, rows, first row, compact slot}; NULL: identity
-  int32_t n_rows;
+  int32_t n_rows, n_groups;
   int32_t M, N;
   const void* A;            // element (row, m) at A + row*lda + m
   int64_t lda;
   int32_t a_per_group;      // shared mode: A rows of group g start at g*n_rows
-  const void* B[2];         // element (row, n) at B + row*ldb + n; B[1]: second product (dual GEMM, or blockIdx.z = 1)
+  const void* B[2];         // element (row, n) at B + row*ldb + n; B[1]: second product (dual GEMM, or second pass)
   int64_t ldb;
   int32_t b_per_group;
   void* C[2];
