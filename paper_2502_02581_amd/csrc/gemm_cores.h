@@ -586,17 +586,22 @@ struct MfmaDmaCore {
         // whose slot the loads of tile it + DEPTH overwrite
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"((DEPTH - 1) * L) : "memory");
         __syncthreads();
-        issue_tile(it + DEPTH);
         const int slot = it % (DEPTH + 1);
         const T* As = lds + slot * A_ELEMS;
         const T* Bs = lds + A_SLOTS * A_ELEMS + slot * B_SET_ELEMS;
+        // the fragments of k-step ks + 1 are read under the MFMAs of ks, the first ones under the tile loads
+        Frags f[2];
+#pragma unroll
+        for (int r = 0; r < kFragLoads; r++) load_frag_n(As, Bs, ao, bo, 0, r, f[0]);
+        issue_tile(it + DEPTH);
 #pragma unroll
         for (int ks = 0; ks < KS; ks++) {
-          Frags f;
+          if (ks + 1 < KS) {
 #pragma unroll
-          for (int r = 0; r < kFragLoads; r++) load_frag_n(As, Bs, ao, bo, ks, r, f);
+            for (int r = 0; r < kFragLoads; r++) load_frag_n(As, Bs, ao, bo, ks + 1, r, f[(ks + 1) & 1]);
+          }
 #pragma unroll
-          for (int m = 0; m < kMfma; m++) mfma_n(acc, f, m);
+          for (int m = 0; m < kMfma; m++) mfma_n(acc, f[ks & 1], m);
         }
       }
     } else if constexpr (!RING) {
