@@ -42,10 +42,16 @@ inline Plan carve_plan(void* ws, int /*n_groups*/, int max_tiles) {
 
 // C[rows, N] (+ second C when dual) = sum over (pair, seg) of A_seg[rows, K] * B_seg[K, N]
 struct RowGemm {
-  const RowTile* tiles;     // NULL: direct tiling of n_rows rows, single group 0
+  const RowTile* tiles;     // NULL: no plan, n_groups groups of n_rows rows in tiles of one height
   const int32_t* n_tiles;
   int32_t n_rows;
-  int32_t direct_kind;      // tiles == NULL on the LDS-DMA path: tile kind (height: that of the full tile >> kind) of the direct tiling
+  // without a plan:
+  int32_t n_groups;
+  int32_t direct_kind;      // tile kind: height of the full tile >> kind
+  int32_t n_parts, k_part;  // the values of K of a segment are summed in n_parts parts of k_part
+  int32_t part_blocks;      // blocks of one part
+  float* part;              // n_parts > 1: fp32 sums [n_parts][products][part_stride]
+  int64_t part_stride;
   int32_t N, K;
   int32_t n_pairs, n_segs;
   const void* A[2];         // per pair; element (row, k) at A + seg*a_seg + row*lda + k
@@ -69,8 +75,13 @@ struct RowGemm {
 
 // per group: C[M, N] = A_g^T B_g over the rows of the group (K = rows of the group)
 struct WGemm {
-  const int4* ginfo;        // per launch index (descending rows): {group, rows, first row, compact slot}; NULL: identity
+  const int4* ginfo;        // per launch index (descending rows): {group, rows, first row, compact slot}; NULL: no plan
   int32_t n_rows, n_groups;
+  // without a plan:
+  int32_t n_parts, k_part;  // the rows are summed in n_parts parts of k_part
+  float* part;              // n_parts > 1: fp32 sums [n_parts][products][part_stride]
+  int64_t part_stride;
+  int32_t *active_ids, *n_active;  // all groups, if not NULL
   int32_t M, N;
   const void* A;            // element (row, m) at A + row*lda + m
   int64_t lda;

@@ -4,7 +4,7 @@
 // pipeline only), 2: K loop done, 3: epilogue done (first wavefront) -- and every tile of the GEMM
 // kernels leaves one record {block, kernel id, group, column tile | kind << 8 | rows << 16, start,
 // end, phase cycles}: times from the 100 MHz wall clock, phases (set-up and first loads, K loop,
-// epilogue, rest) in shader-clock cycles.  moe_trace_read copies the records to the host.
+// epilogue, rest) in shader-clock cycles.  moe_trace_read_{f32,bf16,tail} copy the records to the host.
 #pragma once
 
 #ifdef MOE_TRACE
@@ -12,15 +12,15 @@
 #include <stdint.h>
 
 namespace moe {
-__device__ long long g_ph[65536 * 4];
+static __device__ long long g_ph[65536 * 4];
 struct TraceRec {
   int32_t block, kernel, group, what;
   unsigned long long t0, t1;
   int32_t ph[4];
 };
 constexpr int kTraceMax = 1 << 18;
-__device__ TraceRec g_trace[kTraceMax];
-__device__ int g_trace_n;
+static __device__ TraceRec g_trace[kTraceMax];
+static __device__ int g_trace_n;
 __device__ __forceinline__ void trace_put(int kernel, int group, int what, unsigned long long t0) {
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -47,8 +47,8 @@ __device__ __forceinline__ void trace_put(int kernel, int group, int what, unsig
   moe::trace_put((kernel), (int)((unsigned long long)clock64() - moe_trace_c0), (what), moe_trace_t0)
 #define MOE_TRACE_W_TILE(kernel, group, what) moe::trace_put((kernel), (group), (what), moe_trace_t0)
 // copies the trace records to the host buffer (at most max_records), returns their number and clears the trace
-#define MOE_TRACE_DEFINE_READER                                                                                       \
-  extern "C" int moe_trace_read(void* host, int max_records) {                                                        \
+#define MOE_TRACE_DEFINE_READER(name)                                                                                 \
+  extern "C" int name(void* host, int max_records) {                                                                  \
     int n = 0;                                                                                                        \
     if (hipMemcpyFromSymbol(&n, HIP_SYMBOL(moe::g_trace_n), sizeof(int)) != hipSuccess) return -1;                   \
     if (n > moe::kTraceMax) n = moe::kTraceMax;                                                                       \
@@ -64,5 +64,5 @@ __device__ __forceinline__ void trace_put(int kernel, int group, int what, unsig
 #define MOE_TRACE_BEGIN() do {} while (0)
 #define MOE_TRACE_ROW_TILE(kernel, what) do {} while (0)
 #define MOE_TRACE_W_TILE(kernel, group, what) do {} while (0)
-#define MOE_TRACE_DEFINE_READER
+#define MOE_TRACE_DEFINE_READER(name)
 #endif
