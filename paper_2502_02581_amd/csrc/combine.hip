@@ -146,16 +146,6 @@ __global__ __launch_bounds__(512) void combine_bwd_kernel(const T* __restrict__ 
   }
 }
 
-// Threads per token block: the 16-byte pieces of a row are spread over as few equal trips as fit 512
-// threads, so that no lane idles in the last trip (d = 7168 in bf16: 896 pieces = 2 trips of 448).
-static unsigned row_block_threads(int d, int elems_per_piece) {
-  const int pieces = d / elems_per_piece;
-  const int trips = (pieces + 511) / 512;
-  const int per_trip = (pieces + trips - 1) / trips;
-  const int threads = (per_trip + 63) / 64 * 64;
-  return (unsigned)(threads < 64 ? 64 : threads);
-}
-
 template <typename T>
 static void launch_combine(const moe_shape_t* s, const void* Yp, const int32_t* row_of, const float* topk_w,
                            const void* Yadd, void* Y, hipStream_t st) {
@@ -163,13 +153,7 @@ static void launch_combine(const moe_shape_t* s, const void* Yp, const int32_t* 
 #define MOE_COMBINE(K)                                                                                       \
   hipLaunchKernelGGL((combine_kernel<T, K>), grid, block, 0, st, (const T*)Yp, row_of, topk_w, (const T*)Yadd, \
                      (T*)Y, s->d, s->k)
-  switch (s->k) {
-    case 1: MOE_COMBINE(1); break;
-    case 2: MOE_COMBINE(2); break;
-    case 4: MOE_COMBINE(4); break;
-    case 8: MOE_COMBINE(8); break;
-    default: MOE_COMBINE(0); break;
-  }
+  MOE_BY_TOP_K(s->k, MOE_COMBINE);
 #undef MOE_COMBINE
 }
 
@@ -180,13 +164,7 @@ static void launch_combine_bwd(const moe_shape_t* s, const void* dY, const void*
 #define MOE_COMBINE_BWD(K)                                                                                    \
   hipLaunchKernelGGL((combine_bwd_kernel<T, K>), grid, block, 0, st, (const T*)dY, (const T*)Yp, row_of, topk_w, \
                      (T*)dYp, dw, s->d, s->k)
-  switch (s->k) {
-    case 1: MOE_COMBINE_BWD(1); break;
-    case 2: MOE_COMBINE_BWD(2); break;
-    case 4: MOE_COMBINE_BWD(4); break;
-    case 8: MOE_COMBINE_BWD(8); break;
-    default: MOE_COMBINE_BWD(0); break;
-  }
+  MOE_BY_TOP_K(s->k, MOE_COMBINE_BWD);
 #undef MOE_COMBINE_BWD
 }
 

@@ -228,7 +228,7 @@ __global__ __launch_bounds__(64) void dispatch_rank(const int32_t* __restrict__ 
 
 // Xp[row_of[t*k+j], :] = X[t, :], 16 bytes per lane per access.  K > 0: k known at compile time.
 template <int K>
-__global__ __launch_bounds__(256) void dispatch_rows(const uint4* __restrict__ X,
+__global__ __launch_bounds__(512) void dispatch_rows(const uint4* __restrict__ X,
                                                      const int32_t* __restrict__ row_of, int k_rt,
                                                      int vec_per_row, uint4* __restrict__ Xp) {
   constexpr int KM = K > 0 ? K : 1;
@@ -282,16 +282,11 @@ static void dispatch_place(const moe_shape_t* shape, const void* X, const int32_
   }
   ProfScope prof("dispatch_rows", st);
   const int vec_per_row = (int)((size_t)shape->d * elem_size(shape->dtype) / 16);
+  const unsigned threads = row_block_threads(shape->d, 16 / (int)elem_size(shape->dtype));
 #define MOE_ROWS(K)                                                                                       \
-  hipLaunchKernelGGL(dispatch_rows<K>, dim3(shape->T), dim3(256), 0, st, (const uint4*)X, row_of, shape->k, \
+  hipLaunchKernelGGL(dispatch_rows<K>, dim3(shape->T), dim3(threads), 0, st, (const uint4*)X, row_of, shape->k, \
                      vec_per_row, (uint4*)Xp)
-  switch (shape->k) {
-    case 1: MOE_ROWS(1); break;
-    case 2: MOE_ROWS(2); break;
-    case 4: MOE_ROWS(4); break;
-    case 8: MOE_ROWS(8); break;
-    default: MOE_ROWS(0); break;
-  }
+  MOE_BY_TOP_K(shape->k, MOE_ROWS);
 #undef MOE_ROWS
 }
 

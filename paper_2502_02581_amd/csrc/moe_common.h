@@ -133,4 +133,28 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
+// ---- one block per token row ----------------------------------------------------------------
+// Instances of a row kernel by top-k: the common values at compile time, 0 for any other.
+#define MOE_BY_TOP_K(k, CALL) \
+  switch (k) {                \
+    case 1: CALL(1); break;   \
+    case 2: CALL(2); break;   \
+    case 3: CALL(3); break;   \
+    case 4: CALL(4); break;   \
+    case 5: CALL(5); break;   \
+    case 6: CALL(6); break;   \
+    case 7: CALL(7); break;   \
+    case 8: CALL(8); break;   \
+    default: CALL(0); break;  \
+  }
+// Threads per block: the 16-byte pieces of a row are spread over as few equal trips as fit 512 threads, so
+// that no lane idles in the last trip (d = 7168 in bf16: 896 pieces = 2 trips of 448).
+inline unsigned row_block_threads(int d, int elems_per_piece) {
+  const int pieces = d / elems_per_piece;
+  const int trips = (pieces + 511) / 512;
+  const int per_trip = (pieces + trips - 1) / trips;
+  const int threads = (per_trip + 63) / 64 * 64;
+  return (unsigned)(threads < 64 ? 64 : threads);
+}
+
 }  // namespace moe
