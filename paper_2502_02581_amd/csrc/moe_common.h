@@ -133,6 +133,28 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
+// Inclusive scan over a block of 1024 threads: in the wavefronts by shuffles, then each thread adds the totals of
+// the wavefronts before its own.  `wsum` (16 ints of LDS, 16-byte aligned) is this scan's alone; one barrier.
+__device__ __forceinline__ int block_scan_1024(int v, int32_t* wsum, int& total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int m = 1; m < kWave; m <<= 1) {
+    const int u = __shfl_up(v, m, kWave);
+    if (lane >= m) v += u;
+  }
+  if (lane == kWave - 1) wsum[wave] = v;
+  __syncthreads();
+  int before = 0;
+  total = 0;
+#pragma unroll
+  for (int w = 0; w < 16; w++) {
+    const int s = wsum[w];
+    before += w < wave ? s : 0;
+    total += s;
+  }
+  return v + before;
+}
+
 // ---- one block per token row ----------------------------------------------------------------
 // Instances of a row kernel by top-k: the common values at compile time, 0 for any other.
 #define MOE_BY_TOP_K(k, CALL) \
