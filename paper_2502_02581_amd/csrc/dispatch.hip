@@ -5,10 +5,8 @@
 //                      on their order), written to ws as hist[chunk][e].
 //   2. dispatch_scan   one block: exclusive scan over chunks per expert (in place), counts,
 //                      and the exclusive scan over experts (offsets).
-//   3. dispatch_rank   one wavefront per chunk: walks its chunk in assignment order; the rank of
-//                      an assignment among equal experts inside a 64-wide step comes from
-//                      ballots in lane order, so row_of is the same on every run (stable sort).
-//   4. dispatch_rows   one block per token: reads the token row once, writes it to its k rows.
+//   3. dispatch_rows   one block per token: finds the rows of its k assignments, reads the token row once and
+//                      writes it to them.
 #include <algorithm>
 #include <mutex>
 
@@ -17,7 +15,7 @@
 
 namespace moe {
 
-constexpr int kChunk = 256;  // most assignments per wavefront in steps 1 and 3
+constexpr int kChunk = 256;  // most assignments per chunk
 constexpr int kShareFloats = 8192;  // LDS floats of the fused prologue for the per-wave share sums
 
 __global__ __launch_bounds__(64) void dispatch_count(const int32_t* __restrict__ topk_idx, int A, int E, int chunk_len,
@@ -186,117 +184,95 @@ __global__ __launch_bounds__(1024) void route_hist_kernel(const float* __restric
   }
 }
 
-__global__ __launch_bounds__(64) void dispatch_rank(const int32_t* __restrict__ topk_idx, int A, int E, int chunk_len,
-                                                    const int32_t* __restrict__ hist,
-                                                    const int32_t* __restrict__ offsets,
-                                                    int32_t* __restrict__ row_of,
-                                                    int32_t* __restrict__ src_of) {
-  __shared__ int32_t nxt[MOE_MAX_EXPERTS];
-  const int lane = threadIdx.x;
-  const int chunk = blockIdx.x;
-  for (int e = lane; e < E; e += 64) nxt[e] = offsets[e] + hist[(size_t)chunk * E + e];
-  __syncthreads();
-  const int a0 = chunk * chunk_len, a1 = min(A, a0 + chunk_len);
-  const uint64_t lt_mask = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-  for (int s = 0; s < chunk_len; s += 64) {
-    const int a = a0 + s + lane;
-    int e = -1;
-    if (a < a1) {
-      e = topk_idx[a];
-      if (e < 0 || e >= E) e = -1;
-    }
-    const bool valid = e >= 0;
-    uint64_t todo = __ballot(valid);
-    int rank = 0, group = 0;
-    bool last = false;
-    while (todo) {
-      int leader = __ffsll((unsigned long long)todo) - 1;
-      int le = __shfl(e, leader, kWave);
-      uint64_t same = __ballot(valid && e == le);
-      if (valid && e == le) {
-        rank = __popcll(same & lt_mask);
-        group = __popcll(same);
-        last = (same >> lane) == 1ull;  // highest lane of the group
-      }
-      todo &= ~same;
-    }
-    int r = 0;
-    if (valid) r = nxt[e] + rank;
-    __syncthreads();
-    if (valid && last) nxt[e] += group;
-    __syncthreads();
-    if (valid) {
-      row_of[a] = r;
-      src_of[r] = a;
-    }
-  }
-}
-
-// Xp[row_of[t*k+j], :] = X[t, :], 16 bytes per lane per access.  K > 0: k known at compile time.
+// Ranks and rows of one token per block.  Wavefronts first place the token's assignments, one each at a time: the rows
+// before its own are those of the experts before, those of the earlier chunks, and, inside its chunk, the earlier
+// assignments to the same expert, counted by ballots over the at most kChunk indices before it (so row_of is the same on
+// every run: a stable sort).  Then Xp[row_of[t*k+j], :] = X[t, :], 16 bytes per lane per access; the first pieces are
+// loaded ahead of the barrier between.  An index out of range has no row.  K > 0: k known at compile time.
+// (Ranks in a launch of their own, one wavefront per chunk: T = 16, top-4: 3.3 + 2.7 us, now 3.7; T = 2777, top-3: 4.9 +
+// 8.9, now 10.9; T = 8192, d = 768, top-2: 5.0 + 9.0, now 11.7.)
 template <int K>
-__global__ __launch_bounds__(512) void dispatch_rows(const uint4* __restrict__ X,
-                                                     const int32_t* __restrict__ row_of, int k_rt,
-                                                     int vec_per_row, uint4* __restrict__ Xp) {
+__global__ __launch_bounds__(512) void dispatch_rows(const uint4* __restrict__ X, const int32_t* __restrict__ topk_idx,
+                                                     const int32_t* __restrict__ hist, const int32_t* __restrict__ offsets,
+                                                     int E, int chunk_len, int k_rt, int vec_per_row,
+                                                     int32_t* __restrict__ row_of, int32_t* __restrict__ src_of,
+                                                     uint4* __restrict__ Xp) {
+  __shared__ int32_t rows[MOE_MAX_TOPK];
   constexpr int KM = K > 0 ? K : 1;
   const int k = K > 0 ? K : k_rt;
-  const int t = blockIdx.x;
+  const int t = blockIdx.x, nthr = blockDim.x;
+  const int lane = threadIdx.x & 63;
   const uint4* src = X + (size_t)t * vec_per_row;
-  if (K > 0) {
-    uint4* dst[KM];
+  int c = threadIdx.x;
+  uint4 v0 = {}, v1 = {};
+  if (c < vec_per_row) v0 = src[c];
+  if (c + nthr < vec_per_row) v1 = src[c + nthr];
+  for (int j = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); j < k; j += nthr >> 6) {
+    const int a = t * k + j;
+    const int chunk = (int)((uint32_t)a / (uint32_t)chunk_len), a0 = chunk * chunk_len;
+    const int e = topk_idx[a];
+    int x[kChunk / 64];
 #pragma unroll
-    for (int j = 0; j < KM; j++) dst[j] = Xp + (size_t)row_of[(size_t)t * k + j] * vec_per_row;
+    for (int q = 0; q < kChunk / 64; q++) x[q] = a0 + 64 * q + lane < a ? topk_idx[a0 + 64 * q + lane] : -1;
+    int r = -1;
+    if (e >= 0 && e < E) {
+      r = offsets[e] + hist[(size_t)chunk * E + e];
+#pragma unroll
+      for (int q = 0; q < kChunk / 64; q++) r += __popcll(__ballot(x[q] == e));
+    }
+    if (lane == 0) {
+      rows[j] = r;
+      if (r >= 0) {
+        row_of[a] = r;
+        src_of[r] = a;
+      }
+    }
+  }
+  __syncthreads();
+  if (K > 0) {
+    int row[KM];
+#pragma unroll
+    for (int j = 0; j < KM; j++) row[j] = __builtin_amdgcn_readfirstlane(rows[j]);
     // two pieces per thread and trip: both loads are issued before the 2k stores
-    int c = threadIdx.x;
-    for (; c + (int)blockDim.x < vec_per_row; c += 2 * blockDim.x) {
-      const uint4 v0 = src[c], v1 = src[c + blockDim.x];
+    while (c < vec_per_row) {
 #pragma unroll
       for (int j = 0; j < KM; j++) {
-        dst[j][c] = v0;
-        dst[j][c + blockDim.x] = v1;
+        if (row[j] < 0) continue;
+        uint4* dst = Xp + (size_t)row[j] * vec_per_row;
+        dst[c] = v0;
+        if (c + nthr < vec_per_row) dst[c + nthr] = v1;
       }
-    }
-    if (c < vec_per_row) {
-      const uint4 v0 = src[c];
-#pragma unroll
-      for (int j = 0; j < KM; j++) dst[j][c] = v0;
+      c += 2 * nthr;
+      if (c < vec_per_row) v0 = src[c];
+      if (c + nthr < vec_per_row) v1 = src[c + nthr];
     }
   } else {
-    for (int c = threadIdx.x; c < vec_per_row; c += blockDim.x) {
-      uint4 v = src[c];
-      for (int j = 0; j < k; j++) {
-        int r = row_of[(size_t)t * k + j];
-        Xp[(size_t)r * vec_per_row + c] = v;
-      }
+    for (; c < vec_per_row; c += nthr) {
+      const uint4 v = src[c];
+      for (int j = 0; j < k; j++)
+        if (rows[j] >= 0) Xp[(size_t)rows[j] * vec_per_row + c] = v;
     }
   }
 }
 
-}  // namespace moe
-
-namespace moe {
-// rank and row copy of a dispatch whose per-chunk histograms `hist` (chunks of chunk_len assignments)
+// ranks and row copy of a dispatch whose per-chunk histograms `hist` (chunks of chunk_len assignments)
 // have been scanned
 static void dispatch_place(const moe_shape_t* shape, const void* X, const int32_t* topk_idx, const int32_t* offsets,
-                           int32_t* row_of, int32_t* src_of, void* Xp, const int32_t* hist, int chunk_len, int n_chunks,
+                           int32_t* row_of, int32_t* src_of, void* Xp, const int32_t* hist, int chunk_len,
                            hipStream_t st) {
-  const int A = shape->T * shape->k;
-  if (n_chunks <= 0) return;
-  {
-    ProfScope prof("dispatch_rank", st);
-    hipLaunchKernelGGL(dispatch_rank, dim3(n_chunks), dim3(64), 0, st, topk_idx, A, shape->E, chunk_len, hist, offsets,
-                       row_of, src_of);
-  }
+  if (shape->T == 0) return;
   ProfScope prof("dispatch_rows", st);
   const int vec_per_row = (int)((size_t)shape->d * elem_size(shape->dtype) / 16);
-  const unsigned threads = row_block_threads(shape->d, 16 / (int)elem_size(shape->dtype));
-#define MOE_ROWS(K)                                                                                       \
-  hipLaunchKernelGGL(dispatch_rows<K>, dim3(shape->T), dim3(threads), 0, st, (const uint4*)X, row_of, shape->k, \
-                     vec_per_row, (uint4*)Xp)
+  // short rows get more threads than pieces, so that up to four assignments are placed at a time
+  const unsigned threads = std::max(row_block_threads(shape->d, 16 / (int)elem_size(shape->dtype)), 64u * std::min(shape->k, 4));
+#define MOE_ROWS(K)                                                                                                     \
+  hipLaunchKernelGGL(dispatch_rows<K>, dim3(shape->T), dim3(threads), 0, st, (const uint4*)X, topk_idx, hist, offsets, \
+                     shape->E, chunk_len, shape->k, vec_per_row, row_of, src_of, (uint4*)Xp)
   MOE_BY_TOP_K(shape->k, MOE_ROWS);
 #undef MOE_ROWS
 }
 
-// the four launches of a dispatch; `hist` is scratch of n_chunks * E counters (every one is written
+// the three launches of a dispatch; `hist` is scratch of n_chunks * E counters (every one is written
 // by dispatch_count before anything reads it)
 static void dispatch_launch(const moe_shape_t* shape, const void* X, const int32_t* topk_idx, int32_t* counts,
                             int32_t* offsets, int32_t* row_of, int32_t* src_of, void* Xp, int32_t* hist,
@@ -312,7 +288,7 @@ static void dispatch_launch(const moe_shape_t* shape, const void* X, const int32
     hipLaunchKernelGGL(dispatch_scan, dim3(1), dim3(1024), 0, st, hist, n_chunks, shape->E, counts, offsets,
                        (const float*)nullptr, (float*)nullptr, (float*)nullptr, 0, 1, 0.f);
   }
-  dispatch_place(shape, X, topk_idx, offsets, row_of, src_of, Xp, hist, kChunk, n_chunks, st);
+  dispatch_place(shape, X, topk_idx, offsets, row_of, src_of, Xp, hist, kChunk, st);
 }
 
 // chunks of the fused prologue: whole tokens, at most kChunk assignments, and fewer than that while the
@@ -461,6 +437,6 @@ extern "C" int moe_route_dispatch(const moe_shape_t* shape, const float* logits,
     hipLaunchKernelGGL(dispatch_scan, dim3(1), dim3(1024), 0, st, hist, n_chunks, E, counts, offsets,
                        (const float*)partial, aux_P, aux_loss, T, k, aux_alpha);
   }
-  dispatch_place(shape, X, topk_idx, offsets, row_of, src_of, Xp, hist, tpc * k, n_chunks, st);
+  dispatch_place(shape, X, topk_idx, offsets, row_of, src_of, Xp, hist, tpc * k, st);
   return launch_status("moe_route_dispatch");
 }

@@ -1,0 +1,97 @@
+"""GPU: the calls that move whole token rows, and the tile plan, at the edges of their ranges.
+
+Dispatch: every top-k with an instance of its own and two without, rows of one piece up to several trips of a block, a
+batch whose tokens straddle the chunks of the counting sort (256 assignments).  The sort is exact.  Combine: fp32
+sums of k + 1 terms and one rounding; adjoint dots over d <= 7168: sqrt(7168) * 2^-24 = 5e-6.  Plan: group counts on
+both sides of a wavefront and at the limit, with ties and empty groups; K <= 16 in fp32.
+"""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+def rel(got, ref):
+    return float((got.double().cpu() - ref).norm() / ref.norm())
+
+
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("d,dtype", [(8, "f32"), (8, "bf16"), (520, "f32"), (1000, "bf16"), (7168, "bf16"), (5000, "f32")])
+@pytest.mark.parametrize("k", [1, 2, 3, 4, 5, 6, 7, 8, 9, 17])
+def test_rows(k, d, dtype, fused):
+    import paper_2502_02581_amd as moe
+
+    T, E = 259, 21
+    s = moe.MoEShape(T, d, E, k, 8, dtype)
+    dt = s.torch_dtype
+    g = torch.Generator().manual_seed(k * 10007 + d)
+    X = torch.randn(T, d, generator=g).to(dt)
+    logits = torch.randn(T, E, generator=g)
+    logits[:, 3] += 2.0
+    i32 = lambda *n: torch.full(n, -7, dtype=torch.int32, device=DEV)
+    new = lambda *n: torch.full(n, float("nan"), dtype=dt, device=DEV)
+    idx, w = i32(T, k), torch.empty(T, k, device=DEV)
+    counts, offsets, row_of, src_of, Xp = i32(E), i32(E + 1), i32(T * k), i32(T * k), new(T * k, d)
+    ws = torch.full((max(moe.moe_dispatch_workspace_bytes(s), moe.moe_route_dispatch_workspace_bytes(s)),), 0xff,
+                    dtype=torch.uint8, device=DEV)
+    if fused:
+        moe.moe_route_dispatch(s, logits.to(DEV), X.to(DEV), 0.0, idx, w, counts, offsets, row_of, src_of, Xp, None, None, ws)
+    else:
+        moe.moe_route(s, logits.to(DEV), idx, w)
+        moe.moe_dispatch(s, X.to(DEV), idx, counts, offsets, row_of, src_of, Xp, ws)
+    flat = idx.cpu().numpy().reshape(-1)
+    order = np.argsort(flat, kind="stable")
+    inverse = np.empty_like(order)
+    inverse[order] = np.arange(T * k)
+    assert np.array_equal(src_of.cpu().numpy(), order) and np.array_equal(row_of.cpu().numpy(), inverse)
+    assert np.array_equal(counts.cpu().numpy(), np.bincount(flat, minlength=E))
+    assert offsets.cpu().tolist() == [0] + np.cumsum(np.bincount(flat, minlength=E)).tolist()
+    assert torch.equal(Xp.cpu(), X[torch.from_numpy(order // k)])
+
+    Yp, dY, add = torch.randn(T * k, d, generator=g).to(dt), torch.randn(T, d, generator=g).to(dt), torch.randn(T, d, generator=g).to(dt)
+    Y, Y1, dYp, dw = new(T, d), new(T, d), new(T * k, d), torch.empty(T, k, device=DEV)
+    moe.moe_combine(s, Yp.to(DEV), row_of, w, add.to(DEV), Y)
+    moe.moe_combine(s, Yp.to(DEV), row_of, None, None, Y1)
+    moe.moe_combine_bwd(s, dY.to(DEV), Yp.to(DEV), row_of, w, dYp, dw)
+    rows, w64 = Yp.double()[torch.from_numpy(inverse).reshape(T, k)], w.cpu().double()
+    tol = 1e-6 if dtype == "f32" else 4e-3   # one rounding: 2^-24, 2^-9 at most
+    assert rel(Y, (rows * w64[:, :, None]).sum(1) + add.double()) <= tol
+    assert rel(Y1, rows.sum(1)) <= tol
+    assert rel(dYp[row_of.long()].reshape(T, k, d), dY.double()[:, None, :] * w64[:, :, None]) <= tol
+    assert rel(dw, (rows * dY.double()[:, None, :]).sum(2)) <= 1e-5
+
+
+@pytest.mark.parametrize("E", [1, 3, 63, 64, 65, 200, 1023, 1024])
+def test_plan_of_many_groups(E):
+    import paper_2502_02581_amd as moe
+
+    d = F = 16
+    rng = np.random.default_rng(E)
+    rows = rng.choice([0, 0, 1, 2, 8, 9, 16, 17, 40, 41, 57, 64, 65, 130], size=E)  # many ties
+    rows[E // 2] = 700
+    n = int(rows.sum())
+    off = np.concatenate([[0], np.cumsum(rows)])
+    s = moe.MoEShape(n, d, E, 1, F, "f32")
+    g = torch.Generator().manual_seed(E)
+    X, dY = torch.randn(n, d, generator=g), torch.randn(n, d, generator=g)
+    Wg, Wd = torch.randn(E, d, F, generator=g) / 4, torch.randn(E, F, d, generator=g) / 4
+    new = lambda *m: torch.full(m, float("nan"), device=DEV)
+    G, H, Y, dX, dWg, dWd = new(n, F), new(n, F), new(n, d), new(n, d), new(E, d, F), new(E, F, d)
+    ids, n_act = torch.empty(E, dtype=torch.int32, device=DEV), torch.empty(1, dtype=torch.int32, device=DEV)
+    ws = torch.full((max(moe.moe_expert_fwd_workspace_bytes(s, E, n, False), moe.moe_expert_bwd_workspace_bytes(s, E, n, False)),),
+                    0xff, dtype=torch.uint8, device=DEV)
+    offs, Xd, dYd, w = torch.from_numpy(off).int().to(DEV), X.to(DEV), dY.to(DEV), [Wg.to(DEV), None, Wd.to(DEV)]
+    moe.moe_expert_fwd(s, E, offs, n, Xd, *w, G, None, H, Y, ws)
+    moe.moe_expert_bwd(s, E, offs, n, Xd, *w, G, None, H, dYd, dX, ids, n_act, dWg, None, dWd, ws)
+    active = np.flatnonzero(rows)
+    assert ids.tolist() == active.tolist() + [-1] * (E - len(active)) and int(n_act) == len(active)
+    wg, wd = Wg.double().requires_grad_(True), Wd.double().requires_grad_(True)
+    x = X.double().requires_grad_(True)
+    y = torch.cat([torch.nn.functional.gelu(x[off[e]:off[e + 1]] @ wg[e]) @ wd[e] for e in active])
+    y.backward(dY.double())
+    at = torch.from_numpy(active)
+    for got, ref in ((Y, y.detach()), (dX, x.grad), (dWg[: len(active)], wg.grad[at]), (dWd[: len(active)], wd.grad[at])):
+        assert rel(got, ref) <= 5e-6
