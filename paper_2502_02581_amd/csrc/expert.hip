@@ -136,6 +136,7 @@ static size_t bwd_base(const moe_shape_t* s, int n_groups, int n_rows, bool shar
   return plan_size_for(n_groups, n_rows, shared) + 2 * grad_size_for(s, n_groups, n_rows, shared);
 }
 static size_t shared_parts(const moe_shape_t* s, int n_groups, int n_rows, bool bwd) {
+  if (s->d <= 0 || s->d_ff <= 0) return 0;  // a shape that the calls refuse: there are no products to divide
   switch (pick_path(s)) {
     case PATH_F32: return expert_part_bytes<PATH_F32>(s->d, s->d_ff, n_groups, n_rows, bwd);
     case PATH_BF16_TAIL: return expert_part_bytes<PATH_BF16_TAIL>(s->d, s->d_ff, n_groups, n_rows, bwd);

@@ -42,6 +42,15 @@ def test_abi_version_matches_header(lib):
     assert lib.moe_abi_version() == ver
 
 
+@pytest.mark.parametrize("d, d_ff", [(0, 128), (-8, 128), (128, 0)])
+def test_workspace_queries_answer_for_shapes_that_the_calls_refuse(lib, d, d_ff):
+    import paper_2502_02581_amd as moe
+
+    shape = moe.MoEShape(64, d, 8, 2, d_ff, "bf16", "softmax", True)
+    assert moe.moe_expert_fwd_workspace_bytes(shape, 2, 64, True) == 768   # the plan of 2 groups in tiles of 64 rows
+    assert moe.moe_expert_bwd_workspace_bytes(shape, 2, 64, True) == 768 + 2 * 2 * 64 * d_ff * 2
+
+
 def test_host_side_validation(lib):
     import paper_2502_02581_amd as moe
     from paper_2502_02581_amd.binding import _CShape
