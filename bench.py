@@ -35,12 +35,12 @@ MFMA_PROBE_BLOCKS = 2048     # blocks (8 per CU) and rounds of the register-resi
 MFMA_PROBE_ITERS = 1000
 # kernel behind each profiling label on the bf16 LDS-DMA path, as rocprofv3 names it (one label = one kernel symbol)
 SYMBOL = {
-    "gemm_fwd_gate_up": "moe::row_gemm_kernel<moe::RowCores<2, 2, false>, 2, 1, false>(moe::RowGemm)",
-    "gemm_fwd_down": "moe::row_gemm_kernel<moe::RowCores<2, 1, false>, 1, 0, false>(moe::RowGemm)",
+    "gemm_fwd_gate_up": "moe::row_gemm_kernel<moe::RowCores<2, 2, false>, 2, 1, false, true>(moe::RowGemm)",
+    "gemm_fwd_down": "moe::row_gemm_kernel<moe::RowCores<2, 1, false>, 1, 0, false, true>(moe::RowGemm)",
     "gemm_bwd_dh_dwd": "moe::row_w_gemm_kernel<moe::RowCores<2, 1, true>, 2, moe::MfmaDmaCore<unsigned short, 256, 256, 1, "
-                       "false, false, 2, 2, 1, false>, 1>(moe::RowGemm, moe::WGemm, int)",
+                       "false, false, 2, 2, 1, false>, 1, true>(moe::RowGemm, moe::WGemm, int, int, int)",
     "gemm_bwd_dx_dwgu": "moe::row_w_gemm_kernel<moe::RowCores<2, 1, true>, 0, moe::MfmaDmaCore<unsigned short, 256, 128, 2, "
-                        "false, false, 2, 2, 1, false>, 2>(moe::RowGemm, moe::WGemm, int)",
+                        "false, false, 2, 2, 1, false>, 2, true>(moe::RowGemm, moe::WGemm, int, int, int)",
     "gemm_bwd_dw_light": "moe::w_light_kernel<moe::MfmaDmaCore<unsigned short, 128, 128, 1, false, false, 2, 2, 0, false>>"
                          "(moe::WGemm, moe::WGemm, int)",
 }
@@ -343,7 +343,8 @@ def main():
             ent["gbs"] = round(byts[label] / (per_step_ms * 1e-3) / 1e9, 1)
             ent["frac_hbm_peak"] = round(ent["gbs"] / HBM_PEAK_GBS, 4)
         kernels[label] = ent
-    gemm_ms = sum(kernels[l]["ms_per_step"] for l in GEMM_LABELS if l in kernels)
+    # (the sums of products that are computed in parts belong to the products)
+    gemm_ms = sum(kernels[l]["ms_per_step"] for l in GEMM_LABELS + ("gemm_reduce",) if l in kernels)
     gemm_tflops = sum(flops.values()) / (gemm_ms * 1e-3) / 1e12 if gemm_ms > 0 else 0.0
     # route, dispatch and combine kernels together: their algorithmic bytes over their summed time
     stream_ms = sum(kernels[l]["ms_per_step"] for l in kernels if l in byts or l.startswith("dispatch_"))
