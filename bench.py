@@ -34,14 +34,14 @@ COLD_STEPS = 3               # steps of the cold-cache variant
 MFMA_PROBE_BLOCKS = 2048     # blocks (8 per CU) and rounds of the register-resident matrix loop
 MFMA_PROBE_ITERS = 1000
 # kernel behind each profiling label on the bf16 LDS-DMA path, as rocprofv3 names it (one label = one kernel symbol)
-SYMBOL = {
+SYMBOL = {   # (launches over the routed experts; the shared experts' instances of a label differ in the last flag)
     "gemm_fwd_gate_up": "moe::row_gemm_kernel<moe::RowCores<2, 2, false>, 2, 1, false, true>(moe::RowGemm)",
     "gemm_fwd_down": "moe::row_gemm_kernel<moe::RowCores<2, 1, false>, 1, 0, false, true>(moe::RowGemm)",
     "gemm_bwd_dh_dwd": "moe::row_w_gemm_kernel<moe::RowCores<2, 1, true>, 2, moe::MfmaDmaCore<unsigned short, 256, 256, 1, "
                        "false, false, 2, 2, 1, false>, 1, true>(moe::RowGemm, moe::WGemm, int, int, int)",
     "gemm_bwd_dx_dwgu": "moe::row_w_gemm_kernel<moe::RowCores<2, 1, true>, 0, moe::MfmaDmaCore<unsigned short, 256, 128, 2, "
                         "false, false, 2, 2, 1, false>, 2, true>(moe::RowGemm, moe::WGemm, int, int, int)",
-    "gemm_bwd_dw_light": "moe::w_light_kernel<moe::MfmaDmaCore<unsigned short, 128, 128, 1, false, false, 2, 2, 0, false>>"
+    "gemm_bwd_dw_light": "moe::w_light_kernel<moe::MfmaDmaCore<unsigned short, 128, 128, 1, false, false, 2, 2, 0, false> >"
                          "(moe::WGemm, moe::WGemm, int)",
 }
 
