@@ -6,7 +6,8 @@
 //   2. dispatch_scan   one block: exclusive scan over chunks per expert (in place), counts,
 //                      and the exclusive scan over experts (offsets).
 //   3. dispatch_rows   one block per token: finds the rows of its k assignments, reads the token row once and
-//                      writes it to them.
+//                      writes it to them.  Many assignments of short rows are ranked before, by dispatch_rank,
+//                      one wavefront per chunk (dispatch_place says when).
 #include <algorithm>
 #include <mutex>
 
@@ -184,14 +185,52 @@ __global__ __launch_bounds__(1024) void route_hist_kernel(const float* __restric
   }
 }
 
-// Ranks and rows of one token per block.  Wavefronts first place the token's assignments, one each at a time: the rows
-// before its own are those of the experts before, those of the earlier chunks, and, inside its chunk, the earlier
-// assignments to the same expert, counted by ballots over the at most kChunk indices before it (so row_of is the same on
-// every run: a stable sort).  Then Xp[row_of[t*k+j], :] = X[t, :], 16 bytes per lane per access; the first pieces are
-// loaded ahead of the barrier between.  An index out of range has no row.  K > 0: k known at compile time.
+// Ranks of one chunk per wavefront, in a launch of their own: walks the chunk in assignment order, the rank of an
+// assignment among equal experts inside a 64-wide step comes from ballots in lane order (the same rows as
+// dispatch_rows finds by itself).  An index out of range gets row -1.
+__global__ __launch_bounds__(64) void dispatch_rank(const int32_t* __restrict__ topk_idx, int A, int E, int chunk_len,
+                                                    const int32_t* __restrict__ hist, const int32_t* __restrict__ offsets,
+                                                    int32_t* __restrict__ row_of, int32_t* __restrict__ src_of) {
+  __shared__ int32_t nxt[MOE_MAX_EXPERTS];
+  const int lane = threadIdx.x, chunk = blockIdx.x;
+  for (int e = lane; e < E; e += 64) nxt[e] = offsets[e] + hist[(size_t)chunk * E + e];
+  __syncthreads();
+  const int a0 = chunk * chunk_len, n = min(A - a0, chunk_len);
+  const uint64_t below = lane == 0 ? 0ull : ~0ull >> (64 - lane);
+  for (int s = 0; s < n; s += 64) {
+    const int i = s + lane;
+    int e = i < n ? topk_idx[a0 + i] : -1;
+    if (e < 0 || e >= E) e = -1;
+    uint64_t todo = __ballot(e >= 0);
+    int rank = 0, group = 0;
+    bool last = false;
+    while (todo) {
+      const int le = __shfl(e, __ffsll((unsigned long long)todo) - 1, kWave);
+      const uint64_t same = __ballot(e == le);
+      if (e == le) {
+        rank = __popcll(same & below);
+        group = __popcll(same);
+        last = (same >> lane) == 1ull;  // highest lane of the group
+      }
+      todo &= ~same;
+    }
+    const int r = e >= 0 ? nxt[e] + rank : -1;
+    __syncthreads();
+    if (last) nxt[e] += group;
+    __syncthreads();
+    if (i < n) row_of[a0 + i] = r;
+    if (r >= 0) src_of[r] = a0 + i;
+  }
+}
+
+// Rows of one token per block, and with PLACE their ranks.  Wavefronts first place the token's assignments, one each at a
+// time: the rows before its own are those of the experts before, those of the earlier chunks, and, inside its chunk, the
+// earlier assignments to the same expert, counted by ballots over the at most kChunk indices before it (so row_of is the
+// same on every run: a stable sort).  Then Xp[row_of[t*k+j], :] = X[t, :], 16 bytes per lane per access; the first pieces
+// are loaded ahead of the barrier between.  An index out of range has no row.  K > 0: k known at compile time.
 // (Ranks in a launch of their own, one wavefront per chunk: T = 16, top-4: 3.3 + 2.7 us, now 3.7; T = 2777, top-3: 4.9 +
-// 8.9, now 10.9; T = 8192, d = 768, top-2: 5.0 + 9.0, now 11.7.)
-template <int K>
+// 8.9, now 10.9; T = 8192, d = 768, top-2: 5.0 + 9.0, now 11.7.  Where that loses: see dispatch_place.)
+template <int K, bool PLACE>
 __global__ __launch_bounds__(512) void dispatch_rows(const uint4* __restrict__ X, const int32_t* __restrict__ topk_idx,
                                                      const int32_t* __restrict__ hist, const int32_t* __restrict__ offsets,
                                                      int E, int chunk_len, int k_rt, int vec_per_row,
@@ -207,32 +246,35 @@ __global__ __launch_bounds__(512) void dispatch_rows(const uint4* __restrict__ X
   uint4 v0 = {}, v1 = {};
   if (c < vec_per_row) v0 = src[c];
   if (c + nthr < vec_per_row) v1 = src[c + nthr];
-  for (int j = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); j < k; j += nthr >> 6) {
-    const int a = t * k + j;
-    const int chunk = (int)((uint32_t)a / (uint32_t)chunk_len), a0 = chunk * chunk_len;
-    const int e = topk_idx[a];
-    int x[kChunk / 64];
+  if (PLACE) {
+    for (int j = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); j < k; j += nthr >> 6) {
+      const int a = t * k + j;
+      const int chunk = (int)((uint32_t)a / (uint32_t)chunk_len), a0 = chunk * chunk_len;
+      const int e = topk_idx[a];
+      int x[kChunk / 64];
 #pragma unroll
-    for (int q = 0; q < kChunk / 64; q++) x[q] = a0 + 64 * q + lane < a ? topk_idx[a0 + 64 * q + lane] : -1;
-    int r = -1;
-    if (e >= 0 && e < E) {
-      r = offsets[e] + hist[(size_t)chunk * E + e];
+      for (int q = 0; q < kChunk / 64; q++) x[q] = a0 + 64 * q + lane < a ? topk_idx[a0 + 64 * q + lane] : -1;
+      int r = -1;
+      if (e >= 0 && e < E) {
+        r = offsets[e] + hist[(size_t)chunk * E + e];
 #pragma unroll
-      for (int q = 0; q < kChunk / 64; q++) r += __popcll(__ballot(x[q] == e));
-    }
-    if (lane == 0) {
-      rows[j] = r;
-      if (r >= 0) {
-        row_of[a] = r;
-        src_of[r] = a;
+        for (int q = 0; q < kChunk / 64; q++) r += __popcll(__ballot(x[q] == e));
+      }
+      if (lane == 0) {
+        rows[j] = r;
+        if (r >= 0) {
+          row_of[a] = r;
+          src_of[r] = a;
+        }
       }
     }
+    __syncthreads();
   }
-  __syncthreads();
+  auto row_at = [&](int j) { return PLACE ? rows[j] : row_of[(size_t)t * k + j]; };
   if (K > 0) {
     int row[KM];
 #pragma unroll
-    for (int j = 0; j < KM; j++) row[j] = __builtin_amdgcn_readfirstlane(rows[j]);
+    for (int j = 0; j < KM; j++) row[j] = __builtin_amdgcn_readfirstlane(row_at(j));
     // two pieces per thread and trip: both loads are issued before the 2k stores
     while (c < vec_per_row) {
 #pragma unroll
@@ -249,8 +291,10 @@ __global__ __launch_bounds__(512) void dispatch_rows(const uint4* __restrict__ X
   } else {
     for (; c < vec_per_row; c += nthr) {
       const uint4 v = src[c];
-      for (int j = 0; j < k; j++)
-        if (rows[j] >= 0) Xp[(size_t)rows[j] * vec_per_row + c] = v;
+      for (int j = 0; j < k; j++) {
+        const int r = row_at(j);
+        if (r >= 0) Xp[(size_t)r * vec_per_row + c] = v;
+      }
     }
   }
 }
@@ -258,21 +302,43 @@ __global__ __launch_bounds__(512) void dispatch_rows(const uint4* __restrict__ X
 // ranks and row copy of a dispatch whose per-chunk histograms `hist` (chunks of chunk_len assignments)
 // have been scanned
 static void dispatch_place(const moe_shape_t* shape, const void* X, const int32_t* topk_idx, const int32_t* offsets,
-                           int32_t* row_of, int32_t* src_of, void* Xp, const int32_t* hist, int chunk_len,
+                           int32_t* row_of, int32_t* src_of, void* Xp, const int32_t* hist, int chunk_len, int n_chunks,
                            hipStream_t st) {
   if (shape->T == 0) return;
-  ProfScope prof("dispatch_rows", st);
   const int vec_per_row = (int)((size_t)shape->d * elem_size(shape->dtype) / 16);
-  // short rows get more threads than pieces, so that up to four assignments are placed at a time
-  const unsigned threads = std::max(row_block_threads(shape->d, 16 / (int)elem_size(shape->dtype)), 64u * std::min(shape->k, 4));
-#define MOE_ROWS(K)                                                                                                     \
-  hipLaunchKernelGGL(dispatch_rows<K>, dim3(shape->T), dim3(threads), 0, st, (const uint4*)X, topk_idx, hist, offsets, \
+  // Ranks found by the row blocks save a launch, but every block pays their chain of dependent reads: with short rows there
+  // is no copy to hide it under, and its cost grows with the assignments.  A launch of their own costs 2 us and up to
+  // 25 more for the rounds of a step of 64 assignments over many experts.  Whole moe_dispatch calls, ranks in the row blocks
+  // against a launch of their own, bf16: T = 131072, top-8 of 8 experts, d = 128: 233 against 115 us; top-4 of 60, d = 256: 184
+  // against 111; T = 32768, d = 128, top-4 of 8: 40 against 25, of 60: 43 against 42, of 256: 56 against 62; rows of 4 KB
+  // (T = 131072, top-4 of 8): 484 against 503; top-1 (T = 131072, d = 128): 39 against 44.  The line is where the two meet over
+  // T = 1024 .. 400000, top-2 .. top-32, 8 to 256 experts, d = 8 .. 1024 (worst misses on either side: 10 %).
+  const int64_t row_bytes = (int64_t)vec_per_row * 16;
+  const bool ranked = shape->k > 1 && row_bytes <= 2048 &&
+                      (int64_t)shape->T * shape->k >= (40960 + 2048 * std::min(shape->E, 64)) * (2048 + row_bytes) / 2048;
+  if (ranked) {
+    ProfScope prof("dispatch_rank", st);
+    hipLaunchKernelGGL(dispatch_rank, dim3(n_chunks), dim3(64), 0, st, topk_idx, shape->T * shape->k, shape->E, chunk_len, hist,
+                       offsets, row_of, src_of);
+  }
+  ProfScope prof("dispatch_rows", st);
+  const unsigned copy_threads = row_block_threads(shape->d, 16 / (int)elem_size(shape->dtype));
+  // Short rows get more threads than pieces, so that up to four assignments are placed at a time; rows of at least 64
+  // pieces whose ranks are known get twice as many (T = 131072, top-8, d = 512: 258 -> 233 us, d = 1024: 475 -> 451; below, the
+  // second wavefront costs: d = 256: 137 -> 163).
+  const unsigned threads = !ranked ? std::max(copy_threads, 64u * std::min(shape->k, 4)) : vec_per_row < 64 ? copy_threads : 2 * copy_threads;
+#define MOE_ROWS_KERNEL(K, PLACE)                                                                                               \
+  hipLaunchKernelGGL((dispatch_rows<K, PLACE>), dim3(shape->T), dim3(threads), 0, st, (const uint4*)X, topk_idx, hist, offsets, \
                      shape->E, chunk_len, shape->k, vec_per_row, row_of, src_of, (uint4*)Xp)
+#define MOE_ROWS(K)                      \
+  if (ranked) MOE_ROWS_KERNEL(K, false); \
+  else MOE_ROWS_KERNEL(K, true)
   MOE_BY_TOP_K(shape->k, MOE_ROWS);
 #undef MOE_ROWS
+#undef MOE_ROWS_KERNEL
 }
 
-// the three launches of a dispatch; `hist` is scratch of n_chunks * E counters (every one is written
+// the launches of a dispatch; `hist` is scratch of n_chunks * E counters (every one is written
 // by dispatch_count before anything reads it)
 static void dispatch_launch(const moe_shape_t* shape, const void* X, const int32_t* topk_idx, int32_t* counts,
                             int32_t* offsets, int32_t* row_of, int32_t* src_of, void* Xp, int32_t* hist,
@@ -288,7 +354,7 @@ static void dispatch_launch(const moe_shape_t* shape, const void* X, const int32
     hipLaunchKernelGGL(dispatch_scan, dim3(1), dim3(1024), 0, st, hist, n_chunks, shape->E, counts, offsets,
                        (const float*)nullptr, (float*)nullptr, (float*)nullptr, 0, 1, 0.f);
   }
-  dispatch_place(shape, X, topk_idx, offsets, row_of, src_of, Xp, hist, kChunk, st);
+  dispatch_place(shape, X, topk_idx, offsets, row_of, src_of, Xp, hist, kChunk, n_chunks, st);
 }
 
 // chunks of the fused prologue: whole tokens, at most kChunk assignments, and fewer than that while the
@@ -437,6 +503,6 @@ extern "C" int moe_route_dispatch(const moe_shape_t* shape, const float* logits,
     hipLaunchKernelGGL(dispatch_scan, dim3(1), dim3(1024), 0, st, hist, n_chunks, E, counts, offsets,
                        (const float*)partial, aux_P, aux_loss, T, k, aux_alpha);
   }
-  dispatch_place(shape, X, topk_idx, offsets, row_of, src_of, Xp, hist, tpc * k, st);
+  dispatch_place(shape, X, topk_idx, offsets, row_of, src_of, Xp, hist, tpc * k, n_chunks, st);
   return launch_status("moe_route_dispatch");
 }

@@ -64,6 +64,47 @@ def test_rows(k, d, dtype, fused):
     assert rel(dw, (rows * dY.double()[:, None, :]).sum(2)) <= 1e-5
 
 
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("E,k,d,dtype,T", [(5, 2, 8, "bf16", 25800), (5, 2, 8, "bf16", 25799), (21, 17, 8, "f32", 5017),
+                                           (70, 3, 264, "f32", 87047), (1024, 8, 520, "bf16", 32769), (9, 9, 1024, "bf16", 13204)])
+def test_many_assignments_of_short_rows(E, k, d, dtype, T, fused):
+    """Both sides of the line from which ranks get a launch of their own (2, 17, 3, 8 and 9 per token: chunks end inside
+    a token or a step of 64), every size of the copy's blocks; entries out of range are skipped."""
+    import paper_2502_02581_amd as moe
+
+    s = moe.MoEShape(T, d, E, k, 8, dtype)
+    row = d * (4 if dtype == "f32" else 2)
+    ranked = T * k >= (40960 + 2048 * min(E, 64)) * (2048 + row) // 2048
+    assert ranked == (T != 25799)
+    X = torch.randn(T, d, generator=torch.Generator().manual_seed(T)).to(s.torch_dtype).to(DEV)
+    logits = torch.randn(T, E, generator=torch.Generator().manual_seed(E))
+    logits[:, E // 2] += 2.0
+    i32 = lambda *n: torch.full(n, -7, dtype=torch.int32, device=DEV)
+    idx, w = i32(T, k), torch.empty(T, k, device=DEV)
+    counts, offsets, row_of, src_of = i32(E), i32(E + 1), i32(T * k), i32(T * k)
+    Xp = torch.full((T * k, d), float("nan"), dtype=s.torch_dtype, device=DEV)
+    ws = torch.empty(max(moe.moe_dispatch_workspace_bytes(s), moe.moe_route_dispatch_workspace_bytes(s)), dtype=torch.uint8, device=DEV)
+    moe.moe_route(s, logits.to(DEV), idx, w)
+    if not fused:
+        idx.view(-1)[5::1009] = torch.tensor([-1, E], dtype=torch.int32, device=DEV).repeat(T * k)[: idx.view(-1)[5::1009].numel()]
+    moe.moe_profile_enable(True)
+    if fused:
+        moe.moe_route_dispatch(s, logits.to(DEV), X, 0.0, idx, w, counts, offsets, row_of, src_of, Xp, None, None, ws)
+    else:
+        moe.moe_dispatch(s, X, idx, counts, offsets, row_of, src_of, Xp, ws)
+    labels = moe.moe_profile_report()
+    moe.moe_profile_enable(False)
+    assert ("dispatch_rank" in labels) == ranked and "dispatch_rows" in labels
+    flat = idx.cpu().numpy().reshape(-1)
+    valid = np.flatnonzero((flat >= 0) & (flat < E))
+    order = valid[np.argsort(flat[valid], kind="stable")]
+    assert np.array_equal(counts.cpu().numpy(), np.bincount(flat[valid], minlength=E))
+    assert np.array_equal(src_of.cpu().numpy()[: len(order)], order)
+    assert np.array_equal(row_of.cpu().numpy()[order], np.arange(len(order)))
+    assert torch.equal(Xp[: len(order)], X[torch.from_numpy(order // k).to(DEV)])
+    assert bool(Xp[len(order):].isnan().all())
+
+
 @pytest.mark.parametrize("E", [1, 3, 63, 64, 65, 200, 1023, 1024])
 def test_plan_of_many_groups(E):
     import paper_2502_02581_amd as moe
