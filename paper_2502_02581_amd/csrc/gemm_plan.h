@@ -53,6 +53,7 @@ struct RowGemm {
   float* part;              // n_parts > 1: fp32 sums [n_parts][products][part_stride]
   int64_t part_stride;
   int32_t N, K;
+  int32_t wide;             // rows too long for the tile cores (see wide_rows)
   int32_t n_pairs, n_segs;
   const void* A[2];         // per pair; element (row, k) at A + seg*a_seg + row*lda + k
   int64_t lda, a_seg;
@@ -83,6 +84,7 @@ struct WGemm {
   int64_t part_stride;
   int32_t *active_ids, *n_active;  // all groups, if not NULL
   int32_t M, N;
+  int32_t wide;             // rows too long for the tile cores (see wide_rows)
   const void* A;            // element (row, m) at A + row*lda + m
   int64_t lda;
   int32_t a_per_group;      // shared mode: A rows of group g start at g*n_rows
