@@ -162,7 +162,11 @@ def check_mfma_sources(lines: List[str], wait_states: int = 2) -> List[str]:
     return findings
 
 
-def check_no_scratch(lines: List[str], name_part: str = "gemm_kernel") -> List[str]:
+# every kernel of the GEMM sources: row_gemm_, row_w_gemm_, wide_*_gemm_, the light weight gradients and the sums of parts
+GEMM_KERNELS = ("gemm_kernel", "w_light_kernel", "reduce_kernel")
+
+
+def check_no_scratch(lines: List[str], name_parts=GEMM_KERNELS) -> List[str]:
     findings = []
     kernel = None
     for raw in lines:
@@ -171,7 +175,7 @@ def check_no_scratch(lines: List[str], name_part: str = "gemm_kernel") -> List[s
         if m:
             kernel = m.group(1)
         m = re.match(r"^; ScratchSize: (\d+)", t)
-        if m and kernel and name_part in kernel and int(m.group(1)) != 0:
+        if m and kernel and any(n in kernel for n in name_parts) and int(m.group(1)) != 0:
             findings.append(f"{kernel}: {m.group(1)} bytes of scratch memory per lane")
     return findings
 

@@ -3,6 +3,7 @@ the assembly of the current build when the build step has left it in place.  CPU
 from __future__ import annotations
 
 import os
+import re
 
 import pytest
 
@@ -68,6 +69,20 @@ def test_scratch_in_a_gemm_kernel_is_flagged():
              "_ZN3moe12route_kernelIxEEv:", "\ts_endpgm", "; ScratchSize: 16"]
     found = asm_check.check_no_scratch(lines)
     assert len(found) == 1 and "row_gemm_kernel" in found[0] and "1088" in found[0]
+
+
+def test_every_matrix_kernel_of_the_gemm_sources_is_checked_for_scratch():
+    """By the names in the sources: a kernel that is renamed or added must not drop out of the check."""
+    for src in ("expert.hip", "expert_impl.h"):
+        with open(os.path.join(build.CSRC, src)) as f:
+            text = f.read()
+        names = re.findall(r"__global__[^;{]*?(\w+)\(", re.sub(r"__launch_bounds__\([^;{]*?\) (?=void)", "", text))
+        assert len(names) == text.count("__global__")
+        for name in names:
+            if name in ("plan_kernel", "recolumn_kernel"):   # no accumulators, no matrix instructions
+                continue
+            lines = [f"_ZN3moe{len(name)}{name}IxEEv:", "\ts_endpgm", "; ScratchSize: 64"]
+            assert len(asm_check.check_no_scratch(lines)) == 1, name
 
 
 def test_packed_fp32_is_flagged():
