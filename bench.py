@@ -33,8 +33,9 @@ PROBE_LAUNCHES = 5
 COLD_STEPS = 3               # steps of the cold-cache variant
 MFMA_PROBE_BLOCKS = 2048     # blocks (8 per CU) and rounds of the register-resident matrix loop
 MFMA_PROBE_ITERS = 1000
-# kernel behind each profiling label on the bf16 LDS-DMA path, as rocprofv3 names it (one label = one kernel symbol)
-SYMBOL = {   # (launches over the routed experts; the shared experts' instances of a label differ in the last flag)
+# kernel behind each profiling label on the bf16 LDS-DMA path, as rocprofv3 names it: the launches over the routed
+# experts.  Those over the shared experts, which the label counts too, are the instance without a plan (`symbols`).
+SYMBOL = {
     "gemm_fwd_gate_up": "moe::row_gemm_kernel<moe::RowCores<2, 2, false>, 2, 1, false, true>(moe::RowGemm)",
     "gemm_fwd_down": "moe::row_gemm_kernel<moe::RowCores<2, 1, false>, 1, 0, false, true>(moe::RowGemm)",
     "gemm_bwd_dh_dwd": "moe::row_w_gemm_kernel<moe::RowCores<2, 1, true>, 2, moe::MfmaDmaCore<unsigned short, 256, 256, 1, "
@@ -44,6 +45,13 @@ SYMBOL = {   # (launches over the routed experts; the shared experts' instances 
     "gemm_bwd_dw_light": "moe::w_light_kernel<moe::MfmaDmaCore<unsigned short, 128, 128, 1, false, false, 2, 2, 0, false> >"
                          "(moe::WGemm, moe::WGemm, int)",
 }
+
+
+def symbols(label):
+    """Every kernel that the launches of a label run: the routed experts' instance, then the shared experts'."""
+    routed = SYMBOL[label]
+    shared = routed.replace("true>(moe::RowGemm", "false>(moe::RowGemm")
+    return (routed,) if shared == routed else (routed, shared)
 
 
 def algorithmic_work(cfg: wl.MoEConfig, counts):
@@ -74,18 +82,19 @@ def algorithmic_work(cfg: wl.MoEConfig, counts):
     return flops, byts
 
 
-def measured_traffic(cfg_name, symbol):
-    """(HBM bytes per launch of `symbol`, where that figure comes from).  The counters cannot be read
+def measured_traffic(cfg_name, label):
+    """(HBM bytes per launch of a label's kernels, where that figure comes from): the mean over the routed and the shared
+    experts' launches, as the label's time and FLOPs are.  The counters cannot be read
     from inside this process: the figure is the one `rocprofv3 --pmc` measured for this workload when the
     summary under profiles/ was last regenerated (the file names its command and the commit it ran)."""
-    from paper_2502_02581_amd.rocprof_summary import read_traffic
+    from paper_2502_02581_amd.rocprof_summary import read_mean_traffic
 
     rel = os.path.join("profiles", f"hbm_traffic_{cfg_name}.txt")
     path = os.path.join(ROOT, rel)
     if not os.path.exists(path):
         return None, None
     commit = next((ln.split(":", 1)[1].strip() for ln in open(path) if ln.startswith("# commit:")), "not recorded")
-    return read_traffic(path).get(symbol), f"{rel} (rocprofv3 --pmc FETCH_SIZE, WRITE_SIZE; kernels of commit {commit})"
+    return read_mean_traffic(path, symbols(label)), f"{rel} (rocprofv3 --pmc FETCH_SIZE, WRITE_SIZE; kernels of commit {commit})"
 
 
 class LazyExperts:
@@ -354,8 +363,9 @@ def main():
     peak = MFMA_BF16_PEAK_TF if cfg.dtype == "bf16" else FP32_VEC_PEAK_TF
     achieved = flops[dom] * args.steps / (dom_ms * 1e-3) / 1e12
     dma_path = cfg.dtype == "bf16" and cfg.d % 64 == 0 and cfg.d_ff % 64 == 0   # SYMBOL names that path's kernels
-    traffic, traffic_src = measured_traffic(cfg.name, SYMBOL[dom]) if dma_path else (None, None)
+    traffic, traffic_src = measured_traffic(cfg.name, dom) if dma_path else (None, None)
     roofline = {"bound": "mfma" if cfg.dtype == "bf16" else "alu", "kernel": dom, "symbol": SYMBOL[dom] if dma_path else None,
+                "shared_symbol": (symbols(dom)[1:] or (None,))[0] if dma_path and cfg.n_shared else None,
                 "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s", "frac": round(achieved / peak, 4),
                 "avg_launch_ms": round(dom_ms / dom_n, 4), "launches": dom_n,
                 "flop_per_launch_avg": flops[dom] * args.steps / dom_n,

@@ -124,6 +124,21 @@ def read_traffic(path):
     return out
 
 
+def read_mean_traffic(path, names):
+    """Bytes per launch over all launches of the kernels `names` in such a file (those of them that it lists); None
+    where it does not list the first."""
+    sums, launches, listed = 0.0, 0, set()
+    for line in open(path):
+        if line.startswith("#") or not line.strip():
+            continue
+        n, _, _, total, name = line.rstrip("\n").split("\t")
+        if name in names:
+            sums += int(n) * float(total)
+            launches += int(n)
+            listed.add(name)
+    return sums / launches if names[0] in listed else None
+
+
 def main():
     ap = argparse.ArgumentParser()
     sub = ap.add_subparsers(dest="what", required=True)

@@ -3,6 +3,8 @@ import os
 import subprocess
 import sys
 
+import pytest
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
@@ -24,3 +26,24 @@ def test_a_multi_rank_launch_is_refused_too():
     r = run_bench("--gpus", "1", env={"WORLD_SIZE": "2", "RANK": "0"})
     assert r.returncode != 0
     assert "one-GPU" in r.stderr + r.stdout
+
+
+@pytest.mark.parametrize("cfg", ["dsv3", "qwen", "stress"])
+def test_traffic_of_a_label_is_that_of_all_its_launches(cfg):
+    """The roofline's time and FLOPs per launch are means over the routed and the shared experts' launches of a label, so
+    its bytes have to be."""
+    sys.path.insert(0, ROOT)
+    import bench
+
+    path = os.path.join(ROOT, "profiles", f"hbm_traffic_{cfg}.txt")
+    rows = [ln.rstrip("\n").split("\t") for ln in open(path) if not ln.startswith("#")]
+    of = {r[4]: (int(r[0]), float(r[3])) for r in rows}
+    gemms = [n for n in of if "gemm_kernel" in n or "w_light_kernel" in n]
+    named = []
+    for label in bench.GEMM_LABELS:
+        here = [of[s] for s in bench.symbols(label) if s in of]
+        assert bench.symbols(label)[0] in of, label
+        assert bench.measured_traffic(cfg, label)[0] == pytest.approx(sum(n * b for n, b in here) / sum(n for n, _ in here))
+        named += [s for s in bench.symbols(label) if s in of]
+    assert sorted(named) == sorted(gemms)   # every GEMM kernel of the profile belongs to one label
+    assert bench.measured_traffic("tiny", bench.GEMM_LABELS[0])[0] is None
