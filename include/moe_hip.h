@@ -70,7 +70,12 @@ const char* moe_last_error(void);
 
 /* Workspace sizes in bytes (host computation, no GPU call; 0 for invalid arguments).
  * n_groups/n_rows as passed to the expert calls, shared = 1 for shared mode (offsets == NULL);
- * `shape` supplies d, d_ff, dtype (and T, k, E for the dispatch). */
+ * `shape` supplies d, d_ff, dtype (and T, k, E for the dispatch).
+ * Expert calls in shared mode and router calls sum long products of few tiles in parts, whose fp32 sums live
+ * in the workspace: their queries ask for as much as the parts can use, the calls need less (they name the
+ * least in their MOE_EWS text).  The parts are chosen from the shape and what ws_bytes leaves for them, so the
+ * same call gives the same bits with every ws_bytes from the query's answer on; with less, other parts or
+ * none are used and the last bits of the results may differ. */
 size_t moe_dispatch_workspace_bytes(const moe_shape_t* shape);
 size_t moe_expert_fwd_workspace_bytes(const moe_shape_t* shape, int32_t n_groups, int32_t n_rows,
                                       int32_t shared);
@@ -84,7 +89,8 @@ size_t moe_expert_bwd_workspace_bytes(const moe_shape_t* shape, int32_t n_groups
  *   X [T, d], Wr [d, E], dWr [d, E], dX [T, d] in shape->dtype; logits, dlogits [T, E] f32.
  * bf16 operands, fp32 accumulation; dlogits is rounded to bf16 for the two backward products.
  * E need not be a multiple of anything: the GEMMs run on zero-padded copies in the workspace
- * (moe_router_*_workspace_bytes, host computation).  With T == 0, moe_router_bwd writes dWr = 0.
+ * (moe_router_*_workspace_bytes, host computation; the rule for ws_bytes above).  With T == 0,
+ * moe_router_bwd writes dWr = 0.
  * These calls are not part of the path the benchmark times (logits are an input there).
  */
 size_t moe_router_fwd_workspace_bytes(const moe_shape_t* shape);
@@ -167,8 +173,8 @@ int moe_dispatch(const moe_shape_t* shape, const void* X, const int32_t* topk_id
 
 /*
  * moe_route_dispatch -- moe_route, moe_dispatch and (with aux_P, aux_loss != NULL) moe_aux_loss in one call
- * of four kernels instead of seven: the gate of Eq. 3 and the counting of Algorithm 3's token assignment
- * read the logits once.  Same arguments and the same results as the three calls: every integer output
+ * of three kernels instead of six (four and seven where many short rows are ranked apart): the gate of
+ * Eq. 3 and the counting of Algorithm 3's token assignment read the logits once.  Same arguments and the same results as the three calls: every integer output
  * and topk_w bit for bit; aux_P and aux_loss up to the order of their fp32 sums (a fixed order, so two
  * runs agree bit for bit).  aux_alpha is ignored when aux_P and aux_loss are NULL (they go together).
  *   ws >= moe_route_dispatch_workspace_bytes(shape)
@@ -238,7 +244,8 @@ int moe_expert_fwd(const moe_shape_t* shape, int32_t n_groups, const int32_t* of
  *   dYin [n_rows, d];  dXin [n_rows, d] out
  *   active_ids [n_groups] i32 out;  n_active [1] i32 out (device)
  *   dWg_c, dWu_c [n_groups, d, d_ff] out;  dWd_c [n_groups, d_ff, d] out
- *   ws >= moe_expert_bwd_workspace_bytes(shape, n_groups, n_rows, offsets == NULL)
+ *   ws_bytes as moe_expert_bwd_workspace_bytes(shape, n_groups, n_rows, offsets == NULL) answers; shared mode
+ *   runs with less (see there)
  */
 int moe_expert_bwd(const moe_shape_t* shape, int32_t n_groups, const int32_t* offsets, int32_t n_rows,
                    const void* Xin, const void* Wg, const void* Wu, const void* Wd, const void* G,

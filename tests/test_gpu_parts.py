@@ -93,6 +93,40 @@ def test_shared_calls(dtype, S, T, d, F, ffn):
         ids.fill_(-7)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_same_bits_with_any_larger_workspace(dtype):
+    """Where a call has what the query answers, how much more there is changes nothing (all four calls use parts here)."""
+    import paper_2502_02581_amd as moe
+
+    S, T, d, F, E = 4, 33, 1024, 712, 128
+    shape, rshape = moe.MoEShape(T, d, S, 1, F, dtype), moe.MoEShape(700, d, E, 1, F, dtype)
+    dt, dev = shape.torch_dtype, "cuda"
+    g = torch.Generator().manual_seed(3)
+    rnd = lambda *s: (torch.randn(*s, generator=g) * d ** -0.5).to(dt).to(dev)
+    X, dY, w = rnd(T, d), rnd(T, d), [rnd(S, d, F), rnd(S, d, F), rnd(S, F, d)]
+    Xr, Wr, dl = rnd(700, d), rnd(d, E), torch.randn(700, E, generator=g).to(dev)
+    new = lambda *s, t=dt: torch.full(s, float("nan"), dtype=t, device=dev)
+    i32 = lambda n: torch.empty(n, dtype=torch.int32, device=dev)
+    fwd, bwd = [new(S, T, F) for _ in range(3)] + [new(T, d)], [new(T, d), new(S, d, F), new(S, d, F), new(S, F, d)]
+    logits, dWr, dXr = new(700, E, t=torch.float32), new(d, E), new(700, d)
+    calls = [(moe.moe_expert_fwd_workspace_bytes(shape, S, T, True), fwd,
+              lambda ws: moe.moe_expert_fwd(shape, S, None, T, X, *w, *fwd, ws)),
+             (moe.moe_expert_bwd_workspace_bytes(shape, S, T, True), bwd,
+              lambda ws: moe.moe_expert_bwd(shape, S, None, T, X, *w, *fwd[:3], dY, bwd[0], i32(S), i32(1), *bwd[1:], ws)),
+             (moe.moe_router_fwd_workspace_bytes(rshape), [logits], lambda ws: moe.moe_router_fwd(rshape, Xr, Wr, logits, ws)),
+             (moe.moe_router_bwd_workspace_bytes(rshape), [dWr, dXr],
+              lambda ws: moe.moe_router_bwd(rshape, Xr, Wr, dl, dWr, dXr, False, ws))]
+    for query, outs, call in calls:
+        assert least(call, moe) < query
+        call(torch.empty(query, dtype=torch.uint8, device=dev))
+        first = [t.clone() for t in outs]
+        for more in (16, 4096, 3 * query):
+            for t in outs:
+                t.fill_(float("nan"))
+            call(torch.empty(query + more, dtype=torch.uint8, device=dev))
+            assert all(torch.equal(a, b) for a, b in zip(first, outs))
+
+
 def test_shared_backward_without_rows():
     """No token: no group is active, and nothing else is written."""
     import paper_2502_02581_amd as moe

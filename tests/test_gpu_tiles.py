@@ -69,3 +69,49 @@ def test_expert_tiles(dtype, d, F, ffn):
             worst[k] = max(worst.get(k, 0.0), rel(got, ref.detach()))
     print(dtype, d, F, ffn, {k: f"{v:.1e}" for k, v in worst.items()})
     assert all(v <= TOL[dtype] for v in worst.values()), worst
+
+
+@pytest.mark.parametrize("poison", [float("inf"), float("nan")])
+@pytest.mark.parametrize("ffn", ["swiglu", "gelu"])
+@pytest.mark.parametrize("d,F", [(72, 104), (264, 520), (64, 192)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_nothing_leaks_from_other_groups(dtype, d, F, ffn, poison):
+    """Tiles read past the rows and columns of their group, into the next group's rows, weights and K values: whatever
+    stands there, the outputs of a group are the same bits."""
+    import paper_2502_02581_amd as moe
+
+    dev, rows = "cuda:0", [33, 70, 1, 300, 17]
+    E, n = len(rows), sum(rows)
+    shape = moe.MoEShape(n, d, E, 1, F, dtype)
+    dt = shape.torch_dtype
+    g = torch.Generator().manual_seed(d + F)
+    rnd = lambda std, *s: (torch.randn(*s, generator=g) * std).to(dt).to(dev)
+    X, dY, w = rnd(1.0, n, d), rnd(1.0, n, d), [rnd(d ** -0.5, E, d, F), rnd(d ** -0.5, E, d, F), rnd(F ** -0.5, E, F, d)]
+    if ffn == "gelu":
+        w[1] = None
+    off = [0, 33, 103, 104, 404, 421]
+    offs = torch.tensor(off, dtype=torch.int32, device=dev)
+    ws = torch.full((max(moe.moe_expert_fwd_workspace_bytes(shape, E, n, False), moe.moe_expert_bwd_workspace_bytes(shape, E, n, False)),),
+                    0xff, dtype=torch.uint8, device=dev)
+
+    def run(X, dY, w):
+        new = lambda *s: torch.full(s, 7.0, dtype=dt, device=dev)
+        G, U, H, Y, dX, dWg, dWu, dWd = (new(*s) for s in ((n, F), (n, F), (n, F), (n, d), (n, d), (E, d, F), (E, d, F), (E, F, d)))
+        ids, n_act = torch.empty(E, dtype=torch.int32, device=dev), torch.empty(1, dtype=torch.int32, device=dev)
+        moe.moe_expert_fwd(shape, E, offs, n, X, *w, G, U, H, Y, ws)
+        moe.moe_expert_bwd(shape, E, offs, n, X, *w, G, U, H, dY, dX, ids, n_act, dWg, dWu, dWd, ws)
+        return [G, U, H, Y, dX], [dWg, dWu, dWd]
+
+    clean = run(X, dY, w)
+    for bad in range(E):
+        X2, dY2, w2 = X.clone(), dY.clone(), [None if t is None else t.clone() for t in w]
+        for t in (X2, dY2):
+            t[off[bad]:off[bad + 1]] = poison
+        for t in w2:
+            if t is not None:
+                t[bad] = poison
+        got = run(X2, dY2, w2)
+        for e in range(E):
+            if e != bad:
+                assert all(torch.equal(a[off[e]:off[e + 1]], b[off[e]:off[e + 1]]) for a, b in zip(clean[0], got[0])), (bad, e)
+                assert all(torch.equal(a[e], b[e]) for a, b in zip(clean[1], got[1])), (bad, e)
