@@ -17,21 +17,17 @@ namespace moe {
 // for the group ranks takes four row counts per LDS read, the scans use one barrier each, and every tile has its own
 // thread, which finds the group by bisection.  (Scans of ten steps with two barriers each, one row count per read and the
 // tiles of a group written by one thread took: 60 groups 8.6 us, 64 groups 9.3, 8 groups 5.3; this form 6.6, 6.7, 3.7.)
-__global__ __launch_bounds__(1024) void plan_kernel(const int32_t* __restrict__ offsets, int n_groups,
-                                                    int n_rows, int BM, Plan pl, int32_t* active_ids,
-                                                    int32_t* n_active) {
+// offsets == NULL (a shared call without rows, whose active_ids and n_active are all there is to write): no group has rows.
+__global__ __launch_bounds__(1024) void plan_kernel(const int32_t* __restrict__ offsets, int n_groups, int BM, Plan pl,
+                                                    int32_t* active_ids, int32_t* n_active) {
   __shared__ __align__(16) int32_t rows_of[1024];                    // by group
   __shared__ int32_t cnt[1024], first[1024], tile0[1024], ord[1024];  // by rank
   __shared__ __align__(16) int32_t wsum[2][16];
   const int e = threadIdx.x;
   int c = 0, st = 0;
-  if (e < n_groups) {
-    if (offsets) {
-      st = offsets[e];
-      c = max(offsets[e + 1] - st, 0);
-    } else {
-      c = n_rows;
-    }
+  if (e < n_groups && offsets) {
+    st = offsets[e];
+    c = max(offsets[e + 1] - st, 0);
   }
   rows_of[e] = e < n_groups ? c : -1;
   int total_active;
@@ -92,15 +88,14 @@ __global__ __launch_bounds__(1024) void plan_kernel(const int32_t* __restrict__ 
     t.group = ord[lo];
     t.row0_in = first[lo] + row;
     t.rows = min(BM >> kind, rows - row) | (kind << 16);
-    t.row0_out = offsets ? t.row0_in : t.group * n_rows + row;
+    t.row0_out = t.row0_in;
     pl.tiles[i] = t;
   }
 }
 
-void launch_plan(const int32_t* offsets, int n_groups, int n_rows, int BM, const Plan& pl, int32_t* active_ids, int32_t* n_active,
-                 hipStream_t st) {
+void launch_plan(const int32_t* offsets, int n_groups, int BM, const Plan& pl, int32_t* active_ids, int32_t* n_active, hipStream_t st) {
   ProfScope prof("plan_kernel", st);
-  hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(1024), 0, st, offsets, n_groups, n_rows, BM, pl, active_ids, n_active);
+  hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(1024), 0, st, offsets, n_groups, BM, pl, active_ids, n_active);
 }
 
 // one translation unit each
@@ -121,7 +116,8 @@ static int pick_path(const moe_shape_t* s) {
 }
 
 static size_t plan_size_for(int n_groups, int n_rows, bool shared) {
-  // sized for the smallest row tile of any path, so the query does not depend on the path taken
+  // Sized for the smallest row tile of any path, so the query does not depend on the path taken.  A shared call with rows
+  // has no plan; it asks for the space all the same, so that it refuses what it always refused.
   const int bound = shared ? n_groups * (n_rows / 64 + 2) : max_row_tiles(n_groups, n_rows, 64);
   return align_up(plan_bytes(n_groups, bound + 1), 256);
 }

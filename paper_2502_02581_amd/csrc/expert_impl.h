@@ -529,8 +529,7 @@ struct LdsAttr {
 // upper bound of the row tiles the plan kernel may emit (at most two remainder tiles per group)
 static int max_row_tiles(int n_groups, int n_rows, int BM) { return n_rows / BM + 2 * n_groups; }
 
-void launch_plan(const int32_t* offsets, int n_groups, int n_rows, int BM, const Plan& pl, int32_t* active_ids, int32_t* n_active,
-                 hipStream_t st);
+void launch_plan(const int32_t* offsets, int n_groups, int BM, const Plan& pl, int32_t* active_ids, int32_t* n_active, hipStream_t st);
 
 // LDS of a launch: one block may run any of the tile kinds
 template <class CoreSet> constexpr int row_lds_bytes() {
@@ -805,7 +804,7 @@ void expert_fwd_impl(const FwdArgs& a, hipStream_t st) {
   Plan pl = {};
   if (!shared) {
     pl = carve_plan(a.ws, a.n_groups, max_tiles);
-    launch_plan(a.offsets, a.n_groups, a.n_rows, Cores<PATH>::BM, pl, nullptr, nullptr, st);
+    launch_plan(a.offsets, a.n_groups, Cores<PATH>::BM, pl, nullptr, nullptr, st);
   }
   // F4: dual GEMM with the SwiGLU epilogue, or (two-matrix expert, Wu == NULL) one GEMM with the GELU epilogue
   RowGemm p = {};
@@ -869,7 +868,7 @@ void expert_bwd_impl(const BwdArgs& a, hipStream_t st) {
   Plan pl = {};
   if (!shared || a.n_rows == 0) {
     pl = carve_plan(a.ws, a.n_groups, max_tiles);
-    launch_plan(a.offsets, a.n_groups, a.n_rows, Cores<PATH>::BM, pl, a.active_ids, a.n_active, st);
+    launch_plan(a.offsets, a.n_groups, Cores<PATH>::BM, pl, a.active_ids, a.n_active, st);
   }
   if (a.n_rows == 0) return;  // no group is active
   // B2a: dH = dYin Wd^T, epilogue turns it into dG, dU
