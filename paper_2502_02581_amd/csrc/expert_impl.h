@@ -599,9 +599,14 @@ static void launch_row_w(const char* label, const RowGemm& p, int max_tiles, con
 // gradient had 28 tiles of 128 steps, 145 us, and followed dX, 51 us: now in one launch 74 + 6 us.  Shared
 // expert of T = 3001, d = 1000, d_ff = 712, backward: 65 + 67 -> 38 + 44 us (and 11 us of sums).
 //
-// The choice minimises an estimate made of measured figures, in microseconds: a K step of a tile, by height
-// (`iter`), what a tile costs besides (`fixed`: first loads, epilogue), a launch with the sums of the parts at 5 TB/s.  It
-// has to promise 8 % over one part of full tiles, for the estimate does not see the other stream.
+// The choice minimises an estimate, in microseconds: a K step of a tile, by height (`iter`), what a tile costs besides
+// (`fixed`: first loads, epilogue), a launch with the sums of the parts at 5 TB/s.  Measured for comparison with 256 tiles, one
+// per compute unit, 16 and 64 K steps, operands in cache (dual products in brackets): bf16 1.53, 0.83, 0.60 and 0.54 (1.45, 0.79,
+// 0.51, 0.48) a step of 256, 128, 64 and 32 rows, and 12 to 7 (16 to 8) besides, launch included; fp32 1.07 a step of 64
+// rows, 0.61 of fewer (1.02 of any height), and 8 to 6 (11 to 8).  The table's steps are within a fifth of that, those of
+// the short bf16 tiles up to half above it; the weight gradients' were not measured apart.  It has no term for the rate
+// at which weights arrive (decode's gate/up and down products over 16 rows: 9 and 10 us by the estimate, 19 and 21 by
+// measure) nor for the other stream; hence the 8 % that a choice has to promise over one part of full tiles.
 struct TileCost {
   int bm, bn, bk;
   float iter[4], fixed[4];
