@@ -53,7 +53,6 @@ struct RowGemm {
   float* part;              // n_parts > 1: fp32 sums [n_parts][products][part_stride]
   int64_t part_stride;
   int32_t N, K;
-  int32_t wide;             // rows too long for the tile cores (see wide_rows)
   int32_t n_pairs, n_segs;
   const void* A[2];         // per pair; element (row, k) at A + seg*a_seg + row*lda + k
   int64_t lda, a_seg;
@@ -72,6 +71,7 @@ struct RowGemm {
   const float* c_scale;
   int64_t ldc;
   int32_t c_rows_out;       // outputs indexed by row0_out
+  int32_t wide;             // rows too long for the tile cores (see wide_rows)
 };
 
 // per group: C[M, N] = A_g^T B_g over the rows of the group (K = rows of the group)
@@ -84,7 +84,6 @@ struct WGemm {
   int64_t part_stride;
   int32_t *active_ids, *n_active;  // all groups, if not NULL
   int32_t M, N;
-  int32_t wide;             // rows too long for the tile cores (see wide_rows)
   const void* A;            // element (row, m) at A + row*lda + m
   int64_t lda;
   int32_t a_per_group;      // shared mode: A rows of group g start at g*n_rows
@@ -95,6 +94,7 @@ struct WGemm {
   int64_t c_slot;           // elements per slot
   int32_t k_min, k_max;     // only groups with k_min <= rows <= k_max are processed by this launch
   int32_t n_reps;           // consecutive column tiles per block (0 or 1: one)
+  int32_t wide;             // rows too long for the tile cores (see wide_rows)
 };
 
 }  // namespace moe
