@@ -33,8 +33,7 @@ def stats(args):
     rows = list(csv.DictReader(open(args.csv)))
     with open(args.out, "w") as f:
         f.write("# rocprofv3 --kernel-trace --stats summary\n\nCommand (run from the repo root on one MI355X):\n\n")
-        f.write(f"    {args.cmd}\n\nKernels of commit {args.commit}.  Calls include the warm-up steps and the profiled pass "
-                "(every step runs twice: timed, then with the library's own events). Durations in microseconds.\n\n")
+        f.write(f"    {args.cmd}\n\nKernels of commit {args.commit}.  {args.note} Durations in microseconds.\n\n")
         f.write("| kernel | calls | total us | avg us | min us | max us | % |\n|---|---|---|---|---|---|---|\n")
         for r in rows:
             if float(r["Percentage"]) < 0.01:
@@ -147,6 +146,8 @@ def main():
     s.add_argument("out")
     s.add_argument("--cmd", required=True)
     s.add_argument("--commit", default="not recorded")
+    s.add_argument("--note", default="Calls include the warm-up steps and the profiled pass (every step runs twice: timed, then with "
+                                     "the library's own events).")
     s.set_defaults(fn=stats)
     t = sub.add_parser("traffic")
     t.add_argument("fetch_csv")
