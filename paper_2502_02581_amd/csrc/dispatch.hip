@@ -322,7 +322,12 @@ static void dispatch_place(const moe_shape_t* shape, const void* X, const int32_
                        offsets, row_of, src_of);
   }
   ProfScope prof("dispatch_rows", st);
-  const unsigned copy_threads = row_block_threads(shape->d, 16 / (int)elem_size(shape->dtype));
+  // Blocks as wide as a row, but copies of long rows that leave the caches behind run with 256 threads: 8 rows a compute
+  // unit stay in flight (T = 32768, top-3 of 16, d = 7168: 365 -> 350 us, d = 12288: 628 -> 610; T = 8192, top-8, d = 7168: 214
+  // -> 211).  Below some 600 MB written it is even or slower (T = 4096, top-4, d = 12288: 108 against 111), and rows of up to
+  // 512 pieces prefer it only now and then (d = 4096: T = 8192, top-8: 123 against 121, T = 32768, top-3: 188 against 201).
+  const bool long_rows = vec_per_row > 512 && (int64_t)shape->T * shape->k * row_bytes >= (int64_t)576 << 20;
+  const unsigned copy_threads = long_rows ? 256 : row_block_threads(shape->d, 16 / (int)elem_size(shape->dtype));
   // Short rows get more threads than pieces, so that up to four assignments are placed at a time; rows of at least 64
   // pieces whose ranks are known get twice as many (T = 131072, top-8, d = 512: 258 -> 233 us, d = 1024: 475 -> 451; below, the
   // second wavefront costs: d = 256: 137 -> 163).

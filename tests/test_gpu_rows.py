@@ -105,6 +105,26 @@ def test_many_assignments_of_short_rows(E, k, d, dtype, T, fused):
     assert bool(Xp[len(order):].isnan().all())
 
 
+@pytest.mark.parametrize("T", [32711, 32712])
+def test_large_copy_of_long_rows(T):
+    """Both sides of the 576 MB from which rows of more than 512 pieces (here 577: two trips and a remainder of either
+    block) are copied by narrower blocks."""
+    import paper_2502_02581_amd as moe
+
+    E, k, d = 6, 2, 4616
+    s = moe.MoEShape(T, d, E, k, 8, "bf16")
+    assert (T * k * d * 2 >= 576 << 20) == (T == 32712)
+    g = torch.Generator(device=DEV).manual_seed(T)
+    X = torch.randn(T, d, generator=g, device=DEV).to(torch.bfloat16)
+    idx = torch.stack([torch.randperm(E, generator=g, device=DEV)[:k] for _ in range(64)]).repeat(T // 64 + 1, 1)[:T].int().contiguous()
+    i32 = lambda *n: torch.full(n, -7, dtype=torch.int32, device=DEV)
+    counts, offsets, row_of, src_of = i32(E), i32(E + 1), i32(T * k), i32(T * k)
+    Xp = torch.full((T * k, d), float("nan"), dtype=torch.bfloat16, device=DEV)
+    moe.moe_dispatch(s, X, idx, counts, offsets, row_of, src_of, Xp, torch.empty(moe.moe_dispatch_workspace_bytes(s), dtype=torch.uint8, device=DEV))
+    order = torch.argsort(idx.view(-1), stable=True)
+    assert torch.equal(src_of.long(), order) and torch.equal(Xp, X[order // k])
+
+
 @pytest.mark.parametrize("E", [1, 3, 63, 64, 65, 200, 1023, 1024])
 def test_plan_of_many_groups(E):
     import paper_2502_02581_amd as moe
