@@ -187,7 +187,7 @@ __global__ __launch_bounds__(1024) void route_hist_kernel(const float* __restric
 
 // Ranks of one chunk per wavefront, in a launch of their own: walks the chunk in assignment order, the rank of an
 // assignment among equal experts inside a 64-wide step comes from ballots in lane order (the same rows as
-// dispatch_rows finds by itself).  An index out of range gets row -1.
+// dispatch_rows finds by itself).  An index out of range has no row: its row_of stays as it is.
 __global__ __launch_bounds__(64) void dispatch_rank(const int32_t* __restrict__ topk_idx, int A, int E, int chunk_len,
                                                     const int32_t* __restrict__ hist, const int32_t* __restrict__ offsets,
                                                     int32_t* __restrict__ row_of, int32_t* __restrict__ src_of) {
@@ -218,8 +218,10 @@ __global__ __launch_bounds__(64) void dispatch_rank(const int32_t* __restrict__ 
     __syncthreads();
     if (last) nxt[e] += group;
     __syncthreads();
-    if (i < n) row_of[a0 + i] = r;
-    if (r >= 0) src_of[r] = a0 + i;
+    if (r >= 0) {
+      row_of[a0 + i] = r;
+      src_of[r] = a0 + i;
+    }
   }
 }
 
@@ -270,11 +272,22 @@ __global__ __launch_bounds__(512) void dispatch_rows(const uint4* __restrict__ X
     }
     __syncthreads();
   }
+  // ranked before: the indices are looked at again only if some are out of range (fewer rows than assignments)
+  const bool some_out = !PLACE && offsets[E] != (int)gridDim.x * k;
   auto row_at = [&](int j) { return PLACE ? rows[j] : row_of[(size_t)t * k + j]; };
+  auto no_row = [&](int j) {
+    const int e = topk_idx[(size_t)t * k + j];
+    return e < 0 || e >= E;
+  };
   if (K > 0) {
     int row[KM];
 #pragma unroll
     for (int j = 0; j < KM; j++) row[j] = __builtin_amdgcn_readfirstlane(row_at(j));
+    if (some_out) {
+#pragma unroll
+      for (int j = 0; j < KM; j++)
+        if (no_row(j)) row[j] = -1;
+    }
     // two pieces per thread and trip: both loads are issued before the 2k stores
     while (c < vec_per_row) {
 #pragma unroll
@@ -292,7 +305,7 @@ __global__ __launch_bounds__(512) void dispatch_rows(const uint4* __restrict__ X
     for (; c < vec_per_row; c += nthr) {
       const uint4 v = src[c];
       for (int j = 0; j < k; j++) {
-        const int r = row_at(j);
+        const int r = some_out && no_row(j) ? -1 : row_at(j);
         if (r >= 0) Xp[(size_t)r * vec_per_row + c] = v;
       }
     }

@@ -102,7 +102,7 @@ def test_many_assignments_of_short_rows(E, k, d, dtype, T, fused):
     assert np.array_equal(src_of.cpu().numpy()[: len(order)], order)
     assert np.array_equal(row_of.cpu().numpy()[order], np.arange(len(order)))
     assert torch.equal(Xp[: len(order)], X[torch.from_numpy(order // k).to(DEV)])
-    assert bool(Xp[len(order):].isnan().all())
+    assert bool(Xp[len(order):].isnan().all()) and (np.delete(row_of.cpu().numpy(), order) == -7).all()
 
 
 @pytest.mark.parametrize("T", [32711, 32712])
