@@ -33,25 +33,23 @@ PROBE_LAUNCHES = 5
 COLD_STEPS = 3               # steps of the cold-cache variant
 MFMA_PROBE_BLOCKS = 2048     # blocks (8 per CU) and rounds of the register-resident matrix loop
 MFMA_PROBE_ITERS = 1000
-# kernel behind each profiling label on the bf16 LDS-DMA path, as rocprofv3 names it: the launches over the routed
-# experts.  Those over the shared experts, which the label counts too, are the instance without a plan (`symbols`).
+# kernel behind each profiling label on the bf16 LDS-DMA path, as rocprofv3 names it; a launch of the expert products
+# holds the tiles of the routed and of the shared experts
 SYMBOL = {
-    "gemm_fwd_gate_up": "moe::row_gemm_kernel<moe::RowCores<2, 2, false>, 2, 1, false, true>(moe::RowGemm)",
-    "gemm_fwd_down": "moe::row_gemm_kernel<moe::RowCores<2, 1, false>, 1, 0, false, true>(moe::RowGemm)",
+    "gemm_fwd_gate_up": "moe::row_gemm_kernel<moe::RowCores<2, 2, false>, 2, 1, false>(moe::RowGemm, moe::RowGemm, int)",
+    "gemm_fwd_down": "moe::row_gemm_kernel<moe::RowCores<2, 1, false>, 1, 0, false>(moe::RowGemm, moe::RowGemm, int)",
     "gemm_bwd_dh_dwd": "moe::row_w_gemm_kernel<moe::RowCores<2, 1, true>, 2, moe::MfmaDmaCore<unsigned short, 256, 256, 1, "
-                       "false, false, 2, 2, 1, false>, 1, true>(moe::RowGemm, moe::WGemm, int, int, int)",
+                       "false, false, 2, 2, 1, false>, 1>(moe::RowGemm, moe::RowGemm, moe::WGemm, moe::WGemm, moe::RowWOrder)",
     "gemm_bwd_dx_dwgu": "moe::row_w_gemm_kernel<moe::RowCores<2, 1, true>, 0, moe::MfmaDmaCore<unsigned short, 256, 128, 2, "
-                        "false, false, 2, 2, 1, false>, 2, true>(moe::RowGemm, moe::WGemm, int, int, int)",
+                        "false, false, 2, 2, 1, false>, 2>(moe::RowGemm, moe::RowGemm, moe::WGemm, moe::WGemm, moe::RowWOrder)",
     "gemm_bwd_dw_light": "moe::w_light_kernel<moe::MfmaDmaCore<unsigned short, 128, 128, 1, false, false, 2, 2, 0, false> >"
                          "(moe::WGemm, moe::WGemm, int)",
 }
 
 
 def symbols(label):
-    """Every kernel that the launches of a label run: the routed experts' instance, then the shared experts'."""
-    routed = SYMBOL[label]
-    shared = routed.replace("true>(moe::RowGemm", "false>(moe::RowGemm")
-    return (routed,) if shared == routed else (routed, shared)
+    """Every kernel that the launches of a label run."""
+    return (SYMBOL[label],)
 
 
 def algorithmic_work(cfg: wl.MoEConfig, counts):
@@ -83,8 +81,8 @@ def algorithmic_work(cfg: wl.MoEConfig, counts):
 
 
 def measured_traffic(cfg_name, label):
-    """(HBM bytes per launch of a label's kernels, where that figure comes from): the mean over the routed and the shared
-    experts' launches, as the label's time and FLOPs are.  The counters cannot be read
+    """(HBM bytes per launch of a label's kernels, where that figure comes from): the mean over its
+    launches, as the label's time and FLOPs are.  The counters cannot be read
     from inside this process: the figure is the one `rocprofv3 --pmc` measured for this workload when the
     summary under profiles/ was last regenerated (the file names its command and the commit it ran)."""
     from paper_2502_02581_amd.rocprof_summary import read_mean_traffic
@@ -238,7 +236,7 @@ def main():
     ap.add_argument("--config", default="dsv3", choices=list(wl.CONFIGS))
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-overlap-shared", action="store_true",
-                    help="keep the shared experts on the main stream in the timed region too (default: second stream)")
+                    help="accepted; the shared experts run in the launches of the routed ones either way")
     ap.add_argument("--no-graph", action="store_true",
                     help="launch every kernel of the timed steps from the host (default: one captured HIP graph per step)")
     ap.add_argument("--gather", action="store_true",
@@ -261,8 +259,8 @@ def main():
     weights = wl.make_weights(cfg, dev)
     g = {k: v.to(dev) for k, v in inp.items()}
     shape = moe.MoEShape(cfg.T, cfg.d, cfg.E, cfg.k, cfg.d_ff, cfg.dtype, cfg.gate, cfg.renorm)
-    hp = moe.MoEHotPath(shape, cfg.n_shared, cfg.d_ff_shared, dev, overlap_shared=not args.no_overlap_shared,
-                        aux_alpha=cfg.aux_alpha, gather=args.gather)
+    hp = moe.MoEHotPath(shape, cfg.n_shared, cfg.d_ff_shared, dev, aux_alpha=cfg.aux_alpha,
+                        gather=args.gather)
     sh = [weights.get("Wsg"), weights.get("Wsu"), weights.get("Wsd")]
 
     def step():
@@ -275,8 +273,8 @@ def main():
     sampled_err = verify(cfg, inp, weights, hp)
     # ---- the timed region: exactly `steps` bare steps (no per-kernel events), wall clock around all of
     # them, and one pair of HIP events per step on the launch stream for the median.  A step is the
-    # same ~40 launches every time, so it is captured once into a HIP graph and replayed (the small
-    # workloads are otherwise bound by the host's launch rate); the shared experts run on a second stream.
+    # same launches every time, so it is captured once into a HIP graph and replayed (the small
+    # workloads are otherwise bound by the host's launch rate).
     run = step
     if not args.no_graph:
         graph = torch.cuda.CUDAGraph()
@@ -300,7 +298,6 @@ def main():
 
     # ---- a second, profiled pass of the same steps: the library brackets every launch with HIP events on
     # the launch stream (this costs a little time per launch, which is why it is not the headline)
-    hp.overlap = False   # serial launches: the per-kernel durations then do not overlap
     moe.moe_profile_enable(True)
     t0p = time.perf_counter()
     for _ in range(args.steps):
@@ -323,7 +320,6 @@ def main():
     moe.moe_profile_enable(False)
     # cold-cache variant (outside the timed region, reported beside `value`): L2 and the infinity cache are
     # overwritten before every step by filling the 2 GiB probe buffer, and each step is timed on its own
-    hp.overlap = bool(cfg.n_shared) and not args.no_overlap_shared
     cold = []
     for _ in range(COLD_STEPS):
         probe.fill_(2)
@@ -365,7 +361,6 @@ def main():
     dma_path = cfg.dtype == "bf16" and cfg.d % 64 == 0 and cfg.d_ff % 64 == 0   # SYMBOL names that path's kernels
     traffic, traffic_src = measured_traffic(cfg.name, dom) if dma_path else (None, None)
     roofline = {"bound": "mfma" if cfg.dtype == "bf16" else "alu", "kernel": dom, "symbol": SYMBOL[dom] if dma_path else None,
-                "shared_symbol": (symbols(dom)[1:] or (None,))[0] if dma_path and cfg.n_shared else None,
                 "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s", "frac": round(achieved / peak, 4),
                 "avg_launch_ms": round(dom_ms / dom_n, 4), "launches": dom_n,
                 "flop_per_launch_avg": flops[dom] * args.steps / dom_n,
@@ -380,7 +375,7 @@ def main():
         "metric": "moe_layer_fwd_bwd_tokens_per_s", "value": round(cfg.T / (ms_per_step * 1e-3), 1), "unit": "tokens/s",
         "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": round(ms_per_step, 4),
         "median_step_ms": round(median_ms, 4), "profiled_pass_ms_per_step": round(dt_prof / args.steps * 1e3, 4),
-        "launch": {"hip_graph": not args.no_graph, "shared_experts_on_second_stream": bool(cfg.n_shared) and not args.no_overlap_shared,
+        "launch": {"hip_graph": not args.no_graph, "shared_experts": "in the launches of the routed ones" if cfg.n_shared else None,
                    "profiled_pass": "host launches, one stream, HIP events around every kernel"},
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": "bf16" if cfg.dtype == "bf16" else "f32", "data": "synthetic",

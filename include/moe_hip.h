@@ -277,6 +277,35 @@ int moe_expert_bwd_gather(const moe_shape_t* shape, const int32_t* offsets, cons
                           size_t ws_bytes, void* stream);
 
 /*
+ * moe_experts_fwd / moe_experts_bwd -- the routed and the shared experts of a layer in one call: the products of both
+ * run in common launches, so that the shared experts' few tiles and the last tiles of the routed ones fill the chip
+ * together.  Arguments and results are those of moe_expert_fwd(_gather) / moe_expert_bwd(_gather) for the routed set and
+ * of moe_expert_fwd / moe_expert_bwd in shared mode for the shared one, each set with a workspace of its own (the size
+ * queries of those calls); only the last bits of shared results may differ (sums over K in another number of parts).
+ * Both sets are given (each of the calls above serves one set alone); they have shape's d and dtype and their own d_ff.
+ */
+typedef struct moe_expert_set {
+  int32_t d_ff, n_groups, n_rows;
+  const int32_t* offsets;  /* routed set: [n_groups + 1]; shared set: NULL */
+  const int32_t* src_of;   /* routed set: not NULL: rows are read in place (n_groups = E, n_rows = T*k) */
+  const void* Xin;         /* [n_rows, d]; with src_of: X [T, d] in the forward pass, Xp in the backward pass */
+  const void *Wg, *Wu, *Wd;
+  void *G, *U, *H;         /* out in the forward pass, in in the backward pass */
+  void* Yout;              /* forward: out */
+  /* backward pass only */
+  const void* dYin;
+  const void* dY;          /* with src_of: [T, d] */
+  const float* row_w;      /* with src_of: topk_w */
+  void* dXin;
+  int32_t *active_ids, *n_active;
+  void *dWg_c, *dWu_c, *dWd_c;
+  void* ws;
+  size_t ws_bytes;
+} moe_expert_set_t;
+int moe_experts_fwd(const moe_shape_t* shape, const moe_expert_set_t* routed, const moe_expert_set_t* shared, void* stream);
+int moe_experts_bwd(const moe_shape_t* shape, const moe_expert_set_t* routed, const moe_expert_set_t* shared, void* stream);
+
+/*
  * moe_combine -- the weighted sum of Eq. 3:
  *   Y[t, :] = Yadd[t, :] + sum_j topk_w[t, j] * Yp[row_of[t*k + j], :]
  * accumulated in fp32 and rounded once.  topk_w == NULL means unit weights (this is then the

@@ -21,7 +21,8 @@ EXPORTS = ["moe_abi_version", "moe_last_error", "moe_route_bwd", "moe_router_fwd
            "moe_aux_loss_workspace_bytes", "moe_aux_loss", "moe_aux_loss_bwd",
            "moe_plan_overlap_degree", "moe_plan_predict_load", "moe_plan_materialize", "moe_plan_dispatch",
            "moe_dispatch_static", "moe_mfma_probe", "moe_expert_fwd_gather", "moe_expert_bwd_gather",
-           "moe_route_dispatch_workspace_bytes", "moe_route_dispatch", "moe_route_aux_bwd"]
+           "moe_route_dispatch_workspace_bytes", "moe_route_dispatch", "moe_route_aux_bwd", "moe_experts_fwd",
+           "moe_experts_bwd"]
 
 
 class MoEError(RuntimeError):
@@ -30,6 +31,19 @@ class MoEError(RuntimeError):
 
 class _CShape(ctypes.Structure):
     _fields_ = [(n, ctypes.c_int32) for n in ("T", "d", "E", "k", "d_ff", "dtype", "gate", "renorm")]
+
+
+# one set of experts of moe_experts_fwd / _bwd: the members of moe_expert_set_t, tensors with their element types
+# ("data": that of the layer)
+_SET_TENSORS = (("offsets", torch.int32), ("src_of", torch.int32), ("Xin", "data"), ("Wg", "data"), ("Wu", "data"), ("Wd", "data"),
+                ("G", "data"), ("U", "data"), ("H", "data"), ("Yout", "data"), ("dYin", "data"), ("dY", "data"),
+                ("row_w", torch.float32), ("dXin", "data"), ("active_ids", torch.int32), ("n_active", torch.int32),
+                ("dWg_c", "data"), ("dWu_c", "data"), ("dWd_c", "data"), ("ws", None))
+
+
+class _CExpertSet(ctypes.Structure):
+    _fields_ = ([(n, ctypes.c_int32) for n in ("d_ff", "n_groups", "n_rows")] + [(n, ctypes.c_void_p) for n, _ in _SET_TENSORS] +
+                [("ws_bytes", ctypes.c_size_t)])
 
 
 @dataclasses.dataclass(frozen=True)
@@ -119,6 +133,9 @@ def load_library():
     lib.moe_expert_fwd_gather.argtypes = [shp] + [vp] * 11 + [sz, vp]
     lib.moe_expert_bwd_gather.restype = ctypes.c_int
     lib.moe_expert_bwd_gather.argtypes = [shp] + [vp] * 19 + [sz, vp]
+    for f in (lib.moe_experts_fwd, lib.moe_experts_bwd):
+        f.restype = ctypes.c_int
+        f.argtypes = [shp, ctypes.POINTER(_CExpertSet), ctypes.POINTER(_CExpertSet), vp]
     lib.moe_combine.restype = ctypes.c_int
     lib.moe_combine.argtypes = [shp, vp, vp, vp, vp, vp, vp]
     lib.moe_combine_bwd.restype = ctypes.c_int
@@ -383,6 +400,31 @@ def moe_expert_bwd_gather(shape: MoEShape, offsets, src_of, Xp, Wg, Wu, Wd, G, U
     _check(rc, "moe_expert_bwd_gather")
 
 
+def _expert_set(shape: MoEShape, d_ff, n_groups, n_rows, **tensors) -> _CExpertSet:
+    s = _CExpertSet(d_ff=d_ff, n_groups=n_groups, n_rows=n_rows)
+    for name, dt in _SET_TENSORS:
+        setattr(s, name, _ptr(tensors.pop(name, None), shape.torch_dtype if dt == "data" else dt, name))
+    s.ws_bytes = tensors.pop("ws_bytes")
+    if tensors:
+        raise MoEError(f"unknown members of an expert set: {sorted(tensors)}")
+    return s
+
+
+def moe_experts_fwd(shape: MoEShape, routed: dict, shared: dict, stream=None):
+    """moe_expert_fwd (or, with src_of, _gather) of the routed experts and of the shared ones in common launches.  The
+    dicts hold the members of moe_expert_set_t: d_ff, n_groups, n_rows, tensors, ws and ws_bytes."""
+    rc = load_library().moe_experts_fwd(ctypes.byref(shape.c()), ctypes.byref(_expert_set(shape, **routed)),
+                                        ctypes.byref(_expert_set(shape, **shared)), _stream(stream))
+    _check(rc, "moe_experts_fwd")
+
+
+def moe_experts_bwd(shape: MoEShape, routed: dict, shared: dict, stream=None):
+    """moe_expert_bwd (or, with src_of, _gather) of the routed experts and of the shared ones in common launches."""
+    rc = load_library().moe_experts_bwd(ctypes.byref(shape.c()), ctypes.byref(_expert_set(shape, **routed)),
+                                        ctypes.byref(_expert_set(shape, **shared)), _stream(stream))
+    _check(rc, "moe_experts_bwd")
+
+
 def moe_combine(shape: MoEShape, Yp, row_of, topk_w, Yadd, Y, stream=None):
     dt = shape.torch_dtype
     rc = load_library().moe_combine(ctypes.byref(shape.c()), _ptr(Yp, dt, "Yp"), _ptr(row_of, torch.int32, "row_of"),
@@ -438,19 +480,19 @@ def moe_profile_report() -> Dict[str, tuple]:
 class MoEHotPath:
     """Owns the device buffers of one layer and chains the C calls of a training step.
 
-    forward():  moe_route -> moe_dispatch -> moe_expert_fwd (routed, then shared) -> moe_combine
-    backward(): moe_combine_bwd -> moe_expert_bwd (routed, then shared) -> moe_combine (unit weights)
-                -> moe_route_bwd (gradient of the router logits)
+    forward():  moe_route -> moe_dispatch -> moe_expert_fwd (with shared experts: moe_experts_fwd) -> moe_combine
+    backward(): moe_combine_bwd -> moe_expert_bwd (with shared experts: moe_experts_bwd) -> moe_combine (unit
+                weights) -> moe_route_bwd (gradient of the router logits)
     With aux_alpha > 0, forward() also evaluates the auxiliary load-balancing loss (moe_aux_loss, after
     the dispatch has counted the loads) and backward() adds its gradient to dlogits (moe_aux_loss_bwd).
     With fused (the default), gate + dispatch + loss go through moe_route_dispatch and the two backward
     calls of the gate through moe_route_aux_bwd: the same results from four launches fewer.
     No arithmetic happens here; tensors are only allocated and handed to the library.
 
-    The shared experts depend on nothing the routed experts produce, so with overlap_shared their
-    calls go to a second stream of the same (default) priority and join before the combine: their
-    blocks then fill the CUs that the tail of a routed launch leaves idle (about 1 % of a step on the
-    DeepSeek-V3-shaped workload; off by default because per-kernel durations then overlap).
+    The shared experts depend on nothing the routed experts produce, so their products run in the launches of the
+    routed ones and fill the CUs that those leave idle.  overlap_shared asked for them on a second stream, which is
+    slower (training step of T = 4096, d = 2048, 60 experts, 4 shared: 2.19 ms, in common launches 2.16); it is
+    accepted and changes nothing.
     """
 
     def __init__(self, shape: MoEShape, n_shared: int = 0, d_ff_shared: int = 0, device="cuda:0",
@@ -478,8 +520,8 @@ class MoEHotPath:
             "dWg_c": torch.empty(s.E, s.d, s.d_ff, **f), "dWu_c": torch.empty(s.E, s.d, s.d_ff, **f),
             "dWd_c": torch.empty(s.E, s.d_ff, s.d, **f),
         }
-        ws = max(moe_dispatch_workspace_bytes(s), moe_route_dispatch_workspace_bytes(s),
-                 moe_expert_fwd_workspace_bytes(s, s.E, A, False), moe_expert_bwd_workspace_bytes(s, s.E, A, False))
+        self.ws_routed = max(moe_expert_fwd_workspace_bytes(s, s.E, A, False), moe_expert_bwd_workspace_bytes(s, s.E, A, False))
+        ws = max(moe_dispatch_workspace_bytes(s), moe_route_dispatch_workspace_bytes(s), self.ws_routed)
         if n_shared:
             self.sshape = dataclasses.replace(s, d_ff=d_ff_shared)
             S, Fs = n_shared, d_ff_shared
@@ -490,40 +532,25 @@ class MoEHotPath:
                 "dWsg": torch.empty(S, s.d, Fs, **f), "dWsu": torch.empty(S, s.d, Fs, **f),
                 "dWsd": torch.empty(S, Fs, s.d, **f),
             })
-            ws = max(ws, moe_expert_fwd_workspace_bytes(self.sshape, S, s.T, True),
-                     moe_expert_bwd_workspace_bytes(self.sshape, S, s.T, True))
+            # the experts' calls take the workspace in two pieces, the routed experts' and the shared ones'
+            self.ws_routed = (self.ws_routed + 255) // 256 * 256
+            ws = max(ws, self.ws_routed + max(moe_expert_fwd_workspace_bytes(self.sshape, S, s.T, True),
+                                              moe_expert_bwd_workspace_bytes(self.sshape, S, s.T, True)))
         if self.aux_alpha > 0:
             self.b.update({"aux_P": torch.empty(s.E, dtype=torch.float32, device=dev),
                            "aux_loss": torch.empty(1, dtype=torch.float32, device=dev)})
             ws = max(ws, moe_aux_loss_workspace_bytes(s))
         self.ws = torch.empty(ws, dtype=torch.uint8, device=dev)
-        self.ws_shared = self.ws
-        if self.overlap:  # concurrent calls need a workspace each
-            self.ws_shared = torch.empty(max(moe_expert_fwd_workspace_bytes(self.sshape, n_shared, s.T, True),
-                                             moe_expert_bwd_workspace_bytes(self.sshape, n_shared, s.T, True)),
-                                         dtype=torch.uint8, device=dev)
-            self.side = torch.cuda.Stream(device=dev)
-            self.ev_fork, self.ev_join = torch.cuda.Event(), torch.cuda.Event()
 
-    def _fork(self, stream):
-        """The side stream starts after everything already queued on the main stream."""
-        main = stream if stream is not None else torch.cuda.current_stream(self.device)
-        self.ev_fork.record(main)
-        self.side.wait_event(self.ev_fork)
-        return main
-
-    def _join(self, main):
-        self.ev_join.record(self.side)
-        main.wait_event(self.ev_join)
+    def _ws_pieces(self):
+        """The workspace of the routed and that of the shared experts (keywords of an expert set)."""
+        return {"ws": self.ws[:self.ws_routed], "ws_bytes": self.ws_routed}, \
+               {"ws": self.ws[self.ws_routed:], "ws_bytes": self.ws.numel() - self.ws_routed}
 
     def forward(self, logits, X, Wg, Wu, Wd, Wsg=None, Wsu=None, Wsd=None, stream=None):
         s, b = self.shape, self.b
         A = s.T * s.k
         self._logits = logits  # the gate's backward reads them again
-        if self.overlap:
-            main = self._fork(stream)
-            moe_expert_fwd(self.sshape, self.S, None, s.T, X, Wsg, Wsu, Wsd, b["Gs"], b["Us"], b["Hs"], b["Ysh"],
-                           self.ws_shared, self.side)
         if self.fused:
             moe_route_dispatch(s, logits, X, self.aux_alpha, b["topk_idx"], b["topk_w"], b["counts"], b["offsets"],
                                b["row_of"], b["src_of"], b["Xp"], b.get("aux_P"), b.get("aux_loss"), self.ws, stream)
@@ -533,39 +560,43 @@ class MoEHotPath:
                          stream)
             if self.aux_alpha > 0:
                 moe_aux_loss(s, logits, b["counts"], self.aux_alpha, b["aux_P"], b["aux_loss"], self.ws, stream)
-        if self.gather:
+        if self.S:
+            ws, ws_shared = self._ws_pieces()
+            moe_experts_fwd(s, dict(d_ff=s.d_ff, n_groups=s.E, n_rows=A, offsets=b["offsets"],
+                                    src_of=b["src_of"] if self.gather else None, Xin=X if self.gather else b["Xp"],
+                                    Wg=Wg, Wu=Wu, Wd=Wd, G=b["G"], U=b["U"], H=b["H"], Yout=b["Yp"], **ws),
+                            dict(d_ff=self.Fs, n_groups=self.S, n_rows=s.T, Xin=X, Wg=Wsg, Wu=Wsu, Wd=Wsd, G=b["Gs"],
+                                 U=b["Us"], H=b["Hs"], Yout=b["Ysh"], **ws_shared), stream)
+        elif self.gather:
             moe_expert_fwd_gather(s, b["offsets"], b["src_of"], X, Wg, Wu, Wd, b["G"], b["U"], b["H"], b["Yp"], self.ws,
                                   stream)
         else:
             moe_expert_fwd(s, s.E, b["offsets"], A, b["Xp"], Wg, Wu, Wd, b["G"], b["U"], b["H"], b["Yp"], self.ws, stream)
-        if self.overlap:
-            self._join(main)
-        elif self.S:
-            moe_expert_fwd(self.sshape, self.S, None, s.T, X, Wsg, Wsu, Wsd, b["Gs"], b["Us"], b["Hs"], b["Ysh"],
-                           self.ws, stream)
         moe_combine(s, b["Yp"], b["row_of"], b["topk_w"], b["Ysh"] if self.S else None, b["Y"], stream)
         return b["Y"]
 
     def backward(self, dY, X, Wg, Wu, Wd, Wsg=None, Wsu=None, Wsd=None, stream=None):
         s, b = self.shape, self.b
         A = s.T * s.k
-        if self.overlap:
-            main = self._fork(stream)
-            moe_expert_bwd(self.sshape, self.S, None, s.T, X, Wsg, Wsu, Wsd, b["Gs"], b["Us"], b["Hs"], dY, b["dXsh"],
-                           b["s_active_ids"], b["s_n_active"], b["dWsg"], b["dWsu"], b["dWsd"], self.ws_shared, self.side)
         moe_combine_bwd(s, dY, b["Yp"], b["row_of"], b["topk_w"], b["dYp"], b["dw"], stream)
-        if self.gather:
+        if self.S:
+            ws, ws_shared = self._ws_pieces()
+            in_place = dict(src_of=b["src_of"], dY=dY, row_w=b["topk_w"]) if self.gather else {}
+            moe_experts_bwd(s, dict(d_ff=s.d_ff, n_groups=s.E, n_rows=A, offsets=b["offsets"], Xin=b["Xp"], Wg=Wg, Wu=Wu,
+                                    Wd=Wd, G=b["G"], U=b["U"], H=b["H"], dYin=b["dYp"], dXin=b["dXp"],
+                                    active_ids=b["active_ids"], n_active=b["n_active"], dWg_c=b["dWg_c"],
+                                    dWu_c=b["dWu_c"], dWd_c=b["dWd_c"], **in_place, **ws),
+                            dict(d_ff=self.Fs, n_groups=self.S, n_rows=s.T, Xin=X, Wg=Wsg, Wu=Wsu, Wd=Wsd, G=b["Gs"],
+                                 U=b["Us"], H=b["Hs"], dYin=dY, dXin=b["dXsh"], active_ids=b["s_active_ids"],
+                                 n_active=b["s_n_active"], dWg_c=b["dWsg"], dWu_c=b["dWsu"], dWd_c=b["dWsd"],
+                                 **ws_shared), stream)
+        elif self.gather:
             moe_expert_bwd_gather(s, b["offsets"], b["src_of"], b["Xp"], Wg, Wu, Wd, b["G"], b["U"], b["H"], dY,
                                   b["topk_w"], b["dYp"], b["dXp"], b["active_ids"], b["n_active"], b["dWg_c"],
                                   b["dWu_c"], b["dWd_c"], self.ws, stream)
         else:
             moe_expert_bwd(s, s.E, b["offsets"], A, b["Xp"], Wg, Wu, Wd, b["G"], b["U"], b["H"], b["dYp"], b["dXp"],
                            b["active_ids"], b["n_active"], b["dWg_c"], b["dWu_c"], b["dWd_c"], self.ws, stream)
-        if self.overlap:
-            self._join(main)
-        elif self.S:
-            moe_expert_bwd(self.sshape, self.S, None, s.T, X, Wsg, Wsu, Wsd, b["Gs"], b["Us"], b["Hs"], dY, b["dXsh"],
-                           b["s_active_ids"], b["s_n_active"], b["dWsg"], b["dWsu"], b["dWsd"], self.ws, stream)
         moe_combine(s, b["dXp"], b["row_of"], None, b["dXsh"] if self.S else None, b["dX"], stream)
         if self.fused and self.aux_alpha > 0:
             moe_route_aux_bwd(s, self._logits, b["topk_idx"], b["dw"], b["counts"], self.aux_alpha, 1.0, b["dlogits"],

@@ -100,8 +100,8 @@ void launch_plan(const int32_t* offsets, int n_groups, int BM, const Plan& pl, i
 
 // one translation unit each
 #define MOE_CORES(PATH)                                                                                                 \
-  extern template void expert_fwd_impl<PATH>(const FwdArgs&, hipStream_t);                                            \
-  extern template void expert_bwd_impl<PATH>(const BwdArgs&, hipStream_t);                                            \
+  extern template void expert_fwd_impl<PATH>(const FwdArgs*, const FwdArgs*, hipStream_t);                                            \
+  extern template void expert_bwd_impl<PATH>(const BwdArgs*, const BwdArgs*, hipStream_t);                                            \
   extern template void router_fwd_impl<PATH>(const moe_shape_t*, const void*, const void*, float*, char*, char*,      \
                                              size_t, hipStream_t);                                                     \
   extern template void router_bwd_impl<PATH>(const moe_shape_t*, const void*, const void*, const float*, void*, void*, \
@@ -113,6 +113,21 @@ MOE_CORES(PATH_BF16)
 static int pick_path(const moe_shape_t* s) {
   if (s->dtype == MOE_F32) return PATH_F32;
   return (s->d % 64 == 0 && s->d_ff % 64 == 0) ? PATH_BF16 : PATH_BF16_TAIL;
+}
+
+static void run_fwd(int path, const FwdArgs* routed, const FwdArgs* shared, hipStream_t st) {
+  switch (path) {
+    case PATH_F32: expert_fwd_impl<PATH_F32>(routed, shared, st); break;
+    case PATH_BF16_TAIL: expert_fwd_impl<PATH_BF16_TAIL>(routed, shared, st); break;
+    default: expert_fwd_impl<PATH_BF16>(routed, shared, st); break;
+  }
+}
+static void run_bwd(int path, const BwdArgs* routed, const BwdArgs* shared, hipStream_t st) {
+  switch (path) {
+    case PATH_F32: expert_bwd_impl<PATH_F32>(routed, shared, st); break;
+    case PATH_BF16_TAIL: expert_bwd_impl<PATH_BF16_TAIL>(routed, shared, st); break;
+    default: expert_bwd_impl<PATH_BF16>(routed, shared, st); break;
+  }
 }
 
 static size_t plan_size_for(int n_groups, int n_rows, bool shared) {
@@ -191,11 +206,7 @@ extern "C" int moe_expert_fwd(const moe_shape_t* shape, int32_t n_groups, const 
   if (n_rows == 0) return MOE_OK;
   FwdArgs a = {shape->d, shape->d_ff, n_groups, n_rows, offsets, Xin, Wg, Wu, Wd, G, U, H, Yout,
                (char*)ws, (char*)ws + need, ws_bytes - need};
-  switch (pick_path(shape)) {
-    case PATH_F32: expert_fwd_impl<PATH_F32>(a, (hipStream_t)stream); break;
-    case PATH_BF16_TAIL: expert_fwd_impl<PATH_BF16_TAIL>(a, (hipStream_t)stream); break;
-    default: expert_fwd_impl<PATH_BF16>(a, (hipStream_t)stream); break;
-  }
+  run_fwd(pick_path(shape), offsets ? &a : nullptr, offsets ? nullptr : &a, (hipStream_t)stream);
   return launch_status("moe_expert_fwd");
 }
 
@@ -227,11 +238,7 @@ extern "C" int moe_expert_bwd(const moe_shape_t* shape, int32_t n_groups, const 
   BwdArgs a = {shape->d, shape->d_ff, n_groups, n_rows, offsets, Xin, Wg, Wu, Wd, G, U, H, dYin, dXin,
                active_ids, n_active, dWg_c, dWu_c, dWd_c, (char*)ws, dG,
                dG + grad_size_for(shape, n_groups, n_rows, offsets == nullptr), (char*)ws + need, ws_bytes - need};
-  switch (pick_path(shape)) {
-    case PATH_F32: expert_bwd_impl<PATH_F32>(a, (hipStream_t)stream); break;
-    case PATH_BF16_TAIL: expert_bwd_impl<PATH_BF16_TAIL>(a, (hipStream_t)stream); break;
-    default: expert_bwd_impl<PATH_BF16>(a, (hipStream_t)stream); break;
-  }
+  run_bwd(pick_path(shape), offsets ? &a : nullptr, offsets ? nullptr : &a, (hipStream_t)stream);
   return launch_status("moe_expert_bwd");
 }
 
@@ -265,11 +272,7 @@ extern "C" int moe_expert_fwd_gather(const moe_shape_t* shape, const int32_t* of
   if (n_rows == 0) return MOE_OK;
   FwdArgs a = {shape->d, shape->d_ff, n_groups, n_rows, offsets, X, Wg, Wu, Wd, G, U, H, Yout, (char*)ws, nullptr, 0};
   a.src_of = src_of; a.src_div = shape->k; a.src_rows = shape->T;
-  switch (pick_path(shape)) {
-    case PATH_F32: expert_fwd_impl<PATH_F32>(a, (hipStream_t)stream); break;
-    case PATH_BF16_TAIL: expert_fwd_impl<PATH_BF16_TAIL>(a, (hipStream_t)stream); break;
-    default: expert_fwd_impl<PATH_BF16>(a, (hipStream_t)stream); break;
-  }
+  run_fwd(pick_path(shape), &a, nullptr, (hipStream_t)stream);
   return launch_status("moe_expert_fwd_gather");
 }
 
@@ -306,12 +309,128 @@ extern "C" int moe_expert_bwd_gather(const moe_shape_t* shape, const int32_t* of
   BwdArgs a = {shape->d, shape->d_ff, n_groups, n_rows, offsets, Xp, Wg, Wu, Wd, G, U, H, dYp, dXp,
                active_ids, n_active, dWg_c, dWu_c, dWd_c, (char*)ws, dG, dG + grad_size_for(shape, n_groups, n_rows, false), nullptr, 0};
   a.dY = dY; a.src_of = src_of; a.row_w = topk_w; a.src_div = shape->k; a.src_rows = shape->T;
-  switch (pick_path(shape)) {
-    case PATH_F32: expert_bwd_impl<PATH_F32>(a, (hipStream_t)stream); break;
-    case PATH_BF16_TAIL: expert_bwd_impl<PATH_BF16_TAIL>(a, (hipStream_t)stream); break;
-    default: expert_bwd_impl<PATH_BF16>(a, (hipStream_t)stream); break;
-  }
+  run_bwd(pick_path(shape), &a, nullptr, (hipStream_t)stream);
   return launch_status("moe_expert_bwd_gather");
+}
+
+// Routed and shared experts of one layer: see include/moe_hip.h.
+namespace moe {
+
+// the checks of the calls for one set of experts, and their argument block; 0, or the error code
+static int check_set(const moe_shape_t* shape, const moe_expert_set_t* x, bool routed, bool bwd, const char* who, moe_shape_t& s,
+                     size_t& need) {
+  s = *shape;
+  s.d_ff = x->d_ff;
+  int rc = check_expert_args(&s, x->n_groups, x->n_rows, who);
+  if (rc) return rc;
+  const bool gather = routed && x->src_of != nullptr;
+  bool null = !x->Wg || !x->Wd || !x->ws || (routed ? !x->offsets : x->offsets != nullptr || x->src_of != nullptr);
+  if (x->n_rows > 0) null = null || !x->Xin || !x->G || (x->Wu && !x->U) || !x->H;
+  if (bwd) {
+    null = null || !x->active_ids || !x->n_active || !x->dWg_c || (x->Wu && !x->dWu_c) || !x->dWd_c;
+    if (x->n_rows > 0) null = null || !x->dYin || !x->dXin || (gather && (!x->dY || !x->row_w));
+  } else if (x->n_rows > 0) {
+    null = null || !x->Yout;
+  }
+  if (null) {
+    set_error("%s: null pointer (offsets are the routed experts' alone)", who);
+    return MOE_EINVAL;
+  }
+  const void* fwd_ptrs[] = {x->Xin, x->Wg, x->Wu, x->Wd, x->G, x->U, x->H, x->ws, bwd ? nullptr : x->Yout};
+  const void* bwd_ptrs[] = {x->dYin, x->dY, x->dXin, x->dWg_c, x->dWu_c, x->dWd_c};
+  bool aligned = true;
+  for (const void* p : fwd_ptrs) aligned = aligned && aligned16(p);
+  if (bwd)
+    for (const void* p : bwd_ptrs) aligned = aligned && aligned16(p);
+  if (!aligned) {
+    set_error("%s: every tensor must be 16-byte aligned", who);
+    return MOE_EINVAL;
+  }
+  if (gather && (x->n_groups != shape->E || x->n_rows != shape->T * shape->k)) {
+    set_error("%s: rows read in place are those of the shape: E groups, T*k rows", who);
+    return MOE_EINVAL;
+  }
+  if (gather && (int64_t)shape->T * shape->d * (int64_t)elem_size(shape->dtype) >= ((int64_t)1 << 32) - 4096) {
+    set_error("%s: rows read in place must take less than 4 GiB (32-bit byte offsets)", who);
+    return MOE_EINVAL;
+  }
+  need = bwd ? bwd_base(&s, x->n_groups, x->n_rows, !routed) : fwd_base(&s, x->n_groups, x->n_rows, !routed);
+  if (x->ws_bytes < need) {
+    set_error("%s: workspace of %zu bytes, need %zu", who, x->ws_bytes, need);
+    return MOE_EWS;
+  }
+  return MOE_OK;
+}
+static int check_sets(const moe_shape_t* shape, const moe_expert_set_t* routed, const moe_expert_set_t* shared, bool bwd, const char* who,
+                      moe_shape_t (&s)[2], size_t (&need)[2]) {
+  if (!shape || !routed || !shared) {
+    set_error("%s: null pointer", who);
+    return MOE_EINVAL;
+  }
+  const int rc = check_set(shape, routed, true, bwd, who, s[0], need[0]);
+  return rc ? rc : check_set(shape, shared, false, bwd, who, s[1], need[1]);
+}
+// Common launches need the same kernels for both: one activation, and cores that take both widths.  Anything else (no
+// rows on one side, rows beyond the tile cores' offsets) goes one after the other, as the two calls would.
+static bool can_share(const moe_shape_t (&s)[2], const moe_expert_set_t* routed, const moe_expert_set_t* shared) {
+  const int64_t ld = std::max({s[0].d, s[0].d_ff, s[1].d_ff});
+  return routed->n_rows > 0 && shared->n_rows > 0 && !routed->Wu == !shared->Wu && !wide_rows(ld, elem_size(s[0].dtype));
+}
+
+}  // namespace moe
+
+extern "C" int moe_experts_fwd(const moe_shape_t* shape, const moe_expert_set_t* routed, const moe_expert_set_t* shared, void* stream) {
+  using namespace moe;
+  moe_shape_t s[2];
+  size_t need[2];
+  const int rc = check_sets(shape, routed, shared, false, "moe_experts_fwd", s, need);
+  if (rc) return rc;
+  const moe_expert_set_t* sets[2] = {routed, shared};
+  FwdArgs a[2];
+  for (int i = 0; i < 2; i++) {
+    const moe_expert_set_t* x = sets[i];
+    a[i] = {shape->d, x->d_ff, x->n_groups, x->n_rows, x->offsets, x->Xin, x->Wg, x->Wu, x->Wd, x->G, x->U, x->H, x->Yout,
+            (char*)x->ws, (char*)x->ws + need[i], x->ws_bytes - need[i]};
+    if (x->src_of) { a[i].src_of = x->src_of; a[i].src_div = shape->k; a[i].src_rows = shape->T; }
+  }
+  const int p0 = pick_path(&s[0]), p1 = pick_path(&s[1]);
+  hipStream_t st = (hipStream_t)stream;
+  if (can_share(s, routed, shared)) {
+    run_fwd(std::min(p0, p1), &a[0], &a[1], st);  // (PATH_BF16_TAIL takes what PATH_BF16 takes, with the same results)
+  } else {
+    if (routed->n_rows > 0) run_fwd(p0, &a[0], nullptr, st);
+    if (shared->n_rows > 0) run_fwd(p1, nullptr, &a[1], st);
+  }
+  return launch_status("moe_experts_fwd");
+}
+
+extern "C" int moe_experts_bwd(const moe_shape_t* shape, const moe_expert_set_t* routed, const moe_expert_set_t* shared, void* stream) {
+  using namespace moe;
+  moe_shape_t s[2];
+  size_t need[2];
+  const int rc = check_sets(shape, routed, shared, true, "moe_experts_bwd", s, need);
+  if (rc) return rc;
+  const moe_expert_set_t* sets[2] = {routed, shared};
+  BwdArgs a[2];
+  for (int i = 0; i < 2; i++) {
+    const moe_expert_set_t* x = sets[i];
+    char* dG = (char*)x->ws + plan_size_for(x->n_groups, x->n_rows, i == 1);
+    a[i] = {shape->d, x->d_ff, x->n_groups, x->n_rows, x->offsets, x->Xin, x->Wg, x->Wu, x->Wd, x->G, x->U, x->H, x->dYin, x->dXin,
+            x->active_ids, x->n_active, x->dWg_c, x->dWu_c, x->dWd_c, (char*)x->ws, dG,
+            dG + grad_size_for(&s[i], x->n_groups, x->n_rows, i == 1), (char*)x->ws + need[i], x->ws_bytes - need[i]};
+    if (x->src_of) {
+      a[i].dY = x->dY; a[i].src_of = x->src_of; a[i].row_w = x->row_w; a[i].src_div = shape->k; a[i].src_rows = shape->T;
+    }
+  }
+  const int p0 = pick_path(&s[0]), p1 = pick_path(&s[1]);
+  hipStream_t st = (hipStream_t)stream;
+  if (can_share(s, routed, shared)) {
+    run_bwd(std::min(p0, p1), &a[0], &a[1], st);
+  } else {
+    run_bwd(p0, &a[0], nullptr, st);
+    run_bwd(p1, nullptr, &a[1], st);
+  }
+  return launch_status("moe_experts_bwd");
 }
 
 // ------------------------------------------------------------------------------------ router

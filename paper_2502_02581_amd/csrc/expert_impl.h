@@ -250,8 +250,11 @@ __device__ __forceinline__ void w_gemm_block(const WGemm& p, int block, char* sm
       p.active_ids[i] = i;
       if (i == 0) *p.n_active = p.n_groups;
     }
-  const int part = PLAN || p.n_parts == 1 ? 0 : block / (p.n_groups * per_group);
-  if (!PLAN) block -= part * (p.n_groups * per_group);
+  const int part = PLAN ? 0 : block / (p.n_groups * per_group);
+  if (!PLAN) {
+    if (part >= p.n_parts) return;  // the launch is rounded up
+    block -= part * (p.n_groups * per_group);
+  }
   const int item = block / per_group, tile = block - item * per_group;
   // single-product kernels serve the two products of a dual GEMM one after the other
   const int z = NB == 1 ? item / p.n_groups : 0;
@@ -307,27 +310,37 @@ __device__ __forceinline__ void w_gemm_block(const WGemm& p, int block, char* sm
 }
 
 // ---------------------------------------------------------------------------------- kernels
-template <class CoreSet, int NB, int EPI, bool B_KC, bool PLAN>
-__global__ __launch_bounds__(CoreSet::template tile<0>::NT, CoreSet::template tile<0>::BLOCKS_PER_CU) void row_gemm_kernel(RowGemm p) {
+// A product over the rows of shared experts (or of the router: no plan), `s_blocks` blocks, and the same product over
+// those of the routed experts (a plan), in one launch; either may be missing.  The shared tiles are full and even, so
+// they come first: the light tiles of the routed groups end the launch.  (In launches of their own the shared experts' few tiles leave
+// compute units idle, and so do the last routed ones.  Before and now, whole passes: 16 tokens through 4 shared of width 1408 and
+// 60 experts, d = 2048, forward 137 -> 122 us; training, T = 3001, d = 1000, one shared 673 -> 603, T = 2777, d = 2048, four shared
+// 1629 -> 1518.  Against the shared experts on a second stream: T = 4096 of the last, 2188 -> 2162.)
+template <class CoreSet, int NB, int EPI, bool B_KC>
+__global__ __launch_bounds__(CoreSet::template tile<0>::NT, CoreSet::template tile<0>::BLOCKS_PER_CU) void row_gemm_kernel(RowGemm s, RowGemm r, int s_blocks) {
   extern __shared__ __align__(16) char smem[];
-  row_gemm_block<CoreSet, NB, EPI, B_KC, PLAN>(p, blockIdx.x, smem);
+  const int b = (int)blockIdx.x - s_blocks;
+  if (b < 0) row_gemm_block<CoreSet, NB, EPI, B_KC, false>(s, blockIdx.x, smem);
+  else row_gemm_block<CoreSet, NB, EPI, B_KC, true>(r, b, smem);
 }
-// An input gradient and a weight gradient that does not depend on it in one launch: the first `row_blocks` blocks
-// are row tiles (the longer ones), the others weight-gradient tiles, which fill the compute units that the
-// last row tiles leave idle.  (One launch per product against dH + dWd and dX + dWg + dWu, and one
+// An input gradient and a weight gradient that does not depend on it in one launch: first the row tiles (the longer
+// ones), then weight-gradient tiles, which fill the compute units that the last row tiles leave idle.
+// (One launch per product against dH + dWd and dX + dWg + dWu, and one
 // instead of two for the light groups: training steps of T = 2777, d = 2048, 60 experts, top-3: 1.87 -> 1.69 ms;
 // T = 3001, d = 1000: 0.88 -> 0.76; T = 8192, d = 768 GELU: 1.08 -> 1.03; fp32 T = 2048, d = 1024: 2.32 -> 2.14.)
-// first_w > 0 (without a plan only): `first_w` blocks, a multiple of 8, for the weight gradient come first.
-template <class CoreSet, int EPI, class WCore, int WNB, bool PLAN>
-__global__ __launch_bounds__(WCore::NT, CoreSet::template tile<0>::BLOCKS_PER_CU) void row_w_gemm_kernel(RowGemm p, WGemm w, int row_blocks, int w_blocks, int first_w) {
+// Blocks in this order, all counts but the last multiples of 8: weight gradients of shared experts where their tiles
+// are the longest, row tiles of shared, of routed experts, weight gradients of shared, of routed experts.
+struct RowWOrder {
+  int32_t first_sw, s_rows, r_rows, last_sw;
+};
+template <class CoreSet, int EPI, class WCore, int WNB>
+__global__ __launch_bounds__(WCore::NT, CoreSet::template tile<0>::BLOCKS_PER_CU) void row_w_gemm_kernel(RowGemm s, RowGemm r, WGemm sw, WGemm rw, RowWOrder o) {
   extern __shared__ __align__(16) char smem[];
-  const int r = (int)blockIdx.x - (PLAN ? 0 : first_w);
-  if (r >= 0 && r < row_blocks) {
-    row_gemm_block<CoreSet, 1, EPI, true, PLAN>(p, r, smem);
-  } else {
-    const int b = r < 0 ? (int)blockIdx.x : r - row_blocks;
-    if (PLAN || b < w_blocks) w_gemm_block<WCore, WNB, PLAN>(w, b, smem);
-  }
+  const int b = (int)blockIdx.x - o.first_sw, w = b - o.s_rows - o.r_rows;
+  if (b < 0 || (w >= 0 && w < o.last_sw)) w_gemm_block<WCore, WNB, false>(sw, b < 0 ? (int)blockIdx.x : w, smem);
+  else if (b < o.s_rows) row_gemm_block<CoreSet, 1, EPI, true, false>(s, b, smem);
+  else if (w < 0) row_gemm_block<CoreSet, 1, EPI, true, true>(r, b - o.s_rows, smem);
+  else w_gemm_block<WCore, WNB, true>(rw, w - o.last_sw, smem);
 }
 // The weight gradients of the groups with few rows: all matrices of an expert in one launch.
 template <class Core>
@@ -465,39 +478,7 @@ template <class Core> static unsigned w_block_count(const WGemm& p, int n_produc
   return (unsigned)tiles * (unsigned)p.n_groups * (unsigned)n_products;
 }
 
-// Launches on the tiles of a plan.
-template <class CoreSet, int NB, int EPI, bool B_KC>
-static void launch_row(const char* label, const RowGemm& p, int max_tiles, hipStream_t st) {
-  typedef typename CoreSet::template tile<0> Core;
-  if (p.wide) return launch_wide_row<typename Core::T, NB, EPI, B_KC>(label, p, Core::BM, max_tiles, st);
-  const unsigned blocks = row_block_count(max_tiles, p.N, CoreSet::template tile<0>::BN);
-  if (blocks == 0) return;
-  auto kern = row_gemm_kernel<CoreSet, NB, EPI, B_KC, true>;
-  static LdsAttr attr;
-  constexpr int kLds = row_lds_bytes<CoreSet>();
-  attr.ensure((const void*)kern, kLds);
-  ProfScope prof(label, st);
-  hipLaunchKernelGGL(kern, dim3(blocks), dim3(CoreSet::template tile<0>::NT), kLds, st, p);
-}
-
-template <class CoreSet, int EPI, class WCore, int WNB>
-static void launch_row_w(const char* label, const RowGemm& p, int max_tiles, const WGemm& w, hipStream_t st) {
-  typedef typename CoreSet::template tile<0> Core;
-  if (p.wide) {
-    launch_wide_row<typename Core::T, 1, EPI, true>(label, p, Core::BM, max_tiles, st);
-    return launch_wide_w<typename Core::T>(label, w, WNB, st);
-  }
-  const unsigned rb = row_block_count(max_tiles, p.N, CoreSet::template tile<0>::BN), wb = w_block_count<WCore>(w);
-  if (rb + wb == 0) return;
-  auto kern = row_w_gemm_kernel<CoreSet, EPI, WCore, WNB, true>;
-  static LdsAttr attr;
-  constexpr int kLds = std::max(row_lds_bytes<CoreSet>(), WCore::LDS_BYTES);
-  attr.ensure((const void*)kern, kLds);
-  ProfScope prof(label, st);
-  hipLaunchKernelGGL(kern, dim3(rb + wb), dim3(WCore::NT), kLds, st, p, w, (int)rb, (int)wb, 0);
-}
-
-// Launches without a plan: the host knows how many tiles there are, and picks the tile height and the number of
+// Products without a plan: the host knows how many tiles there are, and picks the tile height and the number of
 // parts along K.  A layer's few shared experts and the router have few, long products: 16 tokens through 4 shared
 // experts of width 1408 (d = 2048) gave the down product 8 blocks of 88 K steps, 112 us, in parts 21 + 5 us (the sums);
 // gate/up 30 -> 19 + 5 us.  The router of d = 7168, E = 256, T = 8192: forward 83 -> 47 + 8 us; the weight
@@ -532,6 +513,7 @@ struct DirectShape {      // one product (or pair of products, `nb` = 2) without
   int groups, rows, N, K, nb;  // (weight gradient: rows is M)
   int sums;                    // segments times pairs: how often K values are summed
   int64_t out_elems;           // elements of an output matrix
+  double routed_us;            // the launch's tiles of routed experts, summed (an estimate: their row counts are on the device)
 };
 struct DirectChoice {
   int kind = 0, n_parts = 1, k_part = 0;
@@ -566,10 +548,11 @@ static void choose_direct(const DirectShape* r, const DirectShape* w, size_t ava
         const DirectChoice b = w ? direct_option(*w, 0, pw) : DirectChoice();
         if (pw > 1 && (!w || b.n_parts == 1 || a.part_bytes + b.part_bytes > avail)) continue;
         double us;
-        if (!w) us = (double)((a.blocks + kCUs - 1) / kCUs) * a.block_us;
+        const double routed = r ? r->routed_us : 0;
+        if (!w && routed == 0) us = (double)((a.blocks + kCUs - 1) / kCUs) * a.block_us;
         else {
           const double longest = std::max(a.block_us, b.block_us);
-          us = std::max(longest, (a.blocks * a.block_us + b.blocks * b.block_us) / kCUs + 0.3 * longest);
+          us = std::max(longest, (a.blocks * a.block_us + b.blocks * b.block_us + routed) / kCUs + 0.3 * longest);
         }
         us += a.reduce_us + b.reduce_us;
         if (first || us < best) {
@@ -594,60 +577,94 @@ static void launch_reduce(const float* part, int n_parts, int64_t n, void* const
   hipLaunchKernelGGL((reduce_kernel<T, NB, EPI>), dim3((unsigned)std::min<int64_t>((n / 4 + 255) / 256, 4096)), dim3(256), 0, st, q);
 }
 
-// The row product p alone, or (w) with a weight gradient in the launch; p and w come filled but for the choice.
-template <class CoreSet, int NB, int EPI, bool B_KC>
-static void launch_row_direct(const char* label, RowGemm p, const DirectShape& s, char* parts, size_t avail, hipStream_t st) {
-  typedef typename CoreSet::template tile<0> Core;
-  if (p.wide)
-    return launch_wide_row<typename Core::T, NB, EPI, B_KC>(label, p, Core::BM, s.groups * ceil_div(s.rows, Core::BM), st);
-  DirectChoice c, none;
-  choose_direct(&s, nullptr, avail, &c, &none);
+// The shared side of a launch: the product without a plan (filled but for the choice) and room for its parts.
+struct Direct {
+  RowGemm p;
+  DirectShape shape;
+  WGemm w;
+  DirectShape w_shape;
+  char* parts;
+  size_t avail;
+};
+static void set_choice(RowGemm& p, const DirectShape& s, const DirectChoice& c, char* parts, int bm, int bn) {
   p.direct_kind = c.kind; p.n_parts = c.n_parts; p.k_part = c.k_part;
   p.part = (float*)parts; p.part_stride = s.out_elems;
-  p.part_blocks = (int)row_block_count(s.groups * ceil_div(s.rows, Core::BM >> c.kind), p.N, Core::BN);
-  const unsigned blocks = (unsigned)p.part_blocks * c.n_parts;
-  if (blocks == 0) return;
-  auto kern = row_gemm_kernel<CoreSet, NB, EPI, B_KC, false>;
+  p.part_blocks = (int)row_block_count(s.groups * ceil_div(s.rows, bm >> c.kind), p.N, bn);
+}
+
+// One product over the shared rows (sd), the routed rows (r, at most r_tiles tiles), or both.
+template <class CoreSet, int NB, int EPI, bool B_KC>
+static void launch_row(const char* label, const Direct* sd, const RowGemm* r, int r_tiles, hipStream_t st) {
+  typedef typename CoreSet::template tile<0> Core;
+  if (sd && sd->p.wide)
+    launch_wide_row<typename Core::T, NB, EPI, B_KC>(label, sd->p, Core::BM, sd->shape.groups * ceil_div(sd->shape.rows, Core::BM), st);
+  if (r && r->wide) launch_wide_row<typename Core::T, NB, EPI, B_KC>(label, *r, Core::BM, r_tiles, st);
+  if (sd && sd->p.wide) sd = nullptr;
+  if (r && r->wide) r = nullptr;
+  DirectChoice c, none;
+  RowGemm p = {};
+  if (sd) {
+    choose_direct(&sd->shape, nullptr, sd->avail, &c, &none);
+    p = sd->p;
+    set_choice(p, sd->shape, c, sd->parts, Core::BM, Core::BN);
+  }
+  const unsigned sb = (unsigned)p.part_blocks * c.n_parts, rb = r ? row_block_count(r_tiles, r->N, Core::BN) : 0;
+  if (sb + rb == 0) return;
+  auto kern = row_gemm_kernel<CoreSet, NB, EPI, B_KC>;
   static LdsAttr attr;
   constexpr int kLds = row_lds_bytes<CoreSet>();
   attr.ensure((const void*)kern, kLds);
   {
     ProfScope prof(label, st);
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(Core::NT), kLds, st, p);
+    hipLaunchKernelGGL(kern, dim3(sb + rb), dim3(Core::NT), kLds, st, p, r ? *r : RowGemm{}, (int)sb);
   }
-  if (c.n_parts > 1) launch_reduce<typename Core::T, NB, EPI>(p.part, c.n_parts, s.out_elems, p.out, p.in, st);
+  if (c.n_parts > 1) launch_reduce<typename Core::T, NB, EPI>(p.part, c.n_parts, sd->shape.out_elems, p.out, p.in, st);
 }
 
+// The same with a weight gradient that does not depend on the product.
 template <class CoreSet, int EPI, class WCore, int WNB>
-static void launch_row_w_direct(const char* label, RowGemm p, const DirectShape& rs, WGemm w, const DirectShape& ws, char* parts,
-                                size_t avail, hipStream_t st) {
+static void launch_row_w(const char* label, const Direct* sd, const RowGemm* r, int r_tiles, const WGemm* rw, hipStream_t st) {
   typedef typename CoreSet::template tile<0> Core;
   typedef typename Core::T T;
-  if (p.wide) {
-    launch_wide_row<T, 1, EPI, true>(label, p, Core::BM, rs.groups * ceil_div(rs.rows, Core::BM), st);
-    return launch_wide_w<T>(label, w, WNB, st);
+  if (sd && sd->p.wide) {
+    launch_wide_row<T, 1, EPI, true>(label, sd->p, Core::BM, sd->shape.groups * ceil_div(sd->shape.rows, Core::BM), st);
+    launch_wide_w<T>(label, sd->w, WNB, st);
+    sd = nullptr;
+  }
+  if (r && r->wide) {
+    launch_wide_row<T, 1, EPI, true>(label, *r, Core::BM, r_tiles, st);
+    launch_wide_w<T>(label, *rw, WNB, st);
+    r = nullptr;
   }
   DirectChoice rc, wc;
-  choose_direct(&rs, &ws, avail, &rc, &wc);
-  p.direct_kind = rc.kind; p.n_parts = rc.n_parts; p.k_part = rc.k_part;
-  p.part = (float*)parts; p.part_stride = rs.out_elems;
-  p.part_blocks = (int)row_block_count(rs.groups * ceil_div(rs.rows, Core::BM >> rc.kind), p.N, Core::BN);
-  w.n_parts = wc.n_parts; w.k_part = wc.k_part;
-  w.part = (float*)(parts + rc.part_bytes); w.part_stride = ws.out_elems;
-  const unsigned rb = (unsigned)p.part_blocks * rc.n_parts, wb = w_block_count<WCore>(w) * (unsigned)wc.n_parts;
-  if (rb + wb == 0) return;
-  // the longer blocks first
-  const unsigned first_w = wc.block_us > rc.block_us ? (wb + 7) / 8 * 8 : 0;
-  auto kern = row_w_gemm_kernel<CoreSet, EPI, WCore, WNB, false>;
+  RowGemm p = {};
+  WGemm w = {};
+  RowWOrder o = {};
+  if (sd) {
+    choose_direct(&sd->shape, &sd->w_shape, sd->avail, &rc, &wc);
+    p = sd->p;
+    set_choice(p, sd->shape, rc, sd->parts, Core::BM, Core::BN);
+    w = sd->w;
+    w.n_parts = wc.n_parts; w.k_part = wc.k_part;
+    w.part = (float*)(sd->parts + rc.part_bytes); w.part_stride = sd->w_shape.out_elems;
+    o.s_rows = p.part_blocks * rc.n_parts;
+    const int wb = (int)((w_block_count<WCore>(w) * (unsigned)wc.n_parts + 7) / 8 * 8);
+    if (wc.block_us > rc.block_us) o.first_sw = wb;  // the longer blocks first
+    else o.last_sw = wb;
+  }
+  if (r) o.r_rows = (int)row_block_count(r_tiles, r->N, Core::BN);
+  const unsigned blocks = (unsigned)(o.first_sw + o.s_rows + o.r_rows + o.last_sw) + (r ? w_block_count<WCore>(*rw) : 0);
+  if (blocks == 0) return;
+  auto kern = row_w_gemm_kernel<CoreSet, EPI, WCore, WNB>;
   static LdsAttr attr;
   constexpr int kLds = std::max(row_lds_bytes<CoreSet>(), WCore::LDS_BYTES);
   attr.ensure((const void*)kern, kLds);
   {
     ProfScope prof(label, st);
-    hipLaunchKernelGGL(kern, dim3(first_w ? first_w + rb : rb + wb), dim3(WCore::NT), kLds, st, p, w, (int)rb, (int)wb, (int)first_w);
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(WCore::NT), kLds, st, p, r ? *r : RowGemm{}, w, r ? *rw : WGemm{}, o);
   }
-  if (rc.n_parts > 1) launch_reduce<T, 1, EPI>(p.part, rc.n_parts, rs.out_elems, p.out, p.in, st);
-  if (wc.n_parts > 1) launch_reduce<T, WNB, EPI_STORE>(w.part, wc.n_parts, ws.out_elems, w.C, nullptr, st);
+  if (rc.n_parts > 1) launch_reduce<T, 1, EPI>(p.part, rc.n_parts, sd->shape.out_elems, p.out, p.in, st);
+  if (wc.n_parts > 1) launch_reduce<T, WNB, EPI_STORE>(w.part, wc.n_parts, sd->w_shape.out_elems, w.C, nullptr, st);
 }
 
 template <class Core>
@@ -664,11 +681,22 @@ static void launch_w_light(const char* label, const WGemm& a, const WGemm& b, in
 // The products without a plan: of a shared call, then of the router.
 template <int PATH, int NB>
 static DirectShape row_shape(int groups, int rows, int N, int K, int sums = 1) {
-  return {row_cost<PATH, NB>(), groups, rows, N, K, NB, sums, (int64_t)groups * rows * N};
+  return {row_cost<PATH, NB>(), groups, rows, N, K, NB, sums, (int64_t)groups * rows * N, 0.};
 }
 template <int PATH, int NB>
 static DirectShape w_shape(int groups, int M, int N, int rows) {
-  return {w_cost<PATH, NB>(), groups, M, N, rows, NB, 1, (int64_t)groups * M * N};
+  return {w_cost<PATH, NB>(), groups, M, N, rows, NB, 1, (int64_t)groups * M * N, 0.};
+}
+// The routed experts' share of a launch, in microseconds of one compute unit: n_rows rows over groups of unknown sizes.
+template <int PATH, int NB> static double routed_row_us(int n_groups, int n_rows, int N, int K, int sums = 1) {
+  constexpr TileCost c = row_cost<PATH, NB>();
+  const double steps = (double)sums * ceil_div(K, c.bk);
+  return ceil_div(N, c.bn) * ((double)(n_rows / c.bm) * (c.fixed[0] + steps * c.iter[0]) +
+                              std::min(n_groups, n_rows) * (c.fixed[2] + steps * c.iter[2]));
+}
+template <int PATH, int NB> static double routed_w_us(int n_rows, int M, int N) {
+  constexpr TileCost c = w_cost<PATH, NB>();
+  return (double)ceil_div(M, c.bm) * ceil_div(N, c.bn) * ceil_div(n_rows, c.bk) * c.iter[0];
 }
 template <int PATH> struct Products {
   int d, F, groups, rows;
@@ -707,48 +735,62 @@ struct FwdArgs {
   int src_div = 1, src_rows = 0;
 };
 
+// The forward pass of the routed experts (r), of the shared ones (s), or of both in common launches.
 template <int PATH>
-void expert_fwd_impl(const FwdArgs& a, hipStream_t st) {
-  const bool shared = a.offsets == nullptr;
-  const int max_tiles = max_row_tiles(a.n_groups, a.n_rows, Cores<PATH>::BM);
-  Plan pl = {};
-  if (!shared) {
-    pl = carve_plan(a.ws, a.n_groups, max_tiles);
-    launch_plan(a.offsets, a.n_groups, Cores<PATH>::BM, pl, nullptr, nullptr, st);
+void expert_fwd_impl(const FwdArgs* r, const FwdArgs* s, hipStream_t st) {
+  struct Gemms {
+    RowGemm gate_up, down;
+  };
+  auto fill = [](const FwdArgs& a, const Plan& pl) {
+    const bool shared = a.offsets == nullptr;
+    // F4: dual GEMM with the SwiGLU epilogue, or (two-matrix expert, Wu == NULL) one GEMM with the GELU epilogue
+    RowGemm p = {};
+    p.tiles = pl.tiles; p.n_tiles = pl.n_tiles; p.n_rows = a.n_rows; p.n_groups = a.n_groups;
+    p.N = a.F; p.K = a.d; p.n_pairs = 1; p.n_segs = 1;
+    p.A[0] = a.Xin; p.lda = a.d; p.a_seg = 0; p.a_rows_out = 0;
+    p.a_index = a.src_of; p.a_index_div = a.src_div; p.a_src_rows = a.src_rows;
+    p.B[0] = a.Wg; p.Bdual = a.Wu; p.ldb = a.F; p.b_group = (int64_t)a.d * a.F; p.b_seg = 0;
+    p.out[0] = a.G; p.out[1] = a.Wu ? a.U : a.H; p.out[2] = a.H; p.ldc = a.F; p.c_rows_out = 1;
+    // F5: Yout = H Wd (shared mode: summed over groups through K segments)
+    RowGemm q = {};
+    q.tiles = pl.tiles; q.n_tiles = pl.n_tiles;
+    q.n_rows = a.n_rows; q.n_groups = 1; q.N = a.d; q.K = a.F; q.n_pairs = 1;
+    q.A[0] = a.H; q.lda = a.F; q.a_rows_out = 1;
+    q.B[0] = a.Wd; q.ldb = a.d;
+    q.out[0] = a.Yout; q.ldc = a.d; q.c_rows_out = 0;
+    q.n_segs = shared ? a.n_groups : 1;
+    if (shared) { q.a_seg = (int64_t)a.n_rows * a.F; q.b_seg = (int64_t)a.F * a.d; }
+    else q.b_group = (int64_t)a.F * a.d;
+    p.wide = q.wide = wide_rows(std::max(a.d, a.F), sizeof(typename Cores<PATH>::template core<1, true, false>::T));
+    return Gemms{p, q};
+  };
+  const bool gated = (r ? r->Wu : s->Wu) != nullptr;  // (the same for both)
+  Gemms rg;
+  int max_tiles = 0;
+  if (r) {
+    max_tiles = max_row_tiles(r->n_groups, r->n_rows, Cores<PATH>::BM);
+    const Plan pl = carve_plan(r->ws, r->n_groups, max_tiles);
+    launch_plan(r->offsets, r->n_groups, Cores<PATH>::BM, pl, nullptr, nullptr, st);
+    rg = fill(*r, pl);
   }
-  // F4: dual GEMM with the SwiGLU epilogue, or (two-matrix expert, Wu == NULL) one GEMM with the GELU epilogue
-  RowGemm p = {};
-  p.tiles = pl.tiles; p.n_tiles = pl.n_tiles; p.n_rows = a.n_rows; p.n_groups = a.n_groups;
-  p.N = a.F; p.K = a.d; p.n_pairs = 1; p.n_segs = 1;
-  p.A[0] = a.Xin; p.lda = a.d; p.a_seg = 0; p.a_rows_out = 0;
-  p.a_index = a.src_of; p.a_index_div = a.src_div; p.a_src_rows = a.src_rows;
-  p.B[0] = a.Wg; p.Bdual = a.Wu; p.ldb = a.F; p.b_group = (int64_t)a.d * a.F; p.b_seg = 0;
-  p.out[0] = a.G; p.out[1] = a.Wu ? a.U : a.H; p.out[2] = a.H; p.ldc = a.F; p.c_rows_out = 1;
-  // F5: Yout = H Wd (shared mode: summed over groups through K segments)
-  RowGemm q = {};
-  q.n_rows = a.n_rows; q.n_groups = 1; q.N = a.d; q.K = a.F; q.n_pairs = 1;
-  q.A[0] = a.H; q.lda = a.F; q.a_rows_out = 1;
-  q.B[0] = a.Wd; q.ldb = a.d;
-  q.out[0] = a.Yout; q.ldc = a.d; q.c_rows_out = 0;
-  if (shared) {
-    q.tiles = nullptr; q.n_segs = a.n_groups; q.a_seg = (int64_t)a.n_rows * a.F; q.b_seg = (int64_t)a.F * a.d;
-    q.b_group = 0;
-  } else {
-    q.tiles = pl.tiles; q.n_tiles = pl.n_tiles; q.n_segs = 1; q.b_group = (int64_t)a.F * a.d;
+  Direct up = {}, down = {};
+  if (s) {
+    const Gemms sg = fill(*s, Plan{});
+    const Products<PATH> ps = {s->d, s->F, s->n_groups, s->n_rows};
+    up.p = sg.gate_up; up.shape = gated ? ps.template gate_up<2>() : ps.template gate_up<1>();
+    down.p = sg.down; down.shape = ps.down();
+    up.parts = down.parts = s->parts; up.avail = down.avail = s->part_avail;
+    if (r) {
+      up.shape.routed_us = gated ? routed_row_us<PATH, 2>(r->n_groups, r->n_rows, r->F, r->d) : routed_row_us<PATH, 1>(r->n_groups, r->n_rows, r->F, r->d);
+      down.shape.routed_us = routed_row_us<PATH, 1>(r->n_groups, r->n_rows, r->d, r->F);
+    }
   }
-  p.wide = q.wide = wide_rows(std::max(a.d, a.F), sizeof(typename Cores<PATH>::template core<1, true, false>::T));
+  const Direct *su = s ? &up : nullptr, *sd = s ? &down : nullptr;
   typedef RowCores<PATH, 1, false> Rows1;
   typedef RowCores<PATH, 2, false> Rows2;
-  if (shared) {
-    const Products<PATH> s = {a.d, a.F, a.n_groups, a.n_rows};
-    if (a.Wu) launch_row_direct<Rows2, 2, EPI_SWIGLU_FWD, false>("gemm_fwd_gate_up", p, s.template gate_up<2>(), a.parts, a.part_avail, st);
-    else launch_row_direct<Rows1, 1, EPI_GELU_FWD, false>("gemm_fwd_gate_up", p, s.template gate_up<1>(), a.parts, a.part_avail, st);
-    launch_row_direct<Rows1, 1, EPI_STORE, false>("gemm_fwd_down", q, s.down(), a.parts, a.part_avail, st);
-  } else {
-    if (a.Wu) launch_row<Rows2, 2, EPI_SWIGLU_FWD, false>("gemm_fwd_gate_up", p, max_tiles, st);
-    else launch_row<Rows1, 1, EPI_GELU_FWD, false>("gemm_fwd_gate_up", p, max_tiles, st);
-    launch_row<Rows1, 1, EPI_STORE, false>("gemm_fwd_down", q, max_tiles, st);
-  }
+  if (gated) launch_row<Rows2, 2, EPI_SWIGLU_FWD, false>("gemm_fwd_gate_up", su, r ? &rg.gate_up : nullptr, max_tiles, st);
+  else launch_row<Rows1, 1, EPI_GELU_FWD, false>("gemm_fwd_gate_up", su, r ? &rg.gate_up : nullptr, max_tiles, st);
+  launch_row<Rows1, 1, EPI_STORE, false>("gemm_fwd_down", sd, r ? &rg.down : nullptr, max_tiles, st);
 }
 
 struct BwdArgs {
@@ -769,67 +811,78 @@ struct BwdArgs {
   int src_div = 1, src_rows = 0;
 };
 
+// The backward pass of the routed experts (r), of the shared ones (s), or of both in common launches.  With both, either
+// all row counts are positive or the calls come one by one.
 template <int PATH>
-void expert_bwd_impl(const BwdArgs& a, hipStream_t st) {
+void expert_bwd_impl(const BwdArgs* r, const BwdArgs* s, hipStream_t st) {
   typedef Cores<PATH> C;
-  const bool shared = a.offsets == nullptr;
-  const int max_tiles = max_row_tiles(a.n_groups, a.n_rows, Cores<PATH>::BM);
-  char *dG = a.dG, *dU = a.dU;
-  Plan pl = {};
-  if (!shared || a.n_rows == 0) {
-    pl = carve_plan(a.ws, a.n_groups, max_tiles);
-    launch_plan(a.offsets, a.n_groups, Cores<PATH>::BM, pl, a.active_ids, a.n_active, st);
+  struct Gemms {
+    RowGemm dh, dx;
+    WGemm dwd, dwgu;
+  };
+  auto fill = [](const BwdArgs& a, const Plan& pl) {
+    const bool shared = a.offsets == nullptr;
+    // B2a: dH = dYin Wd^T, epilogue turns it into dG, dU
+    RowGemm p = {};
+    p.tiles = pl.tiles; p.n_tiles = pl.n_tiles; p.n_rows = a.n_rows; p.n_groups = a.n_groups;
+    p.N = a.F; p.K = a.d; p.n_pairs = 1; p.n_segs = 1;
+    p.A[0] = a.dYin; p.lda = a.d; p.a_rows_out = 0;
+    if (a.src_of) {
+      p.A[0] = a.dY; p.a_index = a.src_of; p.a_index_div = a.src_div; p.a_src_rows = a.src_rows; p.c_scale = a.row_w;
+    }
+    p.B[0] = a.Wd; p.ldb = a.d; p.b_group = (int64_t)a.F * a.d;
+    p.in[0] = a.G; p.in[1] = a.U; p.out[0] = a.dG; p.out[1] = a.dU; p.ldc = a.F; p.c_rows_out = 1;
+    // B2b: dXin = dG Wg^T + dU Wu^T (two-matrix expert: dG is dZ, there is no dU)
+    RowGemm q = {};
+    q.tiles = pl.tiles; q.n_tiles = pl.n_tiles;
+    q.n_rows = a.n_rows; q.n_groups = 1; q.N = a.d; q.K = a.F; q.n_pairs = a.Wu ? 2 : 1;
+    q.A[0] = a.dG; q.A[1] = a.dU; q.lda = a.F; q.a_rows_out = 1;
+    q.B[0] = a.Wg; q.B[1] = a.Wu; q.ldb = a.F;
+    q.out[0] = a.dXin; q.ldc = a.d; q.c_rows_out = 0;
+    q.n_segs = shared ? a.n_groups : 1;
+    if (shared) { q.a_seg = (int64_t)a.n_rows * a.F; q.b_seg = (int64_t)a.d * a.F; }
+    else q.b_group = (int64_t)a.d * a.F;
+    // B3: weight gradients, compacted to active groups, largest group first
+    WGemm w = {};
+    w.ginfo = pl.ginfo; w.n_rows = a.n_rows; w.n_groups = a.n_groups;
+    w.M = a.F; w.N = a.d;
+    w.A = a.H; w.lda = a.F; w.a_per_group = shared;
+    w.B[0] = a.dYin; w.ldb = a.d; w.b_per_group = 0;
+    w.C[0] = a.dWd; w.c_slot = (int64_t)a.F * a.d;
+    WGemm v = {};
+    v.ginfo = pl.ginfo; v.n_rows = a.n_rows; v.n_groups = a.n_groups;
+    v.M = a.d; v.N = a.F;
+    v.A = a.Xin; v.lda = a.d; v.a_per_group = 0;
+    v.B[0] = a.dG; v.B[1] = a.dU; v.ldb = a.F; v.b_per_group = shared;
+    v.C[0] = a.dWg; v.C[1] = a.dWu; v.c_slot = (int64_t)a.d * a.F;
+    w.k_min = v.k_min = 1;
+    w.k_max = v.k_max = 0x7fffffff;
+    p.wide = q.wide = w.wide = v.wide = wide_rows(std::max(a.d, a.F), sizeof(typename C::template core<1, true, false>::T));
+    return Gemms{p, q, w, v};
+  };
+  const bool gated = (r ? r->Wu : s->Wu) != nullptr;  // (the same for both)
+  Gemms rg;
+  int max_tiles = 0;
+  if (r) {
+    max_tiles = max_row_tiles(r->n_groups, r->n_rows, C::BM);
+    const Plan pl = carve_plan(r->ws, r->n_groups, max_tiles);
+    launch_plan(r->offsets, r->n_groups, C::BM, pl, r->active_ids, r->n_active, st);
+    if (r->n_rows == 0) return;  // no group is active
+    rg = fill(*r, pl);
   }
-  if (a.n_rows == 0) return;  // no group is active
-  // B2a: dH = dYin Wd^T, epilogue turns it into dG, dU
-  RowGemm p = {};
-  p.tiles = pl.tiles; p.n_tiles = pl.n_tiles; p.n_rows = a.n_rows; p.n_groups = a.n_groups;
-  p.N = a.F; p.K = a.d; p.n_pairs = 1; p.n_segs = 1;
-  p.A[0] = a.dYin; p.lda = a.d; p.a_rows_out = 0;
-  if (a.src_of) {
-    p.A[0] = a.dY; p.a_index = a.src_of; p.a_index_div = a.src_div; p.a_src_rows = a.src_rows; p.c_scale = a.row_w;
+  if (s && s->n_rows == 0) {
+    launch_plan(nullptr, s->n_groups, C::BM, carve_plan(s->ws, s->n_groups, max_row_tiles(s->n_groups, 0, C::BM)), s->active_ids, s->n_active, st);
+    return;
   }
-  p.B[0] = a.Wd; p.ldb = a.d; p.b_group = (int64_t)a.F * a.d;
-  p.in[0] = a.G; p.in[1] = a.U; p.out[0] = dG; p.out[1] = dU; p.ldc = a.F; p.c_rows_out = 1;
-  const bool gated = a.Wu != nullptr;  // two-matrix expert otherwise: dG is dZ, no dU
-  // B2b: dXin = dG Wg^T + dU Wu^T
-  RowGemm q = {};
-  q.n_rows = a.n_rows; q.n_groups = 1; q.N = a.d; q.K = a.F; q.n_pairs = gated ? 2 : 1;
-  q.A[0] = dG; q.A[1] = dU; q.lda = a.F; q.a_rows_out = 1;
-  q.B[0] = a.Wg; q.B[1] = a.Wu; q.ldb = a.F;
-  q.out[0] = a.dXin; q.ldc = a.d; q.c_rows_out = 0;
-  if (shared) {
-    q.tiles = nullptr; q.n_segs = a.n_groups; q.a_seg = (int64_t)a.n_rows * a.F; q.b_seg = (int64_t)a.d * a.F;
-    q.b_group = 0;
-  } else {
-    q.tiles = pl.tiles; q.n_tiles = pl.n_tiles; q.n_segs = 1; q.b_group = (int64_t)a.d * a.F;
-  }
-  // B3: weight gradients, compacted to active groups, largest group first
-  WGemm w = {};
-  w.ginfo = pl.ginfo; w.n_rows = a.n_rows; w.n_groups = a.n_groups;
-  w.M = a.F; w.N = a.d;
-  w.A = a.H; w.lda = a.F; w.a_per_group = shared;
-  w.B[0] = a.dYin; w.ldb = a.d; w.b_per_group = 0;
-  w.C[0] = a.dWd; w.c_slot = (int64_t)a.F * a.d;
-  WGemm v = {};
-  v.ginfo = pl.ginfo; v.n_rows = a.n_rows; v.n_groups = a.n_groups;
-  v.M = a.d; v.N = a.F;
-  v.A = a.Xin; v.lda = a.d; v.a_per_group = 0;
-  v.B[0] = dG; v.B[1] = dU; v.ldb = a.F; v.b_per_group = shared;
-  v.C[0] = a.dWg; v.C[1] = a.dWu; v.c_slot = (int64_t)a.d * a.F;
-  w.k_min = v.k_min = 1;
-  w.k_max = v.k_max = 0x7fffffff;
-  p.wide = q.wide = w.wide = v.wide = wide_rows(std::max(a.d, a.F), sizeof(typename C::template core<1, true, false>::T));
-  WGemm wl_ = w, vl_ = v;  // groups with few rows
+  // groups with few rows are bound by writing their gradient, not by MFMA work: they go to a
+  // kernel that keeps several blocks per CU in flight
+  WGemm wl_ = rg.dwd, vl_ = rg.dwgu;
   bool light = false;
   if constexpr (PATH != PATH_F32) {
-    // groups with few rows are bound by writing their gradient, not by MFMA work: they go to a
-    // kernel that keeps several blocks per CU in flight
-    if (!shared && !w.wide) {
+    if (r && !rg.dwd.wide) {
       light = true;
       const int light_rows = MOE_KNOB("MOE_LIGHT_ROWS", kLightGroupRows);
-      w.k_min = v.k_min = light_rows + 1;
-      wl_.k_min = vl_.k_min = 1;
+      rg.dwd.k_min = rg.dwgu.k_min = light_rows + 1;
       wl_.k_max = vl_.k_max = light_rows;
       // column tiles per block: at most kLightReps, and the same for every block of a row of tiles (11
       // column tiles go 6 + 5, not 8 + 3: consecutive blocks run on different XCDs, and unequal blocks
@@ -843,29 +896,34 @@ void expert_bwd_impl(const BwdArgs& a, hipStream_t st) {
       vl_.n_reps = even_reps(vl_.N);
     }
   }
+  Direct dh = {}, dx = {};
+  if (s) {
+    const Gemms sg = fill(*s, Plan{});
+    const Products<PATH> ps = {s->d, s->F, s->n_groups, s->n_rows};
+    dh.p = sg.dh; dh.shape = ps.dh(); dh.w = sg.dwd; dh.w_shape = ps.dwd();
+    dh.w.active_ids = s->active_ids;
+    dh.w.n_active = s->n_active;
+    dx.p = sg.dx; dx.shape = gated ? ps.template dx<2>() : ps.template dx<1>();
+    dx.w = sg.dwgu; dx.w_shape = gated ? ps.template dwgu<2>() : ps.template dwgu<1>();
+    dh.parts = dx.parts = s->parts; dh.avail = dx.avail = s->part_avail;
+    if (r) {
+      dh.shape.routed_us = routed_row_us<PATH, 1>(r->n_groups, r->n_rows, r->F, r->d) + routed_w_us<PATH, 1>(r->n_rows, r->F, r->d);
+      dx.shape.routed_us = routed_row_us<PATH, 1>(r->n_groups, r->n_rows, r->d, r->F, gated ? 2 : 1) +
+                           (gated ? routed_w_us<PATH, 2>(r->n_rows, r->d, r->F) : routed_w_us<PATH, 1>(r->n_rows, r->d, r->F));
+    }
+  }
+  const Direct *sh = s ? &dh : nullptr, *sx = s ? &dx : nullptr;
+  const RowGemm *rh = r ? &rg.dh : nullptr, *rx = r ? &rg.dx : nullptr;
   // dH with dWd (which needs nothing that dH produces), then dX with dWg and dWu
   typedef RowCores<PATH, 1, true> Rows;
   typedef typename C::template core<1, false, false> W1;
   typedef typename C::template core<2, false, false> W2;
-  if (shared) {
-    const Products<PATH> s = {a.d, a.F, a.n_groups, a.n_rows};
-    w.active_ids = a.active_ids;
-    w.n_active = a.n_active;
-    if (gated) {
-      launch_row_w_direct<Rows, EPI_SWIGLU_BWD, W1, 1>("gemm_bwd_dh_dwd", p, s.dh(), w, s.dwd(), a.parts, a.part_avail, st);
-      launch_row_w_direct<Rows, EPI_STORE, W2, 2>("gemm_bwd_dx_dwgu", q, s.template dx<2>(), v, s.template dwgu<2>(), a.parts, a.part_avail, st);
-    } else {
-      launch_row_w_direct<Rows, EPI_GELU_BWD, W1, 1>("gemm_bwd_dh_dwd", p, s.dh(), w, s.dwd(), a.parts, a.part_avail, st);
-      launch_row_w_direct<Rows, EPI_STORE, W1, 1>("gemm_bwd_dx_dwgu", q, s.template dx<1>(), v, s.template dwgu<1>(), a.parts, a.part_avail, st);
-    }
-    return;
-  }
   if (gated) {
-    launch_row_w<Rows, EPI_SWIGLU_BWD, W1, 1>("gemm_bwd_dh_dwd", p, max_tiles, w, st);
-    launch_row_w<Rows, EPI_STORE, W2, 2>("gemm_bwd_dx_dwgu", q, max_tiles, v, st);
+    launch_row_w<Rows, EPI_SWIGLU_BWD, W1, 1>("gemm_bwd_dh_dwd", sh, rh, max_tiles, &rg.dwd, st);
+    launch_row_w<Rows, EPI_STORE, W2, 2>("gemm_bwd_dx_dwgu", sx, rx, max_tiles, &rg.dwgu, st);
   } else {
-    launch_row_w<Rows, EPI_GELU_BWD, W1, 1>("gemm_bwd_dh_dwd", p, max_tiles, w, st);
-    launch_row_w<Rows, EPI_STORE, W1, 1>("gemm_bwd_dx_dwgu", q, max_tiles, v, st);
+    launch_row_w<Rows, EPI_GELU_BWD, W1, 1>("gemm_bwd_dh_dwd", sh, rh, max_tiles, &rg.dwd, st);
+    launch_row_w<Rows, EPI_STORE, W1, 1>("gemm_bwd_dx_dwgu", sx, rx, max_tiles, &rg.dwgu, st);
   }
   if constexpr (PATH != PATH_F32) {
     if (light) launch_w_light<typename C::template core_light<1>>("gemm_bwd_dw_light", wl_, vl_, gated ? 2 : 1, st);
@@ -933,7 +991,9 @@ void router_fwd_impl(const moe_shape_t* s, const void* X, const void* Wr, float*
   p.B[0] = B; p.ldb = Ep;
   p.out[0] = out; p.ldc = Ep;
   p.wide = wide_rows(std::max(s->d, Ep), sizeof(T));
-  launch_row_direct<RowCores<PATH, 1, false>, 1, EPI_STORE_F32, false>("gemm_router_fwd", p, router_fwd_shape<PATH>(s), parts, part_avail, st);
+  Direct all = {};
+  all.p = p; all.shape = router_fwd_shape<PATH>(s); all.parts = parts; all.avail = part_avail;
+  launch_row<RowCores<PATH, 1, false>, 1, EPI_STORE_F32, false>("gemm_router_fwd", &all, nullptr, 0, st);
   if (padded) recolumn<float, float>("router_pad", out, logits, s->T, Ep, s->E, st);
 }
 
@@ -975,9 +1035,9 @@ void router_bwd_impl(const moe_shape_t* s, const void* X, const void* Wr, const 
   p.wide = w.wide = wide_rows(std::max(s->d, Ep), sizeof(T));
   typedef RowCores<PATH, 1, true> Rows;
   typedef typename C::template core<1, false, false> W1;
-  const DirectShape rs = router_dx_shape<PATH>(s), wsh = router_dw_shape<PATH>(s);
-  if (accumulate) launch_row_w_direct<Rows, EPI_ADD, W1, 1>("gemm_router_bwd", p, rs, w, wsh, parts, part_avail, st);
-  else launch_row_w_direct<Rows, EPI_STORE, W1, 1>("gemm_router_bwd", p, rs, w, wsh, parts, part_avail, st);
+  const Direct all = {p, router_dx_shape<PATH>(s), w, router_dw_shape<PATH>(s), parts, part_avail};
+  if (accumulate) launch_row_w<Rows, EPI_ADD, W1, 1>("gemm_router_bwd", &all, nullptr, 0, nullptr, st);
+  else launch_row_w<Rows, EPI_STORE, W1, 1>("gemm_router_bwd", &all, nullptr, 0, nullptr, st);
   if (padded) recolumn<T, T>("router_pad", dWrP, dWr, s->d, Ep, s->E, st);
 }
 

@@ -1,0 +1,107 @@
+"""moe_experts_fwd / _bwd (routed and shared experts in common launches) against the calls of either set alone."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+# T, d, E, k, d_ff, shared experts, their width, routed activation, shared activation, rows read in place
+CASES = [
+    (1, 64, 4, 2, 64, 1, 64, "swiglu", "swiglu", False),          # one token
+    (16, 256, 12, 4, 192, 4, 192, "swiglu", "swiglu", True),      # a few rows an expert, long shared sums
+    (257, 128, 5, 2, 200, 2, 128, "swiglu", "swiglu", False),     # only the routed width has a K tail
+    (300, 192, 6, 3, 128, 1, 72, "swiglu", "swiglu", True),       # only the shared width has one
+    (700, 136, 6, 2, 264, 3, 328, "gelu", "gelu", False),         # ragged everywhere, two-matrix experts
+    (1500, 512, 3, 1, 320, 1, 640, "swiglu", "swiglu", False),    # tall tiles on both sides
+    (130, 64, 8, 2, 64, 2, 128, "swiglu", "gelu", False),         # two activations: no common launch
+    (130, 64, 8, 2, 64, 2, 128, "gelu", "swiglu", False),
+    (0, 64, 4, 2, 64, 2, 64, "swiglu", "swiglu", False),          # no tokens
+]
+
+
+@pytest.mark.parametrize("T,d,E,k,F,S,Fs,act,act_s,gather", CASES)
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_both_sets_in_one_call(dtype, T, d, E, k, F, S, Fs, act, act_s, gather):
+    """Routed results are the same bits; shared ones differ by the order of fp32 sums (a sum over at most 2 S Fs
+    values) and by the rounding of the output to its type."""
+    import paper_2502_02581_amd as moe
+
+    shape, sshape = moe.MoEShape(T, d, E, k, F, dtype), moe.MoEShape(T, d, E, k, Fs, dtype)
+    dt, dev, A = shape.torch_dtype, "cuda", T * k
+    g = torch.Generator().manual_seed(T + d + F)
+    rnd = lambda *s: (torch.randn(*s, generator=g) * d ** -0.5).to(dt).to(dev)
+    X, dY = rnd(T, d), rnd(T, d)
+    Wg, Wu, Wd = rnd(E, d, F), rnd(E, d, F) if act == "swiglu" else None, rnd(E, F, d)
+    Wsg, Wsu, Wsd = rnd(S, d, Fs), rnd(S, d, Fs) if act_s == "swiglu" else None, rnd(S, Fs, d)
+    i32 = lambda *s: torch.full(s, -7, dtype=torch.int32, device=dev)
+    idx, w = i32(T, k), torch.empty(T, k, device=dev)
+    counts, off, row_of, src_of, Xp, dYp, dw = i32(E), i32(E + 1), i32(A), i32(A), rnd(A, d), rnd(A, d), torch.empty(T, k, device=dev)
+    logits = torch.randn(T, E, generator=g).to(dev)
+    size = max(moe.moe_dispatch_workspace_bytes(shape), moe.moe_expert_fwd_workspace_bytes(shape, E, A, False),
+               moe.moe_expert_bwd_workspace_bytes(shape, E, A, False))
+    size_s = max(moe.moe_expert_fwd_workspace_bytes(sshape, S, T, True), moe.moe_expert_bwd_workspace_bytes(sshape, S, T, True))
+    ws, ws_s = (torch.empty(n, dtype=torch.uint8, device=dev) for n in (size, size_s))
+    moe.moe_route(shape, logits, idx, w)
+    moe.moe_dispatch(shape, X, idx, counts, off, row_of, src_of, Xp, ws)
+
+    def bufs():
+        new = lambda *s: torch.full(s, float("nan"), dtype=dt, device=dev)
+        r = dict(G=new(A, F), U=new(A, F), H=new(A, F), Yout=new(A, d), dXin=new(A, d), active_ids=i32(E), n_active=i32(1),
+                 dWg_c=new(E, d, F), dWu_c=new(E, d, F), dWd_c=new(E, F, d))
+        s = dict(G=new(S, T, Fs), U=new(S, T, Fs), H=new(S, T, Fs), Yout=new(T, d), dXin=new(T, d), active_ids=i32(S),
+                 n_active=i32(1), dWg_c=new(S, d, Fs), dWu_c=new(S, d, Fs), dWd_c=new(S, Fs, d))
+        return r, s
+
+    (r, s), (r2, s2) = bufs(), bufs()
+    gr = ["dXin", "active_ids", "n_active", "dWg_c", "dWu_c", "dWd_c"]
+    if gather:
+        moe.moe_expert_fwd_gather(shape, off, src_of, X, Wg, Wu, Wd, r["G"], r["U"], r["H"], r["Yout"], ws)
+    else:
+        moe.moe_expert_fwd(shape, E, off, A, Xp, Wg, Wu, Wd, r["G"], r["U"], r["H"], r["Yout"], ws)
+    moe.moe_expert_fwd(sshape, S, None, T, X, Wsg, Wsu, Wsd, s["G"], s["U"], s["H"], s["Yout"], ws_s)
+    moe.moe_combine_bwd(shape, dY, r["Yout"], row_of, w, dYp, dw)
+    if gather:
+        moe.moe_expert_bwd_gather(shape, off, src_of, Xp, Wg, Wu, Wd, r["G"], r["U"], r["H"], dY, w, dYp, *[r[n] for n in gr], ws)
+    else:
+        moe.moe_expert_bwd(shape, E, off, A, Xp, Wg, Wu, Wd, r["G"], r["U"], r["H"], dYp, *[r[n] for n in gr], ws)
+    moe.moe_expert_bwd(sshape, S, None, T, X, Wsg, Wsu, Wsd, s["G"], s["U"], s["H"], dY, *[s[n] for n in gr], ws_s)
+
+    fwd = ("G", "U", "H", "Yout")
+    base = dict(d_ff=F, n_groups=E, n_rows=A, offsets=off, Wg=Wg, Wu=Wu, Wd=Wd, ws=ws, ws_bytes=size)
+    base_s = dict(d_ff=Fs, n_groups=S, n_rows=T, Xin=X, Wg=Wsg, Wu=Wsu, Wd=Wsd, ws=ws_s, ws_bytes=size_s)
+    ws.fill_(255), ws_s.fill_(255)
+    moe.moe_experts_fwd(shape, dict(base, Xin=X if gather else Xp, src_of=src_of if gather else None, **{n: r2[n] for n in fwd}),
+                        dict(base_s, **{n: s2[n] for n in fwd}))
+    ws.fill_(255), ws_s.fill_(255)
+    in_place = dict(src_of=src_of, dY=dY, row_w=w) if gather else {}
+    moe.moe_experts_bwd(shape, dict(base, Xin=Xp, dYin=dYp, **in_place, **{n: r2[n] for n in gr + ["G", "U", "H"]}),
+                        dict(base_s, dYin=dY, **{n: s2[n] for n in gr + ["G", "U", "H"]}))
+    torch.cuda.synchronize()
+    for n in r:
+        assert torch.equal(r[n].view(torch.uint8), r2[n].view(torch.uint8)), n
+    for n in s:
+        a, b = s[n], s2[n]
+        if T == 0 or n in ("active_ids", "n_active") or (act_s == "gelu" and n in ("U", "dWu_c")):
+            assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), n
+        else:
+            # fp32: sqrt(2 S Fs) roundings of 2^-24 at most some 3e-6; bf16: half a unit in the last place of both, 2 * 2^-9,
+            # for each of the two roundings on the way to an output
+            err = float((a.double() - b.double()).norm() / a.double().norm())
+            assert err <= (1e-5 if dtype == "f32" else 8e-3), (n, err)
+
+
+def test_sets_are_checked():
+    import paper_2502_02581_amd as moe
+
+    shape = moe.MoEShape(16, 64, 4, 2, 64, "bf16")
+    t = torch.zeros(1 << 20, dtype=torch.uint8, device="cuda")
+    off = torch.zeros(5, dtype=torch.int32, device="cuda")
+    b = t.view(torch.bfloat16)
+    names = ("Xin", "Wg", "Wu", "Wd", "G", "U", "H", "Yout")
+    good = dict({n: b for n in names}, d_ff=64, ws=t, ws_bytes=t.numel())
+    routed, shared = dict(good, n_groups=4, n_rows=32, offsets=off), dict(good, n_groups=1, n_rows=16)
+    for r, s, msg in [(dict(routed, offsets=None), shared, "null"), (routed, dict(shared, offsets=off), "null"),
+                      (dict(routed, ws_bytes=16), shared, "workspace"), (routed, dict(shared, ws_bytes=16), "workspace"),
+                      (routed, dict(shared, Xin=b[1:]), "aligned"), (routed, dict(shared, d_ff=60), "multiples of 8"),
+                      (dict(routed, src_of=off, n_rows=30), shared, "in place"), (routed, dict(shared, Yout=None), "null")]:
+        with pytest.raises(moe.MoEError, match=msg):
+            moe.moe_experts_fwd(shape, r, s)
