@@ -1,4 +1,4 @@
-// Tile cores of the grouped GEMMs for gfx950: matrix-core tiles (bf16: v_mfma_f32_32x32x16_bf16, fp32:
+// Tile cores of the grouped GEMMs for gfx950: matrix-core tiles (bf16: v_mfma_f32_16x16x32_bf16, fp32:
 // v_mfma_f32_32x32x2_f32) with operands staged through LDS.
 //
 // The core computes, for one block, acc[nb][..] = sum over iterations of A_tile * B_tile(nb), and turns
@@ -10,6 +10,9 @@
 // a down projection, the two products of an input gradient); a segment functor supplies where the
 // tiles of a segment start, and the core steps along K from there themselves.
 #pragma once
+
+#include <algorithm>
+#include <utility>
 
 #include "moe_common.h"
 #include "trace.h"
@@ -50,6 +53,17 @@ typedef __attribute__((ext_vector_type(8))) short short8_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
+// f(integral_constant<int, 0>), ... f(integral_constant<int, N - 1>): the K loops are written out by it, so that every
+// position in them is a constant (an unroll pragma gives up on loops whose bounds depend on an outer one's counter)
+template <class F, int... I>
+__device__ __forceinline__ void static_for_impl(F& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>()), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F f) {
+  static_for_impl(f, std::make_integer_sequence<int, (N > 0 ? N : 0)>());
+}
+
 // ------------------------------------------------------------------ MFMA core, LDS DMA loads
 // Tiles travel HBM/L2 -> LDS directly (buffer_load_dwordx4 ... lds),
 // so no registers stage them.  Lane l of a wave-wide load lands at lds_base + 16*l, which fixes
@@ -59,17 +73,24 @@ typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 // rows are K values, of the K tail.  A K tail inside the rows of a K-contiguous operand is masked with
 // KTAIL: the lanes whose piece lies at or beyond K fetch from an offset no descriptor reaches.
 //
-// Types: bf16 (v_mfma_f32_32x32x16_bf16) and fp32 (v_mfma_f32_32x32x2_f32: fp32 products and sums).  The
-// geometry is the same in bytes: a tile row is 128 bytes of K (64 bf16 or 32 fp32 values), a k-step is
-// 32 bytes of them, and a lane's fragment of a k-step is 16 bytes.  In fp32 the four values of a
-// fragment feed four MFMAs, MFMA j taking value j of both half-waves (k = 8 ks + j and 8 ks + 4 + j).
+// Types: bf16 (v_mfma_f32_16x16x32_bf16) and fp32 (v_mfma_f32_32x32x2_f32: fp32 products and sums).  A tile row
+// is 128 bytes of K (64 bf16 or 32 fp32 values) and a lane's fragment of a k-step is 16 bytes.
+// bf16: a k-step is 64 bytes of K, a fragment 16 rows of them.  The 32x32x16 instruction does the same work per cycle
+// from the same fragment bytes, but it reads and writes every accumulator twice as often, and the chip's clock falls further under it:
+// register-resident loops over normally distributed values sustain 1.73 PFLOP/s with it and 1.99 with 16x16x32.
+// That alone changed nothing while the K loop was bound by issue (408 instructions per 128 MFMAs); with 225 (steps of
+// three additions, M0 written by the addition that forms the address, the MFMA as its wait state, LDS addresses carried in bytes)
+// whole training steps gain: T = 8192, d = 4096, 16 experts of 6400 7439 -> 7043 us, T = 8192, d = 7168, 256 experts 22830 -> 21837,
+// fp32 (32x32x2, the same loop) T = 2048, d = 1024 2095 -> 1985.
+// fp32: a k-step is 32 bytes of K, a fragment 32 rows; its four values feed four MFMAs, MFMA j taking value j of both
+// half-waves (k = 8 ks + j and 8 ks + 4 + j).
 //
 // LDS layouts, BK = 128 bytes of K, no padding:
 //  K-contiguous operand [rows][BK]: 16-byte piece c of a row sits at position c ^ ((row/2)%8), so
 //    that the 16 rows one phase of a 16-byte-per-lane read touches cover all banks once.
 //  row-contiguous operand [BK][ROWS]: bf16: piece c (8 columns) of k-row k sits at position
-//    c ^ (4*(k%4)), which spreads the four k rows of a transposing read over all banks (tiles of 64 columns,
-//    whose rows are half as long: c ^ (4*((k/2)%2))).  fp32: the
+//    c ^ (4*(k%4)) ^ (2*((k/8)%2)): the 32 lanes of two 16-lane groups of a transposing read, which take 16 columns of
+//    four k rows and of the four k rows 8 further on, touch all banks once.  fp32: the
 //    fragment is read value by value; piece c (4 columns) sits at c ^ (8*((k/4)%2)), so that the two
 //    half-waves, four k rows apart, use different banks.
 template <typename T_, int BM_, int BN_, int NB, bool A_KC, bool B_KC, int WM_ = 2, int WN_ = 2, int DEPTH = 1,
@@ -79,12 +100,15 @@ struct MfmaDmaCore {
   static constexpr int ES = sizeof(T);
   static constexpr int PE = 16 / ES;  // elements per 16-byte piece
   static constexpr int BM = BM_, BN = BN_, BK = 8 * PE;
-  static constexpr int KS = 4;        // MFMA k-steps per tile slot
+  static constexpr int MT = ES == 4 ? 32 : 16;  // rows and columns of an accumulator tile
+  static constexpr int KS = ES == 4 ? 4 : 2;    // MFMA k-steps per tile slot
   static constexpr int SUB = ES == 4 ? 4 : 1;  // MFMAs per accumulator tile and k-step
   typedef std::conditional_t<ES == 4, f32x4_t, bf16x8_t> frag_t;
+  typedef std::conditional_t<ES == 4, f32x16_t, f32x4_t> acc_t;
+  static constexpr int AR = MT * MT / 64;       // registers of an accumulator tile
   static constexpr int WM = WM_, WN = WN_;
   static constexpr int NW = WM * WN, NT = 64 * NW;  // wavefronts and threads per block
-  static constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
+  static constexpr int TM = BM / WM / MT, TN = BN / WN / MT;
   static constexpr int A_ELEMS = BM * BK, B_ELEMS = BN * BK;
   // Software pipeline of the K loop, by DEPTH:
   //  1  (tall tiles, bound by the matrix pipe): a ring of three A tiles and a ring of two B tile
@@ -105,7 +129,7 @@ struct MfmaDmaCore {
   static constexpr int TILE_BYTES = (A_SLOTS * A_ELEMS + B_SLOTS * B_SET_ELEMS) * ES;
   static constexpr int LDS_BYTES = TILE_BYTES;
   // blocks per CU the register allocation aims at (LDS allows as many)
-  static constexpr int BLOCKS_PER_CU = LDS_BYTES > 80 * 1024 ? 1 : NB * TM * TN <= 4 ? 2 : 1;
+  static constexpr int BLOCKS_PER_CU = LDS_BYTES > 80 * 1024 ? 1 : NB * TM * TN * AR <= 64 ? 2 : 1;
   static constexpr int A_NI = BM / (8 * NW), B_NI = BN / (8 * NW);  // wave-wide loads per wave and tile
   static constexpr int PR_KC = 8;  // 16-byte pieces per row of a K-contiguous tile
   static_assert(NW == 4 || NW == 8, "four or eight wavefronts per block");
@@ -114,20 +138,18 @@ struct MfmaDmaCore {
   static_assert(BM % (32 * WM) == 0 && BN % (32 * WN) == 0, "wave tile must be a multiple of 32");
   static_assert((A_KC || BM * ES % 128 == 0) && (B_KC || BN * ES % 128 == 0),
                 "swizzle of row-contiguous tiles needs >= 8 pieces per k row");
-  static_assert(ES == 2 || ((A_KC || BM <= 128) && (B_KC || BN <= 128)),
-                "fp32: the loads of a wave are a multiple of 8 k rows apart, so the swizzle is the same for all");
+  static_assert(ES == 4 || ((A_KC || BM >= 128) && (B_KC || BN >= 128)), "bf16: 16 pieces per k row");
   static_assert(LDS_BYTES <= 160 * 1024, "LDS budget of a gfx950 CU");
   typedef __attribute__((address_space(3))) void* lds_vptr;
 
-  // Byte offset (from the tile origin in memory) of the piece that lane `lane` of wave `wave`
-  // fetches with its FIRST load.  The j-th load of the same lane is j * load_stride() rows further
-  // on (the swizzle terms do not depend on j); run() keeps one offset register per load, so that
+  // Byte offset (from the tile origin in memory) of the piece that lane `lane` fetches into the 1 KB piece `wave` of
+  // the LDS tile (the j-th load of a wave fills piece wave + j * NW).  run() keeps one offset register per load, so that
   // the K loop spends no instructions on addresses and the whole offset stays inside the
   // descriptor's bounds check.
   __device__ static __forceinline__ int kc_swizzle(int row) { return ((row * PR_KC) >> 4) & (PR_KC - 1); }
   template <int ROWS>
   __device__ static __forceinline__ int rc_swizzle(int k) {
-    return ES == 4 ? 8 * ((k >> 2) & 1) : ROWS >= 128 ? 4 * (k & 3) : 4 * ((k >> 1) & 1);
+    return ES == 4 ? 8 * ((k >> 2) & 1) : 4 * (k & 3) ^ 2 * ((k >> 3) & 1);
   }
   template <int ROWS, bool KC>
   __device__ static __forceinline__ uint32_t piece_offset(int wave, int lane, uint32_t ld) {
@@ -149,10 +171,6 @@ struct MfmaDmaCore {
     const int q = wave * 64 + lane;
     return ((q % PR_KC) ^ kc_swizzle(q / PR_KC)) * PE;
   }
-  // rows of the memory operand (K-contiguous: tile rows; row-contiguous: k rows) between two
-  // consecutive loads of a wave: NW waves x 1 KB of LDS tile per round
-  template <int ROWS, bool KC>
-  __device__ static constexpr int load_stride() { return KC ? 8 * NW : 64 * PE * NW / ROWS; }
 
   // One wave-wide 16-byte-per-lane load straight into LDS: the n-th 1 KB piece of this wave's share
   // of a tile.  Written as inline assembly so that the compiler does not serialise it against the
@@ -175,53 +193,63 @@ struct MfmaDmaCore {
                  : "memory");
   }
 
-  // ---- LDS -> MFMA fragment: lane l holds k = 16*ks + 8*(l/32) + 0..7 of row (row0 + l%32).
+  // ---- LDS -> MFMA fragment: lane l holds k = 32*ks + 8*(l/16) + 0..7 of row (row0 + l%16)
+  // (fp32: k = 8*ks + 4*(l/32) + 0..3 of row (row0 + l%32)).
   // All lane-dependent address arithmetic is done once (lane_offsets); inside the K loop a
   // fragment address is a per-lane base plus a compile-time constant, which the LDS instructions
   // carry in their offset field.
-  //   K-contiguous tile:   off[ks] for the wave's first 32 rows; 32 more rows = +32*BK elements
+  //   K-contiguous tile:   off[ks] for the wave's first MT rows; MT more rows = +MT*BK elements
   //                        (the swizzle repeats every 16 rows)
-  //   row-contiguous tile: off[t] for the t-th group of 32 columns at k-step 0;
-  //                        k-step ks = +16*ks*ROWS elements, second half of the 8 k = +4*ROWS
+  //   row-contiguous tile: off[t] for the t-th group of MT columns at k-step 0;
+  //                        k-step ks = +32*ks*ROWS elements, second half of the 8 k = +4*ROWS
   //                        (fp32: k-step ks = +8*ks*ROWS, value j = +j*ROWS)
+  static constexpr int kOffs = 8;
   template <int ROWS, bool KC, int NTILE>
-  __device__ static __forceinline__ void lane_offsets(int w0, int lane, int (&off)[4]) {
+  __device__ static __forceinline__ void lane_offsets(int w0, int lane, uint32_t (&off)[kOffs]) {
     if (KC) {
-      const int row = w0 + (lane & 31);
+      const int row = w0 + (lane & (MT - 1));
 #pragma unroll
-      for (int ks = 0; ks < KS; ks++) off[ks] = row * BK + ((ks * 2 + (lane >> 5)) ^ kc_swizzle(row)) * PE;
+      for (int ks = 0; ks < KS; ks++) off[ks] = (row * BK + ((ks * (64 / MT) + lane / MT) ^ kc_swizzle(row)) * PE) * ES;
     } else if (ES == 4) {
       const int h = lane >> 5;  // half-wave: k values 8 ks + 4 h + 0..3
 #pragma unroll
-      for (int t = 0; t < 4; t++) {
+      for (int t = 0; t < NTILE; t++) {
         const int col = w0 + t * 32 + (lane & 31);
-        off[t] = 4 * h * ROWS + ((((col >> 2) ^ rc_swizzle<ROWS>(4 * h)) << 2) | (col & 3));
+        off[t] = (4 * h * ROWS + ((((col >> 2) ^ rc_swizzle<ROWS>(4 * h)) << 2) | (col & 3))) * ES;
       }
     } else {
       // transposing read: within 16 lanes, lane s points at 4 consecutive columns of k-row
       // kb + s/4, starting at column 4*(s%4); it receives k = kb..kb+3 of column s.
       const int s = lane & 15;
-      const int k = 8 * (lane >> 5) + (s >> 2);
+      const int k = 8 * (lane >> 4) + (s >> 2);
 #pragma unroll
-      for (int t = 0; t < 4; t++) {
-        const int col = w0 + t * 32 + 16 * ((lane >> 4) & 1) + 4 * (s & 3);
-        off[t] = k * ROWS + (((col >> 3) ^ rc_swizzle<ROWS>(k)) << 3) + (col & 7);
+      for (int t = 0; t < NTILE; t++) {
+        const int col = w0 + t * 16 + 4 * (s & 3);
+        off[t] = (k * ROWS + (((col >> 3) ^ rc_swizzle<ROWS>(k)) << 3) + (col & 7)) * ES;
       }
     }
   }
+  // how many of those offsets an operand has
+  template <bool KC, int NTILE>
+  static constexpr int n_offsets() { return KC ? KS : NTILE; }
+  // fragment of tile t at k-step ks; `at`: LDS address of the operand's tile plus the lane's offsets, `plus` bytes further on
+  template <typename P> __device__ static __forceinline__ const __attribute__((address_space(3))) P* lds_at(uint32_t a) {
+    return (const __attribute__((address_space(3))) P*)(uintptr_t)a;
+  }
   template <int ROWS, bool KC>
-  __device__ static __forceinline__ frag_t frag(const T* tile, const int (&off)[4], int t, int ks) {
-    if (KC) {
-      const uint4 v = *reinterpret_cast<const uint4*>(tile + off[ks] + t * 32 * BK);
-      return __builtin_bit_cast(frag_t, v);
+  __device__ static __forceinline__ frag_t frag(const uint32_t (&at)[kOffs], uint32_t plus, int t, int ks) {
+    if constexpr (KC) {
+      return __builtin_bit_cast(frag_t, *lds_at<u32x4_t>(at[ks] + (plus + t * MT * BK * ES)));
     } else if constexpr (ES == 4) {
-      const T* p = tile + off[t] + ks * 8 * ROWS;
-      return frag_t{p[0], p[ROWS], p[2 * ROWS], p[3 * ROWS]};
+      const uint32_t p = at[t];
+      const uint32_t q = plus + ks * 8 * ROWS * ES;
+      return frag_t{*lds_at<float>(p + q), *lds_at<float>(p + (q + ROWS * ES)), *lds_at<float>(p + (q + 2 * ROWS * ES)),
+                    *lds_at<float>(p + (q + 3 * ROWS * ES))};
     } else {
       typedef __attribute__((address_space(3))) short4_t* lds_ptr;
-      const T* p0 = tile + off[t] + ks * 16 * ROWS;
-      short4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p0));
-      short4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p0 + 4 * ROWS));
+      const uint32_t q = plus + ks * 32 * ROWS * ES;
+      short4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(uintptr_t)(at[t] + q));
+      short4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(uintptr_t)(at[t] + (q + 4 * ROWS * ES)));
       short8_t both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
       return __builtin_bit_cast(frag_t, both);
     }
@@ -232,50 +260,73 @@ struct MfmaDmaCore {
   };
   // the r-th fragment load of a k-step: first the TM fragments of A, then the NB*TN of B
   static constexpr int kFragLoads = TM + NB * TN;
-  __device__ static __forceinline__ void load_frag_n(const T* As, const T* Bs, const int (&ao)[4],
-                                                     const int (&bo)[4], int ks, int r, Frags& f) {
-    if (r < TM) {
-      f.a[r] = frag<BM, A_KC>(As, ao, r, ks);
+  template <int ks, int r>
+  __device__ static __forceinline__ void load_frag_n(const uint32_t (&la)[kOffs], const uint32_t (&lb)[kOffs], Frags& f) {
+    if constexpr (r < TM) {
+      f.a[r] = frag<BM, A_KC>(la, 0, r, ks);
     } else {
-      const int nb = (r - TM) / TN, j = (r - TM) % TN;
-      f.b[nb][j] = frag<BN, B_KC>(Bs + nb * B_ELEMS, bo, j, ks);
+      constexpr int nb = (r - TM) / TN, j = (r - TM) % TN;
+      f.b[nb][j] = frag<BN, B_KC>(lb, nb * B_ELEMS * ES, j, ks);
     }
   }
   // MFMA number m of a k-step.  Inline assembly with a memory clobber: the instruction stream of
   // the K loop is then exactly the order written in run() (LDS reads, tile loads and MFMAs
   // interleaved by hand), the compiler only allocates registers and inserts the waits.
-  // Operands exchanged: result register r of lane l is C[m = l%32][n = 8*(r/4) + 4*(l/32) + r%4].
-  // (fp32: all accumulator tiles take value 0 of the fragments, then value 1, ...)
+  // Operands exchanged: result register r of lane l is C[m = l%16][n = 4*(l/16) + r]
+  // (fp32: C[m = l%32][n = 8*(r/4) + 4*(l/32) + r%4]; all accumulator tiles take value 0 of the fragments, then value 1, ...)
   static constexpr int kTiles = NB * TM * TN;
   static constexpr int kMfma = kTiles * SUB;
-  __device__ static __forceinline__ void mfma_n(f32x16_t (&acc)[NB][TM][TN], const Frags& f, int m) {
-    const int sub = m / kTiles, q = m % kTiles;
-    const int nb = q / (TM * TN), i = (q / TN) % TM, j = q % TN;
+  template <int m>
+  __device__ static __forceinline__ void mfma_n(acc_t (&acc)[NB][TM][TN], const Frags& f) {
+    constexpr int sub = m / kTiles, q = m % kTiles;
+    constexpr int nb = q / (TM * TN), i = (q / TN) % TM, j = q % TN;
     if constexpr (ES == 4) {
       asm volatile("v_mfma_f32_32x32x2_f32 %0, %1, %2, %0"
                    : "+a"(acc[nb][i][j])
                    : "v"(f.b[nb][j][sub]), "v"(f.a[i][sub])
                    : "memory");
     } else {
-      asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0"
+      asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0"
                    : "+a"(acc[nb][i][j])
                    : "v"(f.b[nb][j]), "v"(f.a[i])
                    : "memory");
     }
   }
 
+  // The same, with a tile load (see issue_one) in the instruction's shadow: the write of M0 before it, so that the
+  // MFMA is the wait state that the load needs behind that write.  LDS address: base + plus.
+  template <int m, int plus>
+  __device__ static __forceinline__ void mfma_load_n(acc_t (&acc)[NB][TM][TN], const Frags& f, const rsrc_t& rsrc, uint32_t base,
+                                                     uint32_t voff) {
+    constexpr int sub = m / kTiles, q = m % kTiles;
+    constexpr int nb = q / (TM * TN), i = (q / TN) % TM, j = q % TN;
+    if constexpr (ES == 4) {
+      asm volatile("s_add_u32 m0, %3, %4\n\tv_mfma_f32_32x32x2_f32 %0, %1, %2, %0\n\tbuffer_load_dwordx4 %5, %6, 0 offen lds"
+                   : "+a"(acc[nb][i][j])
+                   : "v"(f.b[nb][j][sub]), "v"(f.a[i][sub]), "s"(base), "n"(plus), "v"(voff), "s"(rsrc)
+                   : "memory", "scc");
+    } else {
+      asm volatile("s_add_u32 m0, %3, %4\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0\n\tbuffer_load_dwordx4 %5, %6, 0 offen lds"
+                   : "+a"(acc[nb][i][j])
+                   : "v"(f.b[nb][j]), "v"(f.a[i]), "s"(base), "n"(plus), "v"(voff), "s"(rsrc)
+                   : "memory", "scc");
+    }
+  }
+
   // Position of a stream of tile loads along K.  The K loop pays for every scalar instruction between
-  // its MFMAs, so stepping is a handful of additions; the segment functor is consulted only where a
-  // segment starts.  Once the product is exhausted the steps are zero and the byte counts stay at
+  // its MFMAs, so a step moves the descriptors' bases and byte counts by 32-bit constants, three additions each; the
+  // segment functor is consulted only at the end of a run of steps (settle): where a segment starts, and before the steps add up
+  // to more than 2 GiB (a byte count saturates at 4 GiB, and one iteration's tile spans at most 1 GiB of an operand whose
+  // rows are K values).  Once the product is exhausted the steps are zero and the byte counts stay at
   // zero: loads issued from there on read nothing and deliver zeros.
   // byte offset beyond any descriptor's range (the operands of a tile span less than that: see the callers)
   static constexpr uint32_t kNowhere = 0xffffff00u;
   struct Cursor {
-    rsrc_t ad, bd[NB];      // buffer descriptors of the A tile and the B tile(s) at this position
-    int64_t a_rem, b_rem;   // bytes from the tile origins to the end of the tile's valid data
-    int64_t a_step, b_step; // bytes by which one iteration moves the origins
-    int k_left, k_step;     // valid values of K from the origins on
-    int ki, sg;
+    rsrc_t ad, bd[NB];        // buffer descriptors of the A tile and the B tile(s) at this position
+    uint32_t a_step, b_step;  // bytes by which one iteration moves the origins
+    int k_left, k_step;       // valid values of K from the origins on
+    int left;                 // steps until the run ends
+    int end, sg;              // the iteration of segment sg where it does
   };
   // byte count of a descriptor: 32 bits, saturating (built from the halves: scalar instructions only)
   __device__ static __forceinline__ int clip_rem(int64_t v) {
@@ -291,25 +342,25 @@ struct MfmaDmaCore {
     r[3] = 0x00020000;
     return r;
   }
-  // moves a descriptor's base by `step` bytes (the base stays below 2^48) and sets its byte count
-  __device__ static __forceinline__ void move_desc(rsrc_t& r, int64_t step, int64_t bytes) {
-    const uint64_t p = (((uint64_t)(uint32_t)r[1] << 32) | (uint32_t)r[0]) + (uint64_t)step;
+  // moves a descriptor by `step` bytes (the base stays below 2^48)
+  __device__ static __forceinline__ void move_desc(rsrc_t& r, uint32_t step) {
+    const uint64_t p = (((uint64_t)(uint32_t)r[1] << 32) | (uint32_t)r[0]) + step;
     r[0] = (int)(uint32_t)p;
     r[1] = (int)(uint32_t)(p >> 32);
-    r[2] = clip_rem(bytes);
+    r[2] = (int)((uint32_t)r[2] - step);
   }
+  // the run of steps that starts at iteration ki of segment sg
   template <class SegFn>
-  __device__ static __forceinline__ void seek(Cursor& c, SegFn& segf, int sg, int n_segs, int nk, int64_t lda,
+  __device__ static __forceinline__ void seek(Cursor& c, SegFn& segf, int sg, int ki, int n_segs, int nk, int64_t lda,
                                               int64_t ldb) {
-    c.ki = 0;
     c.sg = sg;
     if (sg < n_segs && nk > 0) {
       const SegSrc<T, NB> g = segf(sg);
-      c.a_rem = g.a_bytes;
-      c.b_rem = g.b_bytes;
-      c.ad = make_desc(g.a, c.a_rem);
+      const int64_t a_step = A_KC ? (int64_t)BK * ES : (int64_t)BK * ES * lda;
+      const int64_t b_step = B_KC ? (int64_t)BK * ES : (int64_t)BK * ES * ldb;
+      c.ad = make_desc((const T*)((const char*)g.a + ki * a_step), g.a_bytes - ki * a_step);
 #pragma unroll
-      for (int nb = 0; nb < NB; nb++) c.bd[nb] = make_desc(g.b[nb], c.b_rem);
+      for (int nb = 0; nb < NB; nb++) c.bd[nb] = make_desc((const T*)((const char*)g.b[nb] + ki * b_step), g.b_bytes - ki * b_step);
       // The words above come out of v_readfirstlane.  Five wait states must pass before a tile load reads
       // them, wherever the compiler places that load (a segment starts once or twice per tile, so this
       // costs nothing); the statements are tied to the descriptors and keep their order, so the wait
@@ -317,14 +368,18 @@ struct MfmaDmaCore {
 #pragma unroll
       for (int nb = 0; nb < NB; nb++) asm volatile("" : "+s"(c.bd[nb]) : : "memory");
       asm volatile("s_nop 4" : "+s"(c.ad) : : "memory");
-      c.a_step = A_KC ? (int64_t)BK * ES : (int64_t)BK * ES * lda;
-      c.b_step = B_KC ? (int64_t)BK * ES : (int64_t)BK * ES * ldb;
-      c.k_left = g.k_len;
+      c.a_step = (uint32_t)a_step;
+      c.b_step = (uint32_t)b_step;
+      c.k_left = g.k_len - ki * BK;
       c.k_step = BK;
+      const uint32_t most = A_KC && B_KC ? (uint32_t)(BK * ES) : max(c.a_step, c.b_step);
+      c.left = nk - ki;
+      if ((uint64_t)c.left * most > 0x80000000u) c.left = (int)(0x80000000u / most);
     } else {
       // exhausted (or nothing to do): zero-length descriptors that stay where they are
-      c.a_rem = c.b_rem = c.a_step = c.b_step = 0;
+      c.a_step = c.b_step = 0;
       c.k_left = c.k_step = 0;
+      c.left = 0x7fffffff;
       if (sg == 0) {
         c.ad = make_desc(nullptr, 0);
 #pragma unroll
@@ -335,23 +390,25 @@ struct MfmaDmaCore {
         for (int nb = 0; nb < NB; nb++) c.bd[nb][2] = 0;
       }
     }
+    c.end = ki + c.left;
+  }
+  // one iteration further (settle() must follow before the next load)
+  __device__ static __forceinline__ void next(Cursor& c) {
+    c.left--;
+    move_desc(c.ad, c.a_step);
+#pragma unroll
+    for (int nb = 0; nb < NB; nb++) move_desc(c.bd[nb], c.b_step);
+    c.k_left -= c.k_step;
   }
   template <class SegFn>
-  __device__ static __forceinline__ void next(Cursor& c, SegFn& segf, int n_segs, int nk, int64_t lda, int64_t ldb) {
-    c.ki++;
-    if (c.ki != nk) {
-      c.a_rem -= c.a_step;
-      c.b_rem -= c.b_step;
-      move_desc(c.ad, c.a_step, c.a_rem);
-#pragma unroll
-      for (int nb = 0; nb < NB; nb++) move_desc(c.bd[nb], c.b_step, c.b_rem);
-      c.k_left -= c.k_step;
-    } else {
-      seek(c, segf, c.sg + 1, n_segs, nk, lda, ldb);
+  __device__ static __forceinline__ void settle(Cursor& c, SegFn& segf, int n_segs, int nk, int64_t lda, int64_t ldb) {
+    if (c.left == 0) {
+      const bool done = c.end == nk;
+      seek(c, segf, done ? c.sg + 1 : c.sg, done ? 0 : c.end, n_segs, nk, lda, ldb);
     }
   }
 
-  // Epilogue.  In the MFMA result layout a lane owns four consecutive columns of 32 different rows, so direct
+  // Epilogue.  In the MFMA result layout a lane owns four consecutive columns of a row, so direct
   // global accesses would be scatters of 8- or 16-byte pieces.  The arithmetic is done in that layout, on
   // registers; the finished outputs, already in their final type, pass through a private LDS region of the
   // wave in blocks of 32 rows and are picked up again as whole rows, 16 bytes per lane.  Inputs of the epilogue
@@ -367,29 +424,36 @@ struct MfmaDmaCore {
   // left is arithmetic, two transcendentals per value, and the stores and loads of a launch's first tiles, which
   // all CUs issue together.  Whole steps gain 1-3 % only, because the shader clock drops as the matrix pipe idles less.)
   template <class Epi>
-  __device__ static __forceinline__ void epilogue(char* smem, f32x16_t (&acc)[NB][TM][TN], const Epi& epi, int wave, int lane,
+  __device__ static __forceinline__ void epilogue(char* smem, acc_t (&acc)[NB][TM][TN], const Epi& epi, int wave, int lane,
                                                   int wm0, int wn0) {
     constexpr int OES = Epi::OES, NOUT = Epi::NOUT, NAUX = Epi::NAUX;
-    constexpr int RB = TN * 32 * OES;         // bytes per row of the wave's tile
+    constexpr int RB = TN * MT * OES;         // bytes per row of the wave's tile
     constexpr int LPR = RB / 16;              // lanes (16-byte pieces) per row
     constexpr int RPP = 64 / LPR;             // rows per wave-wide access
     constexpr int NPASS = 32 / RPP;
     constexpr int SWZ = (LPR < 16 ? LPR : 16) - 1;
+    constexpr int NI = TM * MT / 32;          // blocks of 32 rows of the wave's tile
     constexpr int BLOCK = 32 * RB;            // one 32-row block of one matrix
     constexpr int NMAT = NOUT > NAUX ? NOUT : NAUX;
     constexpr int NA = NAUX > 0 ? NAUX : 1;
     static_assert(NW * NMAT * BLOCK <= LDS_BYTES, "the waves' staging regions fit into LDS");
     char* stage = smem + wave * (NMAT * BLOCK);
-    // row order: row pass * RPP + lane / LPR, piece lane % LPR;  result layout: row lane % 32
+    // row order: row pass * RPP + lane / LPR, piece lane % LPR;  result layout: row lane % MT of an accumulator tile, of its
+    // columns four (fp32: four of every eight, position g), by lane / MT
     const int rrow = lane / LPR, rpiece = lane % LPR;
     const uint32_t r_off = rrow * RB + ((rpiece ^ (rrow & SWZ)) << 4);
-    const int mrow = lane & 31, h = lane >> 5;
-    const uint32_t m_off = mrow * RB + ((mrow & SWZ) << 4);
+    constexpr int GR = 32 / MT, GC = AR / 4;  // accumulator tiles of a block's rows, positions of a tile
+    const int mrow = lane & (MT - 1), h = lane / MT;
+    uint32_t m_off[GR];
+#pragma unroll
+    for (int rh = 0; rh < GR; rh++) m_off[rh] = (rh * MT + mrow) * RB + (((rh * MT + mrow) & SWZ) << 4);
     auto row_at = [&](int pass) __attribute__((always_inline)) {  // (rrow < RPP, so the row's other bits come from pass)
       return (r_off ^ (((pass * RPP) & SWZ) << 4)) + pass * RPP * RB;
     };
-    auto col_at = [&](int j, int g) __attribute__((always_inline)) {
-      return OES == 2 ? (m_off ^ ((4 * j + g) << 4)) + 8 * h : (m_off ^ ((8 * j + 2 * g + h) << 4));
+    // first of the lane's four columns: MT * j + 8 * g + 4 * h
+    auto col_at = [&](int rh, int j, int g) __attribute__((always_inline)) {
+      return OES == 2 ? (m_off[rh] ^ ((MT / 8 * j + g + (h >> 1)) << 4)) + 8 * (h & 1)
+                      : (m_off[rh] ^ ((MT / 4 * j + 2 * g + h) << 4));
     };
     // global side: byte offsets from the tile's origin in every matrix
     const int c0 = wn0 + rpiece * (16 / OES);
@@ -418,31 +482,32 @@ struct MfmaDmaCore {
     if (NAUX > 0) load_aux(0);
     float scale[TM];
 #pragma unroll
-    for (int i = 0; i < TM; i++) scale[i] = epi.row_scale(wm0 + i * 32 + mrow);
+    for (int i = 0; i < TM; i++) scale[i] = epi.row_scale(wm0 + i * MT + mrow);
 #pragma unroll
-    for (int i = 0; i < TM; i++) {
+    for (int i = 0; i < NI; i++) {
       if (NAUX > 0) {
 #pragma unroll
         for (int x = 0; x < NAUX; x++)
 #pragma unroll
           for (int p = 0; p < NPASS; p++) *reinterpret_cast<u32x4_t*>(stage + x * BLOCK + row_at(p)) = piece[x][p];
         asm volatile("" ::: "memory");
-        if (i + 1 < TM) load_aux(i + 1);
+        if (i + 1 < NI) load_aux(i + 1);
       }
 #pragma unroll
-      for (int j = 0; j < TN; j++)
+      for (int t = 0; t < GR * TN; t++)
 #pragma unroll
-        for (int g = 0; g < 4; g++) {
+        for (int g = 0; g < GC; g++) {
+          const int rh = t / TN, j = t % TN;
           float v[NB][4], a[NA][4], o[NOUT][4];
 #pragma unroll
-          for (int x = 0; x < NAUX; x++) Epi::unpack(stage + x * BLOCK + col_at(j, g), a[x]);
+          for (int x = 0; x < NAUX; x++) Epi::unpack(stage + x * BLOCK + col_at(rh, j, g), a[x]);
 #pragma unroll
           for (int nb = 0; nb < NB; nb++)
 #pragma unroll
-            for (int q = 0; q < 4; q++) asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v[nb][q]) : "a"(acc[nb][i][j][4 * g + q]));
-          epi.apply(v, a, scale[i], o);
+            for (int q = 0; q < 4; q++) asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v[nb][q]) : "a"(acc[nb][GR * i + rh][j][4 * g + q]));
+          epi.apply(v, a, scale[GR * i + rh], o);
 #pragma unroll
-          for (int x = 0; x < NOUT; x++) Epi::pack(stage + x * BLOCK + col_at(j, g), o[x]);
+          for (int x = 0; x < NOUT; x++) Epi::pack(stage + x * BLOCK + col_at(rh, j, g), o[x]);
         }
       asm volatile("" ::: "memory");  // other lanes' values are read back below
       if (NAUX > 0) {
@@ -469,7 +534,7 @@ struct MfmaDmaCore {
       }
       asm volatile("" ::: "memory");
     }
-    if (NAUX == 0) store_out(TM - 1);
+    if (NAUX == 0) store_out(NI - 1);
   }
 
   // (the valid extents are not needed here: the descriptors' byte counts zero-fill the loads and bound
@@ -479,13 +544,12 @@ struct MfmaDmaCore {
                                              const Epi& epi, const RowMap& amap) {
     const int n_iters = n_segs * nk;
     MOE_PHASE(0);
-    T* lds = (T*)smem;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm0 = (wave / WN) * (BM / WM), wn0 = (wave % WN) * (BN / WN);
 
-    f32x16_t acc[NB][TM][TN];
-    // Called once the first tile loads are on their way, so that the 16 * NB * TM * TN register
+    acc_t acc[NB][TM][TN];
+    // Called once the first tile loads are on their way, so that the AR * NB * TM * TN register
     // writes overlap their latency.
     auto zero_acc = [&]() __attribute__((always_inline)) {
 #pragma unroll
@@ -495,7 +559,7 @@ struct MfmaDmaCore {
 #pragma unroll
           for (int j = 0; j < TN; j++)
 #pragma unroll
-            for (int r = 0; r < 16; r++) acc[nb][i][j][r] = 0.f;
+            for (int r = 0; r < AR; r++) acc[nb][i][j][r] = 0.f;
       // Pin the zeroing here.  Left alone, the compiler may materialise an accumulator's zeros right
       // in front of its first MFMA; that MFMA is inline assembly, so nobody would insert the wait
       // states a VALU write to an accumulator register needs before an MFMA reads it.
@@ -512,7 +576,7 @@ struct MfmaDmaCore {
     uint32_t voa[A_NI], vob[B_NI];
 #pragma unroll
     for (int j = 0; j < A_NI; j++)
-      voa[j] = piece_offset<BM, A_KC>(wave, lane, (uint32_t)lda) + (uint32_t)(j * load_stride<BM, A_KC>()) * (uint32_t)lda * ES;
+      voa[j] = piece_offset<BM, A_KC>(wave + j * NW, lane, (uint32_t)lda);
     if constexpr (A_KC) {
       // gathered A rows: the same pieces, from the rows the map names.  The descriptor then spans the
       // whole operand, so the rows beyond the tile's valid ones get an offset no descriptor reaches
@@ -521,14 +585,14 @@ struct MfmaDmaCore {
         const int q = wave * 64 + lane, row = q / PR_KC, c = (q % PR_KC) ^ kc_swizzle(row);
 #pragma unroll
         for (int j = 0; j < A_NI; j++) {
-          const int r = row + j * load_stride<BM, A_KC>();
+          const int r = row + j * (64 / PR_KC) * NW;
           voa[j] = r < amap.rows ? (uint32_t)amap(r) * (uint32_t)lda * ES + (uint32_t)c * 16u : kNowhere;
         }
       }
     }
 #pragma unroll
     for (int j = 0; j < B_NI; j++)
-      vob[j] = piece_offset<BN, B_KC>(wave, lane, (uint32_t)ldb) + (uint32_t)(j * load_stride<BN, B_KC>()) * (uint32_t)ldb * ES;
+      vob[j] = piece_offset<BN, B_KC>(wave + j * NW, lane, (uint32_t)ldb);
     // LDS byte addresses: this wave's first piece of A slot 0 and of B slot 0
     const uint32_t lds_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
     const uint32_t lds_a0 = lds_addr + (uint32_t)wave * 1024u;
@@ -551,15 +615,63 @@ struct MfmaDmaCore {
     auto mask = [&](const Cursor& c, uint32_t& tail) __attribute__((always_inline)) {
       if (KTAIL) tail = pk < c.k_left ? 0u : kNowhere;
     };
-    auto start = [&](Cursor& c) __attribute__((always_inline)) { seek(c, segf, 0, n_segs, nk, lda, ldb); };
-    auto step = [&](Cursor& c) __attribute__((always_inline)) { next(c, segf, n_segs, nk, lda, ldb); };
+    auto start = [&](Cursor& c) __attribute__((always_inline)) { seek(c, segf, 0, 0, n_segs, nk, lda, ldb); };
+    auto settled = [&](Cursor& c) __attribute__((always_inline)) { settle(c, segf, n_segs, nk, lda, ldb); };
+    auto step = [&](Cursor& c) __attribute__((always_inline)) {
+      next(c);
+      settled(c);
+    };
 
-    static_assert(TM <= 4 && TN <= 4, "lane_offsets holds four tiles per operand");
-    int ao[4], bo[4];
+    static_assert(TM <= kOffs && TN <= kOffs, "lane_offsets holds an offset per tile of an operand");
+    uint32_t ao[kOffs], bo[kOffs];
     lane_offsets<BM, A_KC, TM>(wm0, lane, ao);
     lane_offsets<BN, B_KC, TN>(wn0, lane, bo);
+    // LDS addresses of the fragments of the tile that is multiplied (`la`, `lb`), one of operand A or B at a time
+    constexpr int kNA = n_offsets<A_KC, TM>(), kAddr = kNA + n_offsets<B_KC, TN>();
+    uint32_t la[kOffs], lb[kOffs];
+    auto set_address = [&](auto xc, uint32_t a_tile, uint32_t b_tile) __attribute__((always_inline)) {
+      constexpr int x = decltype(xc)::value;
+      if constexpr (x < kNA) la[x] = ao[x] + a_tile;
+      else lb[x - kNA] = bo[x - kNA] + b_tile;
+    };
+    constexpr uint32_t kABytes = A_ELEMS * ES, kBBytes = B_SET_ELEMS * ES;
+    const uint32_t lds_b = lds_addr + A_SLOTS * kABytes;
+    static_for<kAddr>([&](auto x) __attribute__((always_inline)) { set_address(x, lds_addr, lds_b); });
 
     constexpr int kLoadsB = NB * B_NI;  // loads per wave for the B tiles of one iteration
+    // Fragments are read a few MFMAs (16 cycles each in bf16) before the k-step that needs them starts.
+    constexpr int kHalf = kMfma / 2, kLate = kMfma - kHalf;
+    constexpr int kLead = ES == 4 ? 0 : kMfma / 8 < 8 ? kMfma / 8 : 8;
+    constexpr int kSpan = kMfma - kLead, kLateSpan = kLate - kLead;
+    auto upto = [](int r) __attribute__((always_inline)) { return r < kFragLoads ? r : kFragLoads; };
+    // the loads of an iteration are spread over these MFMAs: all before the barrier
+    constexpr int kSlots = (KS - 1) * kMfma + kHalf;
+    Frags f[2];
+    auto first_frags = [&]() __attribute__((always_inline)) {
+      static_for<kFragLoads>([&](auto r) __attribute__((always_inline)) { load_frag_n<0, decltype(r)::value>(la, lb, f[0]); });
+    };
+    // What an iteration does ahead of its MFMA number `slot` besides tile loads: the fragments of the next k-step (of the last
+    // one's: of the next tile, behind the barrier), spread over the k-step's MFMAs; ahead of the barrier the addresses of the
+    // next tile's fragments.  (After the last tile this reads stale but in-bounds LDS data that is never used.)
+    auto ahead = [&](auto slot_c, uint32_t a_next, uint32_t b_next, auto barrier) __attribute__((always_inline)) {
+      constexpr int slot = decltype(slot_c)::value, ks = slot / kMfma, m = slot % kMfma;
+      if constexpr (ks < KS - 1) {
+        constexpr int r0 = std::min(m * kFragLoads / kSpan, kFragLoads), r1 = std::min((m + 1) * kFragLoads / kSpan, kFragLoads);
+        static_for<r1 - r0>([&](auto r) __attribute__((always_inline)) {
+          load_frag_n<ks + 1, r0 + decltype(r)::value>(la, lb, f[(ks + 1) & 1]);
+        });
+      } else if constexpr (m < kHalf) {
+        constexpr int x0 = m * kAddr / kHalf, x1 = (m + 1) * kAddr / kHalf;
+        static_for<x1 - x0>([&](auto x) __attribute__((always_inline)) {
+          set_address(std::integral_constant<int, x0 + decltype(x)::value>(), a_next, b_next);
+        });
+      } else {
+        if constexpr (m == kHalf) barrier();
+        constexpr int h = m - kHalf;
+        constexpr int r0 = std::min(h * kFragLoads / kLateSpan, kFragLoads), r1 = std::min((h + 1) * kFragLoads / kLateSpan, kFragLoads);
+        static_for<r1 - r0>([&](auto r) __attribute__((always_inline)) { load_frag_n<0, r0 + decltype(r)::value>(la, lb, f[0]); });
+      }
+    };
     if constexpr (DEPTH >= 2) {
       // streaming pipeline: tiles t .. t+DEPTH-1 in flight while tile t is multiplied
       constexpr int L = A_NI + kLoadsB;  // loads per wave and iteration
@@ -594,50 +706,32 @@ struct MfmaDmaCore {
       // (Reads before, then all loads, then all MFMAs of an iteration: the loads of four waves alone hold the
       // address unit for 16 cycles each, 768 of the 1950 cycles of a 128-row step.  Down product of 4 shared experts, T = 2777,
       // 176 tiles of 128 rows and 88 steps: 124 -> 79 us, 1.35 -> 0.83 us a step; fp32 step T = 2048: 2138 -> 2088 us.)
-      constexpr int kHalf = kMfma / 2, kLate = kMfma - kHalf;
-      constexpr int kSlots = (KS - 1) * kMfma + kHalf;
-      Frags f[2];
-#pragma unroll
-      for (int r = 0; r < kFragLoads; r++) load_frag_n(lds, lds + A_SLOTS * A_ELEMS, ao, bo, 0, r, f[0]);
-      int cur = 0, fill = DEPTH;  // slots of tile t and of tile t + DEPTH
+      static_assert(L <= kSlots, "at most one load per MFMA");
+      first_frags();
+      int cur = 0;
+      uint32_t fill_a = lds_a0 + DEPTH * kABytes, fill_b = lds_b0 + DEPTH * kBBytes;  // slot of tile t + DEPTH
       for (int it = 0; it < n_iters; it++) {
         const int nxt = cur == DEPTH ? 0 : cur + 1;
-        const T* As = lds + cur * A_ELEMS;
-        const T* Bs = lds + A_SLOTS * A_ELEMS + cur * B_SET_ELEMS;
-        const T* An = lds + nxt * A_ELEMS;
-        const T* Bn = lds + A_SLOTS * A_ELEMS + nxt * B_SET_ELEMS;
         mask(s0, tail_a);
         tail_b = tail_a;
-#pragma unroll
-        for (int ks = 0; ks < KS; ks++) {
-#pragma unroll
-          for (int m = 0; m < kMfma; m++) {
-            if (ks < KS - 1) {
-#pragma unroll
-              for (int r = m * kFragLoads / kMfma; r < (m + 1) * kFragLoads / kMfma; r++)
-                load_frag_n(As, Bs, ao, bo, ks + 1, r, f[(ks + 1) & 1]);
+        static_for<KS * kMfma>([&](auto slot_c) __attribute__((always_inline)) {
+          constexpr int slot = decltype(slot_c)::value, ks = slot / kMfma, m = slot % kMfma, n = slot * L / kSlots;
+          ahead(slot_c, lds_addr + nxt * kABytes, lds_b + nxt * kBBytes, landed);
+          if constexpr (slot < kSlots && n < (slot + 1) * L / kSlots) {
+            if constexpr (n < A_NI) {
+              mfma_load_n<m, n * NW * 1024>(acc, f[ks & 1], s0.ad, fill_a, KTAIL && A_KC ? voa[n] | tail_a : voa[n]);
             } else {
-              if (m == kHalf) landed();
-              // (after the last tile this reads stale but in-bounds LDS data that is never used)
-              if (m >= kHalf) {
-#pragma unroll
-                for (int r = (m - kHalf) * kFragLoads / kLate; r < (m - kHalf + 1) * kFragLoads / kLate; r++)
-                  load_frag_n(An, Bn, ao, bo, 0, r, f[0]);
-              }
+              constexpr int nb = (n - A_NI) / B_NI, j = (n - A_NI) % B_NI;
+              mfma_load_n<m, nb * B_ELEMS * ES + j * NW * 1024>(acc, f[ks & 1], s0.bd[nb], fill_b, KTAIL && B_KC ? vob[j] | tail_b : vob[j]);
             }
-            const int slot = ks * kMfma + m;
-            if (slot < kSlots) {
-#pragma unroll
-              for (int n = slot * L / kSlots; n < (slot + 1) * L / kSlots; n++) {
-                if (n < A_NI) load_a(s0, fill, n);
-                else load_b(s0, fill, n - A_NI);
-              }
-            }
-            mfma_n(acc, f[ks & 1], m);
+          } else {
+            mfma_n<m>(acc, f[ks & 1]);
           }
-        }
-        step(s0);
-        fill = cur;
+          if constexpr (slot == kSlots) next(s0);  // behind the last load
+        });
+        settled(s0);
+        fill_a = lds_a0 + cur * kABytes;
+        fill_b = lds_b0 + cur * kBBytes;
         cur = nxt;
       }
     } else if constexpr (!RING) {
@@ -655,15 +749,12 @@ struct MfmaDmaCore {
         for (int n = 0; n < kLoadsB; n++) load_b(s0, 0, n);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-#pragma unroll
-        for (int ks = 0; ks < KS; ks++) {
-          if (ks * 2 * PE >= s0.k_left) continue;  // uniform: the remaining k rows of the tile are zero
-          Frags f;
-#pragma unroll
-          for (int r = 0; r < kFragLoads; r++) load_frag_n(lds, lds + A_SLOTS * A_ELEMS, ao, bo, ks, r, f);
-#pragma unroll
-          for (int m = 0; m < kMfma; m++) mfma_n(acc, f, m);
-        }
+        static_for<KS>([&](auto ks_c) __attribute__((always_inline)) {
+          constexpr int ks = decltype(ks_c)::value;
+          if (ks * (BK / KS) >= s0.k_left) return;  // uniform: the remaining k rows of the tile are zero
+          static_for<kFragLoads>([&](auto r) __attribute__((always_inline)) { load_frag_n<ks, decltype(r)::value>(la, lb, f[0]); });
+          static_for<kMfma>([&](auto m) __attribute__((always_inline)) { mfma_n<decltype(m)::value>(acc, f[0]); });
+        });
         step(s0);
       }
     } else {
@@ -693,70 +784,53 @@ struct MfmaDmaCore {
 
     // A wave issues in order and a tile load holds it for as long as the memory pipeline has no
     // free slot, so the overlap of loads, LDS reads and MFMAs is written into the instruction
-    // stream itself.  Per K iteration t (4 k-steps
+    // stream itself.  Per K iteration t (KS k-steps
     // of kMfma MFMAs):
-    //   - the fragments of k-step ks+1 are read from LDS during the MFMAs of ks, one per MFMA;
+    //   - the fragments of k-step ks+1 are read from LDS during the MFMAs of ks;
     //   - the loads of B(t+1), then of A(t+2), are spread evenly between the MFMAs;
     //   - half-way through the last k-step all LDS reads of this iteration are done: wait until
     //     B(t+1) has landed (A(t+2) may still be in flight: loads complete in order), barrier, and
     //     read the first fragments of iteration t+1 under the remaining MFMAs.
+    // What else an iteration needs is spread between the MFMAs too: a step of a cursor behind its last load, the addresses of
+    // the next tile's fragments ahead of the barrier.
     constexpr int kLoads = kLoadsB + A_NI;
-    constexpr int kHalf = kMfma / 2;                 // MFMAs of the last k-step before the barrier
-    constexpr int kSlots = (KS - 1) * kMfma + kHalf; // MFMA slots before the barrier: all loads issue here
-    constexpr int kLate = kMfma - kHalf;             // MFMAs after the barrier
-    Frags f[2];
-#pragma unroll
-    for (int r = 0; r < kFragLoads; r++) load_frag_n(lds, lds + A_SLOTS * A_ELEMS, ao, bo, 0, r, f[0]);
-    int a_cur = 0, b_cur = 0;  // slots of this iteration's tiles
+    static_assert(kLoads <= kSlots, "at most one load per MFMA");
+    first_frags();
+    auto landed = [&]() __attribute__((always_inline)) {
+      // B(t+1) must have landed (the A_NI loads of A(t+2) issued after it may still be
+      // outstanding), and every wave must be done reading this iteration's tiles
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(A_NI) : "memory");
+      __syncthreads();
+    };
+    // slots: A(t+1) to multiply next, A(t+2) and B(t+1) to fill
+    uint32_t a_nxt = kABytes, a_nn = 2 * kABytes, a_cur = 0, b_nxt = kBBytes;
     for (int it = 0; it < n_iters; it++) {
-      const int a_nxt = a_cur == A_SLOTS - 1 ? 0 : a_cur + 1;   // A(t+1)
-      const int a_nn = a_nxt == A_SLOTS - 1 ? 0 : a_nxt + 1;    // A(t+2) goes here
-      const int b_nxt = b_cur ^ 1;
-      const T* As = lds + a_cur * A_ELEMS;
-      const T* Bs = lds + A_SLOTS * A_ELEMS + b_cur * B_SET_ELEMS;
-      const T* An = lds + a_nxt * A_ELEMS;
-      const T* Bn = lds + A_SLOTS * A_ELEMS + b_nxt * B_SET_ELEMS;
-#pragma unroll
-      for (int ks = 0; ks < KS; ks++) {
-#pragma unroll
-        for (int m = 0; m < kMfma; m++) {
-          if (ks < KS - 1) {
-            // fragment loads of k-step ks+1, spread over the MFMAs of ks
-#pragma unroll
-            for (int r = m * kFragLoads / kMfma; r < (m + 1) * kFragLoads / kMfma; r++)
-              load_frag_n(As, Bs, ao, bo, ks + 1, r, f[(ks + 1) & 1]);
+      static_for<KS * kMfma>([&](auto slot_c) __attribute__((always_inline)) {
+        constexpr int slot = decltype(slot_c)::value, ks = slot / kMfma, m = slot % kMfma, n = slot * kLoads / kSlots;
+        ahead(slot_c, lds_addr + a_nxt, lds_b + b_nxt, landed);
+        if constexpr (slot < kSlots && n < (slot + 1) * kLoads / kSlots) {
+          if constexpr (n < kLoadsB) {
+            constexpr int nb = n / B_NI, j = n % B_NI;
+            mfma_load_n<m, nb * B_ELEMS * ES + j * NW * 1024>(acc, f[ks & 1], s1.bd[nb], lds_b0 + b_nxt, KTAIL && B_KC ? vob[j] | tail_b : vob[j]);
           } else {
-            if (m == kHalf) {
-              // B(t+1) must have landed (the A_NI loads of A(t+2) issued after it may still be
-              // outstanding), and every wave must be done reading this iteration's tiles
-              asm volatile("s_waitcnt vmcnt(%0)" ::"n"(A_NI) : "memory");
-              __syncthreads();
-            }
-            // first fragments of iteration t+1 under the remaining MFMAs
-            // (after the last tile this reads stale but in-bounds LDS data that is never used)
-            if (m >= kHalf) {
-#pragma unroll
-              for (int r = (m - kHalf) * kFragLoads / kLate; r < (m - kHalf + 1) * kFragLoads / kLate; r++)
-                load_frag_n(An, Bn, ao, bo, 0, r, f[0]);
-            }
+            constexpr int j = n - kLoadsB;
+            mfma_load_n<m, j * NW * 1024>(acc, f[ks & 1], s2.ad, lds_a0 + a_nn, KTAIL && A_KC ? voa[j] | tail_a : voa[j]);
           }
-          const int slot = ks * kMfma + m;
-          if (slot < kSlots) {
-#pragma unroll
-            for (int n = slot * kLoads / kSlots; n < (slot + 1) * kLoads / kSlots; n++) {
-              if (n < kLoadsB) load_b(s1, b_nxt, n);
-              else load_a(s2, a_nn, n - kLoadsB);
-            }
-          }
-          mfma_n(acc, f[ks & 1], m);
+          if constexpr (n == kLoadsB - 1) next(s1);
+        } else {
+          mfma_n<m>(acc, f[ks & 1]);
         }
-      }
-      step(s1);
-      step(s2);
+        if constexpr (slot == kSlots) next(s2);
+      });
+      settled(s1);
+      settled(s2);
       mask(s1, tail_b);
       mask(s2, tail_a);
+      const uint32_t a_old = a_cur;
       a_cur = a_nxt;
-      b_cur = b_nxt;
+      a_nxt = a_nn;
+      a_nn = a_old;
+      b_nxt = kBBytes - b_nxt;
     }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // zero-length loads of the tail

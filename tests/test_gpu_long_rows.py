@@ -104,3 +104,30 @@ def test_router(dtype, d):
     moe.moe_router_bwd(shape, X, Wr, dl, dWr, dX, True, ws)
     assert rel(logits, X.double() @ Wr.double()) <= TOL["f32"]
     assert rel(dX, ref) <= TOL[dtype] and rel(dWr, X.double().T @ dl.to(shape.torch_dtype).double()) <= TOL[dtype]
+
+
+def test_sums_over_more_than_2_gib_of_an_operand():
+    """One group's weight gradients step through operands of 2.3 GB: the tile loads' byte counts are 32 bits and start anew
+    on the way.  Only the last rows, beyond that point, are not zero."""
+    import paper_2502_02581_amd as moe
+
+    R, d, F, last = 140032, 8192, 64, 3000   # rows of 16 KB: 2 GiB are 131072 of them
+    shape = moe.MoEShape(R, d, 1, 1, F, "bf16")
+    g = torch.Generator(device="cuda").manual_seed(5)
+    rnd = lambda *s: (torch.randn(*s, generator=g, device="cuda") * s[-1] ** -0.5).bfloat16()
+    new = lambda *s: torch.zeros(*s, dtype=torch.bfloat16, device="cuda")
+    X, dY, dX, G, U, H = new(R, d), new(R, d), new(R, d), new(R, F), new(R, F), new(R, F)
+    for t in (X, dY, G, U, H):
+        t[-last:] = rnd(last, t.shape[1])
+    Wg, Wu, Wd, dWg, dWu, dWd = rnd(1, d, F), rnd(1, d, F), rnd(1, F, d), new(1, d, F), new(1, d, F), new(1, F, d)
+    off = torch.tensor([0, R], dtype=torch.int32, device="cuda")
+    ids, n_act = torch.empty(1, dtype=torch.int32, device="cuda"), torch.empty(1, dtype=torch.int32, device="cuda")
+    ws = torch.empty(moe.moe_expert_bwd_workspace_bytes(shape, 1, R, False), dtype=torch.uint8, device="cuda")
+    moe.moe_expert_bwd(shape, 1, off, R, X, Wg, Wu, Wd, G, U, H, dY, dX, ids, n_act, dWg, dWu, dWd, ws)
+    x, dy, gg, u, h = (t[-last:].float() for t in (X, dY, G, U, H))
+    s = torch.sigmoid(gg)
+    dh = dy @ Wd[0].float().T
+    dg, du = dh * u * s * (1 + gg * (1 - s)), dh * gg * s
+    for got, ref in ((dWd[0], h.T @ dy), (dWg[0], x.T @ dg), (dWu[0], x.T @ du), (dX[-last:], dg @ Wg[0].float().T + du @ Wu[0].float().T)):
+        assert float((got.float() - ref).norm() / ref.norm()) <= 1e-2   # operands and results in bf16: a few times 2^-9
+    assert not dX[:-last].any()
