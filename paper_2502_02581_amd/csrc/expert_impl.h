@@ -183,29 +183,29 @@ __device__ __forceinline__ void row_gemm_block(const RowGemm& p, int block, char
   // Blocks go to the XCDs round-robin (block b runs on XCD b % 8) and the 32 CUs of an XCD share
   // one L2, so the 32 blocks an XCD holds at a time should read as few different operand tiles as
   // possible.  Tiles are numbered band by band (a band: kBandRows consecutive row tiles), column
-  // by column within a band, and each XCD takes runs of 32 consecutive tiles: 4 row tiles x 8
-  // column tiles, 12 operand streams for 32 tiles.  What is left after the last whole round of 8 runs is
-  // cut into 8 equal runs, so that no XCD is a run ahead of another (a training step with 4 shared experts on a
-  // second stream, T = 4096, d = 2048: 2.40 -> 2.21 ms; launches of many rounds: the same).
+  // by column within a band, and dealt to the XCDs 256 at a time.  Launches of many such rounds deal runs
+  // of 32 consecutive tiles: 4 row tiles x 8 column tiles, 12 operand streams for 32 tiles.  The tiles come longest first,
+  // though, and XCD 0 always gets the first run: in launches of a few rounds, and in the last round, that costs more
+  // than the streams save, so there the runs are of 8 tiles, and a round that is not full is dealt tile by tile.  (Runs of 32 and
+  // eighths of the last round against this, training steps: T = 3001, d = 1000, one shared expert 603 -> 580 us; T = 8192,
+  // d = 768 1029 -> 1004; T = 4096, d = 2048, four shared 2148 -> 2106; T = 2777 of those 1515 -> 1484.  Runs of 8 throughout cost
+  // T = 8192, d = 4096, width 6400, 12 rounds and more, 0.8 %.)
   const int per_band = kBandRows * ntn;
   const int bm = Core0::BM >> p.direct_kind;
   const int per_group = PLAN ? 0 : (p.n_rows + bm - 1) / bm;
   const int n_mt = PLAN ? *p.n_tiles : p.n_groups * per_group;
   const int part = PLAN || p.n_parts == 1 ? 0 : block / p.part_blocks;
   if (!PLAN) block -= part * p.part_blocks;
-  const int total = (n_mt + kBandRows - 1) / kBandRows * per_band;
-  const int xcd = block & 7, j = block >> 3;
-  const int whole = total >> 8, in_run = j & 31;
-  int q = ((j >> 5) * 8 + xcd) * 32 + in_run;
-  if ((j >> 5) >= whole) {
-    const int run = (total - (whole << 8) + 7) >> 3;
-    if ((j >> 5) > whole || in_run >= run) return;
-    q = (whole << 8) + xcd * run + in_run;
-    if (q >= total) return;
-  }
+  const int total = n_mt * ntn, rounds = total >> 8;
+  const int xcd = block & 7, round = block >> 8, i = (block >> 3) & 31;
+  int q = round << 8;
+  if (round < rounds) q += rounds > kFineRounds && round < rounds - 1 ? (xcd << 5) + i : ((i >> 3) << 6) + (xcd << 3) + (i & 7);
+  else q += (i << 3) + xcd;
+  if (q >= total) return;
+  // (the last band may have fewer rows)
   const int band = q / per_band, r = q - band * per_band;
-  const int mt = band * kBandRows + r % kBandRows, nt = r / kBandRows;
-  if (mt >= n_mt) return;
+  const int high = min(kBandRows, n_mt - band * kBandRows);
+  const int mt = band * kBandRows + r % high, nt = r / high;
   RowTile t;
   if (PLAN) {
     t = p.tiles[mt];
@@ -329,18 +329,21 @@ __global__ __launch_bounds__(CoreSet::template tile<0>::NT, CoreSet::template ti
 // instead of two for the light groups: training steps of T = 2777, d = 2048, 60 experts, top-3: 1.87 -> 1.69 ms;
 // T = 3001, d = 1000: 0.88 -> 0.76; T = 8192, d = 768 GELU: 1.08 -> 1.03; fp32 T = 2048, d = 1024: 2.32 -> 2.14.)
 // Blocks in this order, all counts but the last multiples of 8: weight gradients of shared experts where their tiles
-// are the longest, row tiles of shared, of routed experts, weight gradients of shared, of routed experts.
+// are the longest, row tiles of shared experts, weight gradients of shared experts where their tiles are at least half as long as
+// the routed experts' full row tiles (T = 4096, d = 2048, four shared experts: 2148 -> 2108 us a training step against the end), row
+// tiles of routed experts, weight gradients of shared experts otherwise, of routed experts.
 struct RowWOrder {
-  int32_t first_sw, s_rows, r_rows, last_sw;
+  int32_t first_sw, s_rows, mid_sw, r_rows, last_sw;
 };
 template <class CoreSet, int EPI, class WCore, int WNB>
 __global__ __launch_bounds__(WCore::NT, CoreSet::template tile<0>::BLOCKS_PER_CU) void row_w_gemm_kernel(RowGemm s, RowGemm r, WGemm sw, WGemm rw, RowWOrder o) {
   extern __shared__ __align__(16) char smem[];
-  const int b = (int)blockIdx.x - o.first_sw, w = b - o.s_rows - o.r_rows;
-  if (b < 0 || (w >= 0 && w < o.last_sw)) w_gemm_block<WCore, WNB, false>(sw, b < 0 ? (int)blockIdx.x : w, smem);
-  else if (b < o.s_rows) row_gemm_block<CoreSet, 1, EPI, true, false>(s, b, smem);
-  else if (w < 0) row_gemm_block<CoreSet, 1, EPI, true, true>(r, b - o.s_rows, smem);
-  else w_gemm_block<WCore, WNB, true>(rw, w - o.last_sw, smem);
+  // positions from the start of each section on
+  const int b = blockIdx.x, srow = b - o.first_sw, mid = srow - o.s_rows, rrow = mid - o.mid_sw, last = rrow - o.r_rows;
+  if (srow < 0 || (mid >= 0 && rrow < 0) || (last >= 0 && last < o.last_sw)) w_gemm_block<WCore, WNB, false>(sw, srow < 0 ? b : rrow < 0 ? mid : last, smem);
+  else if (mid < 0) row_gemm_block<CoreSet, 1, EPI, true, false>(s, srow, smem);
+  else if (last < 0) row_gemm_block<CoreSet, 1, EPI, true, true>(r, rrow, smem);
+  else w_gemm_block<WCore, WNB, true>(rw, last - o.last_sw, smem);
 }
 // The weight gradients of the groups with few rows: all matrices of an expert in one launch.
 template <class Core>
@@ -469,10 +472,8 @@ void launch_wide_row(const char* label, const RowGemm& p, int bm, int max_tiles,
 template <typename T>
 void launch_wide_w(const char* label, const WGemm& p, int n_products, hipStream_t st);
 
-// whole bands of kBandRows row tiles, handed out in runs of 32 tiles to 8 XCDs
-static unsigned row_block_count(int n_tiles, int N, int bn) {
-  return (unsigned)ceil_div(ceil_div(n_tiles, kBandRows) * kBandRows * ceil_div(N, bn), 256) * 256u;
-}
+// whole rounds of 256 tiles (see row_gemm_block)
+static unsigned row_block_count(int n_tiles, int N, int bn) { return (unsigned)ceil_div(n_tiles * ceil_div(N, bn), 256) * 256u; }
 template <class Core> static unsigned w_block_count(const WGemm& p, int n_products = 1) {
   const int tiles = ceil_div(p.M, Core::BM) * ceil_div(ceil_div(p.N, Core::BN), p.n_reps > 1 ? p.n_reps : 1);
   return (unsigned)tiles * (unsigned)p.n_groups * (unsigned)n_products;
@@ -649,11 +650,12 @@ static void launch_row_w(const char* label, const Direct* sd, const RowGemm* r, 
     w.part = (float*)(sd->parts + rc.part_bytes); w.part_stride = sd->w_shape.out_elems;
     o.s_rows = p.part_blocks * rc.n_parts;
     const int wb = (int)((w_block_count<WCore>(w) * (unsigned)wc.n_parts + 7) / 8 * 8);
-    if (wc.block_us > rc.block_us) o.first_sw = wb;  // the longer blocks first
-    else o.last_sw = wb;
+    const TileCost& c = sd->shape.cost;
+    const double routed_us = r ? c.fixed[0] + (double)r->n_pairs * r->n_segs * ceil_div(r->K, c.bk) * c.iter[0] : 0;
+    (wc.block_us > rc.block_us ? o.first_sw : r && 2 * wc.block_us >= routed_us ? o.mid_sw : o.last_sw) = wb;
   }
   if (r) o.r_rows = (int)row_block_count(r_tiles, r->N, Core::BN);
-  const unsigned blocks = (unsigned)(o.first_sw + o.s_rows + o.r_rows + o.last_sw) + (r ? w_block_count<WCore>(*rw) : 0);
+  const unsigned blocks = (unsigned)(o.first_sw + o.s_rows + o.mid_sw + o.r_rows + o.last_sw) + (r ? w_block_count<WCore>(*rw) : 0);
   if (blocks == 0) return;
   auto kern = row_w_gemm_kernel<CoreSet, EPI, WCore, WNB>;
   static LdsAttr attr;

@@ -17,6 +17,8 @@ __host__ __device__ inline int tile_rows(const RowTile& t) { return t.rows & 0xf
 __host__ __device__ inline int tile_kind(const RowTile& t) { return (t.rows >> 16) & 3; }
 // row tiles per band of the XCD-aware tile order of the LDS-DMA path
 constexpr int kBandRows = 4;
+// launches of at most so many rounds of 256 row tiles deal them to the XCDs in short runs
+constexpr int kFineRounds = 6;
 
 // Device-built plan, laid out in the workspace.
 struct Plan {
