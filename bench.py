@@ -27,7 +27,7 @@ MFMA_BF16_PEAK_TF = 2500.0   # dense bf16 matrix peak, published
 FP32_VEC_PEAK_TF = 157.3
 
 GEMM_LABELS = ("gemm_fwd_gate_up", "gemm_fwd_down", "gemm_bwd_dh_dwd", "gemm_bwd_dx_dwgu", "gemm_bwd_dw_light")
-LIGHT_GROUP_ROWS = 256       # routed experts with at most this many rows take the light weight-gradient kernels
+LIGHT_GROUP_ROWS = 64        # routed experts with at most this many rows take the light weight-gradient kernels
 PROBE_BYTES = 1 << 30        # size of the calibration copy
 PROBE_LAUNCHES = 5
 COLD_STEPS = 3               # steps of the cold-cache variant

@@ -58,8 +58,11 @@ struct Epilogue {
   static constexpr int NAUX = EPI == EPI_SWIGLU_BWD ? 2 : (EPI == EPI_GELU_BWD || EPI == EPI_ADD) ? 1 : 0;
   static constexpr int OES = EPI == EPI_STORE_F32 || EPI == EPI_PART ? 4 : sizeof(T);
   // bf16 outputs carry the streaming hint: every one is read again only by a later kernel, after gigabytes of
-  // other traffic (2-3 % on the row GEMMs of the Qwen- and stress-shaped workloads)
-  static constexpr bool NT = OES == 2;
+  // other traffic (2-3 % on the row GEMMs of the Qwen- and stress-shaped workloads; all launches without it: +0.8 % on a training
+  // step of T = 4096, d = 2048, the light weight gradients +2 to 3 %).  Not where rows are no whole cache lines: two tiles
+  // write parts of the same line then, and the hint sends each part on to memory by itself (T = 3001, d = 1000, width 1368:
+  // 603 us a training step with it, 584 without; the light weight gradients alone 588).
+  __device__ __forceinline__ bool stream() const { return OES == 2 && ldc % 64 == 0; }
   void* out[NOUT];
   const void* in[NAUX > 0 ? NAUX : 1];
   int64_t ldc;
@@ -412,7 +415,10 @@ template <> struct Cores<PATH_BF16> {
   template <int NB> using core_light = MfmaDmaCore<bf16_t, 128, 128, NB, false, false, 2, 2, 0>;
 };
 template <> struct Cores<PATH_BF16_TAIL> : Cores<PATH_BF16> {};
-constexpr int kLightGroupRows = 256;  // groups up to this many rows take the light dW kernel
+// Groups up to this many rows, one K step, take the light dW kernel.  (256 and 64, training steps: T = 3001, d = 1000,
+// 24 experts 603 and 589 us; T = 8192, d = 768, 64 experts 1029 and 1019; T = 16384, d = 2048, stress routing 3696 and 3676; T = 8192,
+// d = 4096, 16 experts 7178 and 7149; the others within 0.3 %.)
+constexpr int kLightGroupRows = 64;
 constexpr int kLightReps = 2;         // column tiles per block of that kernel (1: +5 % time on the DeepSeek shape, 8: +3 %)
 
 // The tile cores a row-tiled GEMM launch may use: tile kinds of heights BM, BM/2, BM/4, BM/8, so that ragged

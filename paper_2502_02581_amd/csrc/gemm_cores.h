@@ -4,7 +4,7 @@
 // The core computes, for one block, acc[nb][..] = sum over iterations of A_tile * B_tile(nb), and turns
 // them into NOUT output matrices (with NAUX input matrices of the same shape) as an epilogue object says:
 //     epi.apply(v, aux, scale, o)   v[nb][0..3] = C[m][n..n+3], aux[x][0..3], scale = epi.row_scale(m) -> o[out][0..3]
-// Its members: NOUT, NAUX, OES (bytes per element of all those matrices), NT (streaming stores);
+// Its members: NOUT, NAUX, OES (bytes per element of all those matrices), stream() (streaming stores);
 // out[], in[] (origins of the tile in them), ldc (their row stride), rows, n_valid (valid extents of the tile).
 // The sum over K runs over n_segs segments of nk iterations each (segments: the shared experts of
 // a down projection, the two products of an input gradient); a segment functor supplies where the
@@ -129,7 +129,7 @@ struct MfmaDmaCore {
   static constexpr int TILE_BYTES = (A_SLOTS * A_ELEMS + B_SLOTS * B_SET_ELEMS) * ES;
   static constexpr int LDS_BYTES = TILE_BYTES;
   // blocks per CU the register allocation aims at (LDS allows as many)
-  static constexpr int BLOCKS_PER_CU = LDS_BYTES > 80 * 1024 ? 1 : NB * TM * TN * AR <= 64 ? 2 : 1;
+  static constexpr int BLOCKS_PER_CU = LDS_BYTES > 80 * 1024 ? 1 : DEPTH == 0 ? 4 : NB * TM * TN * AR <= 64 ? 2 : 1;
   static constexpr int A_NI = BM / (8 * NW), B_NI = BN / (8 * NW);  // wave-wide loads per wave and tile
   static constexpr int PR_KC = 8;  // 16-byte pieces per row of a K-contiguous tile
   static_assert(NW == 4 || NW == 8, "four or eight wavefronts per block");
@@ -469,15 +469,19 @@ struct MfmaDmaCore {
         for (int p = 0; p < NPASS; p++)
           piece[x][p] = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc(epi.in[x], bytes), g0 + (i * 32 + p * RPP) * ldb, 0, 0);
     };
-    auto store_out = [&](int i) __attribute__((always_inline)) {
-      if (col_ok) {
+    // the row pieces of block i
+    auto store_pieces = [&](const auto& r, int i) __attribute__((always_inline)) {
+      auto put = [&](auto hint) __attribute__((always_inline)) {
 #pragma unroll
         for (int x = 0; x < NOUT; x++)
 #pragma unroll
           for (int p = 0; p < NPASS; p++)
-            __builtin_amdgcn_raw_buffer_store_b128(piece[x][p], make_rsrc(epi.out[x], bytes), g0 + (i * 32 + p * RPP) * ldb, 0,
-                                                   Epi::NT ? 2 : 0);
-      }
+            __builtin_amdgcn_raw_buffer_store_b128(r[x][p], make_rsrc(epi.out[x], bytes), g0 + (i * 32 + p * RPP) * ldb, 0,
+                                                   decltype(hint)::value);
+      };
+      if (!col_ok) return;
+      if (epi.stream()) put(std::integral_constant<int, 2>());
+      else put(std::integral_constant<int, 0>());
     };
     if (NAUX > 0) load_aux(0);
     float scale[TM];
@@ -517,16 +521,9 @@ struct MfmaDmaCore {
         for (int x = 0; x < NOUT; x++)
 #pragma unroll
           for (int p = 0; p < NPASS; p++) r[x][p] = *reinterpret_cast<const u32x4_t*>(stage + x * BLOCK + row_at(p));
-        if (col_ok) {
-#pragma unroll
-          for (int x = 0; x < NOUT; x++)
-#pragma unroll
-            for (int p = 0; p < NPASS; p++)
-              __builtin_amdgcn_raw_buffer_store_b128(r[x][p], make_rsrc(epi.out[x], bytes), g0 + (i * 32 + p * RPP) * ldb, 0,
-                                                     Epi::NT ? 2 : 0);
-        }
+        store_pieces(r, i);
       } else {
-        if (i > 0) store_out(i - 1);
+        if (i > 0) store_pieces(piece, i - 1);
 #pragma unroll
         for (int x = 0; x < NOUT; x++)
 #pragma unroll
@@ -534,7 +531,7 @@ struct MfmaDmaCore {
       }
       asm volatile("" ::: "memory");
     }
-    if (NAUX == 0) store_out(NI - 1);
+    if (NAUX == 0) store_pieces(piece, NI - 1);
   }
 
   // (the valid extents are not needed here: the descriptors' byte counts zero-fill the loads and bound
@@ -752,8 +749,13 @@ struct MfmaDmaCore {
         static_for<KS>([&](auto ks_c) __attribute__((always_inline)) {
           constexpr int ks = decltype(ks_c)::value;
           if (ks * (BK / KS) >= s0.k_left) return;  // uniform: the remaining k rows of the tile are zero
-          static_for<kFragLoads>([&](auto r) __attribute__((always_inline)) { load_frag_n<ks, decltype(r)::value>(la, lb, f[0]); });
-          static_for<kMfma>([&](auto m) __attribute__((always_inline)) { mfma_n<decltype(m)::value>(acc, f[0]); });
+          // (one A fragment ahead, no more: the registers of four blocks per CU have no room for all of them)
+          static_assert(NB == 1 && SUB == 1, "one row of accumulator tiles after the other");
+          static_for<TN + 1>([&](auto r) __attribute__((always_inline)) { load_frag_n<ks, (decltype(r)::value + TM) % (TM + TN)>(la, lb, f[0]); });
+          static_for<TM>([&](auto i) __attribute__((always_inline)) {
+            if constexpr (decltype(i)::value + 1 < TM) load_frag_n<ks, decltype(i)::value + 1>(la, lb, f[0]);
+            static_for<TN>([&](auto j) __attribute__((always_inline)) { mfma_n<decltype(i)::value * TN + decltype(j)::value>(acc, f[0]); });
+          });
         });
         step(s0);
       }

@@ -115,3 +115,26 @@ def test_nothing_leaks_from_other_groups(dtype, d, F, ffn, poison):
             if e != bad:
                 assert all(torch.equal(a[off[e]:off[e + 1]], b[off[e]:off[e + 1]]) for a, b in zip(clean[0], got[0])), (bad, e)
                 assert all(torch.equal(a[e], b[e]) for a, b in zip(clean[1], got[1])), (bad, e)
+
+
+# rows of one group, width: row tiles x column tiles (128 wide) that fill no round of 256 tiles, one exactly, a few, and more
+# than are dealt in short runs; last bands of one to four row tiles
+@pytest.mark.parametrize("n,F", [(1280, 51 * 128), (1024, 64 * 128), (1793, 33 * 128), (1536, 256 * 128), (1792, 256 * 128),
+                                 (2304, 200 * 128 - 8), (40, 300 * 128)])
+def test_every_tile_of_a_launch_is_computed(n, F):
+    import paper_2502_02581_amd as moe
+
+    d, dev = 64, "cuda:0"
+    shape = moe.MoEShape(n, d, 1, 1, F, "bf16")
+    g = torch.Generator(device=dev).manual_seed(n)
+    rnd = lambda std, *s: (torch.randn(*s, generator=g, device=dev) * std).bfloat16()
+    X, Wg, Wu, Wd = rnd(1.0, n, d), rnd(d ** -0.5, 1, d, F), rnd(d ** -0.5, 1, d, F), rnd(F ** -0.5, 1, F, d)
+    G, U, H = (torch.full((n, F), float("nan"), dtype=torch.bfloat16, device=dev) for _ in range(3))
+    Y = torch.empty(n, d, dtype=torch.bfloat16, device=dev)
+    ws = torch.empty(moe.moe_expert_fwd_workspace_bytes(shape, 1, n, False), dtype=torch.uint8, device=dev)
+    moe.moe_expert_fwd(shape, 1, torch.tensor([0, n], dtype=torch.int32, device=dev), n, X, Wg, Wu, Wd, G, U, H, Y, ws)
+    for got, w in ((G, Wg), (U, Wu)):
+        want = X.float() @ w[0].float()
+        # one rounding to bf16, at most 2^-9 of the value; fp32 sums of 64 terms beside it
+        assert float(((got.float() - want).abs() - want.abs() * 2 ** -8).max()) <= 1e-5
+    assert bool(torch.isfinite(H).all())
