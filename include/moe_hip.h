@@ -282,7 +282,10 @@ int moe_expert_bwd_gather(const moe_shape_t* shape, const int32_t* offsets, cons
  * together.  Arguments and results are those of moe_expert_fwd(_gather) / moe_expert_bwd(_gather) for the routed set and
  * of moe_expert_fwd / moe_expert_bwd in shared mode for the shared one, each set with a workspace of its own (the size
  * queries of those calls); only the last bits of shared results may differ (sums over K in another number of parts).
- * Both sets are given (each of the calls above serves one set alone); they have shape's d and dtype and their own d_ff.
+ * shared may be NULL.  The sets have shape's d and dtype and their own d_ff.
+ * moe_route_dispatch_plan -- moe_route_dispatch, and the order of the routed experts' tiles, the plan that both passes of
+ * these calls otherwise derive from offsets in a kernel of their own, with active_ids [E] and n_active [1] as moe_expert_bwd
+ * writes them.  plan: moe_expert_plan_bytes(shape) bytes, valid for as long as offsets are.
  */
 typedef struct moe_expert_set {
   int32_t d_ff, n_groups, n_rows;
@@ -301,7 +304,14 @@ typedef struct moe_expert_set {
   void *dWg_c, *dWu_c, *dWd_c;
   void* ws;
   size_t ws_bytes;
+  void* plan;              /* routed set: NULL, or what moe_route_dispatch_plan wrote for these offsets (n_groups = E,
+                              n_rows = T*k); active_ids and n_active are then written by that call, not by the backward pass */
 } moe_expert_set_t;
+size_t moe_expert_plan_bytes(const moe_shape_t* shape);
+int moe_route_dispatch_plan(const moe_shape_t* shape, const float* logits, const void* X, float aux_alpha, int32_t* topk_idx,
+                            float* topk_w, int32_t* counts, int32_t* offsets, int32_t* row_of, int32_t* src_of, void* Xp,
+                            float* aux_P, float* aux_loss, void* plan, size_t plan_size, int32_t* active_ids, int32_t* n_active,
+                            void* ws, size_t ws_bytes, void* stream);
 int moe_experts_fwd(const moe_shape_t* shape, const moe_expert_set_t* routed, const moe_expert_set_t* shared, void* stream);
 int moe_experts_bwd(const moe_shape_t* shape, const moe_expert_set_t* routed, const moe_expert_set_t* shared, void* stream);
 

@@ -22,7 +22,7 @@ EXPORTS = ["moe_abi_version", "moe_last_error", "moe_route_bwd", "moe_router_fwd
            "moe_plan_overlap_degree", "moe_plan_predict_load", "moe_plan_materialize", "moe_plan_dispatch",
            "moe_dispatch_static", "moe_mfma_probe", "moe_expert_fwd_gather", "moe_expert_bwd_gather",
            "moe_route_dispatch_workspace_bytes", "moe_route_dispatch", "moe_route_aux_bwd", "moe_experts_fwd",
-           "moe_experts_bwd"]
+           "moe_experts_bwd", "moe_expert_plan_bytes", "moe_route_dispatch_plan"]
 
 
 class MoEError(RuntimeError):
@@ -33,17 +33,11 @@ class _CShape(ctypes.Structure):
     _fields_ = [(n, ctypes.c_int32) for n in ("T", "d", "E", "k", "d_ff", "dtype", "gate", "renorm")]
 
 
-# one set of experts of moe_experts_fwd / _bwd: the members of moe_expert_set_t, tensors with their element types
-# ("data": that of the layer)
-_SET_TENSORS = (("offsets", torch.int32), ("src_of", torch.int32), ("Xin", "data"), ("Wg", "data"), ("Wu", "data"), ("Wd", "data"),
-                ("G", "data"), ("U", "data"), ("H", "data"), ("Yout", "data"), ("dYin", "data"), ("dY", "data"),
-                ("row_w", torch.float32), ("dXin", "data"), ("active_ids", torch.int32), ("n_active", torch.int32),
-                ("dWg_c", "data"), ("dWu_c", "data"), ("dWd_c", "data"), ("ws", None))
-
-
-class _CExpertSet(ctypes.Structure):
-    _fields_ = ([(n, ctypes.c_int32) for n in ("d_ff", "n_groups", "n_rows")] + [(n, ctypes.c_void_p) for n, _ in _SET_TENSORS] +
-                [("ws_bytes", ctypes.c_size_t)])
+class _CExpertSet(ctypes.Structure):   # moe_expert_set_t
+    _fields_ = ([(n, ctypes.c_int32) for n in ("d_ff", "n_groups", "n_rows")] +
+                [(n, ctypes.c_void_p) for n in ("offsets", "src_of", "Xin", "Wg", "Wu", "Wd", "G", "U", "H", "Yout", "dYin", "dY",
+                                                "row_w", "dXin", "active_ids", "n_active", "dWg_c", "dWu_c", "dWd_c", "ws")] +
+                [("ws_bytes", ctypes.c_size_t), ("plan", ctypes.c_void_p)])
 
 
 @dataclasses.dataclass(frozen=True)
@@ -58,8 +52,12 @@ class MoEShape:
     renorm: bool = True
 
     def c(self) -> _CShape:
-        return _CShape(self.T, self.d, self.E, self.k, self.d_ff, MOE_F32 if self.dtype == "f32" else MOE_BF16,
-                       MOE_GATE_SOFTMAX if self.gate == "softmax" else MOE_GATE_SIGMOID, int(self.renorm))
+        c = self.__dict__.get("_c")   # the members never change, so their C form is made once
+        if c is None:
+            c = _CShape(self.T, self.d, self.E, self.k, self.d_ff, MOE_F32 if self.dtype == "f32" else MOE_BF16,
+                        MOE_GATE_SOFTMAX if self.gate == "softmax" else MOE_GATE_SIGMOID, int(self.renorm))
+            object.__setattr__(self, "_c", c)
+        return c
 
     @property
     def torch_dtype(self) -> torch.dtype:
@@ -121,6 +119,10 @@ def load_library():
     lib.moe_route_dispatch_workspace_bytes.argtypes = [shp]
     lib.moe_route_dispatch.restype = ctypes.c_int
     lib.moe_route_dispatch.argtypes = [shp, vp, vp, ctypes.c_float] + [vp] * 10 + [sz, vp]
+    lib.moe_expert_plan_bytes.restype = sz
+    lib.moe_expert_plan_bytes.argtypes = [shp]
+    lib.moe_route_dispatch_plan.restype = ctypes.c_int
+    lib.moe_route_dispatch_plan.argtypes = [shp, vp, vp, ctypes.c_float] + [vp] * 10 + [sz, vp, vp, vp, sz, vp]
     lib.moe_route_aux_bwd.restype = ctypes.c_int
     lib.moe_route_aux_bwd.argtypes = [shp, vp, vp, vp, vp, ctypes.c_float, ctypes.c_float, vp, vp]
     lib.moe_dispatch_static.restype = ctypes.c_int
@@ -161,13 +163,13 @@ def _ptr(t: Optional[torch.Tensor], dtype=None, what="tensor"):
         raise MoEError(f"{what} must be contiguous")
     if dtype is not None and t.dtype != dtype:
         raise MoEError(f"{what} must be {dtype}, got {t.dtype}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
-def _stream(stream) -> ctypes.c_void_p:
+def _stream(stream) -> int:
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+        return torch.cuda.current_stream().cuda_stream
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _check(rc: int, who: str):
@@ -337,6 +339,24 @@ def moe_route_dispatch(shape: MoEShape, logits, X, aux_alpha, topk_idx, topk_w, 
     _check(rc, "moe_route_dispatch")
 
 
+def moe_expert_plan_bytes(shape: MoEShape) -> int:
+    return int(load_library().moe_expert_plan_bytes(ctypes.byref(shape.c())))
+
+
+def moe_route_dispatch_plan(shape: MoEShape, logits, X, aux_alpha, topk_idx, topk_w, counts, offsets, row_of, src_of, Xp,
+                            aux_P, aux_loss, plan, active_ids, n_active, ws, stream=None):
+    """moe_route_dispatch that also writes the plan of the experts' products, active_ids and n_active."""
+    dt = shape.torch_dtype
+    rc = load_library().moe_route_dispatch_plan(
+        ctypes.byref(shape.c()), _ptr(logits, torch.float32, "logits"), _ptr(X, dt, "X"), float(aux_alpha),
+        _ptr(topk_idx, torch.int32, "topk_idx"), _ptr(topk_w, torch.float32, "topk_w"), _ptr(counts, torch.int32, "counts"),
+        _ptr(offsets, torch.int32, "offsets"), _ptr(row_of, torch.int32, "row_of"), _ptr(src_of, torch.int32, "src_of"),
+        _ptr(Xp, dt, "Xp"), _ptr(aux_P, torch.float32, "aux_P"), _ptr(aux_loss, torch.float32, "aux_loss"),
+        _ptr(plan, torch.uint8, "plan"), plan.numel(), _ptr(active_ids, torch.int32, "active_ids"),
+        _ptr(n_active, torch.int32, "n_active"), _ptr(ws, None, "ws"), ws.numel() * ws.element_size(), _stream(stream))
+    _check(rc, "moe_route_dispatch_plan")
+
+
 def moe_route_aux_bwd(shape: MoEShape, logits, topk_idx, dw, counts, alpha, dloss, dlogits, stream=None):
     """moe_route_bwd + moe_aux_loss_bwd(accumulate) in one kernel."""
     rc = load_library().moe_route_aux_bwd(ctypes.byref(shape.c()), _ptr(logits, torch.float32, "logits"),
@@ -400,28 +420,31 @@ def moe_expert_bwd_gather(shape: MoEShape, offsets, src_of, Xp, Wg, Wu, Wd, G, U
     _check(rc, "moe_expert_bwd_gather")
 
 
-def _expert_set(shape: MoEShape, d_ff, n_groups, n_rows, **tensors) -> _CExpertSet:
-    s = _CExpertSet(d_ff=d_ff, n_groups=n_groups, n_rows=n_rows)
-    for name, dt in _SET_TENSORS:
-        setattr(s, name, _ptr(tensors.pop(name, None), shape.torch_dtype if dt == "data" else dt, name))
-    s.ws_bytes = tensors.pop("ws_bytes")
-    if tensors:
-        raise MoEError(f"unknown members of an expert set: {sorted(tensors)}")
-    return s
+def _expert_set(shape: MoEShape, d_ff, n_groups, n_rows, ws, ws_bytes, Xin=None, Wg=None, Wu=None, Wd=None, G=None, U=None,
+                H=None, Yout=None, offsets=None, src_of=None, dYin=None, dY=None, row_w=None, dXin=None, active_ids=None,
+                n_active=None, dWg_c=None, dWu_c=None, dWd_c=None, plan=None) -> _CExpertSet:
+    dt, i32 = shape.torch_dtype, torch.int32
+    return _CExpertSet(
+        d_ff, n_groups, n_rows, _ptr(offsets, i32, "offsets"), _ptr(src_of, i32, "src_of"), _ptr(Xin, dt, "Xin"),
+        _ptr(Wg, dt, "Wg"), _ptr(Wu, dt, "Wu"), _ptr(Wd, dt, "Wd"), _ptr(G, dt, "G"), _ptr(U, dt, "U"), _ptr(H, dt, "H"),
+        _ptr(Yout, dt, "Yout"), _ptr(dYin, dt, "dYin"), _ptr(dY, dt, "dY"), _ptr(row_w, torch.float32, "row_w"),
+        _ptr(dXin, dt, "dXin"), _ptr(active_ids, i32, "active_ids"), _ptr(n_active, i32, "n_active"),
+        _ptr(dWg_c, dt, "dWg_c"), _ptr(dWu_c, dt, "dWu_c"), _ptr(dWd_c, dt, "dWd_c"), _ptr(ws, None, "ws"), ws_bytes,
+        _ptr(plan, torch.uint8, "plan"))
 
 
-def moe_experts_fwd(shape: MoEShape, routed: dict, shared: dict, stream=None):
+def moe_experts_fwd(shape: MoEShape, routed: dict, shared: Optional[dict], stream=None):
     """moe_expert_fwd (or, with src_of, _gather) of the routed experts and of the shared ones in common launches.  The
     dicts hold the members of moe_expert_set_t: d_ff, n_groups, n_rows, tensors, ws and ws_bytes."""
     rc = load_library().moe_experts_fwd(ctypes.byref(shape.c()), ctypes.byref(_expert_set(shape, **routed)),
-                                        ctypes.byref(_expert_set(shape, **shared)), _stream(stream))
+                                        ctypes.byref(_expert_set(shape, **shared)) if shared else None, _stream(stream))
     _check(rc, "moe_experts_fwd")
 
 
-def moe_experts_bwd(shape: MoEShape, routed: dict, shared: dict, stream=None):
+def moe_experts_bwd(shape: MoEShape, routed: dict, shared: Optional[dict], stream=None):
     """moe_expert_bwd (or, with src_of, _gather) of the routed experts and of the shared ones in common launches."""
     rc = load_library().moe_experts_bwd(ctypes.byref(shape.c()), ctypes.byref(_expert_set(shape, **routed)),
-                                        ctypes.byref(_expert_set(shape, **shared)), _stream(stream))
+                                        ctypes.byref(_expert_set(shape, **shared)) if shared else None, _stream(stream))
     _check(rc, "moe_experts_bwd")
 
 
@@ -480,13 +503,14 @@ def moe_profile_report() -> Dict[str, tuple]:
 class MoEHotPath:
     """Owns the device buffers of one layer and chains the C calls of a training step.
 
-    forward():  moe_route -> moe_dispatch -> moe_expert_fwd (with shared experts: moe_experts_fwd) -> moe_combine
-    backward(): moe_combine_bwd -> moe_expert_bwd (with shared experts: moe_experts_bwd) -> moe_combine (unit
-                weights) -> moe_route_bwd (gradient of the router logits)
+    forward():  moe_route -> moe_dispatch -> moe_experts_fwd (routed and shared) -> moe_combine
+    backward(): moe_combine_bwd -> moe_experts_bwd (routed and shared) -> moe_combine (unit weights)
+                -> moe_route_bwd (gradient of the router logits)
     With aux_alpha > 0, forward() also evaluates the auxiliary load-balancing loss (moe_aux_loss, after
     the dispatch has counted the loads) and backward() adds its gradient to dlogits (moe_aux_loss_bwd).
-    With fused (the default), gate + dispatch + loss go through moe_route_dispatch and the two backward
-    calls of the gate through moe_route_aux_bwd: the same results from four launches fewer.
+    With fused (the default), gate + dispatch + loss + the plan of the experts' products go through
+    moe_route_dispatch_plan and the two backward calls of the gate through moe_route_aux_bwd: the same results from
+    six launches fewer.  The plan belongs to the routing of the last forward(), as row_of and offsets do.
     No arithmetic happens here; tensors are only allocated and handed to the library.
 
     The shared experts depend on nothing the routed experts produce, so their products run in the launches of the
@@ -541,62 +565,52 @@ class MoEHotPath:
                            "aux_loss": torch.empty(1, dtype=torch.float32, device=dev)})
             ws = max(ws, moe_aux_loss_workspace_bytes(s))
         self.ws = torch.empty(ws, dtype=torch.uint8, device=dev)
+        # the order of the routed experts' tiles, written by the fused prologue for both passes
+        self.plan = torch.zeros(moe_expert_plan_bytes(s), dtype=torch.uint8, device=dev)
 
     def _ws_pieces(self):
         """The workspace of the routed and that of the shared experts (keywords of an expert set)."""
-        return {"ws": self.ws[:self.ws_routed], "ws_bytes": self.ws_routed}, \
+        return {"ws": self.ws[:self.ws_routed], "ws_bytes": self.ws_routed, "plan": self.plan if self.fused else None}, \
                {"ws": self.ws[self.ws_routed:], "ws_bytes": self.ws.numel() - self.ws_routed}
 
     def forward(self, logits, X, Wg, Wu, Wd, Wsg=None, Wsu=None, Wsd=None, stream=None):
         s, b = self.shape, self.b
         A = s.T * s.k
+        stream = _stream(stream)
         self._logits = logits  # the gate's backward reads them again
         if self.fused:
-            moe_route_dispatch(s, logits, X, self.aux_alpha, b["topk_idx"], b["topk_w"], b["counts"], b["offsets"],
-                               b["row_of"], b["src_of"], b["Xp"], b.get("aux_P"), b.get("aux_loss"), self.ws, stream)
+            moe_route_dispatch_plan(s, logits, X, self.aux_alpha, b["topk_idx"], b["topk_w"], b["counts"], b["offsets"],
+                                    b["row_of"], b["src_of"], b["Xp"], b.get("aux_P"), b.get("aux_loss"), self.plan,
+                                    b["active_ids"], b["n_active"], self.ws, stream)
         else:
             moe_route(s, logits, b["topk_idx"], b["topk_w"], stream)
             moe_dispatch(s, X, b["topk_idx"], b["counts"], b["offsets"], b["row_of"], b["src_of"], b["Xp"], self.ws,
                          stream)
             if self.aux_alpha > 0:
                 moe_aux_loss(s, logits, b["counts"], self.aux_alpha, b["aux_P"], b["aux_loss"], self.ws, stream)
-        if self.S:
-            ws, ws_shared = self._ws_pieces()
-            moe_experts_fwd(s, dict(d_ff=s.d_ff, n_groups=s.E, n_rows=A, offsets=b["offsets"],
-                                    src_of=b["src_of"] if self.gather else None, Xin=X if self.gather else b["Xp"],
-                                    Wg=Wg, Wu=Wu, Wd=Wd, G=b["G"], U=b["U"], H=b["H"], Yout=b["Yp"], **ws),
-                            dict(d_ff=self.Fs, n_groups=self.S, n_rows=s.T, Xin=X, Wg=Wsg, Wu=Wsu, Wd=Wsd, G=b["Gs"],
-                                 U=b["Us"], H=b["Hs"], Yout=b["Ysh"], **ws_shared), stream)
-        elif self.gather:
-            moe_expert_fwd_gather(s, b["offsets"], b["src_of"], X, Wg, Wu, Wd, b["G"], b["U"], b["H"], b["Yp"], self.ws,
-                                  stream)
-        else:
-            moe_expert_fwd(s, s.E, b["offsets"], A, b["Xp"], Wg, Wu, Wd, b["G"], b["U"], b["H"], b["Yp"], self.ws, stream)
+        ws, ws_shared = self._ws_pieces()
+        shared = dict(d_ff=self.Fs, n_groups=self.S, n_rows=s.T, Xin=X, Wg=Wsg, Wu=Wsu, Wd=Wsd, G=b["Gs"], U=b["Us"],
+                      H=b["Hs"], Yout=b["Ysh"], **ws_shared) if self.S else None
+        moe_experts_fwd(s, dict(d_ff=s.d_ff, n_groups=s.E, n_rows=A, offsets=b["offsets"],
+                                src_of=b["src_of"] if self.gather else None, Xin=X if self.gather else b["Xp"], Wg=Wg,
+                                Wu=Wu, Wd=Wd, G=b["G"], U=b["U"], H=b["H"], Yout=b["Yp"], **ws), shared, stream)
         moe_combine(s, b["Yp"], b["row_of"], b["topk_w"], b["Ysh"] if self.S else None, b["Y"], stream)
         return b["Y"]
 
     def backward(self, dY, X, Wg, Wu, Wd, Wsg=None, Wsu=None, Wsd=None, stream=None):
         s, b = self.shape, self.b
         A = s.T * s.k
+        stream = _stream(stream)
         moe_combine_bwd(s, dY, b["Yp"], b["row_of"], b["topk_w"], b["dYp"], b["dw"], stream)
-        if self.S:
-            ws, ws_shared = self._ws_pieces()
-            in_place = dict(src_of=b["src_of"], dY=dY, row_w=b["topk_w"]) if self.gather else {}
-            moe_experts_bwd(s, dict(d_ff=s.d_ff, n_groups=s.E, n_rows=A, offsets=b["offsets"], Xin=b["Xp"], Wg=Wg, Wu=Wu,
-                                    Wd=Wd, G=b["G"], U=b["U"], H=b["H"], dYin=b["dYp"], dXin=b["dXp"],
-                                    active_ids=b["active_ids"], n_active=b["n_active"], dWg_c=b["dWg_c"],
-                                    dWu_c=b["dWu_c"], dWd_c=b["dWd_c"], **in_place, **ws),
-                            dict(d_ff=self.Fs, n_groups=self.S, n_rows=s.T, Xin=X, Wg=Wsg, Wu=Wsu, Wd=Wsd, G=b["Gs"],
-                                 U=b["Us"], H=b["Hs"], dYin=dY, dXin=b["dXsh"], active_ids=b["s_active_ids"],
-                                 n_active=b["s_n_active"], dWg_c=b["dWsg"], dWu_c=b["dWsu"], dWd_c=b["dWsd"],
-                                 **ws_shared), stream)
-        elif self.gather:
-            moe_expert_bwd_gather(s, b["offsets"], b["src_of"], b["Xp"], Wg, Wu, Wd, b["G"], b["U"], b["H"], dY,
-                                  b["topk_w"], b["dYp"], b["dXp"], b["active_ids"], b["n_active"], b["dWg_c"],
-                                  b["dWu_c"], b["dWd_c"], self.ws, stream)
-        else:
-            moe_expert_bwd(s, s.E, b["offsets"], A, b["Xp"], Wg, Wu, Wd, b["G"], b["U"], b["H"], b["dYp"], b["dXp"],
-                           b["active_ids"], b["n_active"], b["dWg_c"], b["dWu_c"], b["dWd_c"], self.ws, stream)
+        ws, ws_shared = self._ws_pieces()
+        in_place = dict(src_of=b["src_of"], dY=dY, row_w=b["topk_w"]) if self.gather else {}
+        shared = dict(d_ff=self.Fs, n_groups=self.S, n_rows=s.T, Xin=X, Wg=Wsg, Wu=Wsu, Wd=Wsd, G=b["Gs"], U=b["Us"],
+                      H=b["Hs"], dYin=dY, dXin=b["dXsh"], active_ids=b["s_active_ids"], n_active=b["s_n_active"],
+                      dWg_c=b["dWsg"], dWu_c=b["dWsu"], dWd_c=b["dWsd"], **ws_shared) if self.S else None
+        moe_experts_bwd(s, dict(d_ff=s.d_ff, n_groups=s.E, n_rows=A, offsets=b["offsets"], Xin=b["Xp"], Wg=Wg, Wu=Wu, Wd=Wd,
+                                G=b["G"], U=b["U"], H=b["H"], dYin=b["dYp"], dXin=b["dXp"], active_ids=b["active_ids"],
+                                n_active=b["n_active"], dWg_c=b["dWg_c"], dWu_c=b["dWu_c"], dWd_c=b["dWd_c"], **in_place,
+                                **ws), shared, stream)
         moe_combine(s, b["dXp"], b["row_of"], None, b["dXsh"] if self.S else None, b["dX"], stream)
         if self.fused and self.aux_alpha > 0:
             moe_route_aux_bwd(s, self._logits, b["topk_idx"], b["dw"], b["counts"], self.aux_alpha, 1.0, b["dlogits"],

@@ -12,6 +12,7 @@
 #include <mutex>
 
 #include "gate_device.h"
+#include "gemm_plan.h"
 #include "moe_common.h"
 
 namespace moe {
@@ -43,6 +44,10 @@ __global__ __launch_bounds__(64) void dispatch_count(const int32_t* __restrict__
 // over c, then the thread rewrites its run as exclusive prefixes.  Loads go a batch at a time ahead of the dependent
 // additions and stores.  (Batches of 8, the shares read
 // after the counters, as many runs as threads: T = 256, E = 8: 8.5 us, now 5.1; T = 2777, E = 60: 10.7, now 8.4.)
+// With pl.tiles, the block goes on to the plan of the experts' products: 2 to 3 us more here take the place of a launch of its
+// own in the forward pass and one in the backward pass, 4 to 7 us each.  (Each against the same earlier state on its own box,
+// with the two launches and without: T = 8192, d = 768, 64 experts, training 0.978 and 0.967 of its time; T = 4096, d = 2048, 60 experts 0.959 and
+// 0.931; T = 256, d = 128, 8 experts, fp32 0.976 and 0.920, the latter with the cheaper marshalling of the calls.)
 // With `partial` (the fused prologue), the block also finishes the auxiliary load-balancing loss: P_e from
 // the per-chunk sums of the gate's shares (added in the same fixed order as the counters), then
 // L = alpha E sum_e (counts[e] / (T k)) P_e over ascending e.
@@ -51,7 +56,8 @@ __global__ __launch_bounds__(1024) void dispatch_scan(int32_t* __restrict__ hist
                                                       int32_t* __restrict__ counts,
                                                       int32_t* __restrict__ offsets,
                                                       const float* __restrict__ partial, float* __restrict__ P,
-                                                      float* __restrict__ loss, int T, int k, float alpha) {
+                                                      float* __restrict__ loss, int T, int k, float alpha, Plan pl,
+                                                      int plan_bm, int32_t* active_ids, int32_t* n_active) {
   __shared__ __align__(16) float term[MOE_MAX_EXPERTS];
   __shared__ __align__(16) int32_t wsum[16];
   __shared__ int32_t part[1024];
@@ -109,6 +115,7 @@ __global__ __launch_bounds__(1024) void dispatch_scan(int32_t* __restrict__ hist
   const int end = block_scan_1024(run, wsum, all);
   if (e < E) offsets[e + 1] = end;
   if (e == 0) offsets[0] = 0;
+  if (pl.tiles) build_plan(e < E ? run : 0, end - run, E, plan_bm, pl, active_ids, n_active);
   if (partial) {
     float t = 0.f;
     if (e < E) {
@@ -370,7 +377,7 @@ static void dispatch_launch(const moe_shape_t* shape, const void* X, const int32
   {
     ProfScope prof("dispatch_scan", st);
     hipLaunchKernelGGL(dispatch_scan, dim3(1), dim3(1024), 0, st, hist, n_chunks, shape->E, counts, offsets,
-                       (const float*)nullptr, (float*)nullptr, (float*)nullptr, 0, 1, 0.f);
+                       (const float*)nullptr, (float*)nullptr, (float*)nullptr, 0, 1, 0.f, Plan{}, 0, (int32_t*)nullptr, (int32_t*)nullptr);
   }
   dispatch_place(shape, X, topk_idx, offsets, row_of, src_of, Xp, hist, kChunk, n_chunks, st);
 }
@@ -478,31 +485,34 @@ extern "C" size_t moe_route_dispatch_workspace_bytes(const moe_shape_t* shape) {
   return 2 * per;  // integer histograms, then the share sums of the auxiliary loss
 }
 
-extern "C" int moe_route_dispatch(const moe_shape_t* shape, const float* logits, const void* X, float aux_alpha,
-                                  int32_t* topk_idx, float* topk_w, int32_t* counts, int32_t* offsets,
-                                  int32_t* row_of, int32_t* src_of, void* Xp, float* aux_P, float* aux_loss, void* ws,
-                                  size_t ws_bytes, void* stream) {
+// moe_route_dispatch, with the plan of the experts' products if `plan` is not NULL
+static int route_dispatch(const char* who, const moe_shape_t* shape, const float* logits, const void* X, float aux_alpha,
+                          int32_t* topk_idx, float* topk_w, int32_t* counts, int32_t* offsets, int32_t* row_of, int32_t* src_of, void* Xp,
+                          float* aux_P, float* aux_loss, void* plan, int32_t* active_ids, int32_t* n_active, void* ws,
+                          size_t ws_bytes, void* stream) {
   using namespace moe;
-  int rc = check_shape(shape, "moe_route_dispatch");
+  int rc = check_shape(shape, who);
   if (rc) return rc;
   if (!counts || !offsets || !ws || (aux_P != nullptr) != (aux_loss != nullptr) ||
       (shape->T > 0 && (!logits || !topk_idx || !topk_w || !row_of || !src_of || !X || !Xp))) {
-    set_error("moe_route_dispatch: null pointer (aux_P and aux_loss go together)");
+    set_error("%s: null pointer (aux_P and aux_loss go together)", who);
     return MOE_EINVAL;
   }
   if (!aligned16(X) || !aligned16(Xp) || !aligned16(ws)) {
-    set_error("moe_route_dispatch: X, Xp and ws must be 16-byte aligned");
+    set_error("%s: X, Xp and ws must be 16-byte aligned", who);
     return MOE_EINVAL;
   }
   const size_t need = moe_route_dispatch_workspace_bytes(shape);
   if (ws_bytes < need) {
-    set_error("moe_route_dispatch: workspace of %zu bytes, need %zu", ws_bytes, need);
+    set_error("%s: workspace of %zu bytes, need %zu", who, ws_bytes, need);
     return MOE_EWS;
   }
   hipStream_t st = (hipStream_t)stream;
   const int T = shape->T, E = shape->E, k = shape->k;
   const int tpc = prologue_tokens_per_chunk(shape), n_chunks = prologue_chunks(shape);
   int32_t* hist = (int32_t*)ws;
+  const int bm = plan_tile_rows(shape->dtype);
+  const Plan pl = plan ? carve_plan(plan, E, max_row_tiles(E, T * k, bm)) : Plan{};
   float* partial = aux_P ? (float*)((char*)ws + need / 2) : nullptr;
   if (n_chunks > 0) {
     ProfScope prof("route_hist_kernel", st);
@@ -519,8 +529,35 @@ extern "C" int moe_route_dispatch(const moe_shape_t* shape, const float* logits,
   {
     ProfScope prof("dispatch_scan", st);
     hipLaunchKernelGGL(dispatch_scan, dim3(1), dim3(1024), 0, st, hist, n_chunks, E, counts, offsets,
-                       (const float*)partial, aux_P, aux_loss, T, k, aux_alpha);
+                       (const float*)partial, aux_P, aux_loss, T, k, aux_alpha, pl, bm, active_ids, n_active);
   }
   dispatch_place(shape, X, topk_idx, offsets, row_of, src_of, Xp, hist, tpc * k, n_chunks, st);
-  return launch_status("moe_route_dispatch");
+  return launch_status(who);
+}
+
+extern "C" int moe_route_dispatch(const moe_shape_t* shape, const float* logits, const void* X, float aux_alpha,
+                                  int32_t* topk_idx, float* topk_w, int32_t* counts, int32_t* offsets,
+                                  int32_t* row_of, int32_t* src_of, void* Xp, float* aux_P, float* aux_loss, void* ws,
+                                  size_t ws_bytes, void* stream) {
+  return route_dispatch("moe_route_dispatch", shape, logits, X, aux_alpha, topk_idx, topk_w, counts, offsets, row_of, src_of, Xp, aux_P,
+                        aux_loss, nullptr, nullptr, nullptr, ws, ws_bytes, stream);
+}
+
+extern "C" int moe_route_dispatch_plan(const moe_shape_t* shape, const float* logits, const void* X, float aux_alpha,
+                                       int32_t* topk_idx, float* topk_w, int32_t* counts, int32_t* offsets,
+                                       int32_t* row_of, int32_t* src_of, void* Xp, float* aux_P, float* aux_loss, void* plan,
+                                       size_t plan_size, int32_t* active_ids, int32_t* n_active, void* ws, size_t ws_bytes, void* stream) {
+  using namespace moe;
+  const int rc = check_shape(shape, "moe_route_dispatch_plan");
+  if (rc) return rc;
+  if (!plan || !active_ids || !n_active || !aligned16(plan)) {
+    set_error("moe_route_dispatch_plan: null or unaligned plan, active_ids or n_active");
+    return MOE_EINVAL;
+  }
+  if (plan_size < moe_expert_plan_bytes(shape)) {
+    set_error("moe_route_dispatch_plan: plan of %zu bytes, need %zu", plan_size, moe_expert_plan_bytes(shape));
+    return MOE_EWS;
+  }
+  return route_dispatch("moe_route_dispatch_plan", shape, logits, X, aux_alpha, topk_idx, topk_w, counts, offsets, row_of, src_of, Xp, aux_P,
+                        aux_loss, plan, active_ids, n_active, ws, ws_bytes, stream);
 }

@@ -13,84 +13,17 @@
 namespace moe {
 
 // ------------------------------------------------------------------------------------ plan
-// One block of 1024 threads; thread e owns group e.  Bound by latency, nothing runs beside it: the pass
-// for the group ranks takes four row counts per LDS read, the scans use one barrier each, and every tile has its own
-// thread, which finds the group by bisection.  (Scans of ten steps with two barriers each, one row count per read and the
-// tiles of a group written by one thread took: 60 groups 8.6 us, 64 groups 9.3, 8 groups 5.3; this form 6.6, 6.7, 3.7.)
+// For calls that bring no plan (moe_route_dispatch_plan builds one in its own kernels).
 // offsets == NULL (a shared call without rows, whose active_ids and n_active are all there is to write): no group has rows.
 __global__ __launch_bounds__(1024) void plan_kernel(const int32_t* __restrict__ offsets, int n_groups, int BM, Plan pl,
                                                     int32_t* active_ids, int32_t* n_active) {
-  __shared__ __align__(16) int32_t rows_of[1024];                    // by group
-  __shared__ int32_t cnt[1024], first[1024], tile0[1024], ord[1024];  // by rank
-  __shared__ __align__(16) int32_t wsum[2][16];
   const int e = threadIdx.x;
   int c = 0, st = 0;
   if (e < n_groups && offsets) {
     st = offsets[e];
     c = max(offsets[e + 1] - st, 0);
   }
-  rows_of[e] = e < n_groups ? c : -1;
-  int total_active;
-  const int slot = block_scan_1024(e < n_groups && c > 0, wsum[0], total_active) - 1;
-  if (e < n_groups) {
-    // Launch order of the groups: descending row count (ties: ascending id), so that the short tiles
-    // of the light groups fill the end of a launch.  Of the other wavefronts' groups the earlier ones precede
-    // this one in a tie.
-    const int own = e & ~(kWave - 1);
-    int rank = 0;
-    auto count = [&](int from, int to, int limit) __attribute__((always_inline)) {  // groups of more rows than `limit`
-#pragma unroll 4
-      for (int o = from; o < to; o += 4) {
-        const int4 q = *reinterpret_cast<const int4*>(rows_of + o);
-        rank += (q.x > limit) + (q.y > limit) + (q.z > limit) + (q.w > limit);
-      }
-    };
-    count(0, own, c - 1);
-#pragma unroll 4
-    for (int o = own; o < min(own + kWave, n_groups); o++) rank += rows_of[o] > (o < e ? c - 1 : c);
-    count(own + kWave, n_groups, c);
-    ord[rank] = e;
-    cnt[rank] = c;
-    first[rank] = st;
-    pl.ginfo[rank] = make_int4(e, c, st, c > 0 ? slot : -1);
-    if (active_ids) {
-      if (c > 0) active_ids[slot] = e;
-      if (e >= total_active) active_ids[e] = -1;
-    }
-  }
-  if (e == 0 && n_active) *n_active = total_active;
-  __syncthreads();
-  // Row tiles, groups in descending size: full tiles of BM rows, and the remainder r of a group cut into tiles of
-  // BM/2, BM/4 and BM/8 rows so that little MFMA work is spent on padding; in eighths of BM: r > 6: one full tile;
-  // (5,6]: 4 + 2; (4,5]: 4 + 1; (3,4]: 4; (2,3]: 2 + 1; (1,2]: 2; (0,1]: 1.
-  auto eighths = [&](int rows) { return ((rows % BM) * 8 + BM - 1) / BM; };
-  const int cg = e < n_groups ? cnt[e] : 0;
-  const int r8 = eighths(cg);
-  const int nt = cg / BM + (r8 > 0) + (r8 == 3 || r8 == 5 || r8 == 6);
-  int n_tiles;
-  const int end = block_scan_1024(nt, wsum[1], n_tiles);
-  tile0[e] = end - nt;
-  if (e == 0) *pl.n_tiles = n_tiles;
-  __syncthreads();
-  for (int i = e; i < n_tiles; i += 1024) {
-    int lo = 0, hi = n_groups;  // the last group whose tiles start at or before i (groups without tiles come last)
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (tile0[mid] <= i) lo = mid;
-      else hi = mid;
-    }
-    const int rows = cnt[lo], full = rows / BM, r = eighths(rows), in_group = i - tile0[lo];
-    const int k0 = r > 6 ? 0 : r > 3 ? 1 : r > 1 ? 2 : 3;  // kinds (heights BM >> kind) of the remainder's tiles
-    const int k1 = r == 6 ? 2 : 3;
-    const int kind = in_group < full ? 0 : in_group == full ? k0 : k1;
-    const int row = min(in_group, full) * BM + (in_group > full ? BM >> k0 : 0);
-    RowTile t;
-    t.group = ord[lo];
-    t.row0_in = first[lo] + row;
-    t.rows = min(BM >> kind, rows - row) | (kind << 16);
-    t.row0_out = t.row0_in;
-    pl.tiles[i] = t;
-  }
+  build_plan(c, st, n_groups, BM, pl, active_ids, n_active);
 }
 
 void launch_plan(const int32_t* offsets, int n_groups, int BM, const Plan& pl, int32_t* active_ids, int32_t* n_active, hipStream_t st) {
@@ -342,12 +275,12 @@ static int check_set(const moe_shape_t* shape, const moe_expert_set_t* x, bool r
   for (const void* p : fwd_ptrs) aligned = aligned && aligned16(p);
   if (bwd)
     for (const void* p : bwd_ptrs) aligned = aligned && aligned16(p);
-  if (!aligned) {
+  if (!aligned || !aligned16(x->plan)) {
     set_error("%s: every tensor must be 16-byte aligned", who);
     return MOE_EINVAL;
   }
-  if (gather && (x->n_groups != shape->E || x->n_rows != shape->T * shape->k)) {
-    set_error("%s: rows read in place are those of the shape: E groups, T*k rows", who);
+  if ((gather || x->plan) && (!routed || x->n_groups != shape->E || x->n_rows != shape->T * shape->k)) {
+    set_error("%s: rows read in place, and those of a plan, are those of the shape: E groups, T*k rows", who);
     return MOE_EINVAL;
   }
   if (gather && (int64_t)shape->T * shape->d * (int64_t)elem_size(shape->dtype) >= ((int64_t)1 << 32) - 4096) {
@@ -363,21 +296,28 @@ static int check_set(const moe_shape_t* shape, const moe_expert_set_t* x, bool r
 }
 static int check_sets(const moe_shape_t* shape, const moe_expert_set_t* routed, const moe_expert_set_t* shared, bool bwd, const char* who,
                       moe_shape_t (&s)[2], size_t (&need)[2]) {
-  if (!shape || !routed || !shared) {
+  if (!shape || !routed) {
     set_error("%s: null pointer", who);
     return MOE_EINVAL;
   }
   const int rc = check_set(shape, routed, true, bwd, who, s[0], need[0]);
-  return rc ? rc : check_set(shape, shared, false, bwd, who, s[1], need[1]);
+  return rc || !shared ? rc : check_set(shape, shared, false, bwd, who, s[1], need[1]);
 }
 // Common launches need the same kernels for both: one activation, and cores that take both widths.  Anything else (no
 // rows on one side, rows beyond the tile cores' offsets) goes one after the other, as the two calls would.
 static bool can_share(const moe_shape_t (&s)[2], const moe_expert_set_t* routed, const moe_expert_set_t* shared) {
+  if (!shared) return false;
   const int64_t ld = std::max({s[0].d, s[0].d_ff, s[1].d_ff});
   return routed->n_rows > 0 && shared->n_rows > 0 && !routed->Wu == !shared->Wu && !wide_rows(ld, elem_size(s[0].dtype));
 }
 
 }  // namespace moe
+
+extern "C" size_t moe_expert_plan_bytes(const moe_shape_t* shape) {
+  using namespace moe;
+  if (!shape || shape->E < 1 || shape->T < 0 || shape->k < 1) return 0;
+  return align_up(plan_bytes(shape->E, max_row_tiles(shape->E, shape->T * shape->k, plan_tile_rows(shape->dtype))), 256);
+}
 
 extern "C" int moe_experts_fwd(const moe_shape_t* shape, const moe_expert_set_t* routed, const moe_expert_set_t* shared, void* stream) {
   using namespace moe;
@@ -387,19 +327,20 @@ extern "C" int moe_experts_fwd(const moe_shape_t* shape, const moe_expert_set_t*
   if (rc) return rc;
   const moe_expert_set_t* sets[2] = {routed, shared};
   FwdArgs a[2];
-  for (int i = 0; i < 2; i++) {
+  for (int i = 0; i < (shared ? 2 : 1); i++) {
     const moe_expert_set_t* x = sets[i];
     a[i] = {shape->d, x->d_ff, x->n_groups, x->n_rows, x->offsets, x->Xin, x->Wg, x->Wu, x->Wd, x->G, x->U, x->H, x->Yout,
             (char*)x->ws, (char*)x->ws + need[i], x->ws_bytes - need[i]};
+    a[i].plan = x->plan;
     if (x->src_of) { a[i].src_of = x->src_of; a[i].src_div = shape->k; a[i].src_rows = shape->T; }
   }
-  const int p0 = pick_path(&s[0]), p1 = pick_path(&s[1]);
+  const int p0 = pick_path(&s[0]), p1 = shared ? pick_path(&s[1]) : p0;
   hipStream_t st = (hipStream_t)stream;
   if (can_share(s, routed, shared)) {
     run_fwd(std::min(p0, p1), &a[0], &a[1], st);  // (PATH_BF16_TAIL takes what PATH_BF16 takes, with the same results)
   } else {
     if (routed->n_rows > 0) run_fwd(p0, &a[0], nullptr, st);
-    if (shared->n_rows > 0) run_fwd(p1, nullptr, &a[1], st);
+    if (shared && shared->n_rows > 0) run_fwd(p1, nullptr, &a[1], st);
   }
   return launch_status("moe_experts_fwd");
 }
@@ -412,23 +353,24 @@ extern "C" int moe_experts_bwd(const moe_shape_t* shape, const moe_expert_set_t*
   if (rc) return rc;
   const moe_expert_set_t* sets[2] = {routed, shared};
   BwdArgs a[2];
-  for (int i = 0; i < 2; i++) {
+  for (int i = 0; i < (shared ? 2 : 1); i++) {
     const moe_expert_set_t* x = sets[i];
     char* dG = (char*)x->ws + plan_size_for(x->n_groups, x->n_rows, i == 1);
     a[i] = {shape->d, x->d_ff, x->n_groups, x->n_rows, x->offsets, x->Xin, x->Wg, x->Wu, x->Wd, x->G, x->U, x->H, x->dYin, x->dXin,
             x->active_ids, x->n_active, x->dWg_c, x->dWu_c, x->dWd_c, (char*)x->ws, dG,
             dG + grad_size_for(&s[i], x->n_groups, x->n_rows, i == 1), (char*)x->ws + need[i], x->ws_bytes - need[i]};
+    a[i].plan = x->plan;
     if (x->src_of) {
       a[i].dY = x->dY; a[i].src_of = x->src_of; a[i].row_w = x->row_w; a[i].src_div = shape->k; a[i].src_rows = shape->T;
     }
   }
-  const int p0 = pick_path(&s[0]), p1 = pick_path(&s[1]);
+  const int p0 = pick_path(&s[0]), p1 = shared ? pick_path(&s[1]) : p0;
   hipStream_t st = (hipStream_t)stream;
   if (can_share(s, routed, shared)) {
     run_bwd(std::min(p0, p1), &a[0], &a[1], st);
   } else {
     run_bwd(p0, &a[0], nullptr, st);
-    run_bwd(p1, nullptr, &a[1], st);
+    if (shared) run_bwd(p1, nullptr, &a[1], st);
   }
   return launch_status("moe_experts_bwd");
 }

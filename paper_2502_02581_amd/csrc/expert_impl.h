@@ -396,7 +396,7 @@ __global__ __launch_bounds__(256) void reduce_kernel(Reduce p) {
 enum { PATH_F32 = 0, PATH_BF16_TAIL = 1, PATH_BF16 = 2 };
 template <int PATH> struct Cores;
 template <> struct Cores<PATH_F32> {
-  static constexpr int BM = 64, BN = 128;
+  static constexpr int BM = 64, BN = 128;  // (BM: see plan_tile_rows)
   // Bound by the fp32 matrix pipe (157 TFLOP/s).  An fp32 MFMA takes an eighth of the operand bytes per cycle of
   // a bf16 one, so even 64 x 128 tiles (dual GEMMs: 64 x 64 of each product) keep it fed from L2; small tiles
   // balance better and two blocks fit on a CU, one multiplying while the other stores.  Forward + backward of
@@ -454,9 +454,6 @@ struct LdsAttr {
     if (dev < 64) done.fetch_or(bit, std::memory_order_relaxed);
   }
 };
-
-// upper bound of the row tiles the plan kernel may emit (at most two remainder tiles per group)
-static int max_row_tiles(int n_groups, int n_rows, int BM) { return n_rows / BM + 2 * n_groups; }
 
 void launch_plan(const int32_t* offsets, int n_groups, int BM, const Plan& pl, int32_t* active_ids, int32_t* n_active, hipStream_t st);
 
@@ -741,6 +738,7 @@ struct FwdArgs {
   // its row src_of[r] / src_div
   const int32_t* src_of = nullptr;
   int src_div = 1, src_rows = 0;
+  void* plan = nullptr;  // a plan that moe_route_dispatch_plan has built
 };
 
 // The forward pass of the routed experts (r), of the shared ones (s), or of both in common launches.
@@ -777,8 +775,8 @@ void expert_fwd_impl(const FwdArgs* r, const FwdArgs* s, hipStream_t st) {
   int max_tiles = 0;
   if (r) {
     max_tiles = max_row_tiles(r->n_groups, r->n_rows, Cores<PATH>::BM);
-    const Plan pl = carve_plan(r->ws, r->n_groups, max_tiles);
-    launch_plan(r->offsets, r->n_groups, Cores<PATH>::BM, pl, nullptr, nullptr, st);
+    const Plan pl = carve_plan(r->plan ? r->plan : r->ws, r->n_groups, max_tiles);
+    if (!r->plan) launch_plan(r->offsets, r->n_groups, Cores<PATH>::BM, pl, nullptr, nullptr, st);
     rg = fill(*r, pl);
   }
   Direct up = {}, down = {};
@@ -817,6 +815,7 @@ struct BwdArgs {
   const int32_t* src_of = nullptr;
   const float* row_w = nullptr;
   int src_div = 1, src_rows = 0;
+  void* plan = nullptr;
 };
 
 // The backward pass of the routed experts (r), of the shared ones (s), or of both in common launches.  With both, either
@@ -873,8 +872,8 @@ void expert_bwd_impl(const BwdArgs* r, const BwdArgs* s, hipStream_t st) {
   int max_tiles = 0;
   if (r) {
     max_tiles = max_row_tiles(r->n_groups, r->n_rows, C::BM);
-    const Plan pl = carve_plan(r->ws, r->n_groups, max_tiles);
-    launch_plan(r->offsets, r->n_groups, C::BM, pl, r->active_ids, r->n_active, st);
+    const Plan pl = carve_plan(r->plan ? r->plan : r->ws, r->n_groups, max_tiles);
+    if (!r->plan) launch_plan(r->offsets, r->n_groups, C::BM, pl, r->active_ids, r->n_active, st);
     if (r->n_rows == 0) return;  // no group is active
     rg = fill(*r, pl);
   }

@@ -42,6 +42,85 @@ inline Plan carve_plan(void* ws, int /*n_groups*/, int max_tiles) {
   return pl;
 }
 
+// rows of the full row tiles of the tile cores
+inline int plan_tile_rows(int dtype) { return dtype == MOE_F32 ? 64 : 256; }
+// upper bound of the row tiles of a plan (at most two remainder tiles per group)
+inline int max_row_tiles(int n_groups, int n_rows, int BM) { return n_rows / BM + 2 * n_groups; }
+
+// One block of 1024 threads; thread e owns group e, which has c rows from row st on.  Bound by latency, nothing runs beside it: the pass
+// for the group ranks takes four row counts per LDS read, the scans use one barrier each, and every tile has its own
+// thread, which finds the group by bisection.  (Scans of ten steps with two barriers each, one row count per read and the
+// tiles of a group written by one thread took: 60 groups 8.6 us, 64 groups 9.3, 8 groups 5.3; this form 6.6, 6.7, 3.7,
+// as a launch of its own.)
+__device__ __forceinline__ void build_plan(int c, int st, int n_groups, int BM, const Plan& pl, int32_t* active_ids, int32_t* n_active) {
+  __shared__ __align__(16) int32_t rows_of[1024];                    // by group
+  __shared__ int32_t cnt[1024], first[1024], tile0[1024], ord[1024];  // by rank
+  __shared__ __align__(16) int32_t wsum[2][16];
+  const int e = threadIdx.x;
+  rows_of[e] = e < n_groups ? c : -1;
+  int total_active;
+  const int slot = block_scan_1024(e < n_groups && c > 0, wsum[0], total_active) - 1;
+  if (e < n_groups) {
+    // Launch order of the groups: descending row count (ties: ascending id), so that the short tiles
+    // of the light groups fill the end of a launch.  Of the other wavefronts' groups the earlier ones precede
+    // this one in a tie.
+    const int own = e & ~(kWave - 1);
+    int rank = 0;
+    auto count = [&](int from, int to, int limit) __attribute__((always_inline)) {  // groups of more rows than `limit`
+#pragma unroll 4
+      for (int o = from; o < to; o += 4) {
+        const int4 q = *reinterpret_cast<const int4*>(rows_of + o);
+        rank += (q.x > limit) + (q.y > limit) + (q.z > limit) + (q.w > limit);
+      }
+    };
+    count(0, own, c - 1);
+#pragma unroll 4
+    for (int o = own; o < min(own + kWave, n_groups); o++) rank += rows_of[o] > (o < e ? c - 1 : c);
+    count(own + kWave, n_groups, c);
+    ord[rank] = e;
+    cnt[rank] = c;
+    first[rank] = st;
+    pl.ginfo[rank] = make_int4(e, c, st, c > 0 ? slot : -1);
+    if (active_ids) {
+      if (c > 0) active_ids[slot] = e;
+      if (e >= total_active) active_ids[e] = -1;
+    }
+  }
+  if (e == 0 && n_active) *n_active = total_active;
+  __syncthreads();
+  // Row tiles, groups in descending size: full tiles of BM rows, and the remainder r of a group cut into tiles of
+  // BM/2, BM/4 and BM/8 rows so that little MFMA work is spent on padding; in eighths of BM: r > 6: one full tile;
+  // (5,6]: 4 + 2; (4,5]: 4 + 1; (3,4]: 4; (2,3]: 2 + 1; (1,2]: 2; (0,1]: 1.
+  auto eighths = [&](int rows) { return ((rows % BM) * 8 + BM - 1) / BM; };
+  const int cg = e < n_groups ? cnt[e] : 0;
+  const int r8 = eighths(cg);
+  const int nt = cg / BM + (r8 > 0) + (r8 == 3 || r8 == 5 || r8 == 6);
+  int n_tiles;
+  const int end = block_scan_1024(nt, wsum[1], n_tiles);
+  tile0[e] = end - nt;
+  if (e == 0) *pl.n_tiles = n_tiles;
+  __syncthreads();
+  for (int i = e; i < n_tiles; i += 1024) {
+    int lo = 0, hi = n_groups;  // the last group whose tiles start at or before i (groups without tiles come last)
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (tile0[mid] <= i) lo = mid;
+      else hi = mid;
+    }
+    const int rows = cnt[lo], full = rows / BM, r = eighths(rows), in_group = i - tile0[lo];
+    const int k0 = r > 6 ? 0 : r > 3 ? 1 : r > 1 ? 2 : 3;  // kinds (heights BM >> kind) of the remainder's tiles
+    const int k1 = r == 6 ? 2 : 3;
+    const int kind = in_group < full ? 0 : in_group == full ? k0 : k1;
+    const int row = min(in_group, full) * BM + (in_group > full ? BM >> k0 : 0);
+    RowTile t;
+    t.group = ord[lo];
+    t.row0_in = first[lo] + row;
+    t.rows = min(BM >> kind, rows - row) | (kind << 16);
+    t.row0_out = t.row0_in;
+    pl.tiles[i] = t;
+  }
+}
+
 // C[rows, N] (+ second C when dual) = sum over (pair, seg) of A_seg[rows, K] * B_seg[K, N]
 struct RowGemm {
   const RowTile* tiles;     // NULL: no plan, n_groups groups of n_rows rows in tiles of one height

@@ -105,3 +105,46 @@ def test_sets_are_checked():
                       (dict(routed, src_of=off, n_rows=30), shared, "in place"), (routed, dict(shared, Yout=None), "null")]:
         with pytest.raises(moe.MoEError, match=msg):
             moe.moe_experts_fwd(shape, r, s)
+
+
+@pytest.mark.parametrize("T,E,k", [(0, 5, 2), (1, 1, 1), (700, 6, 2), (517, 64, 3), (40, 300, 8), (60, 1024, 4)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_plan_of_the_dispatch(dtype, T, E, k):
+    """A plan that the dispatch wrote gives the bits of the calls that build their own, and the same active_ids."""
+    import paper_2502_02581_amd as moe
+
+    d, F, A, dev = 64, 72, T * k, "cuda"
+    shape = moe.MoEShape(T, d, E, k, F, dtype)
+    dt = shape.torch_dtype
+    g = torch.Generator().manual_seed(T + E)
+    rnd = lambda *s: (torch.randn(*s, generator=g) * d ** -0.5).to(dt).to(dev)
+    i32 = lambda *s: torch.full(s, -7, dtype=torch.int32, device=dev)
+    logits = (torch.randn(T, E, generator=g) + 2.0 * torch.randn(E, generator=g)).to(dev)
+    X, dY, Wg, Wu, Wd = rnd(T, d), rnd(A, d), rnd(E, d, F), rnd(E, d, F), rnd(E, F, d)
+    idx, w, counts, off, row_of, src_of, Xp = i32(T, k), torch.empty(T, k, device=dev), i32(E), i32(E + 1), i32(A), i32(A), rnd(A, d)
+    size = max(moe.moe_route_dispatch_workspace_bytes(shape), moe.moe_expert_fwd_workspace_bytes(shape, E, A, False),
+               moe.moe_expert_bwd_workspace_bytes(shape, E, A, False))
+    ws = torch.full((size,), 255, dtype=torch.uint8, device=dev)
+    need = moe.moe_expert_plan_bytes(shape)
+    big = torch.full((need + 4096,), 0xA5, dtype=torch.uint8, device=dev)
+    with pytest.raises(moe.MoEError, match="plan of"):
+        moe.moe_route_dispatch_plan(shape, logits, X, 0.0, idx, w, counts, off, row_of, src_of, Xp, None, None, big[:need - 16], i32(E), i32(1), ws)
+    outs = []
+    for plan in (big[:need], None):
+        ids, n_act = i32(E), i32(1)
+        if plan is not None:
+            moe.moe_route_dispatch_plan(shape, logits, X, 0.0, idx, w, counts, off, row_of, src_of, Xp, None, None, plan, ids, n_act, ws)
+        else:
+            moe.moe_route_dispatch(shape, logits, X, 0.0, idx, w, counts, off, row_of, src_of, Xp, None, None, ws)
+        new = lambda *s: torch.full(s, float("nan"), dtype=dt, device=dev)
+        o = dict(G=new(A, F), U=new(A, F), H=new(A, F))
+        base = dict(d_ff=F, n_groups=E, n_rows=A, offsets=off, Xin=Xp, Wg=Wg, Wu=Wu, Wd=Wd, ws=ws, ws_bytes=size, plan=plan, **o)
+        Y, gr = new(A, d), dict(dXin=new(A, d), dWg_c=new(E, d, F), dWu_c=new(E, d, F), dWd_c=new(E, F, d))
+        moe.moe_experts_fwd(shape, dict(base, Yout=Y), None)
+        ws.fill_(255)
+        moe.moe_experts_bwd(shape, dict(base, dYin=dY, active_ids=ids, n_active=n_act, **gr), None)
+        outs.append([Y, *o.values(), *gr.values(), ids, n_act, counts.clone(), off.clone()])
+    torch.cuda.synchronize()
+    for a, b in zip(*outs):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+    assert bool((big[need:] == 0xA5).all())
