@@ -508,9 +508,10 @@ class MoEHotPath:
                 -> moe_route_bwd (gradient of the router logits)
     With aux_alpha > 0, forward() also evaluates the auxiliary load-balancing loss (moe_aux_loss, after
     the dispatch has counted the loads) and backward() adds its gradient to dlogits (moe_aux_loss_bwd).
-    With fused (the default), gate + dispatch + loss + the plan of the experts' products go through
+    With fused (the default), gate + dispatch + loss + the plan of the forward products go through
     moe_route_dispatch_plan and the two backward calls of the gate through moe_route_aux_bwd: the same results from
-    six launches fewer.  The plan belongs to the routing of the last forward(), as row_of and offsets do.
+    five launches fewer.  backward() builds its plan from offsets, so that the tensors of b are all that a pass saved and
+    put back (several micro-batches in flight) needs.
     No arithmetic happens here; tensors are only allocated and handed to the library.
 
     The shared experts depend on nothing the routed experts produce, so their products run in the launches of the
@@ -565,12 +566,12 @@ class MoEHotPath:
                            "aux_loss": torch.empty(1, dtype=torch.float32, device=dev)})
             ws = max(ws, moe_aux_loss_workspace_bytes(s))
         self.ws = torch.empty(ws, dtype=torch.uint8, device=dev)
-        # the order of the routed experts' tiles, written by the fused prologue for both passes
+        # the order of the routed experts' tiles, written by the fused prologue for the forward products
         self.plan = torch.zeros(moe_expert_plan_bytes(s), dtype=torch.uint8, device=dev)
 
     def _ws_pieces(self):
         """The workspace of the routed and that of the shared experts (keywords of an expert set)."""
-        return {"ws": self.ws[:self.ws_routed], "ws_bytes": self.ws_routed, "plan": self.plan if self.fused else None}, \
+        return {"ws": self.ws[:self.ws_routed], "ws_bytes": self.ws_routed}, \
                {"ws": self.ws[self.ws_routed:], "ws_bytes": self.ws.numel() - self.ws_routed}
 
     def forward(self, logits, X, Wg, Wu, Wd, Wsg=None, Wsu=None, Wsd=None, stream=None):
@@ -593,7 +594,8 @@ class MoEHotPath:
                       H=b["Hs"], Yout=b["Ysh"], **ws_shared) if self.S else None
         moe_experts_fwd(s, dict(d_ff=s.d_ff, n_groups=s.E, n_rows=A, offsets=b["offsets"],
                                 src_of=b["src_of"] if self.gather else None, Xin=X if self.gather else b["Xp"], Wg=Wg,
-                                Wu=Wu, Wd=Wd, G=b["G"], U=b["U"], H=b["H"], Yout=b["Yp"], **ws), shared, stream)
+                                Wu=Wu, Wd=Wd, G=b["G"], U=b["U"], H=b["H"], Yout=b["Yp"],
+                                plan=self.plan if self.fused else None, **ws), shared, stream)
         moe_combine(s, b["Yp"], b["row_of"], b["topk_w"], b["Ysh"] if self.S else None, b["Y"], stream)
         return b["Y"]
 

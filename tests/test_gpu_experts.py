@@ -148,3 +148,36 @@ def test_plan_of_the_dispatch(dtype, T, E, k):
     for a, b in zip(*outs):
         assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
     assert bool((big[need:] == 0xA5).all())
+
+
+@pytest.mark.parametrize("S", [0, 1])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_backward_of_a_pass_that_was_put_back(dtype, S):
+    """Two micro-batches in flight on one MoEHotPath: the tensors of the first are saved, the second runs forward with another
+    routing, the first ones are put back.  Its backward pass gives the bits of a backward pass right after its forward pass."""
+    import paper_2502_02581_amd as moe
+
+    T, d, E, k, F = 700, 128, 6, 2, 192
+    shape = moe.MoEShape(T, d, E, k, F, dtype)
+    g = torch.Generator().manual_seed(3)
+    new = lambda *n: torch.randn(*n, generator=g).to("cuda", shape.torch_dtype)
+    X, dY = new(T, d), new(T, d)
+    w = [new(E, d, F), new(E, d, F), new(E, F, d)] + ([new(S, d, F), new(S, d, F), new(S, F, d)] if S else [])
+    logits = torch.randn(2, T, E, generator=g)
+    logits[0, :, 0] += 2.0   # the two routings load other experts
+    logits[1, :, 4] += 2.0
+    logits = logits.to("cuda")
+    hp = moe.MoEHotPath(shape, S, F if S else 0, "cuda:0")
+    names = ["dX", "dw", "active_ids", "n_active", "dWg_c", "dWu_c", "dWd_c"] + (["dWsg", "dWsu", "dWsd"] if S else [])
+    for n in names:
+        hp.b[n].zero_()
+    hp.forward(logits[0], X, *w)
+    saved = {n: t.clone() for n, t in hp.b.items()}
+    hp.backward(dY, X, *w)
+    want = {n: hp.b[n].clone() for n in names}
+    hp.forward(logits[1], X, *w)
+    for n, t in saved.items():
+        hp.b[n].copy_(t)
+    hp.backward(dY, X, *w)
+    for n in names:
+        assert torch.equal(hp.b[n], want[n]), n
