@@ -326,6 +326,14 @@ __global__ __launch_bounds__(CoreSet::template tile<0>::NT, CoreSet::template ti
   if (b < 0) row_gemm_block<CoreSet, NB, EPI, B_KC, false>(s, blockIdx.x, smem);
   else row_gemm_block<CoreSet, NB, EPI, B_KC, true>(r, b, smem);
 }
+// The router's product, which never has routed rows beside it: one argument block and none of the plan's code.  (Its launches are
+// single rounds, bound by how fast they start: a kernel of one argument block took 15.8 us where the one above takes 17.1 for T = 300,
+// d = 2048, 64 experts, and 10.6 against 11.6 for T = 4096, d = 1024, 16 experts; router passes of the first: 34.2 -> 33.0 us.)
+template <class CoreSet, int NB, int EPI, bool B_KC>
+__global__ __launch_bounds__(CoreSet::template tile<0>::NT, CoreSet::template tile<0>::BLOCKS_PER_CU) void direct_row_gemm_kernel(RowGemm s) {
+  extern __shared__ __align__(16) char smem[];
+  row_gemm_block<CoreSet, NB, EPI, B_KC, false>(s, blockIdx.x, smem);
+}
 // An input gradient and a weight gradient that does not depend on it in one launch: first the row tiles (the longer
 // ones), then weight-gradient tiles, which fill the compute units that the last row tiles leave idle.
 // (One launch per product against dH + dWd and dX + dWg + dWu, and one
@@ -614,11 +622,16 @@ static void launch_row(const char* label, const Direct* sd, const RowGemm* r, in
   }
   const unsigned sb = (unsigned)p.part_blocks * c.n_parts, rb = r ? row_block_count(r_tiles, r->N, Core::BN) : 0;
   if (sb + rb == 0) return;
-  auto kern = row_gemm_kernel<CoreSet, NB, EPI, B_KC>;
   static LdsAttr attr;
   constexpr int kLds = row_lds_bytes<CoreSet>();
-  attr.ensure((const void*)kern, kLds);
-  {
+  if constexpr (EPI == EPI_STORE_F32) {  // the router's epilogue
+    auto kern = direct_row_gemm_kernel<CoreSet, NB, EPI, B_KC>;
+    attr.ensure((const void*)kern, kLds);
+    ProfScope prof(label, st);
+    hipLaunchKernelGGL(kern, dim3(sb), dim3(Core::NT), kLds, st, p);
+  } else {
+    auto kern = row_gemm_kernel<CoreSet, NB, EPI, B_KC>;
+    attr.ensure((const void*)kern, kLds);
     ProfScope prof(label, st);
     hipLaunchKernelGGL(kern, dim3(sb + rb), dim3(Core::NT), kLds, st, p, r ? *r : RowGemm{}, (int)sb);
   }
