@@ -44,10 +44,9 @@ __global__ __launch_bounds__(64) void dispatch_count(const int32_t* __restrict__
 // over c, then the thread rewrites its run as exclusive prefixes.  Loads go a batch at a time ahead of the dependent
 // additions and stores.  (Batches of 8, the shares read
 // after the counters, as many runs as threads: T = 256, E = 8: 8.5 us, now 5.1; T = 2777, E = 60: 10.7, now 8.4.)
-// With pl.tiles, the block goes on to the plan of the experts' products: 2 to 3 us more here take the place of a launch of its
-// own in the forward pass and one in the backward pass, 4 to 7 us each.  (Each against the same earlier state on its own box,
-// with the two launches and without: T = 8192, d = 768, 64 experts, training 0.978 and 0.967 of its time; T = 4096, d = 2048, 60 experts 0.959 and
-// 0.931; T = 256, d = 128, 8 experts, fp32 0.976 and 0.920, the latter with the cheaper marshalling of the calls.)
+// With pl.tiles, the block goes on to the plan of the experts' products: 2 to 3 us more here take the place of a launch of 4 to 7 us
+// ahead of the forward products.  (Training step of T = 256, d = 128, 8 experts, fp32, with the cheaper marshalling of the calls:
+// 93.6 -> 92.2 us; 16 tokens, 60 experts, d = 2048, forward, all of the common launches included: 138 -> 122.)
 // With `partial` (the fused prologue), the block also finishes the auxiliary load-balancing loss: P_e from
 // the per-chunk sums of the gate's shares (added in the same fixed order as the counters), then
 // L = alpha E sum_e (counts[e] / (T k)) P_e over ascending e.
