@@ -281,7 +281,7 @@ int moe_expert_bwd_gather(const moe_shape_t* shape, const int32_t* offsets, cons
  * run in common launches, so that the shared experts' few tiles and the last tiles of the routed ones fill the chip
  * together.  Arguments and results are those of moe_expert_fwd(_gather) / moe_expert_bwd(_gather) for the routed set and
  * of moe_expert_fwd / moe_expert_bwd in shared mode for the shared one, each set with a workspace of its own (the size
- * queries of those calls); only the last bits of shared results may differ (sums over K in another number of parts).
+ * queries of those calls); only the last bits of shared results may differ, in bf16 (sums over K in another number of parts).
  * shared may be NULL.  The sets have shape's d and dtype and their own d_ff.
  * moe_route_dispatch_plan -- moe_route_dispatch, and the order of the routed experts' tiles, the plan that both passes of
  * these calls otherwise derive from offsets in a kernel of their own, with active_ids [E] and n_active [1] as moe_expert_bwd

@@ -706,6 +706,11 @@ static DirectShape w_shape(int groups, int M, int N, int rows) {
   return {w_cost<PATH, NB>(), groups, M, N, rows, NB, 1, (int64_t)groups * M * N, 0.};
 }
 // The routed experts' share of a launch, in microseconds of one compute unit: n_rows rows over groups of unknown sizes.
+// It makes for fewer parts (prefill of 192 tokens, one shared expert, d = 7168: 1085 us a pass without it, 1035 with it; training, T = 3001,
+// d = 1000: 580 and 543), and so for longer sums.  In bf16 the results' rounding hides that (errors against 64 bits the same to
+// four digits over sizes of T = 16 to 3001, d = 128 to 7168); in fp32 shared results were up to 2.6 times as far off (T = 1743,
+// d = 832, width 64: 3.1e-7 -> 8.1e-7), so fp32 products are in the same parts beside routed rows as alone.
+template <int PATH> constexpr bool kPartsSeeRouted = PATH != PATH_F32;
 template <int PATH, int NB> static double routed_row_us(int n_groups, int n_rows, int N, int K, int sums = 1) {
   constexpr TileCost c = row_cost<PATH, NB>();
   const double steps = (double)sums * ceil_div(K, c.bk);
@@ -799,7 +804,7 @@ void expert_fwd_impl(const FwdArgs* r, const FwdArgs* s, hipStream_t st) {
     up.p = sg.gate_up; up.shape = gated ? ps.template gate_up<2>() : ps.template gate_up<1>();
     down.p = sg.down; down.shape = ps.down();
     up.parts = down.parts = s->parts; up.avail = down.avail = s->part_avail;
-    if (r) {
+    if (r && kPartsSeeRouted<PATH>) {
       up.shape.routed_us = gated ? routed_row_us<PATH, 2>(r->n_groups, r->n_rows, r->F, r->d) : routed_row_us<PATH, 1>(r->n_groups, r->n_rows, r->F, r->d);
       down.shape.routed_us = routed_row_us<PATH, 1>(r->n_groups, r->n_rows, r->d, r->F);
     }
@@ -926,7 +931,7 @@ void expert_bwd_impl(const BwdArgs* r, const BwdArgs* s, hipStream_t st) {
     dx.p = sg.dx; dx.shape = gated ? ps.template dx<2>() : ps.template dx<1>();
     dx.w = sg.dwgu; dx.w_shape = gated ? ps.template dwgu<2>() : ps.template dwgu<1>();
     dh.parts = dx.parts = s->parts; dh.avail = dx.avail = s->part_avail;
-    if (r) {
+    if (r && kPartsSeeRouted<PATH>) {
       dh.shape.routed_us = routed_row_us<PATH, 1>(r->n_groups, r->n_rows, r->F, r->d) + routed_w_us<PATH, 1>(r->n_rows, r->F, r->d);
       dx.shape.routed_us = routed_row_us<PATH, 1>(r->n_groups, r->n_rows, r->d, r->F, gated ? 2 : 1) +
                            (gated ? routed_w_us<PATH, 2>(r->n_rows, r->d, r->F) : routed_w_us<PATH, 1>(r->n_rows, r->d, r->F));
