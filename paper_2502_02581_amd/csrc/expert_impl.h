@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <iterator>
 
 #include "gemm_cores.h"
 #include "gemm_plan.h"
@@ -550,17 +551,27 @@ static DirectChoice direct_option(const DirectShape& s, int kind, int parts) {
 // r: row product or NULL, w: weight gradient of the same launch or NULL; `avail`: bytes for the parts
 static void choose_direct(const DirectShape* r, const DirectShape* w, size_t avail, DirectChoice* rc, DirectChoice* wc) {
   static const int kParts[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16};
+  const double routed = r ? r->routed_us : 0;
+  if (routed > 0) {
+    // No more room than the same product takes alone, which is what the size queries ask for: a larger workspace must not
+    // change the parts, and with them the results' last bits.
+    DirectShape alone = *r;
+    alone.routed_us = 0;
+    choose_direct(&alone, w, avail, rc, wc);
+    avail = rc->part_bytes + wc->part_bytes;
+  }
   double best = 0;
   bool first = true;
+  DirectChoice w_options[std::size(kParts)];
+  for (size_t i = 0; w && i < std::size(kParts); i++) w_options[i] = direct_option(*w, 0, kParts[i]);
   for (int kind = 0; kind < (r ? 4 : 1); kind++)
     for (int pr : kParts) {
       const DirectChoice a = r ? direct_option(*r, kind, pr) : DirectChoice();
       if (pr > 1 && (!r || a.n_parts == 1 || a.part_bytes > avail)) continue;
-      for (int pw : kParts) {
-        const DirectChoice b = w ? direct_option(*w, 0, pw) : DirectChoice();
-        if (pw > 1 && (!w || b.n_parts == 1 || a.part_bytes + b.part_bytes > avail)) continue;
+      for (size_t i = 0; i < std::size(kParts); i++) {
+        const DirectChoice& b = w_options[i];
+        if (i > 0 && (!w || b.n_parts == 1 || a.part_bytes + b.part_bytes > avail)) continue;
         double us;
-        const double routed = r ? r->routed_us : 0;
         if (!w && routed == 0) us = (double)((a.blocks + kCUs - 1) / kCUs) * a.block_us;
         else {
           const double longest = std::max(a.block_us, b.block_us);

@@ -90,6 +90,41 @@ def test_both_sets_in_one_call(dtype, T, d, E, k, F, S, Fs, act, act_s, gather):
             assert err <= 8e-3, (n, err)
 
 
+# sizes at which more room than a set asks for alone would make more parts beside these routed rows
+@pytest.mark.parametrize("T,d,E,k,F,S,Fs", [(256, 256, 120, 2, 1024, 2, 1024), (80, 5376, 48, 1, 128, 4, 64), (85, 3840, 65, 1, 256, 1, 256)])
+def test_room_beyond_the_query_changes_nothing(T, d, E, k, F, S, Fs):
+    """A call gives the same bits with every workspace from the size queries' answer on."""
+    import paper_2502_02581_amd as moe
+
+    shape, sshape = moe.MoEShape(T, d, E, k, F, "bf16"), moe.MoEShape(T, d, E, k, Fs, "bf16")
+    A, dev = T * k, "cuda"
+    g = torch.Generator().manual_seed(T + d)
+    rnd = lambda *s: (torch.randn(*s, generator=g) * d ** -0.5).bfloat16().to(dev)
+    X, dY, Xp, dYp = rnd(T, d), rnd(T, d), rnd(A, d), rnd(A, d)
+    w, ws_ = dict(Wg=rnd(E, d, F), Wu=rnd(E, d, F), Wd=rnd(E, F, d)), dict(Wg=rnd(S, d, Fs), Wu=rnd(S, d, Fs), Wd=rnd(S, Fs, d))
+    off = torch.arange(E + 1, dtype=torch.int32, device=dev) * (A // E)
+    off[-1] = A
+
+    def run(room):
+        new, i32 = lambda *s: torch.zeros(*s, dtype=torch.bfloat16, device=dev), lambda n: torch.zeros(n, dtype=torch.int32, device=dev)
+        a = dict(G=new(A, F), U=new(A, F), H=new(A, F))
+        b = dict(G=new(S, T, Fs), U=new(S, T, Fs), H=new(S, T, Fs))
+        grads = lambda n, f, r: dict(dXin=new(r, d), dWg_c=new(n, d, f), dWu_c=new(n, d, f), dWd_c=new(n, f, d), active_ids=i32(n), n_active=i32(1))
+        outs = []
+        for call, query in ((moe.moe_experts_fwd, moe.moe_expert_fwd_workspace_bytes), (moe.moe_experts_bwd, moe.moe_expert_bwd_workspace_bytes)):
+            n, n_s = query(shape, E, A, False), query(sshape, S, T, True) + room
+            t, t_s = torch.empty(n, dtype=torch.uint8, device=dev), torch.empty(n_s, dtype=torch.uint8, device=dev)
+            more, more_s = (dict(Yout=new(A, d)), dict(Yout=new(T, d))) if call is moe.moe_experts_fwd else \
+                (dict(dYin=dYp, **grads(E, F, A)), dict(dYin=dY, **grads(S, Fs, T)))
+            call(shape, dict(d_ff=F, n_groups=E, n_rows=A, offsets=off, Xin=Xp, ws=t, ws_bytes=n, **w, **a, **more),
+                 dict(d_ff=Fs, n_groups=S, n_rows=T, Xin=X, ws=t_s, ws_bytes=n_s, **ws_, **b, **more_s))
+            outs += [*more.values(), *more_s.values()]
+        return outs + [*a.values(), *b.values()]
+
+    for x, y in zip(run(0), run(16 << 20)):
+        assert torch.equal(x, y)
+
+
 def test_sets_are_checked():
     import paper_2502_02581_amd as moe
 
