@@ -566,7 +566,9 @@ class MoEHotPath:
                            "aux_loss": torch.empty(1, dtype=torch.float32, device=dev)})
             ws = max(ws, moe_aux_loss_workspace_bytes(s))
         self.ws = torch.empty(ws, dtype=torch.uint8, device=dev)
-        # the order of the routed experts' tiles, written by the fused prologue for the forward products
+        # the order of the routed experts' tiles, written by the fused prologue for the forward products, and that call's
+        # active_ids and n_active: those in b belong to the gradients of the last backward pass, which alone writes them
+        self.plan_ids, self.plan_n_active = torch.empty_like(self.b["active_ids"]), torch.empty_like(self.b["n_active"])
         self.plan = torch.zeros(moe_expert_plan_bytes(s), dtype=torch.uint8, device=dev)
 
     def _ws_pieces(self):
@@ -582,7 +584,7 @@ class MoEHotPath:
         if self.fused:
             moe_route_dispatch_plan(s, logits, X, self.aux_alpha, b["topk_idx"], b["topk_w"], b["counts"], b["offsets"],
                                     b["row_of"], b["src_of"], b["Xp"], b.get("aux_P"), b.get("aux_loss"), self.plan,
-                                    b["active_ids"], b["n_active"], self.ws, stream)
+                                    self.plan_ids, self.plan_n_active, self.ws, stream)
         else:
             moe_route(s, logits, b["topk_idx"], b["topk_w"], stream)
             moe_dispatch(s, X, b["topk_idx"], b["counts"], b["offsets"], b["row_of"], b["src_of"], b["Xp"], self.ws,

@@ -217,3 +217,35 @@ def test_backward_of_a_pass_that_was_put_back(dtype, S):
     hp.backward(dY, X, *w)
     for n in names:
         assert torch.equal(hp.b[n], want[n]), n
+
+
+@pytest.mark.parametrize("fused", [True, False])
+@pytest.mark.parametrize("S", [0, 1])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_forward_leaves_the_last_gradients_alone(dtype, S, fused):
+    """A forward pass after a backward pass (validation, the next micro-batch) writes none of that pass's gradients, nor the ids
+    that say which experts the compact slots belong to."""
+    import paper_2502_02581_amd as moe
+
+    T, d, E, k, F = 300, 128, 8, 2, 192
+    shape = moe.MoEShape(T, d, E, k, F, dtype)
+    g = torch.Generator().manual_seed(4)
+    new = lambda *n: torch.randn(*n, generator=g).to("cuda", shape.torch_dtype)
+    X, dY = new(T, d), new(T, d)
+    w = [new(E, d, F), new(E, d, F), new(E, F, d)] + ([new(S, d, F), new(S, d, F), new(S, F, d)] if S else [])
+    logits = torch.randn(2, T, E, generator=g)
+    logits[0, :, :3] -= 100.0   # experts 3 to 7, then 0 to 4
+    logits[1, :, 5:] -= 100.0
+    logits = logits.to("cuda")
+    hp = moe.MoEHotPath(shape, S, F if S else 0, "cuda:0", aux_alpha=0.01, fused=fused)
+    names = ["dX", "dw", "dlogits", "active_ids", "n_active", "dWg_c", "dWu_c", "dWd_c"]
+    names += ["dWsg", "dWsu", "dWsd", "s_active_ids", "s_n_active"] if S else []
+    for n in names:
+        hp.b[n].zero_()
+    hp.forward(logits[0], X, *w)
+    hp.backward(dY, X, *w)
+    want = {n: hp.b[n].clone() for n in names}
+    assert hp.b["active_ids"].tolist() == [3, 4, 5, 6, 7, -1, -1, -1] and hp.b["n_active"].item() == 5
+    hp.forward(logits[1], X, *w)
+    for n in names:
+        assert torch.equal(hp.b[n], want[n]), n
