@@ -515,9 +515,10 @@ class MoEHotPath:
     No arithmetic happens here; tensors are only allocated and handed to the library.
 
     The shared experts depend on nothing the routed experts produce, so their products run in the launches of the
-    routed ones and fill the CUs that those leave idle.  overlap_shared asked for them on a second stream, which is
-    slower (training step of T = 4096, d = 2048, 60 experts, 4 shared: 2.19 ms, in common launches 2.16); it is
-    accepted and changes nothing.
+    routed ones and fill the CUs that those leave idle: faster than on a second stream (training step of T = 4096,
+    d = 2048, 60 experts, 4 shared: 2.16 ms against 2.19).  Where common launches are not possible (one set gated, the
+    other not; rows too long for the tile cores) the shared experts' calls follow the routed ones', or, with
+    overlap_shared, go to a second stream of the same (default) priority beside them and join before the combine.
     """
 
     def __init__(self, shape: MoEShape, n_shared: int = 0, d_ff_shared: int = 0, device="cuda:0",
@@ -547,6 +548,10 @@ class MoEHotPath:
         }
         self.ws_routed = max(moe_expert_fwd_workspace_bytes(s, s.E, A, False), moe_expert_bwd_workspace_bytes(s, s.E, A, False))
         ws = max(moe_dispatch_workspace_bytes(s), moe_route_dispatch_workspace_bytes(s), self.ws_routed)
+        if self.aux_alpha > 0:
+            self.b.update({"aux_P": torch.empty(s.E, dtype=torch.float32, device=dev),
+                           "aux_loss": torch.empty(1, dtype=torch.float32, device=dev)})
+            ws = max(ws, moe_aux_loss_workspace_bytes(s))
         if n_shared:
             self.sshape = dataclasses.replace(s, d_ff=d_ff_shared)
             S, Fs = n_shared, d_ff_shared
@@ -557,14 +562,15 @@ class MoEHotPath:
                 "dWsg": torch.empty(S, s.d, Fs, **f), "dWsu": torch.empty(S, s.d, Fs, **f),
                 "dWsd": torch.empty(S, Fs, s.d, **f),
             })
-            # the experts' calls take the workspace in two pieces, the routed experts' and the shared ones'
-            self.ws_routed = (self.ws_routed + 255) // 256 * 256
-            ws = max(ws, self.ws_routed + max(moe_expert_fwd_workspace_bytes(self.sshape, S, s.T, True),
-                                              moe_expert_bwd_workspace_bytes(self.sshape, S, s.T, True)))
-        if self.aux_alpha > 0:
-            self.b.update({"aux_P": torch.empty(s.E, dtype=torch.float32, device=dev),
-                           "aux_loss": torch.empty(1, dtype=torch.float32, device=dev)})
-            ws = max(ws, moe_aux_loss_workspace_bytes(s))
+            # a piece of the workspace for the shared experts alone, whose calls run beside all the others
+            self.ws_routed = (ws + 255) // 256 * 256
+            ws = self.ws_routed + max(moe_expert_fwd_workspace_bytes(self.sshape, S, s.T, True),
+                                      moe_expert_bwd_workspace_bytes(self.sshape, S, s.T, True))
+            # rows of the tile cores: 256 of them within 32-bit byte offsets
+            self.long_rows = 256 * max(s.d, s.d_ff, Fs) * (4 if s.dtype == "f32" else 2) > (1 << 32) - 4096
+        if self.overlap:
+            self.side = torch.cuda.Stream(device=dev)
+            self.ev_fork, self.ev_join = torch.cuda.Event(), torch.cuda.Event()
         self.ws = torch.empty(ws, dtype=torch.uint8, device=dev)
         # the order of the routed experts' tiles, written by the fused prologue for the forward products, and that call's
         # active_ids and n_active: those in b belong to the gradients of the last backward pass, which alone writes them
@@ -576,11 +582,31 @@ class MoEHotPath:
         return {"ws": self.ws[:self.ws_routed], "ws_bytes": self.ws_routed}, \
                {"ws": self.ws[self.ws_routed:], "ws_bytes": self.ws.numel() - self.ws_routed}
 
+    def _fork(self, Wu, Wsu, stream):
+        """With overlap_shared, where the two sets cannot run in common launches: the main stream, once the side stream waits
+        for everything already queued on it.  None otherwise."""
+        if not self.overlap or ((Wu is None) == (Wsu is None) and not self.long_rows):
+            return None
+        main = torch.cuda.current_stream(self.device) if stream is None else \
+            stream if hasattr(stream, "cuda_stream") else torch.cuda.ExternalStream(int(stream), device=self.device)
+        self.ev_fork.record(main)
+        self.side.wait_event(self.ev_fork)
+        return main
+
+    def _join(self, main):
+        self.ev_join.record(self.side)
+        main.wait_event(self.ev_join)
+
     def forward(self, logits, X, Wg, Wu, Wd, Wsg=None, Wsu=None, Wsd=None, stream=None):
         s, b = self.shape, self.b
         A = s.T * s.k
+        main = self._fork(Wu, Wsu, stream)
         stream = _stream(stream)
         self._logits = logits  # the gate's backward reads them again
+        ws, ws_shared = self._ws_pieces()
+        if main:
+            moe_expert_fwd(self.sshape, self.S, None, s.T, X, Wsg, Wsu, Wsd, b["Gs"], b["Us"], b["Hs"], b["Ysh"],
+                           ws_shared["ws"], self.side)
         if self.fused:
             moe_route_dispatch_plan(s, logits, X, self.aux_alpha, b["topk_idx"], b["topk_w"], b["counts"], b["offsets"],
                                     b["row_of"], b["src_of"], b["Xp"], b.get("aux_P"), b.get("aux_loss"), self.plan,
@@ -591,30 +617,37 @@ class MoEHotPath:
                          stream)
             if self.aux_alpha > 0:
                 moe_aux_loss(s, logits, b["counts"], self.aux_alpha, b["aux_P"], b["aux_loss"], self.ws, stream)
-        ws, ws_shared = self._ws_pieces()
         shared = dict(d_ff=self.Fs, n_groups=self.S, n_rows=s.T, Xin=X, Wg=Wsg, Wu=Wsu, Wd=Wsd, G=b["Gs"], U=b["Us"],
-                      H=b["Hs"], Yout=b["Ysh"], **ws_shared) if self.S else None
+                      H=b["Hs"], Yout=b["Ysh"], **ws_shared) if self.S and not main else None
         moe_experts_fwd(s, dict(d_ff=s.d_ff, n_groups=s.E, n_rows=A, offsets=b["offsets"],
                                 src_of=b["src_of"] if self.gather else None, Xin=X if self.gather else b["Xp"], Wg=Wg,
                                 Wu=Wu, Wd=Wd, G=b["G"], U=b["U"], H=b["H"], Yout=b["Yp"],
                                 plan=self.plan if self.fused else None, **ws), shared, stream)
+        if main:
+            self._join(main)
         moe_combine(s, b["Yp"], b["row_of"], b["topk_w"], b["Ysh"] if self.S else None, b["Y"], stream)
         return b["Y"]
 
     def backward(self, dY, X, Wg, Wu, Wd, Wsg=None, Wsu=None, Wsd=None, stream=None):
         s, b = self.shape, self.b
         A = s.T * s.k
+        main = self._fork(Wu, Wsu, stream)
         stream = _stream(stream)
-        moe_combine_bwd(s, dY, b["Yp"], b["row_of"], b["topk_w"], b["dYp"], b["dw"], stream)
         ws, ws_shared = self._ws_pieces()
+        if main:
+            moe_expert_bwd(self.sshape, self.S, None, s.T, X, Wsg, Wsu, Wsd, b["Gs"], b["Us"], b["Hs"], dY, b["dXsh"],
+                           b["s_active_ids"], b["s_n_active"], b["dWsg"], b["dWsu"], b["dWsd"], ws_shared["ws"], self.side)
+        moe_combine_bwd(s, dY, b["Yp"], b["row_of"], b["topk_w"], b["dYp"], b["dw"], stream)
         in_place = dict(src_of=b["src_of"], dY=dY, row_w=b["topk_w"]) if self.gather else {}
         shared = dict(d_ff=self.Fs, n_groups=self.S, n_rows=s.T, Xin=X, Wg=Wsg, Wu=Wsu, Wd=Wsd, G=b["Gs"], U=b["Us"],
                       H=b["Hs"], dYin=dY, dXin=b["dXsh"], active_ids=b["s_active_ids"], n_active=b["s_n_active"],
-                      dWg_c=b["dWsg"], dWu_c=b["dWsu"], dWd_c=b["dWsd"], **ws_shared) if self.S else None
+                      dWg_c=b["dWsg"], dWu_c=b["dWsu"], dWd_c=b["dWsd"], **ws_shared) if self.S and not main else None
         moe_experts_bwd(s, dict(d_ff=s.d_ff, n_groups=s.E, n_rows=A, offsets=b["offsets"], Xin=b["Xp"], Wg=Wg, Wu=Wu, Wd=Wd,
                                 G=b["G"], U=b["U"], H=b["H"], dYin=b["dYp"], dXin=b["dXp"], active_ids=b["active_ids"],
                                 n_active=b["n_active"], dWg_c=b["dWg_c"], dWu_c=b["dWu_c"], dWd_c=b["dWd_c"], **in_place,
                                 **ws), shared, stream)
+        if main:
+            self._join(main)
         moe_combine(s, b["dXp"], b["row_of"], None, b["dXsh"] if self.S else None, b["dX"], stream)
         if self.fused and self.aux_alpha > 0:
             moe_route_aux_bwd(s, self._logits, b["topk_idx"], b["dw"], b["counts"], self.aux_alpha, 1.0, b["dlogits"],

@@ -249,3 +249,70 @@ def test_forward_leaves_the_last_gradients_alone(dtype, S, fused):
     hp.forward(logits[1], X, *w)
     for n in names:
         assert torch.equal(hp.b[n], want[n]), n
+
+
+@pytest.mark.parametrize("gated", [(True, False), (False, True)])   # the routed set, the shared set
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_overlap_where_no_common_launch_is_possible(dtype, gated, monkeypatch):
+    """One set gated, the other not: with overlap_shared the shared calls go to the second stream, and eager passes, passes on a
+    stream of the caller's and replays of a captured one give the bits of the order one after the other."""
+    import paper_2502_02581_amd as moe
+    from paper_2502_02581_amd import binding
+
+    T, d, E, k, F, S, Fs = 700, 192, 6, 2, 256, 2, 128
+    shape = moe.MoEShape(T, d, E, k, F, dtype)
+    g = torch.Generator().manual_seed(6)
+    new = lambda *n: (torch.randn(*n, generator=g) * 0.1).to("cuda", shape.torch_dtype)
+    w = [new(E, d, F), new(E, d, F) if gated[0] else None, new(E, F, d), new(S, d, Fs), new(S, d, Fs) if gated[1] else None, new(S, Fs, d)]
+    a, b = ((torch.randn(T, E, generator=g).cuda(), new(T, d), new(T, d)) for _ in range(2))
+    names = ["Y", "dX", "dw", "dlogits", "dWg_c", "dWd_c", "dWsg", "dWsd"] + ["dWu_c"] * gated[0] + ["dWsu"] * gated[1]
+    streams = []
+    for call in ("moe_expert_fwd", "moe_expert_bwd"):
+        def spy(*args, real=getattr(binding, call)):
+            streams.append(args[-1].cuda_stream)
+            return real(*args)
+        monkeypatch.setattr(binding, call, spy)
+
+    def layer(overlap):
+        hp = moe.MoEHotPath(shape, S, Fs, "cuda:0", overlap_shared=overlap, aux_alpha=0.01)
+        for n in names:
+            hp.b[n].zero_()
+        return hp
+
+    def step(hp, q, stream=None):
+        hp.forward(q[0], q[1], *w, stream=stream)
+        hp.backward(q[2], q[1], *w, stream=stream)
+
+    def result(hp):
+        torch.cuda.synchronize()
+        return {n: hp.b[n].clone() for n in names}
+
+    hp = layer(False)
+    step(hp, a)
+    want = result(hp)
+    assert not streams
+    hp = layer(True)
+    main = torch.cuda.current_stream().cuda_stream
+    for _ in range(3):   # repeated passes reuse the buffers and the events
+        step(hp, b)
+        step(hp, a)
+    got = result(hp)
+    assert len(streams) == 12 and len(set(streams)) == 1 and streams[0] != main
+    assert all(torch.equal(got[n], want[n]) for n in names)
+    step(hp, b)
+    torch.cuda.synchronize()
+    own = torch.cuda.Stream()
+    step(hp, a, own)
+    assert all(torch.equal(v, want[n]) for n, v in result(hp).items())
+    step(hp, b)
+    torch.cuda.synchronize()
+    step(hp, a, own.cuda_stream)
+    assert all(torch.equal(v, want[n]) for n, v in result(hp).items())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step(hp, a)
+    for _ in range(3):
+        step(hp, b)
+        torch.cuda.synchronize()
+        graph.replay()
+        assert all(torch.equal(v, want[n]) for n, v in result(hp).items())
