@@ -33,23 +33,31 @@ PROBE_LAUNCHES = 5
 COLD_STEPS = 3               # steps of the cold-cache variant
 MFMA_PROBE_BLOCKS = 2048     # blocks (8 per CU) and rounds of the register-resident matrix loop
 MFMA_PROBE_ITERS = 1000
-# kernel behind each profiling label on the bf16 LDS-DMA path, as rocprofv3 names it; a launch of the expert products
-# holds the tiles of the routed and of the shared experts
-SYMBOL = {
-    "gemm_fwd_gate_up": "moe::row_gemm_kernel<moe::RowCores<2, 2, false>, 2, 1, false>(moe::RowGemm, moe::RowGemm, int)",
-    "gemm_fwd_down": "moe::row_gemm_kernel<moe::RowCores<2, 1, false>, 1, 0, false>(moe::RowGemm, moe::RowGemm, int)",
-    "gemm_bwd_dh_dwd": "moe::row_w_gemm_kernel<moe::RowCores<2, 1, true>, 2, moe::MfmaDmaCore<unsigned short, 256, 256, 1, "
-                       "false, false, 2, 2, 1, false>, 1>(moe::RowGemm, moe::RowGemm, moe::WGemm, moe::WGemm, moe::RowWOrder)",
-    "gemm_bwd_dx_dwgu": "moe::row_w_gemm_kernel<moe::RowCores<2, 1, true>, 0, moe::MfmaDmaCore<unsigned short, 256, 128, 2, "
-                        "false, false, 2, 2, 1, false>, 2>(moe::RowGemm, moe::RowGemm, moe::WGemm, moe::WGemm, moe::RowWOrder)",
-    "gemm_bwd_dw_light": "moe::w_light_kernel<moe::MfmaDmaCore<unsigned short, 128, 128, 1, false, false, 2, 2, 0, false> >"
-                         "(moe::WGemm, moe::WGemm, int)",
+# kernel behind each profiling label on the bf16 LDS-DMA path, and its template parameters
+KERNEL = {
+    "gemm_fwd_gate_up": ("row_gemm_kernel", "moe::RowCores<2, 2, false>, 2, 1, false"),
+    "gemm_fwd_down": ("row_gemm_kernel", "moe::RowCores<2, 1, false>, 1, 0, false"),
+    "gemm_bwd_dh_dwd": ("row_w_gemm_kernel", "moe::RowCores<2, 1, true>, 2, moe::MfmaDmaCore<unsigned short, 256, 256, 1, false, "
+                                             "false, 2, 2, 1, false>, 1"),
+    "gemm_bwd_dx_dwgu": ("row_w_gemm_kernel", "moe::RowCores<2, 1, true>, 0, moe::MfmaDmaCore<unsigned short, 256, 128, 2, false, "
+                                              "false, 2, 2, 1, false>, 2"),
+    "gemm_bwd_dw_light": ("w_light_kernel", "moe::MfmaDmaCore<unsigned short, 128, 128, 1, false, false, 2, 2, 0, false> "),
+}
+# arguments of the kernels of one set of experts, and of those that hold the tiles of the routed and the shared ones
+KERNEL_ARGS = {
+    "row_gemm_kernel": ("moe::RowGemm", "moe::RowGemm, moe::RowGemm, int"),
+    "row_w_gemm_kernel": ("moe::RowGemm, moe::WGemm, int, int",
+                          "moe::RowGemm, moe::RowGemm, moe::WGemm, moe::WGemm, moe::RowWOrder"),
 }
 
 
-def symbols(label):
-    """Every kernel that the launches of a label run."""
-    return (SYMBOL[label],)
+def symbol(label, shared):
+    """The kernel that a label's launches run, as rocprofv3 names it; `shared`: the layer has shared experts."""
+    kernel, params = KERNEL[label]
+    if kernel == "w_light_kernel":
+        return f"moe::{kernel}<{params}>(moe::WGemm, moe::WGemm, int)"
+    one, both = KERNEL_ARGS[kernel]
+    return f"moe::both_{kernel}<{params}>({both})" if shared else f"moe::{kernel}<{params}, true>({one})"
 
 
 def algorithmic_work(cfg: wl.MoEConfig, counts):
@@ -92,7 +100,7 @@ def measured_traffic(cfg_name, label):
     if not os.path.exists(path):
         return None, None
     commit = next((ln.split(":", 1)[1].strip() for ln in open(path) if ln.startswith("# commit:")), "not recorded")
-    return read_mean_traffic(path, symbols(label)), f"{rel} (rocprofv3 --pmc FETCH_SIZE, WRITE_SIZE; kernels of commit {commit})"
+    return read_mean_traffic(path, (symbol(label, wl.CONFIGS[cfg_name].n_shared > 0),)), f"{rel} (rocprofv3 --pmc FETCH_SIZE, WRITE_SIZE; kernels of commit {commit})"
 
 
 class LazyExperts:
@@ -358,9 +366,9 @@ def main():
     dom_n, dom_ms = prof[dom]
     peak = MFMA_BF16_PEAK_TF if cfg.dtype == "bf16" else FP32_VEC_PEAK_TF
     achieved = flops[dom] * args.steps / (dom_ms * 1e-3) / 1e12
-    dma_path = cfg.dtype == "bf16" and cfg.d % 64 == 0 and cfg.d_ff % 64 == 0   # SYMBOL names that path's kernels
+    dma_path = cfg.dtype == "bf16" and cfg.d % 64 == 0 and cfg.d_ff % 64 == 0   # KERNEL names that path's
     traffic, traffic_src = measured_traffic(cfg.name, dom) if dma_path else (None, None)
-    roofline = {"bound": "mfma" if cfg.dtype == "bf16" else "alu", "kernel": dom, "symbol": SYMBOL[dom] if dma_path else None,
+    roofline = {"bound": "mfma" if cfg.dtype == "bf16" else "alu", "kernel": dom, "symbol": symbol(dom, cfg.n_shared > 0) if dma_path else None,
                 "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s", "frac": round(achieved / peak, 4),
                 "avg_launch_ms": round(dom_ms / dom_n, 4), "launches": dom_n,
                 "flop_per_launch_avg": flops[dom] * args.steps / dom_n,

@@ -314,26 +314,24 @@ __device__ __forceinline__ void w_gemm_block(const WGemm& p, int block, char* sm
 }
 
 // ---------------------------------------------------------------------------------- kernels
-// A product over the rows of shared experts (or of the router: no plan), `s_blocks` blocks, and the same product over
-// those of the routed experts (a plan), in one launch; either may be missing.  The shared tiles are full and even, so
+// A product over the rows of routed experts (PLAN), of shared ones or of the router (no plan).
+template <class CoreSet, int NB, int EPI, bool B_KC, bool PLAN>
+__global__ __launch_bounds__(CoreSet::template tile<0>::NT, CoreSet::template tile<0>::BLOCKS_PER_CU) void row_gemm_kernel(RowGemm p) {
+  extern __shared__ __align__(16) char smem[];
+  row_gemm_block<CoreSet, NB, EPI, B_KC, PLAN>(p, blockIdx.x, smem);
+}
+// The same product over the rows of shared experts, `s_blocks` blocks, and over those of the routed ones, in one launch.  The shared
+// tiles are full and even, so
 // they come first: the light tiles of the routed groups end the launch.  (In launches of their own the shared experts' few tiles leave
 // compute units idle, and so do the last routed ones.  Before and now, whole passes: 16 tokens through 4 shared of width 1408 and
 // 60 experts, d = 2048, forward 137 -> 122 us; training, T = 3001, d = 1000, one shared 673 -> 603, T = 2777, d = 2048, four shared
 // 1629 -> 1518.  Against the shared experts on a second stream: T = 4096 of the last, 2188 -> 2162.)
 template <class CoreSet, int NB, int EPI, bool B_KC>
-__global__ __launch_bounds__(CoreSet::template tile<0>::NT, CoreSet::template tile<0>::BLOCKS_PER_CU) void row_gemm_kernel(RowGemm s, RowGemm r, int s_blocks) {
+__global__ __launch_bounds__(CoreSet::template tile<0>::NT, CoreSet::template tile<0>::BLOCKS_PER_CU) void both_row_gemm_kernel(RowGemm s, RowGemm r, int s_blocks) {
   extern __shared__ __align__(16) char smem[];
   const int b = (int)blockIdx.x - s_blocks;
   if (b < 0) row_gemm_block<CoreSet, NB, EPI, B_KC, false>(s, blockIdx.x, smem);
   else row_gemm_block<CoreSet, NB, EPI, B_KC, true>(r, b, smem);
-}
-// The router's product, which never has routed rows beside it: one argument block and none of the plan's code.  (Its launches are
-// single rounds, bound by how fast they start: a kernel of one argument block took 15.8 us where the one above takes 17.1 for T = 300,
-// d = 2048, 64 experts, and 10.6 against 11.6 for T = 4096, d = 1024, 16 experts; router passes of the first: 34.2 -> 33.0 us.)
-template <class CoreSet, int NB, int EPI, bool B_KC>
-__global__ __launch_bounds__(CoreSet::template tile<0>::NT, CoreSet::template tile<0>::BLOCKS_PER_CU) void direct_row_gemm_kernel(RowGemm s) {
-  extern __shared__ __align__(16) char smem[];
-  row_gemm_block<CoreSet, NB, EPI, B_KC, false>(s, blockIdx.x, smem);
 }
 // An input gradient and a weight gradient that does not depend on it in one launch: first the row tiles (the longer
 // ones), then weight-gradient tiles, which fill the compute units that the last row tiles leave idle.
@@ -347,8 +345,16 @@ __global__ __launch_bounds__(CoreSet::template tile<0>::NT, CoreSet::template ti
 struct RowWOrder {
   int32_t first_sw, s_rows, mid_sw, r_rows, last_sw;
 };
+// of one set (of the router, without a plan): only the first of those places for weight gradients, and the end
+template <class CoreSet, int EPI, class WCore, int WNB, bool PLAN>
+__global__ __launch_bounds__(WCore::NT, CoreSet::template tile<0>::BLOCKS_PER_CU) void row_w_gemm_kernel(RowGemm p, WGemm w, int first_w, int rows) {
+  extern __shared__ __align__(16) char smem[];
+  const int b = blockIdx.x, row = b - (PLAN ? 0 : first_w);
+  if (row >= 0 && row < rows) row_gemm_block<CoreSet, 1, EPI, true, PLAN>(p, row, smem);
+  else w_gemm_block<WCore, WNB, PLAN>(w, row < 0 ? b : row - rows, smem);
+}
 template <class CoreSet, int EPI, class WCore, int WNB>
-__global__ __launch_bounds__(WCore::NT, CoreSet::template tile<0>::BLOCKS_PER_CU) void row_w_gemm_kernel(RowGemm s, RowGemm r, WGemm sw, WGemm rw, RowWOrder o) {
+__global__ __launch_bounds__(WCore::NT, CoreSet::template tile<0>::BLOCKS_PER_CU) void both_row_w_gemm_kernel(RowGemm s, RowGemm r, WGemm sw, WGemm rw, RowWOrder o) {
   extern __shared__ __align__(16) char smem[];
   // positions from the start of each section on
   const int b = blockIdx.x, srow = b - o.first_sw, mid = srow - o.s_rows, rrow = mid - o.mid_sw, last = rrow - o.r_rows;
@@ -615,7 +621,22 @@ static void set_choice(RowGemm& p, const DirectShape& s, const DirectChoice& c, 
   p.part_blocks = (int)row_block_count(s.groups * ceil_div(s.rows, bm >> c.kind), p.N, bn);
 }
 
+template <auto KERNEL, class... Args>
+static void launch_gemm(const char* label, unsigned blocks, int threads, int lds_bytes, hipStream_t st, Args... args) {
+  static LdsAttr attr;
+  attr.ensure((const void*)KERNEL, lds_bytes);
+  ProfScope prof(label, st);
+  hipLaunchKernelGGL(KERNEL, dim3(blocks), dim3(threads), lds_bytes, st, args...);
+}
+// epilogues of the router's products, which never have routed rows beside them
+template <int EPI> constexpr bool kRouterOnly = EPI == EPI_STORE_F32 || EPI == EPI_ADD;
+
 // One product over the shared rows (sd), the routed rows (r, at most r_tiles tiles), or both.
+// Launches of one set have kernels of their own, with one argument block and without the other set's code: short ones are bound by how
+// fast they start.  (A call of one set in the kernels of both and in these, us, forward / backward: routed, T = 300, d = 1024, 16
+// experts 32.6 / 63.2 and 32.2 / 63.0; T = 1500, d = 384, 4 experts 37.8 / 62.3 and 37.4 / 61.8; T = 2048, d = 1024, 8 experts
+// 54.0 / 86.0 and 52.8 / 86.0; shared, 300 rows, 2 of 1024 31.6 / 34.8 and 30.5 / 34.5; 16 rows, 4 of 1408, d = 2048 41.0 / 54.8 and
+// 40.3 / 54.4.  The router, T = 300, d = 2048, 64 experts: the product 17.1 and 15.8.)
 template <class CoreSet, int NB, int EPI, bool B_KC>
 static void launch_row(const char* label, const Direct* sd, const RowGemm* r, int r_tiles, hipStream_t st) {
   typedef typename CoreSet::template tile<0> Core;
@@ -633,18 +654,12 @@ static void launch_row(const char* label, const Direct* sd, const RowGemm* r, in
   }
   const unsigned sb = (unsigned)p.part_blocks * c.n_parts, rb = r ? row_block_count(r_tiles, r->N, Core::BN) : 0;
   if (sb + rb == 0) return;
-  static LdsAttr attr;
   constexpr int kLds = row_lds_bytes<CoreSet>();
-  if constexpr (EPI == EPI_STORE_F32) {  // the router's epilogue
-    auto kern = direct_row_gemm_kernel<CoreSet, NB, EPI, B_KC>;
-    attr.ensure((const void*)kern, kLds);
-    ProfScope prof(label, st);
-    hipLaunchKernelGGL(kern, dim3(sb), dim3(Core::NT), kLds, st, p);
-  } else {
-    auto kern = row_gemm_kernel<CoreSet, NB, EPI, B_KC>;
-    attr.ensure((const void*)kern, kLds);
-    ProfScope prof(label, st);
-    hipLaunchKernelGGL(kern, dim3(sb + rb), dim3(Core::NT), kLds, st, p, r ? *r : RowGemm{}, (int)sb);
+  if (rb == 0) {
+    launch_gemm<row_gemm_kernel<CoreSet, NB, EPI, B_KC, false>>(label, sb, Core::NT, kLds, st, p);
+  } else if constexpr (!kRouterOnly<EPI>) {
+    if (sb == 0) launch_gemm<row_gemm_kernel<CoreSet, NB, EPI, B_KC, true>>(label, rb, Core::NT, kLds, st, *r);
+    else launch_gemm<both_row_gemm_kernel<CoreSet, NB, EPI, B_KC>>(label, sb + rb, Core::NT, kLds, st, p, *r, (int)sb);
   }
   if (c.n_parts > 1) launch_reduce<typename Core::T, NB, EPI>(p.part, c.n_parts, sd->shape.out_elems, p.out, p.in, st);
 }
@@ -684,13 +699,12 @@ static void launch_row_w(const char* label, const Direct* sd, const RowGemm* r, 
   if (r) o.r_rows = (int)row_block_count(r_tiles, r->N, Core::BN);
   const unsigned blocks = (unsigned)(o.first_sw + o.s_rows + o.mid_sw + o.r_rows + o.last_sw) + (r ? w_block_count<WCore>(*rw) : 0);
   if (blocks == 0) return;
-  auto kern = row_w_gemm_kernel<CoreSet, EPI, WCore, WNB>;
-  static LdsAttr attr;
   constexpr int kLds = std::max(row_lds_bytes<CoreSet>(), WCore::LDS_BYTES);
-  attr.ensure((const void*)kern, kLds);
-  {
-    ProfScope prof(label, st);
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(WCore::NT), kLds, st, p, r ? *r : RowGemm{}, w, r ? *rw : WGemm{}, o);
+  if (!r) {
+    launch_gemm<row_w_gemm_kernel<CoreSet, EPI, WCore, WNB, false>>(label, blocks, WCore::NT, kLds, st, p, w, o.first_sw, o.s_rows);
+  } else if constexpr (!kRouterOnly<EPI>) {
+    if (!sd) launch_gemm<row_w_gemm_kernel<CoreSet, EPI, WCore, WNB, true>>(label, blocks, WCore::NT, kLds, st, *r, *rw, 0, o.r_rows);
+    else launch_gemm<both_row_w_gemm_kernel<CoreSet, EPI, WCore, WNB>>(label, blocks, WCore::NT, kLds, st, p, *r, w, *rw, o);
   }
   if (rc.n_parts > 1) launch_reduce<T, 1, EPI>(p.part, rc.n_parts, sd->shape.out_elems, p.out, p.in, st);
   if (wc.n_parts > 1) launch_reduce<T, WNB, EPI_STORE>(w.part, wc.n_parts, sd->w_shape.out_elems, w.C, nullptr, st);

@@ -96,3 +96,23 @@ def test_current_build_passes():
         if not os.path.exists(path):
             pytest.skip("the build step has not left its device assembly here")
         assert asm_check.check(path) == []
+
+
+@pytest.mark.parametrize("src", ["expert_bf16.hip", "expert_tail.hip", "expert_f32.hip"])
+def test_launches_of_one_set_have_kernels_of_one_argument_block(src):
+    """Every product has a kernel for the routed experts alone and one for the shared ones alone, with half the arguments and
+    a part of the code of the kernel that holds both."""
+    path = build.device_asm(src)
+    if not os.path.exists(path):
+        pytest.skip("the build step has not left its device assembly here")
+    with open(path) as f:
+        text = f.read()
+    args = dict(re.findall(r"\.amdhsa_kernel (\S+)[^.]*(?:\.(?!amdhsa_kernarg_size)[^.]*)*\.amdhsa_kernarg_size (\d+)", text))
+    both = {n: int(b) for n, b in args.items() if "both_row_gemm_kernel" in n or "both_row_w_gemm_kernel" in n}
+    # gate/up gated or not, down; dH gated or not, dX with one product or two
+    assert len([n for n in both if "row_gemm" in n]) == 3 and len([n for n in both if "row_w_gemm" in n]) == 4
+    for name, size in both.items():
+        kernel = re.match(r"_ZN3moe\d+both_(row_\w+?_kernel)(I.*)EEvN", name)
+        for plan in (0, 1):   # template parameter PLAN
+            one = [n for n in args if n.startswith(f"_ZN3moe{len(kernel[1])}{kernel[1]}{kernel[2]}Lb{plan}EEEv")]
+            assert len(one) == 1 and int(args[one[0]]) <= size // 2, name

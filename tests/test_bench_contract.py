@@ -30,10 +30,11 @@ def test_a_multi_rank_launch_is_refused_too():
 
 @pytest.mark.parametrize("cfg", ["dsv3", "qwen", "stress"])
 def test_traffic_of_a_label_is_that_of_all_its_launches(cfg):
-    """The roofline's time and FLOPs per launch are means over the routed and the shared experts' launches of a label, so
-    its bytes have to be."""
+    """The roofline's time and FLOPs per launch are means over a label's launches, so its bytes have to be; the kernel
+    that the label names is the one that layers with shared experts run, or layers without."""
     sys.path.insert(0, ROOT)
     import bench
+    import workloads as wl
 
     path = os.path.join(ROOT, "profiles", f"hbm_traffic_{cfg}.txt")
     rows = [ln.rstrip("\n").split("\t") for ln in open(path) if not ln.startswith("#")]
@@ -41,9 +42,9 @@ def test_traffic_of_a_label_is_that_of_all_its_launches(cfg):
     gemms = [n for n in of if "gemm_kernel" in n or "w_light_kernel" in n]
     named = []
     for label in bench.GEMM_LABELS:
-        here = [of[s] for s in bench.symbols(label) if s in of]
-        assert bench.symbols(label)[0] in of, label
-        assert bench.measured_traffic(cfg, label)[0] == pytest.approx(sum(n * b for n, b in here) / sum(n for n, _ in here))
-        named += [s for s in bench.symbols(label) if s in of]
+        symbol = bench.symbol(label, wl.CONFIGS[cfg].n_shared > 0)
+        assert symbol in of, label
+        assert bench.measured_traffic(cfg, label)[0] == pytest.approx(of[symbol][1])
+        named.append(symbol)
     assert sorted(named) == sorted(gemms)   # every GEMM kernel of the profile belongs to one label
     assert bench.measured_traffic("tiny", bench.GEMM_LABELS[0])[0] is None
