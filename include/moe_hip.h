@@ -356,12 +356,12 @@ int moe_copy_probe(const void* src, void* dst, size_t bytes, void* stream);
 
 /*
  * moe_mfma_probe -- measurement aid, not part of the hot path: a register-resident matrix loop
- * (mfma_probe_kernel).  n_blocks blocks of four wavefronts each issue `iters` rounds of 16 independent
- * v_mfma_f32_32x32x16_bf16 (all 256 accumulator registers in use, one wavefront per SIMD, no loads, no
- * LDS).  Its rate is what the matrix pipe sustains at the clock the chip holds under matrix load: the
- * measured ceiling beside the published 2.5 PFLOP/s.
+ * (mfma_probe_kernel).  n_blocks blocks of four wavefronts each issue `iters` rounds of 32 independent
+ * v_mfma_f32_16x16x32_bf16, the instruction of the bf16 products (no loads, no LDS).  Its rate is what the
+ * matrix pipe sustains at the clock the chip holds under matrix load: the measured ceiling beside the
+ * published 2.5 PFLOP/s.
  *   sink       device buffer of n_blocks * 256 floats (never written in practice; keeps the loop alive)
- *   flops_out  host pointer or NULL: receives the FLOPs of the launch, n_blocks * 4 * iters * 16 * 32768
+ *   flops_out  host pointer or NULL: receives the FLOPs of the launch, n_blocks * 4 * iters * 32 * 16384
  */
 int moe_mfma_probe(int32_t n_blocks, int32_t iters, float* sink, double* flops_out, void* stream);
 

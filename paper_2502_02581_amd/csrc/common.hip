@@ -172,12 +172,11 @@ extern "C" int moe_copy_probe(const void* src, void* dst, size_t bytes, void* st
 }
 
 namespace moe {
-// Register-resident matrix loop: every wavefront issues `iters` rounds of 16 independent
-// v_mfma_f32_32x32x16_bf16 on constant operands (16 accumulator tiles = all 256 accumulator registers,
-// one wavefront per SIMD); no loads, no LDS.  What it sustains is the matrix pipe's rate at the clock
-// the chip holds under that load.
+// Register-resident matrix loop: every wavefront issues `iters` rounds of 32 independent
+// v_mfma_f32_16x16x32_bf16, the instruction of the bf16 tile cores, on constant operands (32 accumulator tiles);
+// no loads, no LDS.  What it sustains is the matrix pipe's rate at the clock the chip holds under that load.
 typedef __attribute__((ext_vector_type(8))) __bf16 probe_bf16x8_t;
-typedef __attribute__((ext_vector_type(16))) float probe_f32x16_t;
+typedef __attribute__((ext_vector_type(4))) float probe_f32x4_t;
 __global__ __launch_bounds__(256) void mfma_probe_kernel(int iters, float* sink) {
   const int lane = threadIdx.x & 63;
   probe_bf16x8_t a, b;
@@ -186,20 +185,28 @@ __global__ __launch_bounds__(256) void mfma_probe_kernel(int iters, float* sink)
     a[i] = (__bf16)(0.001f * (float)((lane + i) % 7));
     b[i] = (__bf16)(0.002f * (float)((lane + 2 * i) % 5));
   }
-  probe_f32x16_t acc[16];
+  probe_f32x4_t acc[32];
 #pragma unroll
-  for (int j = 0; j < 16; j++)
+  for (int j = 0; j < 32; j++)
 #pragma unroll
-    for (int r = 0; r < 16; r++) acc[j][r] = 0.f;
+    for (int r = 0; r < 4; r++) acc[j][r] = 0.f;
+  // Inline assembly, as in the tile cores: the compiler moves accumulators between registers inside the loop otherwise.  The
+  // wait states that it would insert are explicit: behind the zeroing, and between the last MFMA and the first read.
+#pragma unroll
+  for (int j = 0; j < 32; j++) asm volatile("" : "+a"(acc[j]));
+  asm volatile("s_nop 7" : "+v"(a), "+v"(b));
   for (int it = 0; it < iters; it++) {
 #pragma unroll
-    for (int j = 0; j < 16; j++) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[j], 0, 0, 0);
+    for (int j = 0; j < 32; j++) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[j]) : "v"(b), "v"(a));
   }
+  asm volatile("s_nop 15\n\ts_nop 15" : "+a"(acc[31]));
+#pragma unroll
+  for (int j = 0; j < 31; j++) asm volatile("" : "+a"(acc[j]));
   float s = 0.f;
 #pragma unroll
-  for (int j = 0; j < 16; j++)
+  for (int j = 0; j < 32; j++)
 #pragma unroll
-    for (int r = 0; r < 16; r++) s += acc[j][r];
+    for (int r = 0; r < 4; r++) s += acc[j][r];
   // keeps the loop alive; the sums are small positive numbers, so nothing is ever stored
   if (s == -1.f) sink[blockIdx.x * 256 + threadIdx.x] = s;
 }
@@ -215,8 +222,8 @@ extern "C" int moe_mfma_probe(int32_t n_blocks, int32_t iters, float* sink, doub
     ProfScope prof("mfma_probe_kernel", (hipStream_t)stream);
     hipLaunchKernelGGL(mfma_probe_kernel, dim3((unsigned)n_blocks), dim3(256), 0, (hipStream_t)stream, (int)iters, sink);
   }
-  // 4 wavefronts x iters x 16 instructions x (2 * 32 * 32 * 16) FLOPs per block
-  if (flops_out) *flops_out = (double)n_blocks * 4.0 * (double)iters * 16.0 * 32768.0;
+  // 4 wavefronts x iters x 32 instructions x (2 * 16 * 16 * 32) FLOPs per block
+  if (flops_out) *flops_out = (double)n_blocks * 4.0 * (double)iters * 32.0 * 16384.0;
   return launch_status("moe_mfma_probe");
 }
 

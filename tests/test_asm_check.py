@@ -116,3 +116,12 @@ def test_launches_of_one_set_have_kernels_of_one_argument_block(src):
         for plan in (0, 1):   # template parameter PLAN
             one = [n for n in args if n.startswith(f"_ZN3moe{len(kernel[1])}{kernel[1]}{kernel[2]}Lb{plan}EEEv")]
             assert len(one) == 1 and int(args[one[0]]) <= size // 2, name
+
+
+def test_matrix_probe_issues_the_instruction_of_the_tile_cores():
+    """The sustained rate that bench.py divides by is that of the instruction the bf16 products run on."""
+    paths = [build.device_asm(src) for src in ("common.hip", "expert_bf16.hip")]
+    if not all(os.path.exists(p) for p in paths):
+        pytest.skip("the build step has not left its device assembly here")
+    probe, cores = (set(re.findall(r"^\s+(v_mfma_\w+)", open(p).read(), re.M)) for p in paths)
+    assert probe == cores and len(cores) == 1
