@@ -68,16 +68,28 @@ def test_both_sets_in_one_call(dtype, T, d, E, k, F, S, Fs, act, act_s, gather):
     moe.moe_expert_bwd(sshape, S, None, T, X, Wsg, Wsu, Wsd, s["G"], s["U"], s["H"], dY, *[s[n] for n in gr], ws_s)
 
     fwd = ("G", "U", "H", "Yout")
-    base = dict(d_ff=F, n_groups=E, n_rows=A, offsets=off, Wg=Wg, Wu=Wu, Wd=Wd, ws=ws, ws_bytes=size)
-    base_s = dict(d_ff=Fs, n_groups=S, n_rows=T, Xin=X, Wg=Wsg, Wu=Wsu, Wd=Wsd, ws=ws_s, ws_bytes=size_s)
-    ws.fill_(255), ws_s.fill_(255)
+    base = dict(d_ff=F, n_groups=E, n_rows=A, offsets=off, Wg=Wg, Wu=Wu, Wd=Wd)
+    base_s = dict(d_ff=Fs, n_groups=S, n_rows=T, Xin=X, Wg=Wsg, Wu=Wsu, Wd=Wsd)
+    bands = []
+
+    def workspaces(query):   # of exactly the queried sizes, filled, between bands in one buffer: one launch writes both
+        n, n_s = query(shape, E, A, False), query(sshape, S, T, True)
+        at = 4096 + (n + 255) // 256 * 256 + 4096
+        big = torch.full((at + n_s + 4096,), 0xA5, dtype=torch.uint8, device=dev)
+        bands.extend((big[:4096], big[4096 + n:at], big[at + n_s:]))
+        for b, piece, m in ((base, big[4096:4096 + n], n), (base_s, big[at:at + n_s], n_s)):
+            piece.fill_(255)
+            b.update(ws=piece, ws_bytes=m)
+
+    workspaces(moe.moe_expert_fwd_workspace_bytes)
     moe.moe_experts_fwd(shape, dict(base, Xin=X if gather else Xp, src_of=src_of if gather else None, **{n: r2[n] for n in fwd}),
                         dict(base_s, **{n: s2[n] for n in fwd}))
-    ws.fill_(255), ws_s.fill_(255)
+    workspaces(moe.moe_expert_bwd_workspace_bytes)
     in_place = dict(src_of=src_of, dY=dY, row_w=w) if gather else {}
     moe.moe_experts_bwd(shape, dict(base, Xin=Xp, dYin=dYp, **in_place, **{n: r2[n] for n in gr + ["G", "U", "H"]}),
                         dict(base_s, dYin=dY, **{n: s2[n] for n in gr + ["G", "U", "H"]}))
     torch.cuda.synchronize()
+    assert all(bool((band == 0xA5).all()) for band in bands)
     for n in r:
         assert torch.equal(r[n].view(torch.uint8), r2[n].view(torch.uint8)), n
     for n in s:

@@ -410,8 +410,64 @@ def test_router_linear_map(T, d, E, dtype):
         assert scale_rel_err(dX.cpu(), ref_dX + (np64(dX0) if accumulate else 0.0)) <= tol
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("gather", [False, True])
+def test_layer_is_its_separate_calls(dtype, gather):
+    """MoEHotPath (common launches of both sets, fused prologue, one workspace in pieces) against the separate calls of each set, one
+    after the other, each with a workspace of its own.  Routed results are the same bits, in fp32 all results are; in bf16
+    the shared experts' sums have other parts (half a unit in the last place of both, 2 * 2^-9, for each of two roundings)."""
+    import paper_2502_02581_amd as moe
+
+    T, d, E, k, F, S, Fs = 700, 256, 4, 2, 256, 2, 192
+    cfg = small_cfg("calls", T=T, d=d, E=E, k=k, d_ff=F, dtype=dtype, zipf_s=0.8, n_shared=S, d_ff_shared=Fs)
+    g = {n: v.cuda() for n, v in problem(cfg).items()}
+    X, dY, W, Ws = g["X"], g["dY"], (g["Wg"], g["Wu"], g["Wd"]), (g["Wsg"], g["Wsu"], g["Wsd"])
+    shape, sshape = moe.MoEShape(T, d, E, k, F, dtype, cfg.gate, cfg.renorm), moe.MoEShape(T, d, E, k, Fs, dtype, cfg.gate, cfg.renorm)
+    hp = moe.MoEHotPath(shape, S, Fs, "cuda:0", gather=gather)
+    hp.forward(g["logits"], X, *W, *Ws)
+    hp.backward(dY, X, *W, *Ws)
+    b = {n: torch.full_like(t, -1 if t.dtype == torch.int32 else float("nan")) for n, t in hp.b.items()}
+    A, dev = T * k, "cuda"
+
+    def ws(*sizes):
+        return torch.empty(max(sizes), dtype=torch.uint8, device=dev)
+
+    ws_r = ws(moe.moe_dispatch_workspace_bytes(shape), moe.moe_expert_fwd_workspace_bytes(shape, E, A, False),
+              moe.moe_expert_bwd_workspace_bytes(shape, E, A, False))
+    ws_s = ws(moe.moe_expert_fwd_workspace_bytes(sshape, S, T, True), moe.moe_expert_bwd_workspace_bytes(sshape, S, T, True))
+    moe.moe_route(shape, g["logits"], b["topk_idx"], b["topk_w"])
+    moe.moe_dispatch(shape, X, b["topk_idx"], b["counts"], b["offsets"], b["row_of"], b["src_of"], b["Xp"], ws_r)
+    act, grads = [b["G"], b["U"], b["H"]], [b[n] for n in ("dXp", "active_ids", "n_active", "dWg_c", "dWu_c", "dWd_c")]
+    act_s = [b["Gs"], b["Us"], b["Hs"]]
+    if gather:
+        moe.moe_expert_fwd_gather(shape, b["offsets"], b["src_of"], X, *W, *act, b["Yp"], ws_r)
+    else:
+        moe.moe_expert_fwd(shape, E, b["offsets"], A, b["Xp"], *W, *act, b["Yp"], ws_r)
+    moe.moe_expert_fwd(sshape, S, None, T, X, *Ws, *act_s, b["Ysh"], ws_s)
+    moe.moe_combine(shape, b["Yp"], b["row_of"], b["topk_w"], b["Ysh"], b["Y"])
+    moe.moe_combine_bwd(shape, dY, b["Yp"], b["row_of"], b["topk_w"], b["dYp"], b["dw"])
+    if gather:
+        moe.moe_expert_bwd_gather(shape, b["offsets"], b["src_of"], b["Xp"], *W, *act, dY, b["topk_w"], b["dYp"], *grads, ws_r)
+    else:
+        moe.moe_expert_bwd(shape, E, b["offsets"], A, b["Xp"], *W, *act, b["dYp"], *grads, ws_r)
+    moe.moe_expert_bwd(sshape, S, None, T, X, *Ws, *act_s, dY, b["dXsh"], b["s_active_ids"], b["s_n_active"], b["dWsg"], b["dWsu"],
+                       b["dWsd"], ws_s)
+    moe.moe_combine(shape, b["dXp"], b["row_of"], None, b["dXsh"], b["dX"])
+    moe.moe_route_bwd(shape, g["logits"], b["topk_idx"], b["dw"], b["dlogits"])
+    torch.cuda.synchronize()
+    n_act = int(hp.b["n_active"].item())
+    for n, want in b.items():
+        got = hp.b[n]
+        if n in ("dWg_c", "dWu_c", "dWd_c"):
+            got, want = got[:n_act], want[:n_act]
+        if dtype == "bf16" and n in ("Gs", "Us", "Hs", "Ysh", "Y", "dXsh", "dX", "dWsg", "dWsu", "dWsd"):
+            assert float((got.double() - want.double()).norm() / want.double().norm()) <= 8e-3, n
+        else:
+            assert torch.equal(got.contiguous().view(torch.uint8), want.contiguous().view(torch.uint8)), n
+
+
 def test_overlap_shared_is_identical():
-    """Shared experts on a second stream: bit-identical to the single-stream order."""
+    """Both sets gated: common launches, and overlap_shared, which asks for a second stream where there are none, changes nothing."""
     import paper_2502_02581_amd as moe
 
     cfg = small_cfg("ovl", T=700, d=256, E=4, k=2, d_ff=256, dtype="bf16", zipf_s=0.8, n_shared=2, d_ff_shared=192)
@@ -515,9 +571,15 @@ def test_nothing_outside_the_outputs_is_written(cfg):
         big, view = _guarded(hp.b[key])
         keep.append((key, big))
         hp.b[key] = view
-    big_ws, hp.ws = _guarded(hp.ws)
-    hp.ws_shared = hp.ws
-    keep.append(("ws", big_ws))
+    pieces = [dict(p) for p in hp._ws_pieces()]   # the routed and the shared experts' workspaces, which one launch writes
+    for name, piece in zip(("ws of the routed experts", "ws of the shared experts"), pieces):
+        big, piece["ws"] = _guarded(piece["ws"])
+        keep.append((name, big))
+    hp._ws_pieces = lambda: pieces
+    for name in ("ws", "plan", "plan_ids", "plan_n_active"):
+        big, view = _guarded(getattr(hp, name))
+        keep.append((name, big))
+        setattr(hp, name, view)
     g = {k: v.to(hp.device) for k, v in p.items()}
     shared = [g.get("Wsg"), g.get("Wsu"), g.get("Wsd")]
     hp.forward(g["logits"], g["X"], g["Wg"], g.get("Wu"), g["Wd"], *shared)
@@ -536,9 +598,9 @@ def test_nothing_outside_the_outputs_is_written(cfg):
 
 
 def test_step_replayed_from_a_hip_graph():
-    """One forward+backward captured into a HIP graph (the shared experts on a second stream, as the
-    benchmark launches it) and replayed several times, with eager steps on other inputs and
-    synchronisations in between: every replay must reproduce the eager result bit for bit."""
+    """One forward+backward captured into a HIP graph, as the benchmark launches it, and replayed several
+    times, with eager steps on other inputs and synchronisations in between: every replay must reproduce
+    the eager result bit for bit."""
     import paper_2502_02581_amd as moe
 
     cfg = small_cfg("graph", T=620, d=128, E=12, k=3, d_ff=192, dtype="bf16", zipf_s=1.3, gate="sigmoid", n_shared=1,
