@@ -510,8 +510,9 @@ class MoEHotPath:
     the dispatch has counted the loads) and backward() adds its gradient to dlogits (moe_aux_loss_bwd).
     With fused (the default), gate + dispatch + loss + the plan of the forward products go through
     moe_route_dispatch_plan and the two backward calls of the gate through moe_route_aux_bwd: the same results from
-    five launches fewer.  backward() builds its plan from offsets, so that the tensors of b are all that a pass saved and
-    put back (several micro-batches in flight) needs.
+    five launches fewer.  backward() builds its plan from offsets, so that the tensors of b are all that the experts'
+    gradients of a pass saved and put back (several micro-batches in flight) need; dlogits also reads the logits of the last
+    forward().
     No arithmetic happens here; tensors are only allocated and handed to the library.
 
     The shared experts depend on nothing the routed experts produce, so their products run in the launches of the

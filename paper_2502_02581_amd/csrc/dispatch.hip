@@ -44,9 +44,9 @@ __global__ __launch_bounds__(64) void dispatch_count(const int32_t* __restrict__
 // over c, then the thread rewrites its run as exclusive prefixes.  Loads go a batch at a time ahead of the dependent
 // additions and stores.  (Batches of 8, the shares read
 // after the counters, as many runs as threads: T = 256, E = 8: 8.5 us, now 5.1; T = 2777, E = 60: 10.7, now 8.4.)
-// With pl.tiles, the block goes on to the plan of the experts' products: 2 to 3 us more here take the place of a launch of 4 to 7 us
-// ahead of the forward products.  (Training step of T = 256, d = 128, 8 experts, fp32, with the cheaper marshalling of the calls:
-// 93.6 -> 92.2 us; 16 tokens, 60 experts, d = 2048, forward, all of the common launches included: 138 -> 122.)
+// With pl.tiles, the block goes on to the plan of the experts' products, in place of a launch ahead of the forward products.  (More here,
+// and the launch that it saves, by number of experts: 8: 2.6 and 3.6 us, 24: 3.6 and 5.6, 60: 4.2 and 5.3, 256: 6 and 9; and the gap
+// between two launches.  Training step of T = 256, d = 128, 8 experts, fp32, with the cheaper marshalling of the calls: 93.6 -> 92.2 us.)
 // With `partial` (the fused prologue), the block also finishes the auxiliary load-balancing loss: P_e from
 // the per-chunk sums of the gate's shares (added in the same fixed order as the counters), then
 // L = alpha E sum_e (counts[e] / (T k)) P_e over ascending e.

@@ -304,7 +304,11 @@ static int check_sets(const moe_shape_t* shape, const moe_expert_set_t* routed, 
   return rc || !shared ? rc : check_set(shape, shared, false, bwd, who, s[1], need[1]);
 }
 // Common launches need the same kernels for both: one activation, and cores that take both widths.  Anything else (no
-// rows on one side, rows beyond the tile cores' offsets) goes one after the other, as the two calls would.
+// rows on one side, rows beyond the tile cores' offsets) goes one after the other, as the two calls would.  Where only one
+// width has a K tail both sets run on the cores that mask it: the masks cost less than launches apart.  (Apart and together,
+// us a pass, routed width / shared: 1408 / 4 of 1400, 16 tokens, forward 130 and 113; 1408 / 1000, T = 2048, d = 1024, training 392 and
+// 313; 1368 / 2 of 2048, T = 4096 768 and 682; 1408 / 2 of 712, T = 4096, d = 2048 1647 and 1607; 6400 / 3208, T = 8192, d = 4096 8717
+// and 8626.)
 static bool can_share(const moe_shape_t (&s)[2], const moe_expert_set_t* routed, const moe_expert_set_t* shared) {
   if (!shared) return false;
   const int64_t ld = std::max({s[0].d, s[0].d_ff, s[1].d_ff});

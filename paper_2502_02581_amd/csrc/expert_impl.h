@@ -323,9 +323,10 @@ __global__ __launch_bounds__(CoreSet::template tile<0>::NT, CoreSet::template ti
 // The same product over the rows of shared experts, `s_blocks` blocks, and over those of the routed ones, in one launch.  The shared
 // tiles are full and even, so
 // they come first: the light tiles of the routed groups end the launch.  (In launches of their own the shared experts' few tiles leave
-// compute units idle, and so do the last routed ones.  Before and now, whole passes: 16 tokens through 4 shared of width 1408 and
-// 60 experts, d = 2048, forward 137 -> 122 us; training, T = 3001, d = 1000, one shared 673 -> 603, T = 2777, d = 2048, four shared
-// 1629 -> 1518.  Against the shared experts on a second stream: T = 4096 of the last, 2188 -> 2162.)
+// compute units idle, and so do the last routed ones.  Before and now, whole passes: training, T = 3001, d = 1000, one shared
+// 673 -> 603 us, T = 2777, d = 2048, four shared 1629 -> 1518; 16 tokens through 4 shared of width 1408 and 60 experts, d = 2048,
+// forward, with the plan from the dispatch and the cheaper marshalling of the calls, 128 -> 114, by box from 139 -> 129 to 125 -> 110.
+// Against the shared experts on a second stream: training, T = 4096, d = 2048, four shared 2188 -> 2162.)
 template <class CoreSet, int NB, int EPI, bool B_KC>
 __global__ __launch_bounds__(CoreSet::template tile<0>::NT, CoreSet::template tile<0>::BLOCKS_PER_CU) void both_row_gemm_kernel(RowGemm s, RowGemm r, int s_blocks) {
   extern __shared__ __align__(16) char smem[];
@@ -511,7 +512,7 @@ template <class Core> static unsigned w_block_count(const WGemm& p, int n_produc
 // rows, 0.61 of fewer (1.02 of any height), and 8 to 6 (11 to 8).  The table's steps are within a fifth of that, those of
 // the short bf16 tiles up to half above it; the weight gradients' were not measured apart.  It has no term for the rate
 // at which weights arrive (decode's gate/up and down products over 16 rows: 9 and 10 us by the estimate, 19 and 21 by
-// measure) nor for the other stream; hence the 8 % that a choice has to promise over one part of full tiles.
+// measure); hence the 8 % that a choice has to promise over one part of full tiles.
 struct TileCost {
   int bm, bn, bk;
   float iter[4], fixed[4];

@@ -119,7 +119,7 @@ struct MfmaDmaCore {
   //     slots per operand and the loads of iteration t + DEPTH issued in iteration t, so that DEPTH
   //     whole K steps are in flight per CU; the latency of an HBM stream, not the matrix pipe, sets
   //     the pace there.
-  //  0  (weight gradients of groups with a handful of rows: K is one or two steps): one slot, no
+  //  0  (weight gradients of groups with a handful of rows: K is one step): one slot, no
   //     pipeline, small enough in LDS and registers for several blocks per CU, which is what hides
   //     latency when a block's life is one K iteration and an epilogue.
   static constexpr bool RING = DEPTH == 1;
@@ -640,7 +640,6 @@ struct MfmaDmaCore {
     constexpr int kHalf = kMfma / 2, kLate = kMfma - kHalf;
     constexpr int kLead = ES == 4 ? 0 : kMfma / 8 < 8 ? kMfma / 8 : 8;
     constexpr int kSpan = kMfma - kLead, kLateSpan = kLate - kLead;
-    auto upto = [](int r) __attribute__((always_inline)) { return r < kFragLoads ? r : kFragLoads; };
     // the loads of an iteration are spread over these MFMAs: all before the barrier
     constexpr int kSlots = (KS - 1) * kMfma + kHalf;
     Frags f[2];
@@ -841,7 +840,7 @@ struct MfmaDmaCore {
     // volatile asm pins the order); left to itself the compiler copies all 256 at the loop exit,
     // needs every arch VGPR for that and spills the loop's address registers.
     // The MFMAs above are opaque to the compiler's hazard recogniser, so the wait between the last
-    // MFMA (8 passes of 4 cycles, plus write-back) and the first read of any accumulator is
+    // MFMA (bf16: 4 passes of 4 cycles, fp32: 16, plus write-back) and the first read of any accumulator is
     // explicit: 6 x 16 idle cycles, attached to the accumulator of the last MFMA.  The empty
     // statements make every other accumulator depend on a point after that wait (volatile asm
     // statements keep their order), so no compiler-generated accumulator copy can move above it.

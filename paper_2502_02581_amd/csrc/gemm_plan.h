@@ -17,7 +17,9 @@ __host__ __device__ inline int tile_rows(const RowTile& t) { return t.rows & 0xf
 __host__ __device__ inline int tile_kind(const RowTile& t) { return (t.rows >> 16) & 3; }
 // row tiles per band of the XCD-aware tile order of the LDS-DMA path
 constexpr int kBandRows = 4;
-// launches of at most so many rounds of 256 row tiles deal them to the XCDs in short runs
+// Launches of at most so many rounds of 256 row tiles deal them to the XCDs in short runs.  (Long runs above this line against short
+// ones everywhere, training steps of d = d_ff = 4096, 8 experts, whose gate/up launch has twice the rounds given: 6.5 rounds 6475 and
+// 6445 us, 7 6818 and 6846, 8 7711 and 7798, 9 8631 and 8726, 10 9576 and 9691; for launches below it see row_gemm_block.)
 constexpr int kFineRounds = 6;
 
 // Device-built plan, laid out in the workspace.
