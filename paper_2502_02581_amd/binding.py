@@ -605,9 +605,6 @@ class MoEHotPath:
         stream = _stream(stream)
         self._logits = logits  # the gate's backward reads them again
         ws, ws_shared = self._ws_pieces()
-        if main:
-            moe_expert_fwd(self.sshape, self.S, None, s.T, X, Wsg, Wsu, Wsd, b["Gs"], b["Us"], b["Hs"], b["Ysh"],
-                           ws_shared["ws"], self.side)
         if self.fused:
             moe_route_dispatch_plan(s, logits, X, self.aux_alpha, b["topk_idx"], b["topk_w"], b["counts"], b["offsets"],
                                     b["row_of"], b["src_of"], b["Xp"], b.get("aux_P"), b.get("aux_loss"), self.plan,
@@ -620,12 +617,17 @@ class MoEHotPath:
                 moe_aux_loss(s, logits, b["counts"], self.aux_alpha, b["aux_P"], b["aux_loss"], self.ws, stream)
         shared = dict(d_ff=self.Fs, n_groups=self.S, n_rows=s.T, Xin=X, Wg=Wsg, Wu=Wsu, Wd=Wsd, G=b["Gs"], U=b["Us"],
                       H=b["Hs"], Yout=b["Ysh"], **ws_shared) if self.S and not main else None
-        moe_experts_fwd(s, dict(d_ff=s.d_ff, n_groups=s.E, n_rows=A, offsets=b["offsets"],
-                                src_of=b["src_of"] if self.gather else None, Xin=X if self.gather else b["Xp"], Wg=Wg,
-                                Wu=Wu, Wd=Wd, G=b["G"], U=b["U"], H=b["H"], Yout=b["Yp"],
-                                plan=self.plan if self.fused else None, **ws), shared, stream)
-        if main:
-            self._join(main)
+        try:
+            if main:
+                moe_expert_fwd(self.sshape, self.S, None, s.T, X, Wsg, Wsu, Wsd, b["Gs"], b["Us"], b["Hs"], b["Ysh"],
+                               ws_shared["ws"], self.side)
+            moe_experts_fwd(s, dict(d_ff=s.d_ff, n_groups=s.E, n_rows=A, offsets=b["offsets"],
+                                    src_of=b["src_of"] if self.gather else None, Xin=X if self.gather else b["Xp"], Wg=Wg,
+                                    Wu=Wu, Wd=Wd, G=b["G"], U=b["U"], H=b["H"], Yout=b["Yp"],
+                                    plan=self.plan if self.fused else None, **ws), shared, stream)
+        finally:   # a refused call must not leave the caller's tensors in use on a stream that nothing waits for
+            if main:
+                self._join(main)
         moe_combine(s, b["Yp"], b["row_of"], b["topk_w"], b["Ysh"] if self.S else None, b["Y"], stream)
         return b["Y"]
 
@@ -635,20 +637,22 @@ class MoEHotPath:
         main = self._fork(Wu, Wsu, stream)
         stream = _stream(stream)
         ws, ws_shared = self._ws_pieces()
-        if main:
-            moe_expert_bwd(self.sshape, self.S, None, s.T, X, Wsg, Wsu, Wsd, b["Gs"], b["Us"], b["Hs"], dY, b["dXsh"],
-                           b["s_active_ids"], b["s_n_active"], b["dWsg"], b["dWsu"], b["dWsd"], ws_shared["ws"], self.side)
         moe_combine_bwd(s, dY, b["Yp"], b["row_of"], b["topk_w"], b["dYp"], b["dw"], stream)
         in_place = dict(src_of=b["src_of"], dY=dY, row_w=b["topk_w"]) if self.gather else {}
         shared = dict(d_ff=self.Fs, n_groups=self.S, n_rows=s.T, Xin=X, Wg=Wsg, Wu=Wsu, Wd=Wsd, G=b["Gs"], U=b["Us"],
                       H=b["Hs"], dYin=dY, dXin=b["dXsh"], active_ids=b["s_active_ids"], n_active=b["s_n_active"],
                       dWg_c=b["dWsg"], dWu_c=b["dWsu"], dWd_c=b["dWsd"], **ws_shared) if self.S and not main else None
-        moe_experts_bwd(s, dict(d_ff=s.d_ff, n_groups=s.E, n_rows=A, offsets=b["offsets"], Xin=b["Xp"], Wg=Wg, Wu=Wu, Wd=Wd,
-                                G=b["G"], U=b["U"], H=b["H"], dYin=b["dYp"], dXin=b["dXp"], active_ids=b["active_ids"],
-                                n_active=b["n_active"], dWg_c=b["dWg_c"], dWu_c=b["dWu_c"], dWd_c=b["dWd_c"], **in_place,
-                                **ws), shared, stream)
-        if main:
-            self._join(main)
+        try:
+            if main:
+                moe_expert_bwd(self.sshape, self.S, None, s.T, X, Wsg, Wsu, Wsd, b["Gs"], b["Us"], b["Hs"], dY, b["dXsh"],
+                               b["s_active_ids"], b["s_n_active"], b["dWsg"], b["dWsu"], b["dWsd"], ws_shared["ws"], self.side)
+            moe_experts_bwd(s, dict(d_ff=s.d_ff, n_groups=s.E, n_rows=A, offsets=b["offsets"], Xin=b["Xp"], Wg=Wg, Wu=Wu, Wd=Wd,
+                                    G=b["G"], U=b["U"], H=b["H"], dYin=b["dYp"], dXin=b["dXp"], active_ids=b["active_ids"],
+                                    n_active=b["n_active"], dWg_c=b["dWg_c"], dWu_c=b["dWu_c"], dWd_c=b["dWd_c"], **in_place,
+                                    **ws), shared, stream)
+        finally:
+            if main:
+                self._join(main)
         moe_combine(s, b["dXp"], b["row_of"], None, b["dXsh"] if self.S else None, b["dX"], stream)
         if self.fused and self.aux_alpha > 0:
             moe_route_aux_bwd(s, self._logits, b["topk_idx"], b["dw"], b["counts"], self.aux_alpha, 1.0, b["dlogits"],

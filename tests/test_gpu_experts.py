@@ -328,3 +328,13 @@ def test_overlap_where_no_common_launch_is_possible(dtype, gated, monkeypatch):
         torch.cuda.synchronize()
         graph.replay()
         assert all(torch.equal(v, want[n]) for n, v in result(hp).items())
+    # a call that is refused after the shared experts' one was queued: the main stream waits for it all the same
+    joined = []
+    monkeypatch.setattr(hp, "_join", lambda m, real=hp._join: (joined.append(m), real(m)))
+    w[2] = w[2].double()
+    with pytest.raises(moe.MoEError, match="Wd"):
+        hp.forward(a[0], a[1], *w)
+    with pytest.raises(moe.MoEError, match="Wd"):
+        hp.backward(a[2], a[1], *w)
+    torch.cuda.synchronize()
+    assert len(joined) == 2
