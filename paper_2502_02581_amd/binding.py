@@ -576,7 +576,7 @@ class MoEHotPath:
         # the order of the routed experts' tiles, written by the fused prologue for the forward products, and that call's
         # active_ids and n_active: those in b belong to the gradients of the last backward pass, which alone writes them
         self.plan_ids, self.plan_n_active = torch.empty_like(self.b["active_ids"]), torch.empty_like(self.b["n_active"])
-        self.plan = torch.zeros(moe_expert_plan_bytes(s), dtype=torch.uint8, device=dev)
+        self.plan = torch.empty(moe_expert_plan_bytes(s), dtype=torch.uint8, device=dev)
 
     def _ws_pieces(self):
         """The workspace of the routed and that of the shared experts (keywords of an expert set)."""
