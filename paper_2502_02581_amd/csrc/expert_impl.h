@@ -8,6 +8,7 @@
 
 #include "gemm_cores.h"
 #include "gemm_plan.h"
+#include "split_core.h"
 
 namespace moe {
 
@@ -246,7 +247,7 @@ __device__ __forceinline__ void w_gemm_block(const WGemm& p, int block, char* sm
   // tile is a single short K step: the block's set-up, its group record and the latency of its
   // first loads are then paid once for several tiles, and the stores of one tile overlap the loads
   // of the next)
-  const int reps = p.n_reps > 1 ? p.n_reps : 1;
+  const int reps = Core::REPEATS && p.n_reps > 1 ? p.n_reps : 1;
   const int ntb = (ntn + reps - 1) / reps;
   const int per_group = (p.M + BM - 1) / BM * ntb;
   if (!PLAN && p.active_ids && block == 0)  // what plan_kernel writes when there is a plan
@@ -275,7 +276,8 @@ __device__ __forceinline__ void w_gemm_block(const WGemm& p, int block, char* sm
   const int b_row0 = start + (p.b_per_group ? g * p.n_rows : 0);
   const int m0 = mt * BM;
   const int m_valid = min(BM, p.M - m0);
-  for (int nt = nt_first; nt < min(nt_first + reps, ntn); nt++) {
+  // (one trip where the core's tiles are long: what a loop would hoist has no registers there)
+  for (int nt = nt_first; nt < (Core::REPEATS ? min(nt_first + reps, ntn) : nt_first + 1); nt++) {
   const int n0 = nt * BN;
   const int n_valid = min(BN, p.N - n0);
   if (nt > nt_first) __syncthreads();  // the previous tile's epilogue is done with LDS in every wave
@@ -412,23 +414,19 @@ __global__ __launch_bounds__(256) void reduce_kernel(Reduce p) {
 enum { PATH_F32 = 0, PATH_BF16_TAIL = 1, PATH_BF16 = 2 };
 template <int PATH> struct Cores;
 template <> struct Cores<PATH_F32> {
-  static constexpr int BM = 64, BN = 128;  // (BM: see plan_tile_rows)
-  // Bound by the fp32 matrix pipe (157 TFLOP/s).  An fp32 MFMA takes an eighth of the operand bytes per cycle of
-  // a bf16 one, so even 64 x 128 tiles (dual GEMMs: 64 x 64 of each product) keep it fed from L2; small tiles
-  // balance better and two blocks fit on a CU, one multiplying while the other stores.  Forward + backward of
-  // T = 2048, d = 1024, 16 experts, top-2, d_ff = 2816: 4.85 ms with fp32 FMA tiles (44 TFLOP/s), 2.51 ms with
-  // 128 x 128 MFMA tiles, 2.49 ms with 64 x 128 on the ring pipeline, 2.33 ms with two whole K steps in flight
-  // (91 TFLOP/s; the ring requests B too late for an iteration of 32 MFMAs); d = 128, d_ff = 256, T = 256: 275 -> 121 us.
-  template <int NB, bool A_KC, bool B_KC> using core = MfmaDmaCore<float, 128, 128 / NB, NB, A_KC, B_KC, 2, 2, 1, true>;
+  // 128 x 128 outputs (dual GEMMs: 128 x 64 of each product), two blocks per CU, one multiplying while the other stores its planes
+  // or its outputs
+  static constexpr int BM = 128, BN = 128;  // (BM: see plan_tile_rows)
+  template <int NB, bool A_KC, bool B_KC> using core = SplitCore<128, 128 / NB, NB, A_KC, B_KC, 2, 2>;
 };
 template <> struct Cores<PATH_BF16> {
   static constexpr int BM = 256, BN = 256;
   // one block of 4 wavefronts (one per SIMD, each with a 128 x 128 share: the fewest LDS reads and
   // scalar instructions per MFMA, which is what the K loop is short of) computes 256 x 256 outputs
   // (dual GEMMs: 256 x 128 of each product)
-  template <int NB, bool A_KC, bool B_KC> using core = MfmaDmaCore<bf16_t, 256, 256 / NB, NB, A_KC, B_KC, 2, 2>;
+  template <int NB, bool A_KC, bool B_KC> using core = MfmaDmaCore<256, 256 / NB, NB, A_KC, B_KC, 2, 2>;
   // weight gradients of groups with few rows: 128 x 128 outputs per product, one tile slot
-  template <int NB> using core_light = MfmaDmaCore<bf16_t, 128, 128, NB, false, false, 2, 2, 0>;
+  template <int NB> using core_light = MfmaDmaCore<128, 128, NB, false, false, 2, 2, 0>;
 };
 template <> struct Cores<PATH_BF16_TAIL> : Cores<PATH_BF16> {};
 // Groups up to this many rows, one K step, take the light dW kernel.  (256 and 64, training steps: T = 3001, d = 1000,
@@ -444,14 +442,15 @@ template <int PATH, int NB, bool B_KC> struct RowCores {
   // weights, not by MFMA work).  Pipeline depth by height: the 128-row tile fits 3 slots per operand, the
   // 64-row one 4.
   template <int KIND>
-  using tile = MfmaDmaCore<bf16_t, (KIND == 0 ? 256 : KIND == 1 ? 128 : 64), 256 / NB, NB, true, B_KC, 2, 2,
+  using tile = MfmaDmaCore<(KIND == 0 ? 256 : KIND == 1 ? 128 : 64), 256 / NB, NB, true, B_KC, 2, 2,
                            (KIND == 0 ? 1 : KIND == 1 ? 2 : 3), PATH == PATH_BF16_TAIL>;
 };
 template <int NB, bool B_KC> struct RowCores<PATH_F32, NB, B_KC> {
-  // heights 64, 32, 16, 8
+  // heights 128, 64, 32 and 16; the last two share the 32-row core
   template <int KIND>
-  using tile = std::conditional_t<(KIND == 0 || NB == 2), MfmaDmaCore<float, 64, 128 / NB, NB, true, B_KC, 2, 2, 2, true>,
-                                  MfmaDmaCore<float, 32, 128, NB == 2 ? 1 : NB, true, B_KC, 1, 4, 2, true>>;
+  using tile = std::conditional_t<KIND == 0, SplitCore<128, 128 / NB, NB, true, B_KC, 2, 2>,
+                                  std::conditional_t<KIND == 1, SplitCore<64, 128 / NB, NB, true, B_KC, 2, 2>,
+                                                     SplitCore<32, 128 / NB, NB, true, B_KC, 1, 4>>>;
 };
 
 static inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
@@ -517,19 +516,31 @@ struct TileCost {
   int bm, bn, bk;
   float iter[4], fixed[4];
 };
-template <int PATH, int NB> constexpr TileCost row_cost() {
-  if (PATH == PATH_F32)  // two blocks per CU share the matrix pipe: figures of one block that has it for itself
+// fp32 has two tables.  A sum in parts is rounded less often, so the parts of fp32 products are those of the tiles that computed them on the
+// fp32 matrix instructions, to which the results' errors are held (with parts chosen by the costs of today's tiles, fewer, shared results
+// were up to 1.6 times as far off, T = 1, d = 320, width 896: 3.1e-7 -> 4.8e-7); the height is chosen by what today's tiles take.
+template <int PATH, int NB> constexpr TileCost part_cost() {
+  if (PATH == PATH_F32)
     return NB == 2 ? TileCost{64, 64, 32, {0.9f, 0.9f, 0.9f, 0.9f}, {3, 3, 3, 3}}
                    : TileCost{64, 128, 32, {0.9f, 0.5f, 0.5f, 0.5f}, {3, 2, 2, 2}};
   return TileCost{256, 256 / NB, 64, {1.45f, 0.85f, 0.7f, 0.7f}, {7, 5, 4, 4}};
 }
-template <int PATH, int NB> constexpr TileCost w_cost() {
+template <int PATH, int NB> constexpr TileCost w_part_cost() {
   if (PATH == PATH_F32) return TileCost{128, 128 / NB, 32, {1.8f, 0, 0, 0}, {5, 0, 0, 0}};
+  return TileCost{256, 256 / NB, 64, {1.45f, 0, 0, 0}, {7, 0, 0, 0}};
+}
+template <int PATH, int NB> constexpr TileCost row_cost() {
+  if (PATH == PATH_F32)  // two blocks per CU share the matrix pipe: figures of one block that has it for itself
+    return TileCost{128, 128 / NB, 32, {0.9f, 0.5f, 0.35f, 0.35f}, {5, 4, 3, 3}};
+  return TileCost{256, 256 / NB, 64, {1.45f, 0.85f, 0.7f, 0.7f}, {7, 5, 4, 4}};
+}
+template <int PATH, int NB> constexpr TileCost w_cost() {
+  if (PATH == PATH_F32) return TileCost{128, 128 / NB, 32, {0.9f, 0, 0, 0}, {5, 0, 0, 0}};
   return TileCost{256, 256 / NB, 64, {1.45f, 0, 0, 0}, {7, 0, 0, 0}};
 }
 constexpr int kCUs = 256;
 struct DirectShape {      // one product (or pair of products, `nb` = 2) without a plan
-  TileCost cost;
+  TileCost cost, tiles;        // by which the parts are chosen, and then the height
   int groups, rows, N, K, nb;  // (weight gradient: rows is M)
   int sums;                    // segments times pairs: how often K values are summed
   int64_t out_elems;           // elements of an output matrix
@@ -541,14 +552,14 @@ struct DirectChoice {
   int64_t blocks = 0;
   size_t part_bytes = 0;
 };
-static DirectChoice direct_option(const DirectShape& s, int kind, int parts) {
+static DirectChoice direct_option(const DirectShape& s, const TileCost& cost, int kind, int parts) {
   DirectChoice c;
-  const int nk = ceil_div(s.K, s.cost.bk), per = ceil_div(nk, parts);
+  const int nk = ceil_div(s.K, cost.bk), per = ceil_div(nk, parts);
   c.kind = kind;
   c.n_parts = ceil_div(nk, per);
-  c.k_part = per * s.cost.bk;
-  c.blocks = (int64_t)s.groups * ceil_div(s.rows, s.cost.bm >> kind) * ceil_div(s.N, s.cost.bn) * c.n_parts;
-  c.block_us = s.cost.fixed[kind] + s.sums * per * s.cost.iter[kind];
+  c.k_part = per * cost.bk;
+  c.blocks = (int64_t)s.groups * ceil_div(s.rows, cost.bm >> kind) * ceil_div(s.N, cost.bn) * c.n_parts;
+  c.block_us = cost.fixed[kind] + s.sums * per * cost.iter[kind];
   if (c.n_parts > 1) {
     c.part_bytes = align_up((size_t)c.n_parts * s.nb * s.out_elems * 4, 256);
     c.reduce_us = 4 + 2e-6 / 5 * c.part_bytes;
@@ -570,10 +581,10 @@ static void choose_direct(const DirectShape* r, const DirectShape* w, size_t ava
   double best = 0;
   bool first = true;
   DirectChoice w_options[std::size(kParts)];
-  for (size_t i = 0; w && i < std::size(kParts); i++) w_options[i] = direct_option(*w, 0, kParts[i]);
+  for (size_t i = 0; w && i < std::size(kParts); i++) w_options[i] = direct_option(*w, w->cost, 0, kParts[i]);
   for (int kind = 0; kind < (r ? 4 : 1); kind++)
     for (int pr : kParts) {
-      const DirectChoice a = r ? direct_option(*r, kind, pr) : DirectChoice();
+      const DirectChoice a = r ? direct_option(*r, r->cost, kind, pr) : DirectChoice();
       if (pr > 1 && (!r || a.n_parts == 1 || a.part_bytes > avail)) continue;
       for (size_t i = 0; i < std::size(kParts); i++) {
         const DirectChoice& b = w_options[i];
@@ -593,6 +604,20 @@ static void choose_direct(const DirectShape* r, const DirectShape* w, size_t ava
         first = false;
       }
     }
+  // the same parts in the tiles that compute them
+  if (r && r->tiles.bm != r->cost.bm) {
+    const int parts = rc->n_parts;
+    best = 0;
+    for (int kind = 0; kind < 3; kind++) {
+      const DirectChoice a = direct_option(*r, r->tiles, kind, parts);
+      const double us = (double)((a.blocks + kCUs - 1) / kCUs) * a.block_us;
+      if (kind == 0 || us < best) {
+        best = us;
+        *rc = a;
+      }
+    }
+  }
+  if (w) *wc = direct_option(*w, w->tiles, 0, wc->n_parts);
 }
 
 template <typename T, int NB, int EPI>
@@ -693,7 +718,7 @@ static void launch_row_w(const char* label, const Direct* sd, const RowGemm* r, 
     w.part = (float*)(sd->parts + rc.part_bytes); w.part_stride = sd->w_shape.out_elems;
     o.s_rows = p.part_blocks * rc.n_parts;
     const int wb = (int)((w_block_count<WCore>(w) * (unsigned)wc.n_parts + 7) / 8 * 8);
-    const TileCost& c = sd->shape.cost;
+    const TileCost& c = sd->shape.tiles;
     const double routed_us = r ? c.fixed[0] + (double)r->n_pairs * r->n_segs * ceil_div(r->K, c.bk) * c.iter[0] : 0;
     (wc.block_us > rc.block_us ? o.first_sw : r && 2 * wc.block_us >= routed_us ? o.mid_sw : o.last_sw) = wb;
   }
@@ -725,11 +750,11 @@ static void launch_w_light(const char* label, const WGemm& a, const WGemm& b, in
 // The products without a plan: of a shared call, then of the router.
 template <int PATH, int NB>
 static DirectShape row_shape(int groups, int rows, int N, int K, int sums = 1) {
-  return {row_cost<PATH, NB>(), groups, rows, N, K, NB, sums, (int64_t)groups * rows * N, 0.};
+  return {part_cost<PATH, NB>(), row_cost<PATH, NB>(), groups, rows, N, K, NB, sums, (int64_t)groups * rows * N, 0.};
 }
 template <int PATH, int NB>
 static DirectShape w_shape(int groups, int M, int N, int rows) {
-  return {w_cost<PATH, NB>(), groups, M, N, rows, NB, 1, (int64_t)groups * M * N, 0.};
+  return {w_part_cost<PATH, NB>(), w_cost<PATH, NB>(), groups, M, N, rows, NB, 1, (int64_t)groups * M * N, 0.};
 }
 // The routed experts' share of a launch, in microseconds of one compute unit: n_rows rows over groups of unknown sizes.
 // It makes for fewer parts (prefill of 192 tokens, one shared expert, d = 7168: 1085 us a pass without it, 1035 with it; training, T = 3001,

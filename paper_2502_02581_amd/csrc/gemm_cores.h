@@ -1,5 +1,5 @@
-// Tile cores of the grouped GEMMs for gfx950: matrix-core tiles (bf16: v_mfma_f32_16x16x32_bf16, fp32:
-// v_mfma_f32_32x32x2_f32) with operands staged through LDS.
+// Tile core of the bf16 grouped GEMMs for gfx950: matrix-core tiles (v_mfma_f32_16x16x32_bf16) with operands staged through
+// LDS, and the epilogue of a tile, which the fp32 core (split_core.h) shares.
 //
 // The core computes, for one block, acc[nb][..] = sum over iterations of A_tile * B_tile(nb), and turns
 // them into NOUT output matrices (with NAUX input matrices of the same shape) as an epilogue object says:
@@ -50,7 +50,6 @@ struct RowMap {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(4))) short short4_t;
 typedef __attribute__((ext_vector_type(8))) short short8_t;
-typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
 // f(integral_constant<int, 0>), ... f(integral_constant<int, N - 1>): the K loops are written out by it, so that every
@@ -64,6 +63,146 @@ __device__ __forceinline__ void static_for(F f) {
   static_for_impl(f, std::make_integer_sequence<int, (N > 0 ? N : 0)>());
 }
 
+// ------------------------------------------------------------------ epilogue of a tile
+// Epilogue.  In the MFMA result layout a lane owns four consecutive columns of a row, so direct
+// global accesses would be scatters of 8- or 16-byte pieces.  The arithmetic is done in that layout, on
+// registers; the finished outputs, already in their final type, pass through a private LDS region of the
+// wave in blocks of 32 rows and are picked up again as whole rows, 16 bytes per lane.  Inputs of the epilogue
+// (the saved activations of a backward product, an output to add to) take the opposite way: whole rows
+// into registers one block ahead, through the same region into the result layout.  The region's
+// 16-byte pieces are XOR-swizzled by the row; LDS operations of one wave execute in order, so its reads and
+// writes need no waits of their own, and the stores of a block are issued after the next block's
+// arithmetic, under which their LDS reads return.
+// What bounds it is instruction issue: one wave per SIMD, nothing to switch to.  (Staging fp32 values and
+// doing arithmetic, rounding and addresses in row order, one pass of 4 rows after the other, took 10.5 k shader
+// cycles per 256 x 256 tile of plain outputs, 13.8 k with SwiGLU, 50 k with its derivative; without the
+// global stores still 9.9 k, 13.0 k, 39 k.  This form: 7.3 k, 12 k, 41 k, without the stores 4.5 k, 9.7 k, 34 k: what is
+// left is arithmetic, two transcendentals per value, and the stores and loads of a launch's first tiles, which
+// all CUs issue together.  Whole steps gain 1-3 % only, because the shader clock drops as the matrix pipe idles less.)
+// NB products of TM x TN accumulator tiles a wave, NW waves; AGPR: the accumulators live in AGPRs, under
+// inline assembly, and are copied out one by one.
+// ROWS: rows of a block.
+template <int NB, int TM, int TN, int NW, int LDS, bool AGPR, int ROWS = 32>
+struct TileEpilogue {
+  static constexpr int MT = 16;  // rows and columns of an accumulator tile
+  // LDS that the staging regions of `waves` waves take
+  template <class Epi> static constexpr int bytes(int waves) {
+    return waves * (Epi::NOUT > Epi::NAUX ? Epi::NOUT : Epi::NAUX) * ROWS * TN * MT * Epi::OES;
+  }
+  template <class Epi>
+  __device__ static __forceinline__ void run(char* smem, f32x4_t (&acc)[NB][TM][TN], const Epi& epi, int wave, int lane, int wm0, int wn0) {
+    constexpr int OES = Epi::OES, NOUT = Epi::NOUT, NAUX = Epi::NAUX;
+    constexpr int RB = TN * MT * OES;         // bytes per row of the wave's tile
+    constexpr int LPR = RB / 16;              // lanes (16-byte pieces) per row
+    constexpr int RPP = 64 / LPR;             // rows per wave-wide access
+    constexpr int NPASS = ROWS / RPP;
+    constexpr int SWZ = (LPR < 16 ? LPR : 16) - 1;
+    constexpr int NI = TM * MT / ROWS;        // blocks of the wave's tile
+    constexpr int BLOCK = ROWS * RB;          // one block of one matrix
+    constexpr int NMAT = NOUT > NAUX ? NOUT : NAUX;
+    constexpr int NA = NAUX > 0 ? NAUX : 1;
+    static_assert(bytes<Epi>(NW) <= LDS, "the waves' staging regions fit into LDS");
+    char* stage = smem + wave * (NMAT * BLOCK);
+    // row order: row pass * RPP + lane / LPR, piece lane % LPR;  result layout: row lane % MT of an accumulator tile, four of
+    // its columns, by lane / MT
+    const int rrow = lane / LPR, rpiece = lane % LPR;
+    const uint32_t r_off = rrow * RB + ((rpiece ^ (rrow & SWZ)) << 4);
+    constexpr int GR = ROWS / MT;             // accumulator tiles of a block's rows
+    const int mrow = lane & (MT - 1), h = lane / MT;
+    uint32_t m_off[GR];
+#pragma unroll
+    for (int rh = 0; rh < GR; rh++) m_off[rh] = (rh * MT + mrow) * RB + (((rh * MT + mrow) & SWZ) << 4);
+    auto row_at = [&](int pass) __attribute__((always_inline)) {  // (rrow < RPP, so the row's other bits come from pass)
+      return (r_off ^ (((pass * RPP) & SWZ) << 4)) + pass * RPP * RB;
+    };
+    // first of the lane's four columns: MT * j + 4 * h
+    auto col_at = [&](int rh, int j) __attribute__((always_inline)) {
+      return OES == 2 ? (m_off[rh] ^ ((2 * j + (h >> 1)) << 4)) + 8 * (h & 1) : (m_off[rh] ^ ((4 * j + h) << 4));
+    };
+    // global side: byte offsets from the tile's origin in every matrix
+    const int c0 = wn0 + rpiece * (16 / OES);
+    const uint32_t ldb = (uint32_t)epi.ldc * OES;
+    const uint32_t g0 = (uint32_t)(wm0 + rrow) * ldb + (uint32_t)c0 * OES;
+    const bool col_ok = c0 < epi.n_valid;
+    const uint32_t extent = ((uint32_t)epi.rows - 1) * ldb + (uint32_t)epi.n_valid * OES;
+    u32x4_t piece[NMAT][NPASS];
+    auto load_aux = [&](int i) __attribute__((always_inline)) {
+#pragma unroll
+      for (int x = 0; x < NAUX; x++)
+#pragma unroll
+        for (int p = 0; p < NPASS; p++)
+          piece[x][p] = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc(epi.in[x], extent), g0 + (i * ROWS + p * RPP) * ldb, 0, 0);
+    };
+    // the row pieces of block i
+    auto store_pieces = [&](const auto& r, int i) __attribute__((always_inline)) {
+      auto put = [&](auto hint) __attribute__((always_inline)) {
+#pragma unroll
+        for (int x = 0; x < NOUT; x++)
+#pragma unroll
+          for (int p = 0; p < NPASS; p++)
+            __builtin_amdgcn_raw_buffer_store_b128(r[x][p], make_rsrc(epi.out[x], extent), g0 + (i * ROWS + p * RPP) * ldb, 0,
+                                                   decltype(hint)::value);
+      };
+      if (!col_ok) return;
+      if (epi.stream()) put(std::integral_constant<int, 2>());
+      else put(std::integral_constant<int, 0>());
+    };
+    // (short blocks are those of two blocks per CU, with half the registers: no room for the next block's inputs)
+    constexpr bool AHEAD = ROWS == 32;
+    if (NAUX > 0 && AHEAD) load_aux(0);
+    float scale[TM];
+#pragma unroll
+    for (int i = 0; i < TM; i++) scale[i] = epi.row_scale(wm0 + i * MT + mrow);
+#pragma unroll
+    for (int i = 0; i < NI; i++) {
+      if (NAUX > 0) {
+        if (!AHEAD) load_aux(i);
+#pragma unroll
+        for (int x = 0; x < NAUX; x++)
+#pragma unroll
+          for (int p = 0; p < NPASS; p++) *reinterpret_cast<u32x4_t*>(stage + x * BLOCK + row_at(p)) = piece[x][p];
+        asm volatile("" ::: "memory");
+        if (AHEAD && i + 1 < NI) load_aux(i + 1);
+      }
+#pragma unroll
+      for (int t = 0; t < GR * TN; t++) {
+        const int rh = t / TN, j = t % TN;
+        float v[NB][4], a[NA][4], o[NOUT][4];
+#pragma unroll
+        for (int x = 0; x < NAUX; x++) Epi::unpack(stage + x * BLOCK + col_at(rh, j), a[x]);
+#pragma unroll
+        for (int nb = 0; nb < NB; nb++)
+#pragma unroll
+          for (int q = 0; q < 4; q++) {
+            if constexpr (AGPR) asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v[nb][q]) : "a"(acc[nb][GR * i + rh][j][q]));
+            else v[nb][q] = acc[nb][GR * i + rh][j][q];
+          }
+        epi.apply(v, a, scale[GR * i + rh], o);
+#pragma unroll
+        for (int x = 0; x < NOUT; x++) Epi::pack(stage + x * BLOCK + col_at(rh, j), o[x]);
+      }
+      asm volatile("" ::: "memory");  // other lanes' values are read back below
+      if (NAUX > 0) {
+        // the registers of the row pieces hold the next block's inputs: pass the outputs through others
+        u32x4_t r[NOUT][NPASS];
+#pragma unroll
+        for (int x = 0; x < NOUT; x++)
+#pragma unroll
+          for (int p = 0; p < NPASS; p++) r[x][p] = *reinterpret_cast<const u32x4_t*>(stage + x * BLOCK + row_at(p));
+        store_pieces(r, i);
+      } else {
+        if (i > 0) store_pieces(piece, i - 1);
+#pragma unroll
+        for (int x = 0; x < NOUT; x++)
+#pragma unroll
+          for (int p = 0; p < NPASS; p++) piece[x][p] = *reinterpret_cast<const u32x4_t*>(stage + x * BLOCK + row_at(p));
+      }
+      asm volatile("" ::: "memory");
+    }
+    if (NAUX == 0) store_pieces(piece, NI - 1);
+  }
+};
+
 // ------------------------------------------------------------------ MFMA core, LDS DMA loads
 // Tiles travel HBM/L2 -> LDS directly (buffer_load_dwordx4 ... lds),
 // so no registers stage them.  Lane l of a wave-wide load lands at lds_base + 16*l, which fixes
@@ -73,39 +212,32 @@ __device__ __forceinline__ void static_for(F f) {
 // rows are K values, of the K tail.  A K tail inside the rows of a K-contiguous operand is masked with
 // KTAIL: the lanes whose piece lies at or beyond K fetch from an offset no descriptor reaches.
 //
-// Types: bf16 (v_mfma_f32_16x16x32_bf16) and fp32 (v_mfma_f32_32x32x2_f32: fp32 products and sums).  A tile row
-// is 128 bytes of K (64 bf16 or 32 fp32 values) and a lane's fragment of a k-step is 16 bytes.
-// bf16: a k-step is 64 bytes of K, a fragment 16 rows of them.  The 32x32x16 instruction does the same work per cycle
+// A tile row is 128 bytes of K (64 values), a k-step 32 values, and a lane's fragment of a k-step, 16 rows of it, is 16 bytes.
+// The 32x32x16 instruction does the same work per cycle
 // from the same fragment bytes, but it reads and writes every accumulator twice as often, and the chip's clock falls further under it:
 // register-resident loops over normally distributed values sustain 1.73 PFLOP/s with it and 1.99 with 16x16x32.
 // That alone changed nothing while the K loop was bound by issue (408 instructions per 128 MFMAs); with 225 (steps of
 // three additions, M0 written by the addition that forms the address, the MFMA as its wait state, LDS addresses carried in bytes)
-// whole training steps gain: T = 8192, d = 4096, 16 experts of 6400 7439 -> 7043 us, T = 8192, d = 7168, 256 experts 22830 -> 21837,
-// fp32 (32x32x2, the same loop) T = 2048, d = 1024 2095 -> 1985.
-// fp32: a k-step is 32 bytes of K, a fragment 32 rows; its four values feed four MFMAs, MFMA j taking value j of both
-// half-waves (k = 8 ks + j and 8 ks + 4 + j).
+// whole training steps gain: T = 8192, d = 4096, 16 experts of 6400 7439 -> 7043 us, T = 8192, d = 7168, 256 experts 22830 -> 21837.
 //
 // LDS layouts, BK = 128 bytes of K, no padding:
 //  K-contiguous operand [rows][BK]: 16-byte piece c of a row sits at position c ^ ((row/2)%8), so
 //    that the 16 rows one phase of a 16-byte-per-lane read touches cover all banks once.
-//  row-contiguous operand [BK][ROWS]: bf16: piece c (8 columns) of k-row k sits at position
+//  row-contiguous operand [BK][ROWS]: piece c (8 columns) of k-row k sits at position
 //    c ^ (4*(k%4)) ^ (2*((k/8)%2)): the 32 lanes of two 16-lane groups of a transposing read, which take 16 columns of
-//    four k rows and of the four k rows 8 further on, touch all banks once.  fp32: the
-//    fragment is read value by value; piece c (4 columns) sits at c ^ (8*((k/4)%2)), so that the two
-//    half-waves, four k rows apart, use different banks.
-template <typename T_, int BM_, int BN_, int NB, bool A_KC, bool B_KC, int WM_ = 2, int WN_ = 2, int DEPTH = 1,
+//    four k rows and of the four k rows 8 further on, touch all banks once.
+template <int BM_, int BN_, int NB, bool A_KC, bool B_KC, int WM_ = 2, int WN_ = 2, int DEPTH = 1,
           bool KTAIL = false>
 struct MfmaDmaCore {
-  typedef T_ T;
+  typedef bf16_t T;
   static constexpr int ES = sizeof(T);
   static constexpr int PE = 16 / ES;  // elements per 16-byte piece
   static constexpr int BM = BM_, BN = BN_, BK = 8 * PE;
-  static constexpr int MT = ES == 4 ? 32 : 16;  // rows and columns of an accumulator tile
-  static constexpr int KS = ES == 4 ? 4 : 2;    // MFMA k-steps per tile slot
-  static constexpr int SUB = ES == 4 ? 4 : 1;  // MFMAs per accumulator tile and k-step
-  typedef std::conditional_t<ES == 4, f32x4_t, bf16x8_t> frag_t;
-  typedef std::conditional_t<ES == 4, f32x16_t, f32x4_t> acc_t;
-  static constexpr int AR = MT * MT / 64;       // registers of an accumulator tile
+  static constexpr int MT = 16;  // rows and columns of an accumulator tile
+  static constexpr int KS = 2;   // MFMA k-steps per tile slot
+  typedef bf16x8_t frag_t;
+  typedef f32x4_t acc_t;
+  static constexpr int AR = 4;   // registers of an accumulator tile
   static constexpr int WM = WM_, WN = WN_;
   static constexpr int NW = WM * WN, NT = 64 * NW;  // wavefronts and threads per block
   static constexpr int TM = BM / WM / MT, TN = BN / WN / MT;
@@ -123,6 +255,7 @@ struct MfmaDmaCore {
   //     pipeline, small enough in LDS and registers for several blocks per CU, which is what hides
   //     latency when a block's life is one K iteration and an epilogue.
   static constexpr bool RING = DEPTH == 1;
+  static constexpr bool REPEATS = DEPTH == 0;  // a block may compute several tiles (see w_gemm_block)
   static constexpr int A_SLOTS = DEPTH == 0 ? 1 : DEPTH == 1 ? 3 : DEPTH + 1;
   static constexpr int B_SLOTS = DEPTH == 0 ? 1 : DEPTH == 1 ? 2 : DEPTH + 1;
   static constexpr int B_SET_ELEMS = NB * B_ELEMS;
@@ -138,7 +271,7 @@ struct MfmaDmaCore {
   static_assert(BM % (32 * WM) == 0 && BN % (32 * WN) == 0, "wave tile must be a multiple of 32");
   static_assert((A_KC || BM * ES % 128 == 0) && (B_KC || BN * ES % 128 == 0),
                 "swizzle of row-contiguous tiles needs >= 8 pieces per k row");
-  static_assert(ES == 4 || ((A_KC || BM >= 128) && (B_KC || BN >= 128)), "bf16: 16 pieces per k row");
+  static_assert((A_KC || BM >= 128) && (B_KC || BN >= 128), "16 pieces per k row");
   static_assert(LDS_BYTES <= 160 * 1024, "LDS budget of a gfx950 CU");
   typedef __attribute__((address_space(3))) void* lds_vptr;
 
@@ -147,10 +280,7 @@ struct MfmaDmaCore {
   // the K loop spends no instructions on addresses and the whole offset stays inside the
   // descriptor's bounds check.
   __device__ static __forceinline__ int kc_swizzle(int row) { return ((row * PR_KC) >> 4) & (PR_KC - 1); }
-  template <int ROWS>
-  __device__ static __forceinline__ int rc_swizzle(int k) {
-    return ES == 4 ? 8 * ((k >> 2) & 1) : 4 * (k & 3) ^ 2 * ((k >> 3) & 1);
-  }
+  __device__ static __forceinline__ int rc_swizzle(int k) { return 4 * (k & 3) ^ 2 * ((k >> 3) & 1); }
   template <int ROWS, bool KC>
   __device__ static __forceinline__ uint32_t piece_offset(int wave, int lane, uint32_t ld) {
     const int q = wave * 64 + lane;  // linear 16-byte piece of the LDS tile
@@ -161,7 +291,7 @@ struct MfmaDmaCore {
     } else {
       constexpr int PR = ROWS / PE;
       const int k = q / PR, pos = q % PR;
-      const int c = pos ^ rc_swizzle<ROWS>(k);
+      const int c = pos ^ rc_swizzle(k);
       return (uint32_t)k * ld * ES + (uint32_t)c * 16u;
     }
   }
@@ -193,8 +323,7 @@ struct MfmaDmaCore {
                  : "memory");
   }
 
-  // ---- LDS -> MFMA fragment: lane l holds k = 32*ks + 8*(l/16) + 0..7 of row (row0 + l%16)
-  // (fp32: k = 8*ks + 4*(l/32) + 0..3 of row (row0 + l%32)).
+  // ---- LDS -> MFMA fragment: lane l holds k = 32*ks + 8*(l/16) + 0..7 of row (row0 + l%16).
   // All lane-dependent address arithmetic is done once (lane_offsets); inside the K loop a
   // fragment address is a per-lane base plus a compile-time constant, which the LDS instructions
   // carry in their offset field.
@@ -202,7 +331,6 @@ struct MfmaDmaCore {
   //                        (the swizzle repeats every 16 rows)
   //   row-contiguous tile: off[t] for the t-th group of MT columns at k-step 0;
   //                        k-step ks = +32*ks*ROWS elements, second half of the 8 k = +4*ROWS
-  //                        (fp32: k-step ks = +8*ks*ROWS, value j = +j*ROWS)
   static constexpr int kOffs = 8;
   template <int ROWS, bool KC, int NTILE>
   __device__ static __forceinline__ void lane_offsets(int w0, int lane, uint32_t (&off)[kOffs]) {
@@ -210,13 +338,6 @@ struct MfmaDmaCore {
       const int row = w0 + (lane & (MT - 1));
 #pragma unroll
       for (int ks = 0; ks < KS; ks++) off[ks] = (row * BK + ((ks * (64 / MT) + lane / MT) ^ kc_swizzle(row)) * PE) * ES;
-    } else if (ES == 4) {
-      const int h = lane >> 5;  // half-wave: k values 8 ks + 4 h + 0..3
-#pragma unroll
-      for (int t = 0; t < NTILE; t++) {
-        const int col = w0 + t * 32 + (lane & 31);
-        off[t] = (4 * h * ROWS + ((((col >> 2) ^ rc_swizzle<ROWS>(4 * h)) << 2) | (col & 3))) * ES;
-      }
     } else {
       // transposing read: within 16 lanes, lane s points at 4 consecutive columns of k-row
       // kb + s/4, starting at column 4*(s%4); it receives k = kb..kb+3 of column s.
@@ -225,7 +346,7 @@ struct MfmaDmaCore {
 #pragma unroll
       for (int t = 0; t < NTILE; t++) {
         const int col = w0 + t * 16 + 4 * (s & 3);
-        off[t] = (k * ROWS + (((col >> 3) ^ rc_swizzle<ROWS>(k)) << 3) + (col & 7)) * ES;
+        off[t] = (k * ROWS + (((col >> 3) ^ rc_swizzle(k)) << 3) + (col & 7)) * ES;
       }
     }
   }
@@ -240,11 +361,6 @@ struct MfmaDmaCore {
   __device__ static __forceinline__ frag_t frag(const uint32_t (&at)[kOffs], uint32_t plus, int t, int ks) {
     if constexpr (KC) {
       return __builtin_bit_cast(frag_t, *lds_at<u32x4_t>(at[ks] + (plus + t * MT * BK * ES)));
-    } else if constexpr (ES == 4) {
-      const uint32_t p = at[t];
-      const uint32_t q = plus + ks * 8 * ROWS * ES;
-      return frag_t{*lds_at<float>(p + q), *lds_at<float>(p + (q + ROWS * ES)), *lds_at<float>(p + (q + 2 * ROWS * ES)),
-                    *lds_at<float>(p + (q + 3 * ROWS * ES))};
     } else {
       typedef __attribute__((address_space(3))) short4_t* lds_ptr;
       const uint32_t q = plus + ks * 32 * ROWS * ES;
@@ -273,24 +389,14 @@ struct MfmaDmaCore {
   // the K loop is then exactly the order written in run() (LDS reads, tile loads and MFMAs
   // interleaved by hand), the compiler only allocates registers and inserts the waits.
   // Operands exchanged: result register r of lane l is C[m = l%16][n = 4*(l/16) + r]
-  // (fp32: C[m = l%32][n = 8*(r/4) + 4*(l/32) + r%4]; all accumulator tiles take value 0 of the fragments, then value 1, ...)
-  static constexpr int kTiles = NB * TM * TN;
-  static constexpr int kMfma = kTiles * SUB;
+  static constexpr int kMfma = NB * TM * TN;
   template <int m>
   __device__ static __forceinline__ void mfma_n(acc_t (&acc)[NB][TM][TN], const Frags& f) {
-    constexpr int sub = m / kTiles, q = m % kTiles;
-    constexpr int nb = q / (TM * TN), i = (q / TN) % TM, j = q % TN;
-    if constexpr (ES == 4) {
-      asm volatile("v_mfma_f32_32x32x2_f32 %0, %1, %2, %0"
-                   : "+a"(acc[nb][i][j])
-                   : "v"(f.b[nb][j][sub]), "v"(f.a[i][sub])
-                   : "memory");
-    } else {
-      asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0"
-                   : "+a"(acc[nb][i][j])
-                   : "v"(f.b[nb][j]), "v"(f.a[i])
-                   : "memory");
-    }
+    constexpr int nb = m / (TM * TN), i = (m / TN) % TM, j = m % TN;
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0"
+                 : "+a"(acc[nb][i][j])
+                 : "v"(f.b[nb][j]), "v"(f.a[i])
+                 : "memory");
   }
 
   // The same, with a tile load (see issue_one) in the instruction's shadow: the write of M0 before it, so that the
@@ -298,19 +404,11 @@ struct MfmaDmaCore {
   template <int m, int plus>
   __device__ static __forceinline__ void mfma_load_n(acc_t (&acc)[NB][TM][TN], const Frags& f, const rsrc_t& rsrc, uint32_t base,
                                                      uint32_t voff) {
-    constexpr int sub = m / kTiles, q = m % kTiles;
-    constexpr int nb = q / (TM * TN), i = (q / TN) % TM, j = q % TN;
-    if constexpr (ES == 4) {
-      asm volatile("s_add_u32 m0, %3, %4\n\tv_mfma_f32_32x32x2_f32 %0, %1, %2, %0\n\tbuffer_load_dwordx4 %5, %6, 0 offen lds"
-                   : "+a"(acc[nb][i][j])
-                   : "v"(f.b[nb][j][sub]), "v"(f.a[i][sub]), "s"(base), "n"(plus), "v"(voff), "s"(rsrc)
-                   : "memory", "scc");
-    } else {
-      asm volatile("s_add_u32 m0, %3, %4\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0\n\tbuffer_load_dwordx4 %5, %6, 0 offen lds"
-                   : "+a"(acc[nb][i][j])
-                   : "v"(f.b[nb][j]), "v"(f.a[i]), "s"(base), "n"(plus), "v"(voff), "s"(rsrc)
-                   : "memory", "scc");
-    }
+    constexpr int nb = m / (TM * TN), i = (m / TN) % TM, j = m % TN;
+    asm volatile("s_add_u32 m0, %3, %4\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0\n\tbuffer_load_dwordx4 %5, %6, 0 offen lds"
+                 : "+a"(acc[nb][i][j])
+                 : "v"(f.b[nb][j]), "v"(f.a[i]), "s"(base), "n"(plus), "v"(voff), "s"(rsrc)
+                 : "memory", "scc");
   }
 
   // Position of a stream of tile loads along K.  The K loop pays for every scalar instruction between
@@ -406,132 +504,6 @@ struct MfmaDmaCore {
       const bool done = c.end == nk;
       seek(c, segf, done ? c.sg + 1 : c.sg, done ? 0 : c.end, n_segs, nk, lda, ldb);
     }
-  }
-
-  // Epilogue.  In the MFMA result layout a lane owns four consecutive columns of a row, so direct
-  // global accesses would be scatters of 8- or 16-byte pieces.  The arithmetic is done in that layout, on
-  // registers; the finished outputs, already in their final type, pass through a private LDS region of the
-  // wave in blocks of 32 rows and are picked up again as whole rows, 16 bytes per lane.  Inputs of the epilogue
-  // (the saved activations of a backward product, an output to add to) take the opposite way: whole rows
-  // into registers one block ahead, through the same region into the result layout.  The region's
-  // 16-byte pieces are XOR-swizzled by the row; LDS operations of one wave execute in order, so its reads and
-  // writes need no waits of their own, and the stores of a block are issued after the next block's
-  // arithmetic, under which their LDS reads return.
-  // What bounds it is instruction issue: one wave per SIMD, nothing to switch to.  (Staging fp32 values and
-  // doing arithmetic, rounding and addresses in row order, one pass of 4 rows after the other, took 10.5 k shader
-  // cycles per 256 x 256 tile of plain outputs, 13.8 k with SwiGLU, 50 k with its derivative; without the
-  // global stores still 9.9 k, 13.0 k, 39 k.  This form: 7.3 k, 12 k, 41 k, without the stores 4.5 k, 9.7 k, 34 k: what is
-  // left is arithmetic, two transcendentals per value, and the stores and loads of a launch's first tiles, which
-  // all CUs issue together.  Whole steps gain 1-3 % only, because the shader clock drops as the matrix pipe idles less.)
-  template <class Epi>
-  __device__ static __forceinline__ void epilogue(char* smem, acc_t (&acc)[NB][TM][TN], const Epi& epi, int wave, int lane,
-                                                  int wm0, int wn0) {
-    constexpr int OES = Epi::OES, NOUT = Epi::NOUT, NAUX = Epi::NAUX;
-    constexpr int RB = TN * MT * OES;         // bytes per row of the wave's tile
-    constexpr int LPR = RB / 16;              // lanes (16-byte pieces) per row
-    constexpr int RPP = 64 / LPR;             // rows per wave-wide access
-    constexpr int NPASS = 32 / RPP;
-    constexpr int SWZ = (LPR < 16 ? LPR : 16) - 1;
-    constexpr int NI = TM * MT / 32;          // blocks of 32 rows of the wave's tile
-    constexpr int BLOCK = 32 * RB;            // one 32-row block of one matrix
-    constexpr int NMAT = NOUT > NAUX ? NOUT : NAUX;
-    constexpr int NA = NAUX > 0 ? NAUX : 1;
-    static_assert(NW * NMAT * BLOCK <= LDS_BYTES, "the waves' staging regions fit into LDS");
-    char* stage = smem + wave * (NMAT * BLOCK);
-    // row order: row pass * RPP + lane / LPR, piece lane % LPR;  result layout: row lane % MT of an accumulator tile, of its
-    // columns four (fp32: four of every eight, position g), by lane / MT
-    const int rrow = lane / LPR, rpiece = lane % LPR;
-    const uint32_t r_off = rrow * RB + ((rpiece ^ (rrow & SWZ)) << 4);
-    constexpr int GR = 32 / MT, GC = AR / 4;  // accumulator tiles of a block's rows, positions of a tile
-    const int mrow = lane & (MT - 1), h = lane / MT;
-    uint32_t m_off[GR];
-#pragma unroll
-    for (int rh = 0; rh < GR; rh++) m_off[rh] = (rh * MT + mrow) * RB + (((rh * MT + mrow) & SWZ) << 4);
-    auto row_at = [&](int pass) __attribute__((always_inline)) {  // (rrow < RPP, so the row's other bits come from pass)
-      return (r_off ^ (((pass * RPP) & SWZ) << 4)) + pass * RPP * RB;
-    };
-    // first of the lane's four columns: MT * j + 8 * g + 4 * h
-    auto col_at = [&](int rh, int j, int g) __attribute__((always_inline)) {
-      return OES == 2 ? (m_off[rh] ^ ((MT / 8 * j + g + (h >> 1)) << 4)) + 8 * (h & 1)
-                      : (m_off[rh] ^ ((MT / 4 * j + 2 * g + h) << 4));
-    };
-    // global side: byte offsets from the tile's origin in every matrix
-    const int c0 = wn0 + rpiece * (16 / OES);
-    const uint32_t ldb = (uint32_t)epi.ldc * OES;
-    const uint32_t g0 = (uint32_t)(wm0 + rrow) * ldb + (uint32_t)c0 * OES;
-    const bool col_ok = c0 < epi.n_valid;
-    const uint32_t bytes = ((uint32_t)epi.rows - 1) * ldb + (uint32_t)epi.n_valid * OES;
-    u32x4_t piece[NMAT][NPASS];
-    auto load_aux = [&](int i) __attribute__((always_inline)) {
-#pragma unroll
-      for (int x = 0; x < NAUX; x++)
-#pragma unroll
-        for (int p = 0; p < NPASS; p++)
-          piece[x][p] = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc(epi.in[x], bytes), g0 + (i * 32 + p * RPP) * ldb, 0, 0);
-    };
-    // the row pieces of block i
-    auto store_pieces = [&](const auto& r, int i) __attribute__((always_inline)) {
-      auto put = [&](auto hint) __attribute__((always_inline)) {
-#pragma unroll
-        for (int x = 0; x < NOUT; x++)
-#pragma unroll
-          for (int p = 0; p < NPASS; p++)
-            __builtin_amdgcn_raw_buffer_store_b128(r[x][p], make_rsrc(epi.out[x], bytes), g0 + (i * 32 + p * RPP) * ldb, 0,
-                                                   decltype(hint)::value);
-      };
-      if (!col_ok) return;
-      if (epi.stream()) put(std::integral_constant<int, 2>());
-      else put(std::integral_constant<int, 0>());
-    };
-    if (NAUX > 0) load_aux(0);
-    float scale[TM];
-#pragma unroll
-    for (int i = 0; i < TM; i++) scale[i] = epi.row_scale(wm0 + i * MT + mrow);
-#pragma unroll
-    for (int i = 0; i < NI; i++) {
-      if (NAUX > 0) {
-#pragma unroll
-        for (int x = 0; x < NAUX; x++)
-#pragma unroll
-          for (int p = 0; p < NPASS; p++) *reinterpret_cast<u32x4_t*>(stage + x * BLOCK + row_at(p)) = piece[x][p];
-        asm volatile("" ::: "memory");
-        if (i + 1 < NI) load_aux(i + 1);
-      }
-#pragma unroll
-      for (int t = 0; t < GR * TN; t++)
-#pragma unroll
-        for (int g = 0; g < GC; g++) {
-          const int rh = t / TN, j = t % TN;
-          float v[NB][4], a[NA][4], o[NOUT][4];
-#pragma unroll
-          for (int x = 0; x < NAUX; x++) Epi::unpack(stage + x * BLOCK + col_at(rh, j, g), a[x]);
-#pragma unroll
-          for (int nb = 0; nb < NB; nb++)
-#pragma unroll
-            for (int q = 0; q < 4; q++) asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v[nb][q]) : "a"(acc[nb][GR * i + rh][j][4 * g + q]));
-          epi.apply(v, a, scale[GR * i + rh], o);
-#pragma unroll
-          for (int x = 0; x < NOUT; x++) Epi::pack(stage + x * BLOCK + col_at(rh, j, g), o[x]);
-        }
-      asm volatile("" ::: "memory");  // other lanes' values are read back below
-      if (NAUX > 0) {
-        // the registers of the row pieces hold the next block's inputs: pass the outputs through others
-        u32x4_t r[NOUT][NPASS];
-#pragma unroll
-        for (int x = 0; x < NOUT; x++)
-#pragma unroll
-          for (int p = 0; p < NPASS; p++) r[x][p] = *reinterpret_cast<const u32x4_t*>(stage + x * BLOCK + row_at(p));
-        store_pieces(r, i);
-      } else {
-        if (i > 0) store_pieces(piece, i - 1);
-#pragma unroll
-        for (int x = 0; x < NOUT; x++)
-#pragma unroll
-          for (int p = 0; p < NPASS; p++) piece[x][p] = *reinterpret_cast<const u32x4_t*>(stage + x * BLOCK + row_at(p));
-      }
-      asm volatile("" ::: "memory");
-    }
-    if (NAUX == 0) store_pieces(piece, NI - 1);
   }
 
   // (the valid extents are not needed here: the descriptors' byte counts zero-fill the loads and bound
@@ -636,9 +608,9 @@ struct MfmaDmaCore {
     static_for<kAddr>([&](auto x) __attribute__((always_inline)) { set_address(x, lds_addr, lds_b); });
 
     constexpr int kLoadsB = NB * B_NI;  // loads per wave for the B tiles of one iteration
-    // Fragments are read a few MFMAs (16 cycles each in bf16) before the k-step that needs them starts.
+    // Fragments are read a few MFMAs (16 cycles each) before the k-step that needs them starts.
     constexpr int kHalf = kMfma / 2, kLate = kMfma - kHalf;
-    constexpr int kLead = ES == 4 ? 0 : kMfma / 8 < 8 ? kMfma / 8 : 8;
+    constexpr int kLead = kMfma / 8 < 8 ? kMfma / 8 : 8;
     constexpr int kSpan = kMfma - kLead, kLateSpan = kLate - kLead;
     // the loads of an iteration are spread over these MFMAs: all before the barrier
     constexpr int kSlots = (KS - 1) * kMfma + kHalf;
@@ -701,7 +673,7 @@ struct MfmaDmaCore {
       // loads of the next iteration overwrite.
       // (Reads before, then all loads, then all MFMAs of an iteration: the loads of four waves alone hold the
       // address unit for 16 cycles each, 768 of the 1950 cycles of a 128-row step.  Down product of 4 shared experts, T = 2777,
-      // 176 tiles of 128 rows and 88 steps: 124 -> 79 us, 1.35 -> 0.83 us a step; fp32 step T = 2048: 2138 -> 2088 us.)
+      // 176 tiles of 128 rows and 88 steps: 124 -> 79 us, 1.35 -> 0.83 us a step.)
       static_assert(L <= kSlots, "at most one load per MFMA");
       first_frags();
       int cur = 0;
@@ -749,7 +721,7 @@ struct MfmaDmaCore {
           constexpr int ks = decltype(ks_c)::value;
           if (ks * (BK / KS) >= s0.k_left) return;  // uniform: the remaining k rows of the tile are zero
           // (one A fragment ahead, no more: the registers of four blocks per CU have no room for all of them)
-          static_assert(NB == 1 && SUB == 1, "one row of accumulator tiles after the other");
+          static_assert(NB == 1, "one row of accumulator tiles after the other");
           static_for<TN + 1>([&](auto r) __attribute__((always_inline)) { load_frag_n<ks, (decltype(r)::value + TM) % (TM + TN)>(la, lb, f[0]); });
           static_for<TM>([&](auto i) __attribute__((always_inline)) {
             if constexpr (decltype(i)::value + 1 < TM) load_frag_n<ks, decltype(i)::value + 1>(la, lb, f[0]);
@@ -840,7 +812,7 @@ struct MfmaDmaCore {
     // volatile asm pins the order); left to itself the compiler copies all 256 at the loop exit,
     // needs every arch VGPR for that and spills the loop's address registers.
     // The MFMAs above are opaque to the compiler's hazard recogniser, so the wait between the last
-    // MFMA (bf16: 4 passes of 4 cycles, fp32: 16, plus write-back) and the first read of any accumulator is
+    // MFMA (4 passes of 4 cycles, plus write-back) and the first read of any accumulator is
     // explicit: 6 x 16 idle cycles, attached to the accumulator of the last MFMA.  The empty
     // statements make every other accumulator depend on a point after that wait (volatile asm
     // statements keep their order), so no compiler-generated accumulator copy can move above it.
@@ -855,7 +827,7 @@ struct MfmaDmaCore {
 #pragma unroll
         for (int j = 0; j < TN; j++) asm volatile("" : "+a"(acc[nb][i][j])::"memory");
     __syncthreads();  // every wave is done with the tile slots (stale fragment reads included)
-    epilogue(smem, acc, epi, wave, lane, wm0, wn0);
+    TileEpilogue<NB, TM, TN, NW, LDS_BYTES, true>::run(smem, acc, epi, wave, lane, wm0, wn0);
     MOE_PHASE(3);
   }
 };

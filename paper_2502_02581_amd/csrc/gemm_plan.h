@@ -45,7 +45,7 @@ inline Plan carve_plan(void* ws, int /*n_groups*/, int max_tiles) {
 }
 
 // rows of the full row tiles of the tile cores
-inline int plan_tile_rows(int dtype) { return dtype == MOE_F32 ? 64 : 256; }
+inline int plan_tile_rows(int dtype) { return dtype == MOE_F32 ? 128 : 256; }
 // upper bound of the row tiles of a plan (at most two remainder tiles per group)
 inline int max_row_tiles(int n_groups, int n_rows, int BM) { return n_rows / BM + 2 * n_groups; }
 

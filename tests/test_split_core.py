@@ -1,0 +1,77 @@
+"""fp32 products at the edges of their tiles, and what a sum of bf16 products must not get wrong: few products, values that no
+finite sum holds, values at the ends of the range."""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import paper_2502_02581_amd as moe
+
+pytestmark = pytest.mark.gpu
+U = 2.0 ** -24
+
+
+def _router(T, d, E, X, W, g):
+    shape = moe.MoEShape(T, d, E, 1, 8, "f32")
+    dev = "cuda:0"
+    X, W, g = X.to(dev), W.to(dev), g.to(dev)
+    ws = torch.empty(max(moe.moe_router_fwd_workspace_bytes(shape), moe.moe_router_bwd_workspace_bytes(shape)), dtype=torch.uint8,
+                     device=dev)
+    logits, dW, dX = torch.empty(T, E, device=dev), torch.empty_like(W), torch.empty_like(X)
+    moe.moe_router_fwd(shape, X, W, logits, ws)
+    moe.moe_router_bwd(shape, X, W, g, dW, dX, False, ws)
+    return logits.cpu(), dW.cpu(), dX.cpu()
+
+
+def _check(got, a, b):
+    """|got - ab| <= (rounded additions + 4) u |a||b|: six additions per 32 values of K (at most one per value), the parts of K, the
+    dropped products (below 4 u)."""
+    ref, scale = a.double() @ b.double(), a.double().abs() @ b.double().abs()
+    k = a.shape[1]
+    bound = (min(k, 6 * ((k + 31) // 32)) + 16 + 4) * U * scale
+    assert ((got.double() - ref).abs() <= bound).all()
+
+
+@pytest.mark.parametrize("T", [1, 2, 8, 9, 15, 16, 17, 31, 33, 64, 65, 127, 128, 129, 300])
+@pytest.mark.parametrize("d,E", [(8, 64), (24, 128), (40, 60), (136, 192), (1032, 8)])
+def test_products_at_the_edges(T, d, E):
+    r = torch.Generator().manual_seed(T * 1000 + d)
+    X, W, g = (torch.randn(*s, generator=r) for s in ((T, d), (d, E), (T, E)))
+    logits, dW, dX = _router(T, d, E, X, W, g)
+    _check(logits, X, W)
+    _check(dW, X.T, g)
+    _check(dX, g, W.T)
+
+
+@pytest.mark.parametrize("T,d,E", [(70, 136, 64), (300, 40, 128)])
+def test_values_that_are_not_finite(T, d, E):
+    """Infinities and NaN go where fp32 arithmetic takes them, whatever else the tile holds; sums that overflow in parts do too."""
+    r = torch.Generator().manual_seed(5)
+    X, W, g = (torch.randn(*s, generator=r) for s in ((T, d), (d, E), (T, E)))
+    X[3, 5], X[17, 2], X[40, 7] = float("inf"), float("nan"), -float("inf")
+    X[41, 7], X[42, 1] = 3.4028234e38, -3.4e38   # the largest values round to infinity in bf16
+    W[1], W[9, 3] = 0.0, float("inf")
+    logits, dW, dX = _router(T, d, E, X, W, g)
+    for got, a, b in ((logits, X, W), (dW, X.T, g), (dX, g, W.T)):
+        ref = a.double() @ b.double()
+        big = ref.abs() > 3.4028235e38   # (no value lies within rounding of it)
+        assert not ((ref.abs() / 3.4028235e38 - 1).abs() < 1e-5).any()
+        finite = torch.isfinite(ref) & ~big
+        assert torch.equal(torch.isnan(got), torch.isnan(ref))
+        assert torch.equal(torch.isinf(got) & (got > 0), (ref > 0) & (torch.isinf(ref) | big))
+        assert torch.equal(torch.isinf(got) & (got < 0), (ref < 0) & (torch.isinf(ref) | big))
+        z = lambda t: torch.nan_to_num(t.double(), 0.0, 0.0, 0.0)
+        scale = z(a).abs() @ z(b).abs()
+        assert ((got.double() - ref).abs()[finite] <= ((a.shape[1] + 20) * U * scale)[finite]).all()
+
+
+@pytest.mark.parametrize("scale", [1e-30, 1e-20, 1e18])
+def test_ends_of_the_range(scale):
+    """Operands down to 2e-31 keep all of their bits."""
+    r = torch.Generator().manual_seed(6)
+    T, d, E = 65, 72, 64
+    X = (torch.rand(T, d, generator=r) + 1.0) * scale   # values of one binade: none below the limit
+    W, g = torch.randn(d, E, generator=r), torch.randn(T, E, generator=r)
+    logits, dW, dX = _router(T, d, E, X, W, g)
+    _check(logits, X, W)
+    _check(dW, X.T, g)
+    _check(dX, g, W.T)
