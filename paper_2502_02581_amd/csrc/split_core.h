@@ -316,7 +316,13 @@ struct SplitCore {
           for (int j = 0; j < TN; j++)
 #pragma unroll
             for (int r = 0; r < 4; r++) bad = fmaf(acc[nb][i][j][r], 0.f, bad);
-      exact = __syncthreads_or(bad != 0.f);
+      __syncthreads();  // every wave is done with the tiles
+      int* found = (int*)smem;
+      if (lane == 0) found[wave] = 0;
+      if (bad != 0.f) found[wave] = 1;  // (in this order: one wave's LDS operations)
+      __syncthreads();
+#pragma unroll
+      for (int w = 0; w < NW; w++) exact = exact || found[w] != 0;
     }
     // (what comes now forms its addresses itself: shared with the loop above they would have to be kept all through it)
     asm volatile("" : "+v"(lane), "+s"(lda), "+s"(ldb));
