@@ -49,7 +49,8 @@ __global__ __launch_bounds__(256) void wide_row_gemm_kernel(RowGemm p, int bm, i
       const int64_t off = ((int64_t)((p.c_rows_out ? t.row0_out : t.row0_in) + m) * p.ldc + n) * Epi::OES;
       float aux[NA][4], o[Epi::NOUT][4];
 #pragma unroll
-      for (int x = 0; x < Epi::NAUX; x++) Epi::unpack((const char*)(EPI == EPI_ADD ? p.out[0] : p.in[x]) + off, aux[x]);
+      for (int x = 0; x < Epi::NAUX; x++)
+        Epi::unpack(*reinterpret_cast<const typename Epi::packed_t*>((const char*)(EPI == EPI_ADD ? p.out[0] : p.in[x]) + off), aux[x]);
       Epi epi;
       epi.apply(v, aux, p.c_scale ? p.c_scale[p.a_index[a_row]] : 1.f, o);
 #pragma unroll
