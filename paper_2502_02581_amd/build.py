@@ -11,10 +11,10 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmoe_hip.so")
 SOURCES = ["common.hip", "route.hip", "dispatch.hip", "combine.hip", "expert.hip", "expert_f32.hip", "expert_bf16.hip",
-           "expert_tail.hip", "expert_wide.hip", "planner.hip"]
+           "expert_tail.hip", "expert_small.hip", "expert_wide.hip", "planner.hip"]
 # sources with device code: their gfx950 assembly is kept and checked (asm_check.py)
 CHECKED = ["common.hip", "route.hip", "dispatch.hip", "combine.hip", "expert.hip", "expert_f32.hip", "expert_bf16.hip",
-           "expert_tail.hip", "expert_wide.hip"]
+           "expert_tail.hip", "expert_small.hip", "expert_wide.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang",
          "-packed-fp32-ops", "-Wno-unused-command-line-argument"]
 

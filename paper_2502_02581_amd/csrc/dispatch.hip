@@ -510,8 +510,8 @@ static int route_dispatch(const char* who, const moe_shape_t* shape, const float
   const int T = shape->T, E = shape->E, k = shape->k;
   const int tpc = prologue_tokens_per_chunk(shape), n_chunks = prologue_chunks(shape);
   int32_t* hist = (int32_t*)ws;
-  const int bm = plan_tile_rows(shape->dtype);
-  const Plan pl = plan ? carve_plan(plan, E, max_row_tiles(E, T * k, bm)) : Plan{};
+  const int bm = plan_tile_rows(shape->dtype, E, T * k, shape->d, shape->d_ff);
+  const Plan pl = plan ? carve_plan(plan, E, plan_cap(E, T * k)) : Plan{};
   float* partial = aux_P ? (float*)((char*)ws + need / 2) : nullptr;
   if (n_chunks > 0) {
     ProfScope prof("route_hist_kernel", st);

@@ -42,16 +42,21 @@ void launch_plan(const int32_t* offsets, int n_groups, int BM, const Plan& pl, i
 MOE_CORES(PATH_F32)
 MOE_CORES(PATH_BF16_TAIL)
 MOE_CORES(PATH_BF16)
+extern template void expert_fwd_impl<PATH_BF16_SMALL>(const FwdArgs*, const FwdArgs*, hipStream_t);
+extern template void expert_bwd_impl<PATH_BF16_SMALL>(const BwdArgs*, const BwdArgs*, hipStream_t);
 
-static int pick_path(const moe_shape_t* s) {
+static int full_path(const moe_shape_t* s) {
   if (s->dtype == MOE_F32) return PATH_F32;
   return (s->d % 64 == 0 && s->d_ff % 64 == 0) ? PATH_BF16 : PATH_BF16_TAIL;
 }
+static bool small_tiles(const moe_shape_t* s, int n_groups, int n_rows) { return small_tiles(s->dtype, n_groups, n_rows, s->d, s->d_ff); }
+static int pick_path(const moe_shape_t* s, int n_groups, int n_rows) { return small_tiles(s, n_groups, n_rows) ? (int)PATH_BF16_SMALL : full_path(s); }
 
 static void run_fwd(int path, const FwdArgs* routed, const FwdArgs* shared, hipStream_t st) {
   switch (path) {
     case PATH_F32: expert_fwd_impl<PATH_F32>(routed, shared, st); break;
     case PATH_BF16_TAIL: expert_fwd_impl<PATH_BF16_TAIL>(routed, shared, st); break;
+    case PATH_BF16_SMALL: expert_fwd_impl<PATH_BF16_SMALL>(routed, shared, st); break;
     default: expert_fwd_impl<PATH_BF16>(routed, shared, st); break;
   }
 }
@@ -59,6 +64,7 @@ static void run_bwd(int path, const BwdArgs* routed, const BwdArgs* shared, hipS
   switch (path) {
     case PATH_F32: expert_bwd_impl<PATH_F32>(routed, shared, st); break;
     case PATH_BF16_TAIL: expert_bwd_impl<PATH_BF16_TAIL>(routed, shared, st); break;
+    case PATH_BF16_SMALL: expert_bwd_impl<PATH_BF16_SMALL>(routed, shared, st); break;
     default: expert_bwd_impl<PATH_BF16>(routed, shared, st); break;
   }
 }
@@ -66,7 +72,7 @@ static void run_bwd(int path, const BwdArgs* routed, const BwdArgs* shared, hipS
 static size_t plan_size_for(int n_groups, int n_rows, bool shared) {
   // Sized for the smallest row tile of any path, so the query does not depend on the path taken.  A shared call with rows
   // has no plan; it asks for the space all the same, so that it refuses what it always refused.
-  const int bound = shared ? n_groups * (n_rows / 64 + 2) : max_row_tiles(n_groups, n_rows, 64);
+  const int bound = shared ? n_groups * (n_rows / 64 + 2) : plan_cap(n_groups, n_rows);
   return align_up(plan_bytes(n_groups, bound + 1), 256);
 }
 // dG and dU: [n_rows, d_ff] each; shared mode keeps them per group
@@ -81,11 +87,11 @@ static size_t bwd_base(const moe_shape_t* s, int n_groups, int n_rows, bool shar
 }
 static size_t shared_parts(const moe_shape_t* s, int n_groups, int n_rows, bool bwd) {
   if (s->d <= 0 || s->d_ff <= 0) return 0;  // a shape that the calls refuse: there are no products to divide
-  switch (pick_path(s)) {
-    case PATH_F32: return expert_part_bytes<PATH_F32>(s->d, s->d_ff, n_groups, n_rows, bwd);
-    case PATH_BF16_TAIL: return expert_part_bytes<PATH_BF16_TAIL>(s->d, s->d_ff, n_groups, n_rows, bwd);
-    default: return expert_part_bytes<PATH_BF16>(s->d, s->d_ff, n_groups, n_rows, bwd);
-  }
+  if (s->dtype == MOE_F32) return expert_part_bytes<PATH_F32>(s->d, s->d_ff, n_groups, n_rows, bwd);
+  // (shared rows may be few where the routed ones beside them are not)
+  const size_t full = full_path(s) == PATH_BF16 ? expert_part_bytes<PATH_BF16>(s->d, s->d_ff, n_groups, n_rows, bwd)
+                                                : expert_part_bytes<PATH_BF16_TAIL>(s->d, s->d_ff, n_groups, n_rows, bwd);
+  return few_rows(s->dtype, n_rows, s->d) ? std::max(full, expert_part_bytes<PATH_BF16_SMALL>(s->d, s->d_ff, n_groups, n_rows, bwd)) : full;
 }
 
 static int check_expert_args(const moe_shape_t* s, int n_groups, int n_rows, const char* who) {
@@ -139,7 +145,7 @@ extern "C" int moe_expert_fwd(const moe_shape_t* shape, int32_t n_groups, const 
   if (n_rows == 0) return MOE_OK;
   FwdArgs a = {shape->d, shape->d_ff, n_groups, n_rows, offsets, Xin, Wg, Wu, Wd, G, U, H, Yout,
                (char*)ws, (char*)ws + need, ws_bytes - need};
-  run_fwd(pick_path(shape), offsets ? &a : nullptr, offsets ? nullptr : &a, (hipStream_t)stream);
+  run_fwd(pick_path(shape, n_groups, n_rows), offsets ? &a : nullptr, offsets ? nullptr : &a, (hipStream_t)stream);
   return launch_status("moe_expert_fwd");
 }
 
@@ -171,7 +177,7 @@ extern "C" int moe_expert_bwd(const moe_shape_t* shape, int32_t n_groups, const 
   BwdArgs a = {shape->d, shape->d_ff, n_groups, n_rows, offsets, Xin, Wg, Wu, Wd, G, U, H, dYin, dXin,
                active_ids, n_active, dWg_c, dWu_c, dWd_c, (char*)ws, dG,
                dG + grad_size_for(shape, n_groups, n_rows, offsets == nullptr), (char*)ws + need, ws_bytes - need};
-  run_bwd(pick_path(shape), offsets ? &a : nullptr, offsets ? nullptr : &a, (hipStream_t)stream);
+  run_bwd(pick_path(shape, n_groups, n_rows), offsets ? &a : nullptr, offsets ? nullptr : &a, (hipStream_t)stream);
   return launch_status("moe_expert_bwd");
 }
 
@@ -205,7 +211,7 @@ extern "C" int moe_expert_fwd_gather(const moe_shape_t* shape, const int32_t* of
   if (n_rows == 0) return MOE_OK;
   FwdArgs a = {shape->d, shape->d_ff, n_groups, n_rows, offsets, X, Wg, Wu, Wd, G, U, H, Yout, (char*)ws, nullptr, 0};
   a.src_of = src_of; a.src_div = shape->k; a.src_rows = shape->T;
-  run_fwd(pick_path(shape), &a, nullptr, (hipStream_t)stream);
+  run_fwd(pick_path(shape, n_groups, n_rows), &a, nullptr, (hipStream_t)stream);
   return launch_status("moe_expert_fwd_gather");
 }
 
@@ -242,7 +248,7 @@ extern "C" int moe_expert_bwd_gather(const moe_shape_t* shape, const int32_t* of
   BwdArgs a = {shape->d, shape->d_ff, n_groups, n_rows, offsets, Xp, Wg, Wu, Wd, G, U, H, dYp, dXp,
                active_ids, n_active, dWg_c, dWu_c, dWd_c, (char*)ws, dG, dG + grad_size_for(shape, n_groups, n_rows, false), nullptr, 0};
   a.dY = dY; a.src_of = src_of; a.row_w = topk_w; a.src_div = shape->k; a.src_rows = shape->T;
-  run_bwd(pick_path(shape), &a, nullptr, (hipStream_t)stream);
+  run_bwd(pick_path(shape, n_groups, n_rows), &a, nullptr, (hipStream_t)stream);
   return launch_status("moe_expert_bwd_gather");
 }
 
@@ -309,6 +315,13 @@ static int check_sets(const moe_shape_t* shape, const moe_expert_set_t* routed, 
 // us a pass, routed width / shared: 1408 / 4 of 1400, 16 tokens, forward 130 and 113; 1408 / 1000, T = 2048, d = 1024, training 392 and
 // 313; 1368 / 2 of 2048, T = 4096 768 and 682; 1408 / 2 of 712, T = 4096, d = 2048 1647 and 1607; 6400 / 3208, T = 8192, d = 4096 8717
 // and 8626.)
+// The cores of common launches: the small ones if both sets' products are short; PATH_BF16_TAIL where either width needs it (it takes what
+// PATH_BF16 takes, with the same results).
+static int common_path(const moe_shape_t (&s)[2], const moe_expert_set_t* routed, const moe_expert_set_t* shared) {
+  if (small_tiles(&s[0], routed->n_groups, routed->n_rows) && short_product((int64_t)shared->n_groups * shared->n_rows, s[1].d, s[1].d_ff))
+    return PATH_BF16_SMALL;
+  return std::min(full_path(&s[0]), full_path(&s[1]));
+}
 static bool can_share(const moe_shape_t (&s)[2], const moe_expert_set_t* routed, const moe_expert_set_t* shared) {
   if (!shared) return false;
   const int64_t ld = std::max({s[0].d, s[0].d_ff, s[1].d_ff});
@@ -320,7 +333,7 @@ static bool can_share(const moe_shape_t (&s)[2], const moe_expert_set_t* routed,
 extern "C" size_t moe_expert_plan_bytes(const moe_shape_t* shape) {
   using namespace moe;
   if (!shape || shape->E < 1 || shape->T < 0 || shape->k < 1) return 0;
-  return align_up(plan_bytes(shape->E, max_row_tiles(shape->E, shape->T * shape->k, plan_tile_rows(shape->dtype))), 256);
+  return align_up(plan_bytes(shape->E, plan_cap(shape->E, shape->T * shape->k)), 256);
 }
 
 extern "C" int moe_experts_fwd(const moe_shape_t* shape, const moe_expert_set_t* routed, const moe_expert_set_t* shared, void* stream) {
@@ -338,10 +351,10 @@ extern "C" int moe_experts_fwd(const moe_shape_t* shape, const moe_expert_set_t*
     a[i].plan = x->plan;
     if (x->src_of) { a[i].src_of = x->src_of; a[i].src_div = shape->k; a[i].src_rows = shape->T; }
   }
-  const int p0 = pick_path(&s[0]), p1 = shared ? pick_path(&s[1]) : p0;
+  const int p0 = pick_path(&s[0], routed->n_groups, routed->n_rows), p1 = shared ? pick_path(&s[1], shared->n_groups, shared->n_rows) : p0;
   hipStream_t st = (hipStream_t)stream;
   if (can_share(s, routed, shared)) {
-    run_fwd(std::min(p0, p1), &a[0], &a[1], st);  // (PATH_BF16_TAIL takes what PATH_BF16 takes, with the same results)
+    run_fwd(common_path(s, routed, shared), &a[0], &a[1], st);
   } else {
     if (routed->n_rows > 0) run_fwd(p0, &a[0], nullptr, st);
     if (shared && shared->n_rows > 0) run_fwd(p1, nullptr, &a[1], st);
@@ -368,10 +381,10 @@ extern "C" int moe_experts_bwd(const moe_shape_t* shape, const moe_expert_set_t*
       a[i].dY = x->dY; a[i].src_of = x->src_of; a[i].row_w = x->row_w; a[i].src_div = shape->k; a[i].src_rows = shape->T;
     }
   }
-  const int p0 = pick_path(&s[0]), p1 = shared ? pick_path(&s[1]) : p0;
+  const int p0 = pick_path(&s[0], routed->n_groups, routed->n_rows), p1 = shared ? pick_path(&s[1], shared->n_groups, shared->n_rows) : p0;
   hipStream_t st = (hipStream_t)stream;
   if (can_share(s, routed, shared)) {
-    run_bwd(std::min(p0, p1), &a[0], &a[1], st);
+    run_bwd(common_path(s, routed, shared), &a[0], &a[1], st);
   } else {
     run_bwd(p0, &a[0], nullptr, st);
     if (shared) run_bwd(p1, nullptr, &a[1], st);

@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <iterator>
 
 #include "gemm_cores.h"
@@ -225,7 +226,14 @@ __device__ __forceinline__ void row_gemm_block(const RowGemm& p, int block, char
   MOE_TRACE_BEGIN();
   auto tile = [&](auto epi) __attribute__((always_inline)) {
     constexpr int E = decltype(epi)::value;
-    switch (tile_kind(t)) {  // uniform over the block
+    if constexpr (CoreSet::KINDS == 1) {  // (a plan may have taller tiles: see plan_cap)
+      for (int r0 = 0; r0 < tile_rows(t); r0 += Core0::BM) {
+        if (r0 > 0) __syncthreads();  // the epilogue before is done with LDS in every wave
+        RowTile u = t;
+        u.row0_in += r0; u.row0_out += r0; u.rows = min(Core0::BM, tile_rows(t) - r0);
+        row_gemm_tile<Core0, NB, E, B_KC>(p, u, nt, part, smem);
+      }
+    } else switch (tile_kind(t)) {  // uniform over the block
       case 0: row_gemm_tile<Core0, NB, E, B_KC>(p, t, nt, part, smem); break;
       case 1: row_gemm_tile<typename CoreSet::template tile<1>, NB, E, B_KC>(p, t, nt, part, smem); break;
       case 2: row_gemm_tile<typename CoreSet::template tile<2>, NB, E, B_KC>(p, t, nt, part, smem); break;
@@ -413,7 +421,7 @@ __global__ __launch_bounds__(256) void reduce_kernel(Reduce p) {
 // operands (a VALU instruction per tile load; the weight gradients have no such operands).  Before, such sizes
 // ran on 128 x 128 tiles staged through registers: forward + backward of T = 3001, d = 1000, d_ff = 1368,
 // 24 experts, top-3, one shared expert: 1.63 ms; on these cores 0.91 ms, with the same bits.
-enum { PATH_F32 = 0, PATH_BF16_TAIL = 1, PATH_BF16 = 2 };
+enum { PATH_F32 = 0, PATH_BF16_TAIL = 1, PATH_BF16 = 2, PATH_BF16_SMALL = 3 };
 template <int PATH> struct Cores;
 template <> struct Cores<PATH_F32> {
   // 128 x 128 outputs (dual GEMMs: 128 x 64 of each product), two blocks per CU, one multiplying while the other stores its planes
@@ -431,6 +439,12 @@ template <> struct Cores<PATH_BF16> {
   template <int NB> using core_light = MfmaDmaCore<128, 128, NB, false, false, 2, 2, 0>;
 };
 template <> struct Cores<PATH_BF16_TAIL> : Cores<PATH_BF16> {};
+// Calls of few rows and short products (small_tiles): 64 x 128 outputs (dual GEMMs: 64 x 64 of each product), weight gradients 128 x 128, two blocks
+// per CU.  Takes any multiples of 8.
+template <> struct Cores<PATH_BF16_SMALL> : Cores<PATH_BF16> {
+  static constexpr int BM = kSmallTileRows, BN = 128;
+  template <int NB, bool A_KC, bool B_KC> using core = MfmaDmaCore<128, 128 / NB, NB, A_KC, B_KC, 2, 2>;
+};
 // Groups up to this many rows, one K step, take the light dW kernel.  (256 and 64, training steps: T = 3001, d = 1000,
 // 24 experts 603 and 589 us; T = 8192, d = 768, 64 experts 1029 and 1019; T = 16384, d = 2048, stress routing 3696 and 3676; T = 8192,
 // d = 4096, 16 experts 7178 and 7149; the others within 0.3 %.)
@@ -440,6 +454,7 @@ constexpr int kLightReps = 2;         // column tiles per block of that kernel (
 // The tile cores a row-tiled GEMM launch may use: tile kinds of heights BM, BM/2, BM/4, BM/8, so that ragged
 // groups waste little MFMA work.
 template <int PATH, int NB, bool B_KC> struct RowCores {
+  static constexpr int KINDS = 4;
   // bf16: heights 256, 128, 64 and 32; the last two share the 64-row core (those tiles are bound by streaming the
   // weights, not by MFMA work).  Pipeline depth by height: the 128-row tile fits 3 slots per operand, the
   // 64-row one 4.
@@ -447,7 +462,12 @@ template <int PATH, int NB, bool B_KC> struct RowCores {
   using tile = MfmaDmaCore<(KIND == 0 ? 256 : KIND == 1 ? 128 : 64), 256 / NB, NB, true, B_KC, 2, 2,
                            (KIND == 0 ? 1 : KIND == 1 ? 2 : 3), PATH == PATH_BF16_TAIL>;
 };
+template <int NB, bool B_KC> struct RowCores<PATH_BF16_SMALL, NB, B_KC> {
+  static constexpr int KINDS = 1;
+  template <int KIND> using tile = MfmaDmaCore<kSmallTileRows, 128 / NB, NB, true, B_KC, 2, 2, 2, true>;
+};
 template <int NB, bool B_KC> struct RowCores<PATH_F32, NB, B_KC> {
+  static constexpr int KINDS = 4;
   // heights 128, 64, 32 and 16; the last two share the 32-row core
   template <int KIND>
   using tile = std::conditional_t<KIND == 0, SplitCore<128, 128 / NB, NB, true, B_KC, 2, 2>,
@@ -517,30 +537,34 @@ template <class Core> static unsigned w_block_count(const WGemm& p, int n_produc
 struct TileCost {
   int bm, bn, bk;
   float iter[4], fixed[4];
+  int slots = 256;  // blocks that run side by side at these costs
 };
 // fp32 has two tables.  A sum in parts is rounded less often, so the parts of fp32 products are those of the tiles that computed them on the
 // fp32 matrix instructions, to which the results' errors are held (with parts chosen by the costs of today's tiles, fewer, shared results
 // were up to 1.6 times as far off, T = 1, d = 320, width 896: 3.1e-7 -> 4.8e-7); the height is chosen by what today's tiles take.
 template <int PATH, int NB> constexpr TileCost part_cost() {
+  if (PATH == PATH_BF16_SMALL) return TileCost{64, 128 / NB, 64, {0.45f, 0.45f, 0.45f, 0.45f}, {4, 4, 4, 4}, 512};
   if (PATH == PATH_F32)
     return NB == 2 ? TileCost{64, 64, 32, {0.9f, 0.9f, 0.9f, 0.9f}, {3, 3, 3, 3}}
                    : TileCost{64, 128, 32, {0.9f, 0.5f, 0.5f, 0.5f}, {3, 2, 2, 2}};
   return TileCost{256, 256 / NB, 64, {1.45f, 0.85f, 0.7f, 0.7f}, {7, 5, 4, 4}};
 }
 template <int PATH, int NB> constexpr TileCost w_part_cost() {
+  if (PATH == PATH_BF16_SMALL) return TileCost{128, 128 / NB, 64, {0.6f, 0, 0, 0}, {5, 0, 0, 0}, 512};
   if (PATH == PATH_F32) return TileCost{128, 128 / NB, 32, {1.8f, 0, 0, 0}, {5, 0, 0, 0}};
   return TileCost{256, 256 / NB, 64, {1.45f, 0, 0, 0}, {7, 0, 0, 0}};
 }
 template <int PATH, int NB> constexpr TileCost row_cost() {
+  if (PATH == PATH_BF16_SMALL) return part_cost<PATH, NB>();
   if (PATH == PATH_F32)  // two blocks per CU share the matrix pipe: figures of one block that has it for itself
     return TileCost{128, 128 / NB, 32, {0.9f, 0.5f, 0.35f, 0.35f}, {5, 4, 3, 3}};
   return TileCost{256, 256 / NB, 64, {1.45f, 0.85f, 0.7f, 0.7f}, {7, 5, 4, 4}};
 }
 template <int PATH, int NB> constexpr TileCost w_cost() {
+  if (PATH == PATH_BF16_SMALL) return w_part_cost<PATH, NB>();
   if (PATH == PATH_F32) return TileCost{128, 128 / NB, 32, {0.9f, 0, 0, 0}, {5, 0, 0, 0}};
   return TileCost{256, 256 / NB, 64, {1.45f, 0, 0, 0}, {7, 0, 0, 0}};
 }
-constexpr int kCUs = 256;
 struct DirectShape {      // one product (or pair of products, `nb` = 2) without a plan
   TileCost cost, tiles;        // by which the parts are chosen, and then the height
   int groups, rows, N, K, nb;  // (weight gradient: rows is M)
@@ -564,7 +588,7 @@ static DirectChoice direct_option(const DirectShape& s, const TileCost& cost, in
   c.block_us = cost.fixed[kind] + s.sums * per * cost.iter[kind];
   if (c.n_parts > 1) {
     c.part_bytes = align_up((size_t)c.n_parts * s.nb * s.out_elems * 4, 256);
-    c.reduce_us = 4 + 2e-6 / 5 * c.part_bytes;
+    c.reduce_us = (cost.slots > 256 ? 7 : 4) + 2e-6 / 5 * c.part_bytes;  // (short launches: the launch as well)
   }
   return c;
 }
@@ -572,6 +596,7 @@ static DirectChoice direct_option(const DirectShape& s, const TileCost& cost, in
 static void choose_direct(const DirectShape* r, const DirectShape* w, size_t avail, DirectChoice* rc, DirectChoice* wc) {
   static const int kParts[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16};
   const double routed = r ? r->routed_us : 0;
+  const int slots = r ? r->cost.slots : w->cost.slots;
   if (routed > 0) {
     // No more room than the same product takes alone, which is what the size queries ask for: a larger workspace must not
     // change the parts, and with them the results' last bits.
@@ -592,14 +617,14 @@ static void choose_direct(const DirectShape* r, const DirectShape* w, size_t ava
         const DirectChoice& b = w_options[i];
         if (i > 0 && (!w || b.n_parts == 1 || a.part_bytes + b.part_bytes > avail)) continue;
         double us;
-        if (!w && routed == 0) us = (double)((a.blocks + kCUs - 1) / kCUs) * a.block_us;
+        if (!w && routed == 0) us = (double)((a.blocks + slots - 1) / slots) * a.block_us;
         else {
           const double longest = std::max(a.block_us, b.block_us);
-          us = std::max(longest, (a.blocks * a.block_us + b.blocks * b.block_us + routed) / kCUs + 0.3 * longest);
+          us = std::max(longest, (a.blocks * a.block_us + b.blocks * b.block_us + routed) / slots + 0.3 * longest);
         }
         us += a.reduce_us + b.reduce_us;
         if (first || us < best) {
-          best = first ? us * 0.92 : us;
+          best = first ? us * (slots > 256 ? 0.8 : 0.92) : us;
           *rc = a;
           *wc = b;
         }
@@ -612,7 +637,7 @@ static void choose_direct(const DirectShape* r, const DirectShape* w, size_t ava
     best = 0;
     for (int kind = 0; kind < 3; kind++) {
       const DirectChoice a = direct_option(*r, r->tiles, kind, parts);
-      const double us = (double)((a.blocks + kCUs - 1) / kCUs) * a.block_us;
+      const double us = (double)((a.blocks + slots - 1) / slots) * a.block_us;
       if (kind == 0 || us < best) {
         best = us;
         *rc = a;
@@ -767,6 +792,8 @@ template <int PATH> constexpr bool kPartsSeeRouted = PATH != PATH_F32;
 template <int PATH, int NB> static double routed_row_us(int n_groups, int n_rows, int N, int K, int sums = 1) {
   constexpr TileCost c = row_cost<PATH, NB>();
   const double steps = (double)sums * ceil_div(K, c.bk);
+  if (PATH == PATH_BF16_SMALL)  // rows that fall on the groups at random
+    return ceil_div(N, c.bn) * ((double)(n_rows / c.bm) + n_groups * (1 - std::exp(-(double)n_rows / n_groups))) * (c.fixed[0] + steps * c.iter[0]);
   return ceil_div(N, c.bn) * ((double)(n_rows / c.bm) * (c.fixed[0] + steps * c.iter[0]) +
                               std::min(n_groups, n_rows) * (c.fixed[2] + steps * c.iter[2]));
 }
@@ -845,9 +872,11 @@ void expert_fwd_impl(const FwdArgs* r, const FwdArgs* s, hipStream_t st) {
   Gemms rg;
   int max_tiles = 0;
   if (r) {
-    max_tiles = max_row_tiles(r->n_groups, r->n_rows, Cores<PATH>::BM);
-    const Plan pl = carve_plan(r->plan ? r->plan : r->ws, r->n_groups, max_tiles);
-    if (!r->plan) launch_plan(r->offsets, r->n_groups, Cores<PATH>::BM, pl, nullptr, nullptr, st);
+    constexpr int dtype = PATH == PATH_F32 ? MOE_F32 : MOE_BF16;
+    const int bm = plan_tile_rows(dtype, r->n_groups, r->n_rows, r->d, r->F);
+    max_tiles = max_row_tiles(dtype, r->n_groups, r->n_rows, r->d);
+    const Plan pl = carve_plan(r->plan ? r->plan : r->ws, r->n_groups, plan_cap(r->n_groups, r->n_rows));
+    if (!r->plan) launch_plan(r->offsets, r->n_groups, bm, pl, nullptr, nullptr, st);
     rg = fill(*r, pl);
   }
   Direct up = {}, down = {};
@@ -942,14 +971,16 @@ void expert_bwd_impl(const BwdArgs* r, const BwdArgs* s, hipStream_t st) {
   Gemms rg;
   int max_tiles = 0;
   if (r) {
-    max_tiles = max_row_tiles(r->n_groups, r->n_rows, C::BM);
-    const Plan pl = carve_plan(r->plan ? r->plan : r->ws, r->n_groups, max_tiles);
-    if (!r->plan) launch_plan(r->offsets, r->n_groups, C::BM, pl, r->active_ids, r->n_active, st);
+    constexpr int dtype = PATH == PATH_F32 ? MOE_F32 : MOE_BF16;
+    const int bm = plan_tile_rows(dtype, r->n_groups, r->n_rows, r->d, r->F);
+    max_tiles = max_row_tiles(dtype, r->n_groups, r->n_rows, r->d);
+    const Plan pl = carve_plan(r->plan ? r->plan : r->ws, r->n_groups, plan_cap(r->n_groups, r->n_rows));
+    if (!r->plan) launch_plan(r->offsets, r->n_groups, bm, pl, r->active_ids, r->n_active, st);
     if (r->n_rows == 0) return;  // no group is active
     rg = fill(*r, pl);
   }
   if (s && s->n_rows == 0) {
-    launch_plan(nullptr, s->n_groups, C::BM, carve_plan(s->ws, s->n_groups, max_row_tiles(s->n_groups, 0, C::BM)), s->active_ids, s->n_active, st);
+    launch_plan(nullptr, s->n_groups, C::BM, carve_plan(s->ws, s->n_groups, plan_cap(s->n_groups, 0)), s->active_ids, s->n_active, st);
     return;
   }
   // groups with few rows are bound by writing their gradient, not by MFMA work: they go to a

@@ -144,7 +144,7 @@ struct TileEpilogue {
                                                    decltype(hint)::value);
       };
       if (!col_ok) return;
-      if (epi.stream()) put(std::integral_constant<int, 2>());
+      if (RB >= 128 && epi.stream()) put(std::integral_constant<int, 2>());
       else put(std::integral_constant<int, 0>());
     };
     // (short blocks are those of two blocks per CU, with half the registers: no room for the next block's inputs)
@@ -236,7 +236,8 @@ struct TileEpilogue {
 //    that the 16 rows one phase of a 16-byte-per-lane read touches cover all banks once.
 //  row-contiguous operand [BK][ROWS]: piece c (8 columns) of k-row k sits at position
 //    c ^ (4*(k%4)) ^ (2*((k/8)%2)): the 32 lanes of two 16-lane groups of a transposing read, which take 16 columns of
-//    four k rows and of the four k rows 8 further on, touch all banks once.
+//    four k rows and of the four k rows 8 further on, touch all banks once (64 columns, two k rows to the width of the banks:
+//    c ^ (2*((k/2)%2)) ^ (4*((k/8)%2))).
 template <int BM_, int BN_, int NB, bool A_KC, bool B_KC, int WM_ = 2, int WN_ = 2, int DEPTH = 1,
           bool KTAIL = false>
 struct MfmaDmaCore {
@@ -282,7 +283,6 @@ struct MfmaDmaCore {
   static_assert(BM % (32 * WM) == 0 && BN % (32 * WN) == 0, "wave tile must be a multiple of 32");
   static_assert((A_KC || BM * ES % 128 == 0) && (B_KC || BN * ES % 128 == 0),
                 "swizzle of row-contiguous tiles needs >= 8 pieces per k row");
-  static_assert((A_KC || BM >= 128) && (B_KC || BN >= 128), "16 pieces per k row");
   static_assert(LDS_BYTES <= 160 * 1024, "LDS budget of a gfx950 CU");
   typedef __attribute__((address_space(3))) void* lds_vptr;
 
@@ -291,7 +291,10 @@ struct MfmaDmaCore {
   // the K loop spends no instructions on addresses and the whole offset stays inside the
   // descriptor's bounds check.
   __device__ static __forceinline__ int kc_swizzle(int row) { return ((row * PR_KC) >> 4) & (PR_KC - 1); }
-  __device__ static __forceinline__ int rc_swizzle(int k) { return 4 * (k & 3) ^ 2 * ((k >> 3) & 1); }
+  template <int ROWS>
+  __device__ static __forceinline__ int rc_swizzle(int k) {
+    return ROWS == 64 ? 2 * ((k >> 1) & 1) ^ 4 * ((k >> 3) & 1) : 4 * (k & 3) ^ 2 * ((k >> 3) & 1);
+  }
   template <int ROWS, bool KC>
   __device__ static __forceinline__ uint32_t piece_offset(int wave, int lane, uint32_t ld) {
     const int q = wave * 64 + lane;  // linear 16-byte piece of the LDS tile
@@ -302,7 +305,7 @@ struct MfmaDmaCore {
     } else {
       constexpr int PR = ROWS / PE;
       const int k = q / PR, pos = q % PR;
-      const int c = pos ^ rc_swizzle(k);
+      const int c = pos ^ rc_swizzle<ROWS>(k);
       return (uint32_t)k * ld * ES + (uint32_t)c * 16u;
     }
   }
@@ -357,7 +360,7 @@ struct MfmaDmaCore {
 #pragma unroll
       for (int t = 0; t < NTILE; t++) {
         const int col = w0 + t * 16 + 4 * (s & 3);
-        off[t] = (k * ROWS + (((col >> 3) ^ rc_swizzle(k)) << 3) + (col & 7)) * ES;
+        off[t] = (k * ROWS + (((col >> 3) ^ rc_swizzle<ROWS>(k)) << 3) + (col & 7)) * ES;
       }
     }
   }

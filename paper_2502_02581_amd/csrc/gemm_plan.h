@@ -44,10 +44,37 @@ inline Plan carve_plan(void* ws, int /*n_groups*/, int max_tiles) {
   return pl;
 }
 
-// rows of the full row tiles of the tile cores
-inline int plan_tile_rows(int dtype) { return dtype == MOE_F32 ? 128 : 256; }
-// upper bound of the row tiles of a plan (at most two remainder tiles per group)
-inline int max_row_tiles(int n_groups, int n_rows, int BM) { return n_rows / BM + 2 * n_groups; }
+// Bf16 calls of few rows whose products are short take small tiles (Cores<PATH_BF16_SMALL>): with four times as many, two on a CU,
+// such launches fill the chip, and a tile's own latency is what counts.  Their plans have tiles of 64 rows only.  Three lines:
+//  rows x d: below it tall tiles would not fill the chip.  (Passes before, on the full family's tiles, and now: T = 911, d = 128, 4 experts of
+//    1088 and four shared, 0.1 million, training 173 and 98 us; T = 1190, top-4, d = 344, 85 experts of 400, 1.6 million, 177 and 146; T = 9871,
+//    top-2, d = 128, 133 experts of 384, 2.4 million, 361 and 288; T = 243, top-6, d = 2304, 31 experts of 128, 3.2 million, 143 and 117; T = 6330,
+//    d = 600, 166 experts of 384, 3.6 million, forward 101 and 104.)
+//  bytes of a matrix of the groups that may have rows: above it the stream of the weights counts, and the full family reads twice as long
+//    pieces of their rows.  (113 MB, training 102 and 82 us; 200 MB, forward 110 and 61; 330 MB, T = 16, top-4, d = 2048, 60 experts, forward 111
+//    and 106; 345 MB, training 747 and 758; 477 MB 701 and 711; 1390 MB 1429 and 1624.)
+//  arithmetic of a product: above it the matrix pipe counts.  (6 GFLOP, training 534 and 429 us; 14 GFLOP 747 and 758; 33 GFLOP, forward 377
+//    and 418.)
+constexpr int kFewRowValues = 13 << 18;
+inline bool few_rows(int dtype, int64_t n_rows, int d) { return dtype != MOE_F32 && n_rows * d <= kFewRowValues; }
+inline bool short_product(int64_t n_rows, int64_t d, int64_t d_ff) { return 2 * n_rows * d * d_ff <= 16000000000; }
+inline bool small_tiles(int dtype, int n_groups, int n_rows, int d, int d_ff) {
+  return few_rows(dtype, n_rows, d) && short_product(n_rows, d, d_ff) &&
+         2 * (int64_t)(n_groups < n_rows ? n_groups : n_rows) * d * d_ff <= (int64_t)340 << 20;
+}
+// rows of the full row tiles of a plan
+constexpr int kSmallTileRows = 64, kSmallTileKind = 2;  // (64-row tiles are kind 2 of the full family, too)
+inline int plan_tile_rows(int dtype, int n_groups, int n_rows, int d, int d_ff) {
+  return dtype == MOE_F32 ? 128 : small_tiles(dtype, n_groups, n_rows, d, d_ff) ? kSmallTileRows : 256;
+}
+// Room for the row tiles of any plan, whatever its tiles.  A dispatch and the calls that use its plan may disagree on those (they need not be
+// given the same width), so the layout does not depend on them, and every family takes any plan.
+inline int plan_cap(int n_groups, int n_rows) { return n_rows / 64 + 2 * n_groups; }
+// upper bound of the row tiles that a plan can have (at most two remainder tiles per group; of 64-row tiles one)
+inline int max_row_tiles(int dtype, int n_groups, int n_rows, int d) {
+  const int g = n_groups < n_rows ? n_groups : n_rows, tall = n_rows / (dtype == MOE_F32 ? 128 : 256) + 2 * g;
+  return few_rows(dtype, n_rows, d) && n_rows / kSmallTileRows + g > tall ? n_rows / kSmallTileRows + g : tall;
+}
 
 // One block of 1024 threads; thread e owns group e, which has c rows from row st on.  Bound by latency, nothing runs beside it: the pass
 // for the group ranks takes four row counts per LDS read, the scans use one barrier each, and every tile has its own
@@ -92,8 +119,8 @@ __device__ __forceinline__ void build_plan(int c, int st, int n_groups, int BM, 
   __syncthreads();
   // Row tiles, groups in descending size: full tiles of BM rows, and the remainder r of a group cut into tiles of
   // BM/2, BM/4 and BM/8 rows so that little MFMA work is spent on padding; in eighths of BM: r > 6: one full tile;
-  // (5,6]: 4 + 2; (4,5]: 4 + 1; (3,4]: 4; (2,3]: 2 + 1; (1,2]: 2; (0,1]: 1.
-  auto eighths = [&](int rows) { return ((rows % BM) * 8 + BM - 1) / BM; };
+  // (5,6]: 4 + 2; (4,5]: 4 + 1; (3,4]: 4; (2,3]: 2 + 1; (1,2]: 2; (0,1]: 1.  Tiles of one height: always a full one.
+  auto eighths = [&](int rows) { return BM == kSmallTileRows ? (rows % BM ? 8 : 0) : ((rows % BM) * 8 + BM - 1) / BM; };
   const int cg = e < n_groups ? cnt[e] : 0;
   const int r8 = eighths(cg);
   const int nt = cg / BM + (r8 > 0) + (r8 == 3 || r8 == 5 || r8 == 6);
@@ -117,7 +144,7 @@ __device__ __forceinline__ void build_plan(int c, int st, int n_groups, int BM, 
     RowTile t;
     t.group = ord[lo];
     t.row0_in = first[lo] + row;
-    t.rows = min(BM >> kind, rows - row) | (kind << 16);
+    t.rows = min(BM >> kind, rows - row) | ((BM == kSmallTileRows ? kSmallTileKind : kind) << 16);
     t.row0_out = t.row0_in;
     pl.tiles[i] = t;
   }
