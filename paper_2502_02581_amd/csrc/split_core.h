@@ -316,10 +316,10 @@ struct SplitCore {
           for (int j = 0; j < TN; j++)
 #pragma unroll
             for (int r = 0; r < 4; r++) bad = fmaf(acc[nb][i][j][r], 0.f, bad);
+      const bool any = __ballot(bad != 0.f) != 0;  // the same in every lane of the wave
       __syncthreads();  // every wave is done with the tiles
       int* found = (int*)smem;
-      if (lane == 0) found[wave] = 0;
-      if (bad != 0.f) found[wave] = 1;  // (in this order: one wave's LDS operations)
+      if (lane == 0) found[wave] = any;
       __syncthreads();
 #pragma unroll
       for (int w = 0; w < NW; w++) exact = exact || found[w] != 0;

@@ -64,6 +64,24 @@ def test_values_that_are_not_finite(T, d, E):
         assert ((got.double() - ref).abs()[finite] <= ((a.shape[1] + 20) * U * scale)[finite]).all()
 
 
+@pytest.mark.parametrize("d,n", [(40, 0), (40, 17), (200, 46), (72, 63), (72, 64), (40, 95), (136, 111), (40, 127)])
+def test_one_lane_asks_for_the_fp32_instruction(d, n):
+    """One value of each tile of 128 x 128 overflows in the sum of its parts and not in fp32 (both operands round up to a power of two
+    in bf16): it is right whichever lane and wavefront finds it."""
+    T, E = 1920, 256
+    r = torch.Generator().manual_seed(7)
+    X, W, g = torch.randn(T, d, generator=r), torch.randn(d, E, generator=r), torch.randn(T, E, generator=r)
+    rows = [128 * i + (37 * i + n) % 128 for i in range(T // 128)]
+    big = 2.0 ** 64 * (1 - 2.0 ** -12)
+    X[:, 3], W[3] = 0.0, 0.0
+    X[rows, 3] = big
+    W[3, [n, 255 - n]] = big
+    logits, _, _ = _router(T, d, E, X, W, g)
+    ref, scale = X.double() @ W.double(), X.double().abs() @ W.double().abs()
+    assert torch.isfinite(logits).all()
+    assert ((logits.double() - ref).abs() <= (d + 20) * U * scale).all()
+
+
 @pytest.mark.parametrize("scale", [1e-30, 1e-20, 1e18])
 def test_ends_of_the_range(scale):
     """Operands down to 2e-31 keep all of their bits."""
