@@ -79,20 +79,21 @@ __device__ __forceinline__ void static_for(F f) {
 // global stores still 9.9 k, 13.0 k, 39 k.  This form: 7.3 k, 12 k, 41 k, without the stores 4.5 k, 9.7 k, 34 k: what is
 // left is arithmetic, two transcendentals per value, and the stores and loads of a launch's first tiles, which
 // all CUs issue together.  Whole steps gain 1-3 % only, because the shader clock drops as the matrix pipe idles less.)
-// NB products of TM x TN accumulator tiles a wave, NW waves; AGPR: the accumulators live in AGPRs, under
-// inline assembly, and are copied out one by one.
-// ROWS: rows of a block.
-template <int NB, int TM, int TN, int NW, int LDS, bool AGPR, int ROWS = 32>
+// NB products of TM x TN tiles a wave, NW waves; AGPR: the accumulators live in AGPRs, under inline assembly, and are
+// copied out one by one.
+// ROWS: rows of a block.  MT: rows of a tile, one per lane % MT; its columns are four for every lane of a row, lane / MT by lane / MT.
+// AHEAD: the next block's inputs are loaded under a block's arithmetic (two blocks per CU have no registers for them).
+template <int NB, int TM, int TN, int NW, int LDS, bool AGPR, int ROWS = 32, int MT = 16, bool AHEAD = true>
 struct TileEpilogue {
-  static constexpr int MT = 16;  // rows and columns of an accumulator tile
+  static constexpr int HP = 64 / MT, CT = 4 * HP;  // lanes of a row, columns of a tile
   // LDS that the staging regions of `waves` waves take
   template <class Epi> static constexpr int bytes(int waves) {
-    return waves * (Epi::NOUT > Epi::NAUX ? Epi::NOUT : Epi::NAUX) * ROWS * TN * MT * Epi::OES;
+    return waves * (Epi::NOUT > Epi::NAUX ? Epi::NOUT : Epi::NAUX) * ROWS * TN * CT * Epi::OES;
   }
   template <class Epi>
   __device__ static __forceinline__ void run(char* smem, f32x4_t (&acc)[NB][TM][TN], const Epi& epi, int wave, int lane, int wm0, int wn0) {
     constexpr int OES = Epi::OES, NOUT = Epi::NOUT, NAUX = Epi::NAUX;
-    constexpr int RB = TN * MT * OES;         // bytes per row of the wave's tile
+    constexpr int RB = TN * CT * OES;         // bytes per row of the wave's tile
     constexpr int LPR = RB / 16;              // lanes (16-byte pieces) per row
     constexpr int RPP = 64 / LPR;             // rows per wave-wide access
     constexpr int NPASS = ROWS / RPP;
@@ -103,11 +104,10 @@ struct TileEpilogue {
     constexpr int NA = NAUX > 0 ? NAUX : 1;
     static_assert(bytes<Epi>(NW) <= LDS, "the waves' staging regions fit into LDS");
     char* stage = smem + wave * (NMAT * BLOCK);
-    // row order: row pass * RPP + lane / LPR, piece lane % LPR;  result layout: row lane % MT of an accumulator tile, four of
-    // its columns, by lane / MT
+    // row order: row pass * RPP + lane / LPR, piece lane % LPR;  result layout: see MT
     const int rrow = lane / LPR, rpiece = lane % LPR;
     const uint32_t r_off = rrow * RB + ((rpiece ^ (rrow & SWZ)) << 4);
-    constexpr int GR = ROWS / MT;             // accumulator tiles of a block's rows
+    constexpr int GR = ROWS / MT;             // tiles of a block's rows
     const int mrow = lane & (MT - 1), h = lane / MT;
     uint32_t m_off[GR];
 #pragma unroll
@@ -115,9 +115,9 @@ struct TileEpilogue {
     auto row_at = [&](int pass) __attribute__((always_inline)) {  // (rrow < RPP, so the row's other bits come from pass)
       return (r_off ^ (((pass * RPP) & SWZ) << 4)) + pass * RPP * RB;
     };
-    // first of the lane's four columns: MT * j + 4 * h
+    // first of the lane's four columns: CT * j + 4 * h
     auto col_at = [&](int rh, int j) __attribute__((always_inline)) {
-      return OES == 2 ? (m_off[rh] ^ ((2 * j + (h >> 1)) << 4)) + 8 * (h & 1) : (m_off[rh] ^ ((4 * j + h) << 4));
+      return OES == 2 ? (m_off[rh] ^ ((HP / 2 * j + (h >> 1)) << 4)) + 8 * (h & 1) : (m_off[rh] ^ ((HP * j + h) << 4));
     };
     // global side: byte offsets from the tile's origin in every matrix
     const int c0 = wn0 + rpiece * (16 / OES);
@@ -147,8 +147,6 @@ struct TileEpilogue {
       if (RB >= 128 && epi.stream()) put(std::integral_constant<int, 2>());
       else put(std::integral_constant<int, 0>());
     };
-    // (short blocks are those of two blocks per CU, with half the registers: no room for the next block's inputs)
-    constexpr bool AHEAD = ROWS == 32;
     if (NAUX > 0 && AHEAD) load_aux(0);
     float scale[TM];
 #pragma unroll
