@@ -17,6 +17,10 @@
  *  - `stream` is a hipStream_t passed as void* (NULL = the default stream).  A call
  *    only enqueues kernels on that stream and returns without synchronising.
  *  - dtype MOE_F32: X, weights, activations, outputs and weight gradients are fp32.
+ *    Products are summed in fp32 from three bf16 parts of each value, with no larger error than fp32 arithmetic that rounds
+ *    every product (3 % larger where a sum has one product).  Infinities, NaN and overflow come out as there.  At the low end of
+ *    the range a value below 2^-102 (2e-31) loses its last bits beside a factor above 2^33, and results whose products all have
+ *    a factor below 2^-134 (5e-41) are zero.
  *    dtype MOE_BF16: they are bfloat16 (round-to-nearest-even at every store),
  *    products accumulate in fp32.  Logits, combine weights and their gradient are
  *    always fp32; all index arrays are int32.

@@ -14,9 +14,12 @@
 // 0.49 to 0.84 and 0.31 to 0.61; gradients of the logits that are zero outside the top 1 to 8 experts 1.04 to 1.85 and 0.42 to 1.00; tokens of
 // which 3 % are not zero 1.15 to 1.94 and 0.46 to 0.96; sums of one product 1.36 and 1.03.  (One value of K, kFew: the fp32 instruction.)
 //
-// Infinities, NaNs and sums that overflow come out as NaN or infinity somewhere among the partial products.  A tile that ends with
-// such a value in any lane is computed again with the fp32 instruction, which treats them as fp32 arithmetic does (EXACT below).
-// Operands below 2^-102 in magnitude (2e-31) lose the last bits of their third part to bf16's range, whose end is that of fp32.
+// Infinities, NaNs and sums that overflow come out as NaN or infinity somewhere among the partial products.  Operands below 2^-102 in
+// magnitude (2e-31) lose the last bits of their third part to bf16's range, whose end is that of fp32: at most 2^-134 of a value, and all
+// of one below 2^-134.  A tile that ends with a value that is not finite, or with one below 2^-76 that is not zero, in any lane
+// is computed again with the fp32 instruction, which treats them as fp32 arithmetic does (EXACT below).  So what range loses of a result is
+// 2^-134 / 2^-76 of the other operand: below 2^-25 of the result while that is below 2^33 -- except in results whose
+// products all have a factor below 2^-134 (5e-41), which are zero.
 //
 // Measured, training steps, with the fp32 instruction (on 64 x 128 tiles) and now: T = 2048, d = 1024, 16 experts, top-2, width 2816
 // 1940 -> 1445 to 1500 us (144 TFLOP/s of fp32 products); T = 256, d = 128, 8 experts of width 256 92.4 -> 82.
@@ -61,6 +64,7 @@ struct SplitCore {
   static constexpr int BLOCKS_PER_CU = 2;
   static constexpr bool REPEATS = false;  // (see w_gemm_block)
   static constexpr uint32_t kNowhere = 0xffffff00u;
+  static constexpr uint32_t kTiny = (127u - 76u) << 23;  // the bits of 2^-76
   typedef __attribute__((ext_vector_type(8))) __bf16 frag_t;
   typedef __attribute__((ext_vector_type(16))) float acc_t;  // 32 x 32: a lane has columns 8 * (r / 4) + 4 * (lane / 32) + r % 4 of row lane % 32
   static_assert(NW == 4 && BM % (32 * WM) == 0 && (BN % (32 * WN) == 0 || (MIX && !B_KC)), "four wavefronts, whole tiles of 32 x 32 each");
@@ -357,13 +361,15 @@ struct SplitCore {
     if (!exact) {
       acc_t hi[MB][TM][TN], lo[MB][TM][TN];
       k_loop<false>(smem, n_segs, nk, segf, lda, ldb, amap, hi, lo, lane, wm0, wn0);
-      float bad = 0.f;  // NaN if any value is not finite
+      float bad = 0.f;              // NaN if any value is not finite
+      uint32_t least = 0xffffffffu;  // of the magnitudes that are not zero, as bits: twice them less one
       each([&](int nb, int i, int j, int r) __attribute__((always_inline)) {
         const float v = hi[nb][i][j][r] + lo[nb][i][j][r];
         bad = fmaf(v, 0.f, bad);
+        least = min(least, 2 * __float_as_uint(v) - 1);
         return v;
       });
-      const bool any = __ballot(bad != 0.f) != 0;  // the same in every lane of the wave
+      const bool any = __ballot(bad != 0.f || least < 2 * kTiny - 1) != 0;  // the same in every lane of the wave
       __syncthreads();  // every wave is done with the tiles
       int* found = (int*)smem;
       if (lane == 0) found[wave] = any;

@@ -118,16 +118,18 @@ def test_sums_of_few_products(T, d, E, k):
         assert (got.double() - ref).norm() <= 1.005 * (_fp32_sum(a, b).double() - ref).norm()
 
 
-@pytest.mark.parametrize("scale", [2.0 ** -102, 1e-30, 1e-20, 1.0, 1e18])
+@pytest.mark.parametrize("scale", [1e-39, 2.0 ** -126, 1e-36, 2.0 ** -110, 2.0 ** -102, 1e-30, 1e-20, 1.0, 1e18])
 def test_ends_of_the_range(scale):
-    """Operands down to 2^-102 keep all of their bits: sums, and single products with one."""
+    """Operands of any magnitude keep all of their bits (below 2^-102 their third part does not fit into bf16's range): sums, and single
+    products with one."""
     r = torch.Generator().manual_seed(6)
     T, d, E = 65, 72, 64
     X = (torch.rand(T, d, generator=r) + 1.0) * scale   # values of one binade: none below the limit
     W, g = torch.randn(d, E, generator=r), torch.randn(T, E, generator=r)
     logits, dW, dX = _router(T, d, E, X, W, g)
-    _check(logits, X, W)
-    _check(dW, X.T, g)
+    if scale >= 2.0 ** -120:   # (below, results themselves are rounded at the end of fp32's range)
+        _check(logits, X, W)
+        _check(dW, X.T, g)
     _check(dX, g, W.T)
     pick = torch.randperm(d, generator=r)[:E]
     one = torch.zeros(d, E)
