@@ -19,6 +19,12 @@ def small_cfg(name="t", T=24, d=8, E=6, k=2, d_ff=12, n_shared=0, d_ff_shared=0,
                         aux_alpha=aux_alpha, ffn=ffn)
 
 
+def small_tiles(n_groups, n_rows, d, d_ff):
+    """Whether a bf16 expert call takes the tiles of short calls (small_tiles() of csrc/gemm_plan.h): tests of either family state
+    which one their sizes are meant for."""
+    return n_rows * d <= 13 << 18 and 2 * n_rows * d * d_ff <= 16_000_000_000 and 2 * min(n_groups, n_rows) * d * d_ff <= 340 << 20
+
+
 def np64(t):
     """A torch tensor (any float dtype) or array as float64 numpy."""
     if isinstance(t, torch.Tensor):

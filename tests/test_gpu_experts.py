@@ -2,6 +2,8 @@
 import pytest
 import torch
 
+from .helpers import small_tiles
+
 pytestmark = pytest.mark.gpu
 
 # T, d, E, k, d_ff, shared experts, their width, routed activation, shared activation, rows read in place
@@ -18,10 +20,17 @@ CASES = [
     (1743, 832, 8, 2, 128, 1, 64, "swiglu", "swiglu", False),     # shared sums in parts alone
     (42, 1472, 8, 2, 1024, 2, 1024, "swiglu", "swiglu", False),
 ]
+# bf16: the cases above are short calls, with tiles of their own; these take the tall ones
+TALL_CASES = [
+    (1701, 1024, 5, 2, 192, 2, 192, "swiglu", "swiglu", True),    # no K tail, rows read in place
+    (1700, 1024, 6, 2, 200, 2, 128, "swiglu", "swiglu", False),   # only the routed width has a K tail
+    (1700, 1024, 6, 2, 128, 1, 72, "swiglu", "swiglu", True),     # only the shared width has one
+    (1743, 1000, 6, 2, 264, 3, 328, "gelu", "gelu", True),        # ragged everywhere, two-matrix experts
+]
 
 
-@pytest.mark.parametrize("T,d,E,k,F,S,Fs,act,act_s,gather", CASES)
-@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("dtype,T,d,E,k,F,S,Fs,act,act_s,gather", [(t, *c) for t in ("f32", "bf16") for c in CASES] +
+                         [("bf16", *c) for c in TALL_CASES])
 def test_both_sets_in_one_call(dtype, T, d, E, k, F, S, Fs, act, act_s, gather):
     """Routed results are the same bits, and in fp32 shared ones are too (the same parts of their sums, so the same error);
     in bf16 shared ones differ by the order of fp32 sums and by the rounding of the output to its type."""
@@ -29,6 +38,7 @@ def test_both_sets_in_one_call(dtype, T, d, E, k, F, S, Fs, act, act_s, gather):
 
     shape, sshape = moe.MoEShape(T, d, E, k, F, dtype), moe.MoEShape(T, d, E, k, Fs, dtype)
     dt, dev, A = shape.torch_dtype, "cuda", T * k
+    assert dtype == "f32" or small_tiles(E, A, d, F) == ((T, d, E, k, F, S, Fs, act, act_s, gather) in CASES)
     g = torch.Generator().manual_seed(T + d + F)
     rnd = lambda *s: (torch.randn(*s, generator=g) * d ** -0.5).to(dt).to(dev)
     X, dY = rnd(T, d), rnd(T, d)
@@ -102,14 +112,18 @@ def test_both_sets_in_one_call(dtype, T, d, E, k, F, S, Fs, act, act_s, gather):
             assert err <= 8e-3, (n, err)
 
 
-# sizes at which more room than a set asks for alone would make more parts beside these routed rows
-@pytest.mark.parametrize("T,d,E,k,F,S,Fs", [(256, 256, 120, 2, 1024, 2, 1024), (80, 5376, 48, 1, 128, 4, 64), (85, 3840, 65, 1, 256, 1, 256)])
+# The first three: sizes at which, without the limit in choose_direct, more room than a set asks for alone would make more parts beside
+# these routed rows, of dH (2 and 1 -> 4 and 2 with 16 MiB more), dH (3 -> 4), gate/up (3 -> 4).  They take the tall tiles: with the costs of
+# the small ones, the others', no size out of 350 thousand drawn ones makes more parts.
+@pytest.mark.parametrize("T,d,E,k,F,S,Fs", [(997, 3968, 8, 1, 64, 2, 192), (667, 2240, 4, 3, 64, 2, 192), (1366, 3136, 6, 2, 128, 1, 384),
+                                            (256, 256, 120, 2, 1024, 2, 1024), (80, 5376, 48, 1, 128, 4, 64), (85, 3840, 65, 1, 256, 1, 256)])
 def test_room_beyond_the_query_changes_nothing(T, d, E, k, F, S, Fs):
     """A call gives the same bits with every workspace from the size queries' answer on."""
     import paper_2502_02581_amd as moe
 
     shape, sshape = moe.MoEShape(T, d, E, k, F, "bf16"), moe.MoEShape(T, d, E, k, Fs, "bf16")
     A, dev = T * k, "cuda"
+    assert small_tiles(E, A, d, F) == (T < 500)
     g = torch.Generator().manual_seed(T + d)
     rnd = lambda *s: (torch.randn(*s, generator=g) * d ** -0.5).bfloat16().to(dev)
     X, dY, Xp, dYp = rnd(T, d), rnd(T, d), rnd(A, d), rnd(A, d)
@@ -155,13 +169,15 @@ def test_sets_are_checked():
             moe.moe_experts_fwd(shape, r, s)
 
 
-@pytest.mark.parametrize("T,E,k", [(0, 5, 2), (1, 1, 1), (700, 6, 2), (517, 64, 3), (40, 300, 8), (60, 1024, 4)])
-@pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_plan_of_the_dispatch(dtype, T, E, k):
+@pytest.mark.parametrize("dtype,T,d,E,k", [(t, *s) for t in ("f32", "bf16") for s in (
+    (0, 64, 5, 2), (1, 64, 1, 1), (700, 64, 6, 2), (517, 64, 64, 3), (40, 64, 300, 8), (60, 64, 1024, 4))] +
+    [("bf16", 700, 2496, 6, 2), ("bf16", 1301, 1000, 64, 3)])   # the last two: the tall tiles
+def test_plan_of_the_dispatch(dtype, T, d, E, k):
     """A plan that the dispatch wrote gives the bits of the calls that build their own, and the same active_ids."""
     import paper_2502_02581_amd as moe
 
-    d, F, A, dev = 64, 72, T * k, "cuda"
+    F, A, dev = 72, T * k, "cuda"
+    assert dtype == "f32" or small_tiles(E, A, d, F) == (d == 64)
     shape = moe.MoEShape(T, d, E, k, F, dtype)
     dt = shape.torch_dtype
     g = torch.Generator().manual_seed(T + E)

@@ -115,6 +115,11 @@ LAYER_CASES = [
     (small_cfg("bf16-heights", T=620, d=128, E=12, k=3, d_ff=192, dtype="bf16", zipf_s=1.3, gate="sigmoid"), False),
     (small_cfg("bf16-stress", T=512, d=128, E=24, k=4, d_ff=96, dtype="bf16", routing="stress", zipf_s=1.5,
                ), True),
+    # the bf16 cases above are short calls, with tiles of their own; these take the tall ones: ragged, all multiples of 64, GELU
+    (small_cfg("bf16-tall-ragged", T=1750, d=1000, E=6, k=2, d_ff=136, dtype="bf16", zipf_s=1.0, gate="sigmoid", n_shared=1,
+               d_ff_shared=72), True),
+    (small_cfg("bf16-tall", T=1200, d=1024, E=12, k=3, d_ff=192, dtype="bf16", zipf_s=1.3, n_shared=2, d_ff_shared=128), True),
+    (small_cfg("bf16-tall-gelu", T=1750, d=1032, E=5, k=2, d_ff=200, dtype="bf16", zipf_s=0.7, ffn="gelu"), True),
 ]
 
 
@@ -176,7 +181,7 @@ def test_configs_reduced(name):
 
 
 GATHER_CASES = ["f32-sig", "f32-gelu", "bf16-a", "bf16-gelu", "bf16-sig-shared", "bf16-many-empty", "bf16-big-tiles",
-                "bf16-heights", "bf16-stress", "bf16-gelu-dma", "bf16-kE"]
+                "bf16-heights", "bf16-stress", "bf16-gelu-dma", "bf16-kE", "bf16-tall-ragged", "bf16-tall", "bf16-tall-gelu"]
 
 
 @pytest.mark.parametrize("name", GATHER_CASES)

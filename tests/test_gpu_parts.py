@@ -10,9 +10,12 @@ import re
 import pytest
 import torch
 
+from .helpers import small_tiles
+
 pytestmark = pytest.mark.gpu
 
 TOL = {"f32": 1e-5, "bf16": 5e-3}
+TALL = [(1, 560, 6144, 128), (2, 3400, 1024, 192), (3, 1200, 3000, 200)]   # bf16: the tall tiles, without and with a K tail (those of SHARED take the small ones)
 SHARED = [(1, 1, 512, 1024), (3, 16, 320, 1368), (4, 33, 1000, 712), (2, 200, 136, 2048), (1, 700, 264, 520), (1, 3001, 136, 200)]
 ROUTER = [(1, 512, 5), (130, 2000, 60), (700, 1024, 128), (2500, 328, 64)]
 
@@ -39,11 +42,11 @@ def workspaces(call, query, moe):
 
 
 @pytest.mark.parametrize("ffn", ["swiglu", "gelu"])
-@pytest.mark.parametrize("S,T,d,F", SHARED)
-@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("dtype,S,T,d,F", [(t, *s) for t in ("f32", "bf16") for s in SHARED] + [("bf16", *s) for s in TALL])
 def test_shared_calls(dtype, S, T, d, F, ffn):
     import paper_2502_02581_amd as moe
 
+    assert dtype == "f32" or small_tiles(S, T, d, F) == ((S, T, d, F) in SHARED)
     shape = moe.MoEShape(T, d, max(S, 2), 1, F, dtype)
     dt, gated = shape.torch_dtype, ffn == "swiglu"
     g = torch.Generator().manual_seed(d * 1000 + F)
@@ -93,12 +96,13 @@ def test_shared_calls(dtype, S, T, d, F, ffn):
         ids.fill_(-7)
 
 
-@pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_same_bits_with_any_larger_workspace(dtype):
+@pytest.mark.parametrize("dtype,S,T,d,F", [("f32", 4, 33, 1024, 712), ("bf16", 4, 33, 1024, 712), ("bf16", 1, 560, 6144, 128)])
+def test_same_bits_with_any_larger_workspace(dtype, S, T, d, F):
     """Where a call has what the query answers, how much more there is changes nothing (all four calls use parts here)."""
     import paper_2502_02581_amd as moe
 
-    S, T, d, F, E = 4, 33, 1024, 712, 128
+    E = 128
+    assert dtype == "f32" or small_tiles(S, T, d, F) == (T == 33)
     shape, rshape = moe.MoEShape(T, d, S, 1, F, dtype), moe.MoEShape(700, d, E, 1, F, dtype)
     dt, dev = shape.torch_dtype, "cuda"
     g = torch.Generator().manual_seed(3)

@@ -6,6 +6,8 @@ torch = pytest.importorskip("torch")
 
 import paper_2502_02581_amd as moe
 
+from .helpers import small_tiles
+
 pytestmark = pytest.mark.gpu
 EDGES = [0, 1, 7, 31, 32, 33, 63, 64, 65, 96, 127, 128, 129, 160, 191, 193, 224, 255, 256, 257, 300, 0, 511, 513]
 DEV = "cuda:0"
@@ -20,7 +22,7 @@ def _err(got, ref):
 def test_groups_at_the_edges(d, F, gated):
     counts = EDGES + ([500] if d > 1000 else [])
     E, A = len(counts), sum(counts)
-    assert (A * d <= 13 << 18) == (d < 1000)
+    assert small_tiles(E, A, d, F) == (d < 1000)
     r = torch.Generator().manual_seed(d + F)
     n = lambda *s: torch.randn(*s, generator=r).bfloat16()
     X, dY = n(A, d), n(A, d)
@@ -69,8 +71,9 @@ def test_groups_at_the_edges(d, F, gated):
 
 @pytest.mark.parametrize("given,used", [(8, 136), (6400, 136), (136, 6400)])
 def test_plan_of_another_width(given, used):
-    """A dispatch need not be told the experts' width: a plan for the other family's tiles gives the same bits."""
+    """A dispatch need not be told the experts' width: a plan for the other family's tiles gives the same bits, forward and backward."""
     T, d, E, k = 1500, 512, 12, 2
+    assert small_tiles(E, T * k, d, used) == (used == 136) and small_tiles(E, T * k, d, given) == (given < 6400)
     r = torch.Generator().manual_seed(1)
     logits = torch.randn(T, E, generator=r)
     logits[:, 3] += 2.0
@@ -85,11 +88,15 @@ def test_plan_of_another_width(given, used):
     ids, na = i32(E), i32(1)
     ws = torch.empty(max(moe.moe_route_dispatch_workspace_bytes(sd), moe.moe_expert_fwd_workspace_bytes(su, E, A, False)), dtype=torch.uint8, device=DEV)
     moe.moe_route_dispatch_plan(sd, logits.to(DEV), X, 0.0, idx, w, counts, off, row, src, Xp, None, None, plan, ids, na, ws)
+    dY = torch.randn(A, d, generator=r).bfloat16().to(DEV)
+    ws = torch.empty(max(ws.numel(), moe.moe_expert_bwd_workspace_bytes(su, E, A, False)), dtype=torch.uint8, device=DEV)
     out = []
     for p in (plan, None):
-        G, U, H, Y = b(A, used), b(A, used), b(A, used), b(A, d)
-        moe.moe_experts_fwd(su, dict(d_ff=used, n_groups=E, n_rows=A, offsets=off, Xin=Xp, Wg=W[0], Wu=W[1], Wd=W[2], G=G, U=U, H=H, Yout=Y,
-                                     ws=ws, ws_bytes=ws.numel(), plan=p), None)
-        out.append((G, U, H, Y))
+        G, U, H, Y, dX, dW = b(A, used), b(A, used), b(A, used), b(A, d), b(A, d), [b(E, d, used), b(E, d, used), b(E, used, d)]
+        own_ids, own_na = (ids, na) if p is not None else (i32(E), i32(1))
+        both = dict(d_ff=used, n_groups=E, n_rows=A, offsets=off, Xin=Xp, Wg=W[0], Wu=W[1], Wd=W[2], G=G, U=U, H=H, ws=ws, ws_bytes=ws.numel(), plan=p)
+        moe.moe_experts_fwd(su, dict(both, Yout=Y), None)
+        moe.moe_experts_bwd(su, dict(both, dYin=dY, dXin=dX, active_ids=own_ids, n_active=own_na, dWg_c=dW[0], dWu_c=dW[1], dWd_c=dW[2]), None)
+        out.append((G, U, H, Y, dX, *dW, own_ids, own_na))
     for x, y in zip(*out):
         assert torch.equal(x, y)
