@@ -1,5 +1,5 @@
 // Kernels and host side of the expert and router GEMMs, instantiated once per family of tile cores
-// (expert_f32.hip, expert_bf16.hip, expert_tail.hip: three translation units, so that they compile side by side).
+// (expert_f32.hip, expert_bf16.hip, expert_tail.hip, expert_small.hip: four translation units, so that they compile side by side).
 #pragma once
 
 #include <algorithm>
@@ -416,9 +416,9 @@ __global__ __launch_bounds__(256) void reduce_kernel(Reduce p) {
 }
 
 // ------------------------------------------------------------------------------ host side
-// Three families of tile cores: fp32 (MOE_F32), bf16 with d and d_ff multiples of 64, and bf16 with any
-// multiples of 8.  The last differs in one point: the row GEMMs mask the K tail of their K-contiguous
-// operands (a VALU instruction per tile load; the weight gradients have no such operands).  Before, such sizes
+// Four families of tile cores: fp32 (MOE_F32), bf16 with d and d_ff multiples of 64, bf16 with any multiples of 8, and
+// bf16 calls of few rows (small_tiles).  The third differs from the second in one point: the row GEMMs mask the K tail of their
+// K-contiguous operands (a VALU instruction per tile load; the weight gradients have no such operands).  Before, such sizes
 // ran on 128 x 128 tiles staged through registers: forward + backward of T = 3001, d = 1000, d_ff = 1368,
 // 24 experts, top-3, one shared expert: 1.63 ms; on these cores 0.91 ms, with the same bits.
 enum { PATH_F32 = 0, PATH_BF16_TAIL = 1, PATH_BF16 = 2, PATH_BF16_SMALL = 3 };
@@ -535,19 +535,21 @@ template <class Core> static unsigned w_block_count(const WGemm& p, int n_produc
 // The choice minimises an estimate, in microseconds: a K step of a tile, by height (`iter`), what a tile costs besides
 // (`fixed`: first loads, epilogue), a launch with the sums of the parts at 5 TB/s.  Measured for comparison with 256 tiles, one
 // per compute unit, 16 and 64 K steps, operands in cache (dual products in brackets): bf16 1.53, 0.83, 0.60 and 0.54 (1.45, 0.79,
-// 0.51, 0.48) a step of 256, 128, 64 and 32 rows, and 12 to 7 (16 to 8) besides, launch included; fp32 1.07 a step of 64
-// rows, 0.61 of fewer (1.02 of any height), and 8 to 6 (11 to 8).  The table's steps are within a fifth of that, those of
-// the short bf16 tiles up to half above it; the weight gradients' were not measured apart.  It has no term for the rate
+// 0.51, 0.48) a step of 256, 128, 64 and 32 rows, and 12 to 7 (16 to 8) besides, launch included; the table's steps are within a fifth
+// of that, those of the short tiles up to half above it.  The weight gradients' and those of the small tiles (PATH_BF16_SMALL) were not
+// measured apart.  fp32 (SplitCore, operands from memory): 1.52, 0.89 and 0.67 a step of 32 values of K and 128, 64 and 32 rows, 9 to 5
+// besides; the table holds 0.5 to 0.6 of that at any height, and only the heights' ratio matters where it is used.  Neither has a term for the rate
 // at which weights arrive (decode's gate/up and down products over 16 rows: 9 and 10 us by the estimate, 19 and 21 by
-// measure); hence the 8 % that a choice has to promise over one part of full tiles.
+// measure); hence the 8 % that a choice has to promise over one part of full tiles, 20 % for the small tiles.
 struct TileCost {
   int bm, bn, bk;
   float iter[4], fixed[4];
   int slots = 256;  // blocks that run side by side at these costs
 };
 // fp32 has two tables.  A sum in parts is rounded less often, so the parts of fp32 products are those of the tiles that computed them on the
-// fp32 matrix instructions, to which the results' errors are held (with parts chosen by the costs of today's tiles, fewer, shared results
-// were up to 1.6 times as far off, T = 1, d = 320, width 896: 3.1e-7 -> 4.8e-7); the height is chosen by what today's tiles take.
+// fp32 matrix instructions (64 rows, 64 and 128 columns: 1.07 us a step of 64 rows, 0.61 of fewer, 1.02 of dual ones, measured as above), to
+// which the results' errors are held (with parts chosen by the costs of SplitCore's tiles, fewer, and all products in one sum, shared results
+// were up to 1.6 times as far off, T = 1, d = 320, width 896: 3.1e-7 -> 4.8e-7); the height is chosen by row_cost and w_cost, those of SplitCore.
 template <int PATH, int NB> constexpr TileCost part_cost() {
   if (PATH == PATH_BF16_SMALL) return TileCost{64, 128 / NB, 64, {0.45f, 0.45f, 0.45f, 0.45f}, {4, 4, 4, 4}, 512};
   if (PATH == PATH_F32)
@@ -687,8 +689,8 @@ static void launch_gemm(const char* label, unsigned blocks, int threads, int lds
   ProfScope prof(label, st);
   hipLaunchKernelGGL(KERNEL, dim3(blocks), dim3(threads), lds_bytes, st, args...);
 }
-// epilogues of the router's products, which never have routed rows beside them
-template <int EPI> constexpr bool kRouterOnly = EPI == EPI_STORE_F32 || EPI == EPI_ADD;
+// launches of the router, which never have routed rows beside them, by their epilogue or their cores
+template <int EPI, class CoreSet> constexpr bool kRouterOnly = EPI == EPI_STORE_F32 || EPI == EPI_ADD || std::is_same_v<CoreSet, RouterDx<PATH_F32>::Rows>;
 
 // One product over the shared rows (sd), the routed rows (r, at most r_tiles tiles), or both.
 // Launches of one set have kernels of their own, with one argument block and without the other set's code: short ones are bound by how
@@ -716,7 +718,7 @@ static void launch_row(const char* label, const Direct* sd, const RowGemm* r, in
   constexpr int kLds = row_lds_bytes<CoreSet>();
   if (rb == 0) {
     launch_gemm<row_gemm_kernel<CoreSet, NB, EPI, B_KC, false>>(label, sb, Core::NT, kLds, st, p);
-  } else if constexpr (!kRouterOnly<EPI>) {
+  } else if constexpr (!kRouterOnly<EPI, CoreSet>) {
     if (sb == 0) launch_gemm<row_gemm_kernel<CoreSet, NB, EPI, B_KC, true>>(label, rb, Core::NT, kLds, st, *r);
     else launch_gemm<both_row_gemm_kernel<CoreSet, NB, EPI, B_KC>>(label, sb + rb, Core::NT, kLds, st, p, *r, (int)sb);
   }
@@ -761,7 +763,7 @@ static void launch_row_w(const char* label, const Direct* sd, const RowGemm* r, 
   constexpr int kLds = std::max(row_lds_bytes<CoreSet>(), WCore::LDS_BYTES);
   if (!r) {
     launch_gemm<row_w_gemm_kernel<CoreSet, EPI, WCore, WNB, false>>(label, blocks, WCore::NT, kLds, st, p, w, o.first_sw, o.s_rows);
-  } else if constexpr (!kRouterOnly<EPI>) {
+  } else if constexpr (!kRouterOnly<EPI, CoreSet>) {
     if (!sd) launch_gemm<row_w_gemm_kernel<CoreSet, EPI, WCore, WNB, true>>(label, blocks, WCore::NT, kLds, st, *r, *rw, 0, o.r_rows);
     else launch_gemm<both_row_w_gemm_kernel<CoreSet, EPI, WCore, WNB>>(label, blocks, WCore::NT, kLds, st, p, *r, w, *rw, o);
   }

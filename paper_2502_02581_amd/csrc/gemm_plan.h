@@ -51,8 +51,12 @@ inline Plan carve_plan(void* ws, int /*n_groups*/, int max_tiles) {
 //    top-2, d = 128, 133 experts of 384, 2.4 million, 361 and 288; T = 243, top-6, d = 2304, 31 experts of 128, 3.2 million, 143 and 117; T = 6330,
 //    d = 600, 166 experts of 384, 3.6 million, forward 101 and 104.)
 //  bytes of a matrix of the groups that may have rows: above it the stream of the weights counts, and the full family reads twice as long
-//    pieces of their rows.  (113 MB, training 102 and 82 us; 200 MB, forward 110 and 61; 330 MB, T = 16, top-4, d = 2048, 60 experts, forward 111
-//    and 106; 345 MB, training 747 and 758; 477 MB 701 and 711; 1390 MB 1429 and 1624.)
+//    pieces of their rows.  A compromise: what decides is how many of the full family's tiles the groups have that do get rows, which the
+//    host does not know.  (373 drawn passes with up to 128 of those in the smaller of the two forward products gain 20 %, 11 of them lose more than 1 %;
+//    147 with more gain 3 %, 44 lose.)  Bytes rule out most of the latter: of 300 drawn passes 263 lie below the line and gain 19 %, 15 lose more
+//    than 1 % and up to 11; 37 lie above, up to 2 GB, and would gain 7 %, 10 lose up to 10.  Near the line families take turns on either side
+//    of it: T = 16 to 64, d = 2048, 48 to 128 experts of 1280 to 2048, 240 to 700 MB, forward, lose 8 % to gain 4 % without shared experts; with four
+//    of 1408 beside them 330 MB takes 111 and 106 us, 352 MB 119 and 110.
 //  arithmetic of a product: above it the matrix pipe counts.  (6 GFLOP, training 534 and 429 us; 14 GFLOP 747 and 758; 33 GFLOP, forward 377
 //    and 418.)
 constexpr int kFewRowValues = 13 << 18;

@@ -4,7 +4,7 @@
 // pipeline only), 2: K loop done, 3: epilogue done (first wavefront) -- and every tile of the GEMM
 // kernels leaves one record {block, kernel id, group, column tile | kind << 8 | rows << 16, start,
 // end, phase cycles}: times from the 100 MHz wall clock, phases (set-up and first loads, K loop,
-// epilogue, rest) in shader-clock cycles.  moe_trace_read_{f32,bf16,tail} copy the records to the host.
+// epilogue, rest) in shader-clock cycles.  moe_trace_read_{f32,bf16,tail,small} copy the records to the host.
 #pragma once
 
 #ifdef MOE_TRACE
