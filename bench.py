@@ -37,11 +37,11 @@ MFMA_PROBE_ITERS = 1000
 KERNEL = {
     "gemm_fwd_gate_up": ("row_gemm_kernel", "moe::RowCores<2, 2, false>, 2, 1, false"),
     "gemm_fwd_down": ("row_gemm_kernel", "moe::RowCores<2, 1, false>, 1, 0, false"),
-    "gemm_bwd_dh_dwd": ("row_w_gemm_kernel", "moe::RowCores<2, 1, true>, 2, moe::MfmaDmaCore<unsigned short, 256, 256, 1, false, "
+    "gemm_bwd_dh_dwd": ("row_w_gemm_kernel", "moe::RowCores<2, 1, true>, 2, moe::MfmaDmaCore<256, 256, 1, false, "
                                              "false, 2, 2, 1, false>, 1"),
-    "gemm_bwd_dx_dwgu": ("row_w_gemm_kernel", "moe::RowCores<2, 1, true>, 0, moe::MfmaDmaCore<unsigned short, 256, 128, 2, false, "
+    "gemm_bwd_dx_dwgu": ("row_w_gemm_kernel", "moe::RowCores<2, 1, true>, 0, moe::MfmaDmaCore<256, 128, 2, false, "
                                               "false, 2, 2, 1, false>, 2"),
-    "gemm_bwd_dw_light": ("w_light_kernel", "moe::MfmaDmaCore<unsigned short, 128, 128, 1, false, false, 2, 2, 0, false> "),
+    "gemm_bwd_dw_light": ("w_light_kernel", "moe::MfmaDmaCore<128, 128, 1, false, false, 2, 2, 0, false> "),
 }
 # arguments of the kernels of one set of experts, and of those that hold the tiles of the routed and the shared ones
 KERNEL_ARGS = {

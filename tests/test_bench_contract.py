@@ -1,5 +1,6 @@
 """Host-side checks of bench.py's command line (no GPU needed)."""
 import os
+import shutil
 import subprocess
 import sys
 
@@ -48,3 +49,18 @@ def test_traffic_of_a_label_is_that_of_all_its_launches(cfg):
         named.append(symbol)
     assert sorted(named) == sorted(gemms)   # every GEMM kernel of the profile belongs to one label
     assert bench.measured_traffic("tiny", bench.GEMM_LABELS[0])[0] is None
+
+
+@pytest.mark.parametrize("shared", [False, True])
+def test_the_kernels_of_the_labels_are_those_of_the_library(shared):
+    """The table of kernel names is written by hand: it names kernels that the built library holds."""
+    sys.path.insert(0, ROOT)
+    import bench
+
+    lib = os.path.join(ROOT, "paper_2502_02581_amd", "libmoe_hip.so")
+    if shutil.which("nm") is None or not os.path.exists(lib):
+        pytest.skip("needs nm and the built library")
+    names = subprocess.run(["nm", "-C", lib], capture_output=True, text=True, check=True, timeout=120).stdout
+    held = {ln.split(" ", 2)[2].removeprefix("void ") for ln in names.splitlines() if "moe::" in ln and ln.count(" ") >= 2}
+    for label in bench.GEMM_LABELS:
+        assert bench.symbol(label, shared) in held, label
