@@ -2,7 +2,7 @@
 //
 // Every fp32 value is the exact sum of three bf16 values, a = a0 + a1 + a2 (each the rounding of what the ones before
 // leave; the second is at most 2^-8, the third at most 2^-17 of the first).  Of the nine products of two such sums the six
-// of at least 2^-17 are computed by v_mfma_f32_32x32x16_bf16; of the other three two are at most 2^-25, half a unit in the last place of an
+// that can reach 2^-17 are computed by v_mfma_f32_32x32x16_bf16; of the other three two are at most 2^-25, half a unit in the last place of an
 // fp32 product, and are computed where TERMS is 8 (see RouterDx).  Six of those instructions take 192 cycles for 32 x 32 x 16 products, the
 // fp32 instruction (v_mfma_f32_32x32x2_f32) 512.
 //
@@ -19,7 +19,8 @@
 // of one below 2^-134.  A tile that ends with a value that is not finite, or with one below 2^-76 that is not zero, in any lane
 // is computed again with the fp32 instruction, which treats them as fp32 arithmetic does (EXACT below).  So what range loses of a result is
 // 2^-134 / 2^-76 of the other operand: below 2^-25 of the result while that is below 2^33 -- except in results whose
-// products all have a factor below 2^-134 (5e-41), which are zero.
+// products all have a factor below 2^-134 (5e-41), which are zero.  (A training step of which every tile is computed again: 1500 -> 3240 us with tokens
+// of 1e-28, 3790 with NaN.)
 //
 // Measured, training steps, with the fp32 instruction (on 64 x 128 tiles) and now: T = 2048, d = 1024, 16 experts, top-2, width 2816
 // 1940 -> 1445 to 1500 us (144 TFLOP/s of fp32 products); T = 256, d = 128, 8 experts of width 256 92.4 -> 82.
